@@ -219,36 +219,33 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   const LaunchCtx ctx{p, stream, t->total_tokens};
 
   // Row statistic delta_i = dO_i . o_i, always for the query rows of the launch scope only (a caller that runs the
-  // list one unit at a time need not have o, lse and dO of later units yet).  fp32: a prepass in front of each dQ
-  // launch.  bf16: normally the dQ kernel computes it for the rows it owns and stores it (with lse in log2 units,
-  // both as bf16 triples) for the dK/dV launch of the same scope, which therefore runs after it; with a very
+  // list one unit at a time need not have o, lse and dO of later units yet): the dQ kernel computes it for the rows it
+  // owns and stores it (bf16: with lse in log2 units, both as bf16 triples) for the dK/dV launch of the same scope,
+  // which therefore runs after it.  In bf16 with a very
   // long sample (its K and V, over all KV heads, far beyond what the caches hold) the dQ blocks depend on
   // streaming the same K/V tiles at the same time, and the longer prologue cost 9 % there (256K sample), so
   // the prepass is kept.  (The dQ launch on a second stream beside the dK/dV launch, with the statistics always
   // from the prepass, was measured: the two kernels cannot share a compute unit and only slow each other --
   // 32K pack, fused 928 -> 893 TFLOP/s, per-unit 734 -> 716 -- so every launch stays on the caller's stream.)
-  const bool own_stats = !f32 && !(p->flags & SLIMATTN_FLAG_STATS_PREPASS) &&
-                         (size_t)t->max_sample_len * p->n_kv_heads * p->head_dim * 4 <= (size_t(128) << 20);
+  const bool own_stats = f32 || (!(p->flags & SLIMATTN_FLAG_STATS_PREPASS) &&
+                                (size_t)t->max_sample_len * p->n_kv_heads * p->head_dim * 4 <= (size_t(128) << 20));
   const int zq = tile_index(dq_q_tile(p->dtype, p->head_dim));
   const int zk = tile_index(dkdv_kv_tile(p->dtype, p->head_dim));
   auto run_dq = [&](const QItem* items, int n) -> int {
     if (!own_stats) {
-      const int e = timed(SLIMATTN_K_DELTA, stream, [&] {
-        return f32 ? launch_bwd_delta_f32(ctx, (const float*)o, (const float*)dO, delta, items, n)
-                   : launch_bwd_stat_bf16(ctx, o, dO, lse, stat3, items, n);
-      });
+      const int e = timed(SLIMATTN_K_DELTA, stream, [&] { return launch_bwd_stat_bf16(ctx, o, dO, lse, stat3, items, n); });
       if (e != 0) return e;
     }
     return timed(SLIMATTN_K_DQ, stream, [&] {
-      return f32 ? launch_bwd_dq_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (const float*)dO, lse, delta,
-                                     (float*)dQ, items, n)
+      return f32 ? launch_bwd_dq_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (const float*)o, (const float*)dO,
+                                     lse, delta, (float*)dQ, items, n)
                  : launch_bwd_dq_bf16(ctx, q, k, v, dO, o, lse, stat3, own_stats ? 1 : 0, dQ, items, n);
     });
   };
   auto run_dkdv = [&](const KvItem* items, int n, const Seg* segs) -> int {
     return timed(SLIMATTN_K_DKDV, stream, [&] {
       return f32 ? launch_bwd_dkdv_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (const float*)dO, lse,
-                                       delta, acc_dk, acc_dv, (float*)dK, (float*)dV, items, n, segs)
+                                       delta, acc_dk, acc_dv, (float*)dK, (float*)dV, items, n, segs, whole && !per_unit ? t->max_sample_len : 0)
                  : launch_bwd_dkdv_wide_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts);
     });
   };

@@ -111,13 +111,13 @@ struct LaunchCtx {
 // Kernel launchers (defined in the .hip files).  Each returns a hipError_t as int.
 int launch_fwd_f32(const LaunchCtx&, const float* q, const float* k, const float* v, float* o, float* lse,
                    const QItem* items, int n_items);
-// delta = rowsum(dO * O) for the rows of the listed query tiles
-int launch_bwd_delta_f32(const LaunchCtx&, const float* o, const float* dO, float* delta, const QItem* items, int n_items);
-int launch_bwd_dq_f32(const LaunchCtx&, const float* q, const float* k, const float* v, const float* dO, const float* lse,
-                      const float* delta, float* dQ, const QItem* items, int n_items);
+// also writes delta = rowsum(dO * O) of the rows of the listed query tiles, which the dK/dV launch reads
+int launch_bwd_dq_f32(const LaunchCtx&, const float* q, const float* k, const float* v, const float* o, const float* dO,
+                      const float* lse, float* delta, float* dQ, const QItem* items, int n_items);
+// longest: rows of the longest walk of a whole-list launch, whose accumulators may be used to divide the walks; 0 otherwise
 int launch_bwd_dkdv_f32(const LaunchCtx&, const float* q, const float* k, const float* v, const float* dO, const float* lse,
                         const float* delta, float* acc_dk, float* acc_dv, float* dK, float* dV, const KvItem* items,
-                        int n_items, const Seg* segs);
+                        int n_items, const Seg* segs, int longest);
 
 int launch_fwd_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, void* o, float* lse,
                     const QItem* items, int n_items);

@@ -1,0 +1,69 @@
+"""GPU parity at the sizes where a kernel's tiling can go wrong: tile edges, remainders and the ends of each variant's
+range, against the CPU fp64 oracle.  Tolerances as in test_gpu_parity.py (max-abs: fp32 1e-5; bf16 2e-2 on O and lse,
+5e-2 on the gradients)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2509_26246_amd as S
+import workloads as W
+from oracle import attention as A
+from paper_2509_26246_amd import harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(L, hq, hkv, d, bf16, slice_size, seed=7):
+    r = np.random.default_rng(seed)
+    T = int(sum(L))
+    f = (0.5, 0.5, 0.5, 0.1) if bf16 else (1.0, 1.0, 1.0, 1.0)
+    arrs = [r.standard_normal((T, h, d), dtype=np.float32) * np.float32(x) for h, x in zip((hq, hkv, hkv, hq), f)]
+    q, k, v, dO = (W.bf16_round(a) if bf16 else a for a in arrs)
+    cu, sl = S.build_slices(L, slice_size)
+    fu = S.build_units(cu, sl, "PREFIX_FILL", m=4, w_quad=2, w_lin=0)
+    bu = S.build_units(cu, sl, "PREFIX_FILL", m=5, w_quad=5, w_lin=0, backward=True)
+    scale = d ** -0.5
+    prob = H.make_problem(q, k, v, dO, cu, sl, fu, bu, bf16=bf16, scale=scale)
+    o, lse = A.fwd_packed(q, k, v, cu, scale)
+    dq, dk, dv = A.bwd_packed(q, k, v, o, lse, dO, cu, scale)
+    return prob, {"o": o, "lse": lse, "dQ": dq, "dK": dk, "dV": dv}
+
+
+def _poison(prob):
+    for t in (prob.o, prob.lse, prob.dQ, prob.dK, prob.dV):
+        t.fill_(float("nan"))
+    prob.workspace.fill_(0xFF)
+
+
+def _check(prob, ref, bf16, tag):
+    for name, want in ref.items():
+        t = getattr(prob, name)
+        got = t.cpu().numpy() if name == "lse" else H.device_to_f32(t)
+        assert np.isfinite(got).all(), f"{tag} {name} not finite"
+        err = float(np.max(np.abs(got.astype(np.float64) - want)))
+        tol = 1e-5 if not bf16 else 2e-2 if name in ("o", "lse") else 5e-2
+        assert err <= tol, f"{tag} {name}: max-abs {err:.3e} > {tol}"
+
+
+def _fused_and_per_unit(L, hq, hkv, d, bf16, slice_size):
+    prob, ref = _problem(L, hq, hkv, d, bf16, slice_size)
+    for flags in (0, S.FLAG_PER_UNIT_LAUNCH):
+        _poison(prob)
+        prob.forward(flags=flags)
+        prob.backward(flags=flags)
+        torch.cuda.synchronize()
+        _check(prob, ref, bf16, f"{hq}/{hkv}/{d} bf16={bf16} flags={flags}")
+    return prob
+
+
+# 32-row blocks of 64-row tiles, four waves taking key (query) tiles in turn; (900, ...) at 4/1 heads: walks divided in two
+@pytest.mark.parametrize("L", [[1, 31, 32, 33, 63, 64, 65], [127, 128, 129, 161], [900, 2, 95]], ids=["sub-tile", "tile", "divided"])
+@pytest.mark.parametrize("hq,hkv,d", [(4, 1, 16), (4, 1, 32), (2, 2, 64), (4, 1, 128)])
+def test_fp32_tile_edges(L, hq, hkv, d):
+    prob = _fused_and_per_unit(L, hq, hkv, d, False, 80)
+    first = []
+    for _ in range(2):                                  # fixed summation order: bitwise repeatable
+        _poison(prob)
+        prob.forward(); prob.backward(); torch.cuda.synchronize()
+        first.append([t.clone() for t in (prob.o, prob.lse, prob.dQ, prob.dK, prob.dV)])
+    assert all(torch.equal(a, b) for a, b in zip(*first))

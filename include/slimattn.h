@@ -304,7 +304,7 @@ void slimattn_tables_destroy(slimattn_tables* t);
 
 /* Counts held by a handle: what = 0 tokens, 1 samples, 2 slices, 3 forward units, 4 backward units,
  * 5..8: 256-row key tiles of the whole-list scope whose dK/dV work is divided among several blocks
- * when the launch has 1, 2, 4, >= 8 KV heads (heavy-tile balancing; informational). */
+ * when the launch has 1, 2, 4, 8 KV heads (heavy-tile balancing; informational). */
 int64_t slimattn_tables_count(const slimattn_tables* t, int what);
 
 /* Bytes of DEVICE scratch slimattn_bwd needs (fp32 dK/dV accumulators, the per-row statistics in

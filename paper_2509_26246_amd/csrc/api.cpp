@@ -212,6 +212,7 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   void* stat3 = (char*)delta + align_up(T * p->n_q_heads * sizeof(float));
   float* parts = (float*)((char*)stat3 + align_up(T * p->n_q_heads * 16));              // partial tiles of divided key tiles
   const int sc = split_class(p->n_kv_heads);
+  const int64_t head_blocks = head_part_blocks(t, p->n_q_heads, p->n_kv_heads, p->head_dim);
   const int n_units = t->n_units[1];
   const bool whole = lo == 0 && hi == n_units;
   const bool per_unit = (p->flags & SLIMATTN_FLAG_PER_UNIT_LAUNCH) != 0;
@@ -242,24 +243,32 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
                  : launch_bwd_dq_bf16(ctx, q, k, v, dO, o, lse, stat3, own_stats ? 1 : 0, dQ, items, n);
     });
   };
-  auto run_dkdv = [&](const KvItem* items, int n, const Seg* segs) -> int {
+  auto run_dkdv = [&](const KvItem* items, int n, const Seg* segs, int hp = 1) -> int {
     return timed(SLIMATTN_K_DKDV, stream, [&] {
       return f32 ? launch_bwd_dkdv_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (const float*)dO, lse,
                                        delta, acc_dk, acc_dv, (float*)dK, (float*)dV, items, n, segs, whole && !per_unit ? t->max_sample_len : 0)
-                 : launch_bwd_dkdv_wide_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts);
+                 : launch_bwd_dkdv_wide_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp);
     });
   };
   // bf16: the key-tile list in which heavy tiles are divided among several blocks, followed by the
-  // launch that adds the parts up (a scope without divided tiles has an empty reduction list)
+  // launch that adds the parts up (a scope without divided tiles has an empty reduction list); small launches also
+  // divide every item by query heads, and then every tile is reduced
   auto run_dkdv_split = [&](const ScopeLists& L, const DeviceLists& D, int u) -> int {
     const int tile_rows = dkdv_kv_tile(p->dtype, p->head_dim), ti = split_tile_index(tile_rows);
     const int a = L.split_off[ti][sc][u], b = L.split_off[ti][sc][u + 1];
-    int e = run_dkdv(D.split_items[ti][sc] + a, b - a, D.segs);
+    const int hp = head_parts(b - a, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, L.longest[ti][sc][u], head_blocks);
+    int e = run_dkdv(D.split_items[ti][sc] + a, b - a, D.segs, hp);
     if (e != 0) return e;
+    if (hp > 1) {
+      const int ta = L.tile_off[ti][sc][u], tb = L.tile_off[ti][sc][u + 1];
+      return timed(SLIMATTN_K_REDUCE, stream, [&] {
+        return launch_bwd_reduce_bf16(ctx, parts, acc_dk, acc_dv, dK, dV, D.tile_items[ti][sc] + ta, tb - ta, tile_rows, hp);
+      });
+    }
     const int ra = L.reduce_off[ti][sc][u], rb = L.reduce_off[ti][sc][u + 1];
     if (rb == ra) return 0;
     return timed(SLIMATTN_K_REDUCE, stream, [&] {
-      return launch_bwd_reduce_bf16(ctx, parts, acc_dk, acc_dv, dK, dV, D.reduce_items[ti][sc] + ra, rb - ra, tile_rows);
+      return launch_bwd_reduce_bf16(ctx, parts, acc_dk, acc_dv, dK, dV, D.reduce_items[ti][sc] + ra, rb - ra, tile_rows, 1);
     });
   };
   auto finish = [&](int e) -> int { return hip_rc(e); };

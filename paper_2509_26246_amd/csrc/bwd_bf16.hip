@@ -286,24 +286,25 @@ __global__ __launch_bounds__(256, 2) void dq_bf16_kernel(const bf16* __restrict_
 // ---------------------------------------------------------------------------------------------
 // Sum of the partial tiles of a divided key tile, in slot order (fixed, so the result does not
 // depend on which block finished first), added to the fp32 accumulators or written as bf16.
-// grid = (tiles x kv heads, kReduceSplit): a block takes a 1/kReduceSplit share of the tile's elements
-// (the launches are small, and few blocks with long dependent loops would only wait on memory);
-// a thread owns four consecutive columns of a row.
+// grid = (tiles x kv heads, 16 .. 64): a block takes a 1 / gridDim.y share of the tile's elements (the launches are small, and
+// few blocks with long loops would only wait on memory: reduce_split), a thread owns four consecutive columns of a row
+// and keeps four partial tiles' loads in flight.
 constexpr int kReduceSplit = 16;
 template <int D>
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restrict__ parts, float* __restrict__ acc_dk,
                                                            float* __restrict__ acc_dv, bf16* __restrict__ dK,
                                                            bf16* __restrict__ dV, const KvReduce* __restrict__ items,
-                                                           int Hkv, int tile_rows) {
+                                                           int Hkv, int tile_rows, int per_slot) {
   const KvReduce it = items[blockIdx.x / Hkv];
   const int hk = blockIdx.x % Hkv;
   const int kTile = tile_rows * D;                     // elements of one partial dK (or dV) tile
-  for (int e = (blockIdx.y * 256 + threadIdx.x) * 4; e < 2 * kTile; e += kReduceSplit * 256 * 4) {
+  for (int e = (blockIdx.y * 256 + threadIdx.x) * 4; e < 2 * kTile; e += (int)gridDim.y * 256 * 4) {
     const int which = e / kTile, r = (e % kTile) / D, c = e % D;
     if (r >= it.kv_rows) continue;
     floatx4 sum = {0.f, 0.f, 0.f, 0.f};
-    for (int p = 0; p < it.n_parts; ++p)
-      sum += *reinterpret_cast<const floatx4*>(parts + ((size_t)(it.first_slot + p) * Hkv + hk) * (2 * kTile) + e);
+#pragma unroll 4
+    for (int p = it.first_slot * per_slot; p < (it.first_slot + it.n_parts) * per_slot; ++p)
+      sum += *reinterpret_cast<const floatx4*>(parts + ((size_t)p * Hkv + hk) * (2 * kTile) + e);
     const size_t off = ((size_t)(it.kv_row0 + r) * Hkv + hk) * D + c;
     float* acc = which ? acc_dv : acc_dk;
     const bool load_acc = it.kv_row0 + r < it.load_until, store_final = it.kv_row0 + r >= it.final_from;
@@ -365,17 +366,26 @@ int launch_bwd_dq_bf16(const LaunchCtx& c, const void* q, const void* k, const v
   return (int)hipGetLastError();
 }
 
+namespace {
+// Blocks per tile: about four per compute unit, down to one float4 per thread (5 tiles of 8 parts: 13.6 us with 16 blocks
+// per tile, 6.2 us with 64).
+unsigned reduce_split(int tiles, int tile_elems) {
+  const int most = 2 * tile_elems / 1024, want = 1024 / tiles;
+  return (unsigned)(want < kReduceSplit ? kReduceSplit : want < most ? want : most);
+}
+}  // namespace
+
 int launch_bwd_reduce_bf16(const LaunchCtx& c, const float* parts, float* acc_dk, float* acc_dv, void* dK, void* dV,
-                           const KvReduce* items, int n_items, int tile_rows) {
+                           const KvReduce* items, int n_items, int tile_rows, int per_slot) {
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
-  const dim3 grid((unsigned)(n_items * p.n_kv_heads), kReduceSplit), block(256);
+  const dim3 grid((unsigned)(n_items * p.n_kv_heads), reduce_split(n_items * p.n_kv_heads, tile_rows * p.head_dim)), block(256);
   if (p.head_dim == 128)
     hipLaunchKernelGGL(reduce_parts_kernel<128>, grid, block, 0, (hipStream_t)c.stream, parts, acc_dk, acc_dv, (bf16*)dK,
-                       (bf16*)dV, items, p.n_kv_heads, tile_rows);
+                       (bf16*)dV, items, p.n_kv_heads, tile_rows, per_slot);
   else
     hipLaunchKernelGGL(reduce_parts_kernel<64>, grid, block, 0, (hipStream_t)c.stream, parts, acc_dk, acc_dv, (bf16*)dK,
-                       (bf16*)dV, items, p.n_kv_heads, tile_rows);
+                       (bf16*)dV, items, p.n_kv_heads, tile_rows, per_slot);
   return (int)hipGetLastError();
 }
 

@@ -265,13 +265,16 @@ __device__ __forceinline__ void dkdv_wide_block(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ dO,
     const bf16x8* __restrict__ stat3, float* __restrict__ acc_dk, float* __restrict__ acc_dv,
     bf16* __restrict__ dK, bf16* __restrict__ dV, const KvItem* __restrict__ items, int n_items, const Seg* __restrict__ segs,
-    int T, int Hq, int Hkv, float scale, float* __restrict__ parts) {
+    int T, int Hq, int Hkv, float scale, float* __restrict__ parts, int head_parts) {
   __shared__ __attribute__((aligned(1024))) char smem[kVBase<D> + kVBytes<D>];   // three [Q, dO] stages, then the V tile
 
   const int g = Hq / Hkv;
-  const int item_idx = blockIdx.x / Hkv, hk = blockIdx.x % Hkv;
+  // head_parts > 1: that many blocks share the item, each with a run of the group's heads; all store partial tiles
+  const int item_idx = blockIdx.x / (Hkv * head_parts), hk = blockIdx.x % Hkv, hpart = blockIdx.x / Hkv % head_parts;
+  const int h_lo = g * hpart / head_parts, h_hi = g * (hpart + 1) / head_parts;
   if (item_idx >= n_items) return;
   const KvItem it = items[item_idx];
+  const int slot = head_parts > 1 ? it.number * head_parts + hpart : it.slot;
   // where the rows' sums come from and go to: rows below load_until continue the partial sum an earlier unit left in
   // the fp32 accumulators; rows from final_from on get no later contribution and are written as dK/dV in the
   // output type, the others into the accumulators
@@ -280,8 +283,8 @@ __device__ __forceinline__ void dkdv_wide_block(
   LDS_PTR(char) lds = (LDS_PTR(char))smem;
 
   // Flattened walk (block-uniform): runs from the last to the first, inside a run steps of 32 rows from
-  // the top down, inside a step the heads of the group.
-  int sgi = it.seg_end - 1, hh = 0;
+  // the top down, inside a step the block's heads of the group.
+  int sgi = it.seg_end - 1, hh = h_lo;
   Seg sg = segs[sgi];
   int lo = max(sg.q_lo, it.kv_row0);
   int n = (sg.q_hi - lo + kQStep - 1) / kQStep - 1;
@@ -298,8 +301,8 @@ __device__ __forceinline__ void dkdv_wide_block(
     return ok;
   };
   auto next_step_b = [&](bool ok) {                     // move on: next head, or next 32 rows down
-    const bool wrap = ok && hh + 1 == g;
-    hh = !ok ? hh : wrap ? 0 : hh + 1;
+    const bool wrap = ok && hh + 1 == h_hi;
+    hh = !ok ? hh : wrap ? h_lo : hh + 1;
     n -= wrap ? 1 : 0;
   };
   auto next_step_c = [&](bool ok) {                     // the run is used up: the one before it, if any
@@ -485,7 +488,7 @@ __device__ __forceinline__ void dkdv_wide_block(
   // compiler does not know that the asm statements are matrix products): explicit wait states
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15");
 
-  if (it.slot < 0 && it.final_from <= it.kv_row0 && it.load_until <= it.kv_row0) {
+  if (slot < 0 && it.final_from <= it.kv_row0 && it.load_until <= it.kv_row0) {
     // The fused launch's case: bf16 rows of dK, then of dV, out through LDS (stages and V tile are free behind
     // the loop's last barrier; each wave uses a part of its own).  A lane owns a row's values in pieces of 4
     // columns, and written as they stand each store instruction would touch 32 rows with 16 bytes each;
@@ -520,9 +523,9 @@ __device__ __forceinline__ void dkdv_wide_block(
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     const int my_key = kv0w + 32 * kb + l32;
-    if (it.slot >= 0) {
+    if (slot >= 0) {
       // one part of a divided key tile: fp32 partial tile [slot][kv head][dK, dV][256 rows][D]
-      float* pk_ = parts + ((size_t)it.slot * Hkv + hk) * (2 * kKeys * D) + (size_t)(64 * wave + 32 * kb + l32) * D;
+      float* pk_ = parts + ((size_t)slot * Hkv + hk) * (2 * kKeys * D) + (size_t)(64 * wave + 32 * kb + l32) * D;
       float* pv_ = pk_ + kKeys * D;
 #pragma unroll
       for (int db = 0; db < kNDB<D>; ++db)
@@ -570,33 +573,33 @@ __global__ __launch_bounds__(256, 1) void dkdv_wide_bf16_kernel_d128(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ dO,
     const bf16x8* __restrict__ stat3, float* __restrict__ acc_dk, float* __restrict__ acc_dv, bf16* __restrict__ dK,
     bf16* __restrict__ dV, const KvItem* __restrict__ items, int n_items, const Seg* __restrict__ segs, int T, int Hq, int Hkv,
-    float scale, float* __restrict__ parts) {
-  dkdv_wide_block<128>(q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n_items, segs, T, Hq, Hkv, scale, parts);
+    float scale, float* __restrict__ parts, int head_parts) {
+  dkdv_wide_block<128>(q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n_items, segs, T, Hq, Hkv, scale, parts, head_parts);
 }
 __global__ __launch_bounds__(256, 1) void dkdv_wide_bf16_kernel_d64(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ dO,
     const bf16x8* __restrict__ stat3, float* __restrict__ acc_dk, float* __restrict__ acc_dv, bf16* __restrict__ dK,
     bf16* __restrict__ dV, const KvItem* __restrict__ items, int n_items, const Seg* __restrict__ segs, int T, int Hq, int Hkv,
-    float scale, float* __restrict__ parts) {
-  dkdv_wide_block<64>(q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n_items, segs, T, Hq, Hkv, scale, parts);
+    float scale, float* __restrict__ parts, int head_parts) {
+  dkdv_wide_block<64>(q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n_items, segs, T, Hq, Hkv, scale, parts, head_parts);
 }
 
 }  // namespace
 
 int launch_bwd_dkdv_wide_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
                             float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
-                            float* parts) {
+                            float* parts, int head_parts) {
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
-  const dim3 grid((unsigned)(n_items * p.n_kv_heads)), block(256);
+  const dim3 grid((unsigned)(n_items * p.n_kv_heads * head_parts)), block(256);
   if (p.head_dim == 128)
     hipLaunchKernelGGL(dkdv_wide_bf16_kernel_d128, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
                        (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv, (bf16*)dK, (bf16*)dV, items, n_items,
-                       segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts);
+                       segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, head_parts);
   else
     hipLaunchKernelGGL(dkdv_wide_bf16_kernel_d64, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
                        (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv, (bf16*)dK, (bf16*)dV, items, n_items,
-                       segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts);
+                       segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, head_parts);
   return (int)hipGetLastError();
 }
 

@@ -30,8 +30,9 @@ struct Seg { int32_t q_lo, q_hi; };
 // every such run and its block owns the tile's dK/dV.  slot >= 0: the item is one part of a heavy
 // tile whose query rows were divided among several blocks; it covers only its own runs and stores
 // its sums as fp32 partial tile number `slot`, which a reduction launch adds up in slot order.
-// load_until, final_from: where the rows' sums come from and go to (below).
-struct KvItem { int32_t kv_row0, kv_rows, seg_begin, seg_end, slot, load_until, final_from, pad; };
+// load_until, final_from: where the rows' sums come from and go to (below).  number: the item's place when every item of
+// the list stores a partial tile (launches divided by query heads): a tile's items have consecutive numbers, in slot order.
+struct KvItem { int32_t kv_row0, kv_rows, seg_begin, seg_end, slot, load_until, final_from, number; };
 
 // A key row collects from every unit of the backward list that has query rows of the sample at or after it
 // (a slice's dK/dV are complete only when all later slices have run: the paper's inter-slice dependency of
@@ -46,8 +47,8 @@ struct KvItem { int32_t kv_row0, kv_rows, seg_begin, seg_end, slot, load_until, 
 // A divided key tile: partial tiles first_slot .. first_slot + n_parts - 1 are its parts.
 struct KvReduce { int32_t kv_row0, kv_rows, first_slot, n_parts, load_until, final_from, pad0, pad1; };
 
-// Divided lists exist for the 256-row key tile (the bf16 dK/dV kernel) and four classes
-// of KV-head count (1, 2, 4, >= 8): a launch has items x KV heads blocks, so the fewer KV heads, the
+// Divided lists exist for the 256-row key tile (the bf16 dK/dV kernel) and six classes
+// of KV-head count (1, 2, 4, 8, 16, >= 32): a launch has items x KV heads blocks, so the fewer KV heads, the
 // fewer blocks share the work and the more a single long sample's first tiles dominate the makespan.
 constexpr int kNumSplitTiles = 1;                               // key-tile sizes for which divided lists are built
 constexpr int kSplitTileRows[kNumSplitTiles] = {256};           // the bf16 dK/dV kernel's tile
@@ -55,8 +56,28 @@ constexpr int kSplitTileRows[kNumSplitTiles] = {256};           // the bf16 dK/d
 // part costs a V tile, K fragments and an fp32 partial tile to set up, and dividing more finely lost 1-4 %).
 constexpr int kSplitBlockSlots[kNumSplitTiles] = {192};
 inline int split_tile_index(int rows) { return rows == 256 ? 0 : -1; }
-constexpr int kNumSplitClasses = 4;
-inline int split_class(int n_kv_heads) { return n_kv_heads >= 8 ? 3 : n_kv_heads >= 4 ? 2 : n_kv_heads >= 2 ? 1 : 0; }
+constexpr int kNumSplitClasses = 6;
+// (The share of a class is taken over its lower end; with 8 as the last one a launch on 32 KV heads was divided four times too
+// finely: 10567-token pack, 32/32 heads, dK/dV 499 + reduction 79 us against 458.)
+inline int split_class(int n_kv_heads) {
+  int c = 0;
+  while (c + 1 < kNumSplitClasses && (2 << c) <= n_kv_heads) ++c;
+  return c;
+}
+
+// Blocks of a dK/dV launch that share one item by query heads: a launch of few items (one small unit, a small pack, few KV
+// heads) leaves most compute units idle while each of its blocks walks the item's rows once per head of the group.  Every
+// block then stores a partial tile and all tiles go through the reduction, so the walk that is saved has to be worth
+// that: a step takes about 1.35 us, the reduction launch and the partial tiles about 15 (876-row pack, 8 heads on one KV
+// head: 5 blocks of up to 128 steps, 177 us; 40 blocks of up to 16, 40 us and 6 for the reduction).
+// max_blocks: one per compute unit, or as many partial tiles as the workspace has room for (head_part_blocks).
+constexpr int kHeadPartBlocks = 256;
+inline int head_parts(int n_items, int n_kv_heads, int group, int longest_rows, int64_t max_blocks) {
+  const int64_t blocks = (int64_t)n_items * n_kv_heads;
+  const int parts = blocks > 0 ? (int)(max_blocks / blocks < group ? max_blocks / blocks : group) : 1;
+  const int64_t steps = (int64_t)longest_rows * group / 32;
+  return parts > 1 && steps - steps / parts >= 20 ? parts : 1;
+}
 
 // A launch scope is either one unit or the whole list ("fused").  Its items are stored heavy-first.
 struct ScopeLists {
@@ -70,7 +91,12 @@ struct ScopeLists {
   std::vector<KvItem> split_items[kNumSplitTiles][kNumSplitClasses];
   std::vector<int32_t> reduce_off[kNumSplitTiles][kNumSplitClasses];
   std::vector<KvReduce> reduce_items[kNumSplitTiles][kNumSplitClasses];
-  int32_t max_slots[kNumSplitTiles][kNumSplitClasses] = {{0, 0, 0, 0}};   // most partial tiles any one scope needs
+  int32_t max_slots[kNumSplitTiles][kNumSplitClasses] = {};   // most partial tiles any one scope needs
+  // the same lists when every item stores a partial tile (head_parts below): one reduction per tile, and per unit the rows
+  // of the longest item's walk
+  std::vector<int32_t> tile_off[kNumSplitTiles][kNumSplitClasses];
+  std::vector<KvReduce> tile_items[kNumSplitTiles][kNumSplitClasses];
+  std::vector<int32_t> longest[kNumSplitTiles][kNumSplitClasses];
 };
 
 struct DeviceLists {                            // device mirrors (pointers into one allocation)
@@ -79,6 +105,7 @@ struct DeviceLists {                            // device mirrors (pointers into
   const Seg* segs;
   const KvItem* split_items[kNumSplitTiles][kNumSplitClasses];
   const KvReduce* reduce_items[kNumSplitTiles][kNumSplitClasses];
+  const KvReduce* tile_items[kNumSplitTiles][kNumSplitClasses];
 };
 
 }  // namespace slimattn
@@ -135,11 +162,15 @@ int launch_bwd_dq_bf16(const LaunchCtx&, const void* q, const void* k, const voi
 // head_dim 128: one wave per SIMD, 256 key rows per block (dkdv_wide_bf16.hip); same arguments
 int launch_bwd_dkdv_wide_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
                             float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
-                            float* parts);
+                            float* parts, int head_parts);
 // adds up the partial tiles (tile_rows rows each) of divided key tiles, in slot order, into dK/dV or the
-// fp32 accumulators
+// fp32 accumulators; per_slot: partial tiles per slot (the blocks that share an item by query heads)
 int launch_bwd_reduce_bf16(const LaunchCtx&, const float* parts, float* acc_dk, float* acc_dv, void* dK, void* dV,
-                           const KvReduce* items, int n_items, int tile_rows);
+                           const KvReduce* items, int n_items, int tile_rows, int per_slot);
+
+// Most partial tiles a launch divided by query heads may store: kHeadPartBlocks, or fewer where they would lift a workspace
+// that fits the built-in scratch array above its size (slimattn_bwd_static then still takes the pack, and computes the same).
+int64_t head_part_blocks(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d);
 
 // Looks up the built-in scratch array of slimattn_bwd_static on the current device (so that the first such call
 // finds it ready); returns a SLIMATTN_* code.

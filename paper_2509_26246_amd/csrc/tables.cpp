@@ -61,11 +61,13 @@ void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const st
     const int64_t target = std::max(kMinPartRows, (share / 2 + 127) / 128 * 128);
     std::vector<KvItem> items;
     std::vector<int64_t> w;
-    int32_t slots = 0;
+    int32_t slots = 0, number = 0;
     for (size_t x = 0; x < ki.size(); ++x) {
       const int64_t parts = std::min<int64_t>((weight[x] + target - 1) / target, weight[x] / kMinPartRows);
+      L.tile_items[ti][c].push_back(KvReduce{ki[x].kv_row0, ki[x].kv_rows, number, 1, ki[x].load_until, ki[x].final_from, 0, 0});
       if (parts < 2 || 4 * weight[x] <= 3 * share) {
         items.push_back(ki[x]);
+        items.back().number = number++;
         w.push_back(weight[x]);
         continue;
       }
@@ -76,9 +78,10 @@ void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const st
       int64_t have = 0;
       int32_t part_seg_begin = (int32_t)L.segs.size();
       auto close_part = [&]() {
-        items.push_back(KvItem{ki[x].kv_row0, ki[x].kv_rows, part_seg_begin, (int32_t)L.segs.size(), slots, 0, 0, 0});
+        items.push_back(KvItem{ki[x].kv_row0, ki[x].kv_rows, part_seg_begin, (int32_t)L.segs.size(), slots, 0, 0, number});
         w.push_back(have);
         ++slots;
+        ++number;
         ++red.n_parts;
         have = 0;
         part_seg_begin = (int32_t)L.segs.size();
@@ -95,6 +98,7 @@ void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const st
         }
       }
       if (have > 0) close_part();
+      L.tile_items[ti][c].back().n_parts = red.n_parts;
     }
     std::vector<int32_t> order(items.size());
     for (size_t x = 0; x < order.size(); ++x) order[x] = (int32_t)x;
@@ -103,6 +107,8 @@ void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const st
     L.split_off[ti][c].push_back((int32_t)L.split_items[ti][c].size());
     L.reduce_off[ti][c].push_back((int32_t)L.reduce_items[ti][c].size());
     L.max_slots[ti][c] = std::max(L.max_slots[ti][c], slots);
+    L.tile_off[ti][c].push_back((int32_t)L.tile_items[ti][c].size());
+    L.longest[ti][c].push_back(order.empty() ? 0 : (int32_t)w[order[0]]);
   }
 }
 
@@ -167,6 +173,25 @@ size_t place(std::vector<char>& blob, const std::vector<T>& v) {
 
 int& last_hip_error() { return g_last_hip_error; }
 
+namespace {
+// Bytes of the workspace without partial tiles, and the partial tiles (per KV head) of tiles divided by rows.
+size_t fixed_bytes(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d) {
+  const size_t T = (size_t)t->total_tokens;
+  return align_up(2 * T * hkv * d * sizeof(float)) + align_up(T * hq * sizeof(float)) + align_up(T * hq * 16) + 256;
+}
+size_t row_slots(const slimattn_tables* t, int32_t hkv) {
+  const int c = split_class(hkv);
+  return (size_t)std::max(t->per_unit[1].max_slots[0][c], t->fused.max_slots[0][c]);
+}
+size_t tile_bytes(int32_t d) { return (size_t)2 * kSplitTileRows[0] * d * sizeof(float); }
+}  // namespace
+
+int64_t head_part_blocks(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d) {
+  const size_t room = SLIMATTN_STATIC_SCRATCH_BYTES, fixed = fixed_bytes(t, hq, hkv, d);
+  if (fixed + align_up(row_slots(t, hkv) * hkv * tile_bytes(d)) > room) return kHeadPartBlocks;
+  return std::min<int64_t>(kHeadPartBlocks, (int64_t)((room - fixed - 256) / tile_bytes(d)));
+}
+
 }  // namespace slimattn
 
 using namespace slimattn;
@@ -211,7 +236,11 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
     for (int pass = 0; pass < 2; ++pass) {
       for (int z = 0; z < kNumTileSizes; ++z) { t->per_unit[pass].q_off[z].push_back(0); t->per_unit[pass].kv_off[z].push_back(0); }
       for (int ti = 0; ti < kNumSplitTiles; ++ti)
-        for (int c = 0; c < kNumSplitClasses; ++c) { t->per_unit[pass].split_off[ti][c].push_back(0); t->per_unit[pass].reduce_off[ti][c].push_back(0); }
+        for (int c = 0; c < kNumSplitClasses; ++c) {
+          t->per_unit[pass].split_off[ti][c].push_back(0);
+          t->per_unit[pass].reduce_off[ti][c].push_back(0);
+          t->per_unit[pass].tile_off[ti][c].push_back(0);
+        }
       // reach[s]: (unit, end of the unit's last query row in sample s), in list order.  A unit collects into the
       // key tiles of the sample that start before that end.
       std::vector<std::vector<std::pair<int32_t, int32_t>>> reach(n);
@@ -239,14 +268,19 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
     for (int32_t i = 0; i < n_slices; ++i) all[i] = i;
     for (int z = 0; z < kNumTileSizes; ++z) { t->fused.q_off[z].push_back(0); t->fused.kv_off[z].push_back(0); }
     for (int ti = 0; ti < kNumSplitTiles; ++ti)
-      for (int c = 0; c < kNumSplitClasses; ++c) { t->fused.split_off[ti][c].push_back(0); t->fused.reduce_off[ti][c].push_back(0); }
+      for (int c = 0; c < kNumSplitClasses; ++c) {
+        t->fused.split_off[ti][c].push_back(0);
+        t->fused.reduce_off[ti][c].push_back(0);
+        t->fused.tile_off[ti][c].push_back(0);
+      }
     append_scope(t->fused, merge_runs(slices, all.data(), n_slices), true,
                  [](int32_t) -> std::pair<int32_t, int32_t> { return {0, 0}; });
 
     // one blob, one upload
     std::vector<char> blob;
     const size_t off_cu = place(blob, t->cu), off_sl = place(blob, t->slices);
-    size_t off_q[3][kNumTileSizes], off_kv[3][kNumTileSizes], off_seg[3], off_sp[3][kNumSplitTiles][kNumSplitClasses], off_rd[3][kNumSplitTiles][kNumSplitClasses];
+    size_t off_q[3][kNumTileSizes], off_kv[3][kNumTileSizes], off_seg[3], off_sp[3][kNumSplitTiles][kNumSplitClasses], off_rd[3][kNumSplitTiles][kNumSplitClasses],
+        off_ta[3][kNumSplitTiles][kNumSplitClasses];
     ScopeLists* lists[3] = {&t->per_unit[0], &t->per_unit[1], &t->fused};
     for (int s = 0; s < 3; ++s) {
       for (int z = 0; z < kNumTileSizes; ++z) {
@@ -258,6 +292,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
         for (int c = 0; c < kNumSplitClasses; ++c) {
           off_sp[s][ti][c] = place(blob, lists[s]->split_items[ti][c]);
           off_rd[s][ti][c] = place(blob, lists[s]->reduce_items[ti][c]);
+          off_ta[s][ti][c] = place(blob, lists[s]->tile_items[ti][c]);
         }
     }
     blob.resize(align_up(blob.size()) + 256);
@@ -293,6 +328,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
         for (int c = 0; c < kNumSplitClasses; ++c) {
           dl[s]->split_items[ti][c] = (const KvItem*)(base + off_sp[s][ti][c]);
           dl[s]->reduce_items[ti][c] = (const KvReduce*)(base + off_rd[s][ti][c]);
+          dl[s]->tile_items[ti][c] = (const KvReduce*)(base + off_ta[s][ti][c]);
         }
     }
   } catch (const std::bad_alloc&) {
@@ -349,14 +385,16 @@ int slimattn_bwd_released_rows(const slimattn_tables* t, int32_t unit, int32_t* 
 
 size_t slimattn_bwd_workspace_bytes(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d) {
   if (!t || hq < 1 || hkv < 1 || d < 1) return 0;
-  const size_t T = (size_t)t->total_tokens;
   const int c = split_class(hkv);
-  size_t parts = 0;                       // the larger of the two tile sizes' needs (which kernel runs depends on dtype, d)
-  for (int ti = 0; ti < kNumSplitTiles; ++ti) {
-    const size_t slots = (size_t)std::max({t->per_unit[0].max_slots[ti][c], t->per_unit[1].max_slots[ti][c], t->fused.max_slots[ti][c]});
-    parts = std::max(parts, slots * hkv * 2 * kSplitTileRows[ti] * d * sizeof(float));
-  }
-  return align_up(2 * T * hkv * d * sizeof(float)) + align_up(T * hq * sizeof(float)) + align_up(T * hq * 16) + align_up(parts) + 256;
+  const int64_t max_blocks = head_part_blocks(t, hq, hkv, d);
+  size_t slots = row_slots(t, hkv);
+  for (const ScopeLists* L : {&t->per_unit[1], &t->fused})
+    for (size_t u = 0; u < L->longest[0][c].size(); ++u) {
+      const int n = L->split_off[0][c][u + 1] - L->split_off[0][c][u];
+      const int hp = head_parts(n, hkv, hq / hkv, L->longest[0][c][u], max_blocks);
+      if (hp > 1) slots = std::max(slots, (size_t)n * hp);
+    }
+  return fixed_bytes(t, hq, hkv, d) + align_up(slots * hkv * tile_bytes(d));
 }
 
 }  // extern "C"

@@ -67,3 +67,23 @@ def test_fp32_tile_edges(L, hq, hkv, d):
         prob.forward(); prob.backward(); torch.cuda.synchronize()
         first.append([t.clone() for t in (prob.o, prob.lse, prob.dQ, prob.dK, prob.dV)])
     assert all(torch.equal(a, b) for a, b in zip(*first))
+
+
+# few key tiles for the chip and several query heads per KV head: every tile's walk divided by heads, group sizes that the
+# number of parts does not divide included, beside tiles divided by rows (4096 rows on one KV head)
+@pytest.mark.parametrize("L,hq,hkv,d", [([511, 37, 200, 128], 8, 1, 128), ([300, 257, 1], 6, 1, 64), ([900, 255, 256], 7, 1, 128),
+                                        ([640, 31], 10, 2, 64), ([2304, 100], 16, 1, 128)])
+def test_bf16_key_tiles_divided_by_heads(L, hq, hkv, d):
+    _fused_and_per_unit(L, hq, hkv, d, True, 320)
+
+
+def test_bf16_head_parts_leave_the_static_scratch_enough():
+    """The partial tiles of a division by heads are limited so that the pack still fits the built-in scratch array."""
+    L = [4000, 1300] + [256] * 17
+    prob, ref = _problem(L, 4, 1, 128, True, 4096)
+    assert S.bwd_workspace_bytes(prob.tables, 4, 1, 128) <= S.STATIC_SCRATCH_BYTES
+    _poison(prob)
+    prob.forward()
+    S.bwd_static(prob.q, prob.k, prob.v, prob.o, prob.lse, prob.dO, prob.tables, prob.dQ, prob.dK, prob.dV, **prob._kw())
+    torch.cuda.synchronize()
+    _check(prob, ref, True, "static scratch")

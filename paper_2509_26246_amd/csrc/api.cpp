@@ -255,14 +255,14 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   // divide every item by query heads, and then every tile is reduced
   auto run_dkdv_split = [&](const ScopeLists& L, const DeviceLists& D, int u) -> int {
     const int tile_rows = dkdv_kv_tile(p->dtype, p->head_dim), ti = split_tile_index(tile_rows);
-    const int a = L.split_off[ti][sc][u], b = L.split_off[ti][sc][u + 1];
+    const int a = L.split_rng[ti][sc][u].begin, b = L.split_rng[ti][sc][u].end;
     const int hp = head_parts(b - a, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, L.longest[ti][sc][u], head_blocks);
-    int e = run_dkdv(D.split_items[ti][sc] + a, b - a, D.segs, hp);
+    int e = run_dkdv(D.split_items[ti] + a, b - a, D.segs, hp);
     if (e != 0) return e;
     if (hp > 1) {
-      const int ta = L.tile_off[ti][sc][u], tb = L.tile_off[ti][sc][u + 1];
+      const int ta = L.tile_rng[ti][sc][u].begin, tb = L.tile_rng[ti][sc][u].end;
       return timed(SLIMATTN_K_REDUCE, stream, [&] {
-        return launch_bwd_reduce_bf16(ctx, parts, acc_dk, acc_dv, dK, dV, D.tile_items[ti][sc] + ta, tb - ta, tile_rows, hp);
+        return launch_bwd_reduce_bf16(ctx, parts, acc_dk, acc_dv, dK, dV, D.tile_items[ti] + ta, tb - ta, tile_rows, hp);
       });
     }
     const int ra = L.reduce_off[ti][sc][u], rb = L.reduce_off[ti][sc][u + 1];

@@ -79,6 +79,8 @@ inline int head_parts(int n_items, int n_kv_heads, int group, int longest_rows, 
   return parts > 1 && steps - steps / parts >= 20 ? parts : 1;
 }
 
+struct Range { int32_t begin, end; };
+
 // A launch scope is either one unit or the whole list ("fused").  Its items are stored heavy-first.
 struct ScopeLists {
   std::vector<int32_t> q_off[kNumTileSizes];    // per-unit offsets into q_items (size n_units + 1)
@@ -86,16 +88,17 @@ struct ScopeLists {
   std::vector<int32_t> kv_off[kNumTileSizes];
   std::vector<KvItem> kv_items[kNumTileSizes];
   std::vector<Seg> segs;                        // all units' runs (and the parts' cut runs), referenced by the items
-  // key tiles with heavy tiles divided, per tile size and KV-head class; same unit-major layout
-  std::vector<int32_t> split_off[kNumSplitTiles][kNumSplitClasses];
-  std::vector<KvItem> split_items[kNumSplitTiles][kNumSplitClasses];
+  // key tiles with heavy tiles divided, per tile size; per KV-head class and unit a range of them (a class in which no tile of
+  // the unit is divided shares the range of the class below if that one has none either)
+  std::vector<Range> split_rng[kNumSplitTiles][kNumSplitClasses];
+  std::vector<KvItem> split_items[kNumSplitTiles];
   std::vector<int32_t> reduce_off[kNumSplitTiles][kNumSplitClasses];
   std::vector<KvReduce> reduce_items[kNumSplitTiles][kNumSplitClasses];
   int32_t max_slots[kNumSplitTiles][kNumSplitClasses] = {};   // most partial tiles any one scope needs
   // the same lists when every item stores a partial tile (head_parts below): one reduction per tile, and per unit the rows
   // of the longest item's walk
-  std::vector<int32_t> tile_off[kNumSplitTiles][kNumSplitClasses];
-  std::vector<KvReduce> tile_items[kNumSplitTiles][kNumSplitClasses];
+  std::vector<Range> tile_rng[kNumSplitTiles][kNumSplitClasses];
+  std::vector<KvReduce> tile_items[kNumSplitTiles];
   std::vector<int32_t> longest[kNumSplitTiles][kNumSplitClasses];
 };
 
@@ -103,9 +106,9 @@ struct DeviceLists {                            // device mirrors (pointers into
   const QItem* q_items[kNumTileSizes];
   const KvItem* kv_items[kNumTileSizes];
   const Seg* segs;
-  const KvItem* split_items[kNumSplitTiles][kNumSplitClasses];
+  const KvItem* split_items[kNumSplitTiles];
   const KvReduce* reduce_items[kNumSplitTiles][kNumSplitClasses];
-  const KvReduce* tile_items[kNumSplitTiles][kNumSplitClasses];
+  const KvReduce* tile_items[kNumSplitTiles];
 };
 
 }  // namespace slimattn

@@ -48,23 +48,53 @@ std::vector<Run> merge_runs(const slimattn_slice* sl, const int32_t* ids, int32_
 // consecutive and the reduction adds them in that order, so results do not depend on scheduling.
 constexpr int64_t kMinPartRows = 256;
 
-void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const std::vector<int64_t>& weight) {
+// (Buffers of append_scope and append_split, kept over the calls of one table build.)
+struct Scratch {
+  std::vector<QItem> qi;
+  std::vector<KvItem> ki, items;
+  std::vector<int64_t> weight, w;
+  std::vector<std::pair<int64_t, int32_t>> order;
+  // indices 0 .. n-1 by descending weight, equal ones in index order
+  const std::vector<std::pair<int64_t, int32_t>>& heavy_first(const std::vector<int64_t>& by) {
+    order.resize(by.size());
+    bool sorted = true;
+    for (size_t x = 0; x < by.size(); ++x) {
+      order[x] = {-by[x], (int32_t)x};
+      sorted = sorted && (x == 0 || by[x - 1] >= by[x]);
+    }
+    if (!sorted) std::sort(order.begin(), order.end());
+    return order;
+  }
+};
+
+void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const std::vector<int64_t>& weight, Scratch& tmp) {
   const int64_t kBlockSlots = kSplitBlockSlots[ti];
   int64_t total = 0;
   for (int64_t w : weight) total += w;
+  bool divided = true;                                       // in the class below
   for (int c = 0; c < kNumSplitClasses; ++c) {
+    if (!divided) {      // shares grow with the class: nothing is divided here either, and the lists are the same
+      L.split_rng[ti][c].push_back(L.split_rng[ti][c - 1].back());
+      L.tile_rng[ti][c].push_back(L.tile_rng[ti][c - 1].back());
+      L.reduce_off[ti][c].push_back((int32_t)L.reduce_items[ti][c].size());
+      L.longest[ti][c].push_back(L.longest[ti][c - 1].back());
+      continue;
+    }
     const int64_t heads = int64_t(1) << c;
     // A tile is divided when it exceeds three quarters of the per-slot share (below that, the
     // heavy-first dispatch already hides it), into parts of about half a share: the divided tiles
     // then no longer decide the makespan.
     const int64_t share = total * heads / kBlockSlots;
     const int64_t target = std::max(kMinPartRows, (share / 2 + 127) / 128 * 128);
-    std::vector<KvItem> items;
-    std::vector<int64_t> w;
+    std::vector<KvItem>& items = tmp.items;
+    std::vector<int64_t>& w = tmp.w;
+    items.clear();
+    w.clear();
     int32_t slots = 0, number = 0;
+    const int32_t item0 = (int32_t)L.split_items[ti].size(), tile0 = (int32_t)L.tile_items[ti].size();
     for (size_t x = 0; x < ki.size(); ++x) {
       const int64_t parts = std::min<int64_t>((weight[x] + target - 1) / target, weight[x] / kMinPartRows);
-      L.tile_items[ti][c].push_back(KvReduce{ki[x].kv_row0, ki[x].kv_rows, number, 1, ki[x].load_until, ki[x].final_from, 0, 0});
+      L.tile_items[ti].push_back(KvReduce{ki[x].kv_row0, ki[x].kv_rows, number, 1, ki[x].load_until, ki[x].final_from, 0, 0});
       if (parts < 2 || 4 * weight[x] <= 3 * share) {
         items.push_back(ki[x]);
         items.back().number = number++;
@@ -98,30 +128,30 @@ void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const st
         }
       }
       if (have > 0) close_part();
-      L.tile_items[ti][c].back().n_parts = red.n_parts;
+      L.tile_items[ti].back().n_parts = red.n_parts;
     }
-    std::vector<int32_t> order(items.size());
-    for (size_t x = 0; x < order.size(); ++x) order[x] = (int32_t)x;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return w[a] > w[b]; });
-    for (int32_t x : order) L.split_items[ti][c].push_back(items[x]);
-    L.split_off[ti][c].push_back((int32_t)L.split_items[ti][c].size());
+    const auto& order = tmp.heavy_first(w);
+    for (const auto& x : order) L.split_items[ti].push_back(items[x.second]);
+    divided = slots > 0;
+    L.split_rng[ti][c].push_back(Range{item0, (int32_t)L.split_items[ti].size()});
     L.reduce_off[ti][c].push_back((int32_t)L.reduce_items[ti][c].size());
     L.max_slots[ti][c] = std::max(L.max_slots[ti][c], slots);
-    L.tile_off[ti][c].push_back((int32_t)L.tile_items[ti][c].size());
-    L.longest[ti][c].push_back(order.empty() ? 0 : (int32_t)w[order[0]]);
+    L.tile_rng[ti][c].push_back(Range{tile0, (int32_t)L.tile_items[ti].size()});
+    L.longest[ti][c].push_back(order.empty() ? 0 : (int32_t)w[order[0].second]);
   }
 }
 
 // `row_marks(sample)`: {load_until, final_from} of the sample's key rows for this scope.
 // want_kv: key-tile lists are only needed by the backward pass.
 template <class Marks>
-void append_scope(ScopeLists& L, const std::vector<Run>& runs, bool want_kv, Marks&& row_marks) {
+void append_scope(ScopeLists& L, const std::vector<Run>& runs, bool want_kv, Scratch& tmp, Marks&& row_marks) {
   const int32_t seg_base = (int32_t)L.segs.size();
   for (const Run& r : runs) L.segs.push_back(Seg{r.q_lo, r.q_hi});
   for (int z = 0; z < kNumTileSizes; ++z) {
     const int32_t B = kTileSizes[z];
     // query tiles, heavy-first by visible prefix length
-    std::vector<QItem> qi;
+    std::vector<QItem>& qi = tmp.qi;
+    qi.clear();
     if (is_query_tile(B))
       for (const Run& r : runs)
         for (int32_t a = r.q_lo; a < r.q_hi; a += B) qi.push_back(QItem{a, std::min(B, r.q_hi - a), r.kv_start, 0});
@@ -131,8 +161,10 @@ void append_scope(ScopeLists& L, const std::vector<Run>& runs, bool want_kv, Mar
     L.q_items[z].insert(L.q_items[z].end(), qi.begin(), qi.end());
     L.q_off[z].push_back((int32_t)L.q_items[z].size());
     // key tiles: per sample, prefix [kv_start, last run's end); heavy-first by query rows at or after the tile
-    std::vector<KvItem> ki;
-    std::vector<int64_t> weight;
+    std::vector<KvItem>& ki = tmp.ki;
+    std::vector<int64_t>& weight = tmp.weight;
+    ki.clear();
+    weight.clear();
     size_t i = (want_kv && is_key_tile(B)) ? 0 : runs.size();
     while (i < runs.size()) {
       size_t j = i;
@@ -150,12 +182,9 @@ void append_scope(ScopeLists& L, const std::vector<Run>& runs, bool want_kv, Mar
       }
       i = j;
     }
-    std::vector<int32_t> order(ki.size());
-    for (size_t x = 0; x < order.size(); ++x) order[x] = (int32_t)x;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return weight[a] > weight[b]; });
-    for (int32_t x : order) L.kv_items[z].push_back(ki[x]);
+    for (const auto& x : tmp.heavy_first(weight)) L.kv_items[z].push_back(ki[x.second]);
     L.kv_off[z].push_back((int32_t)L.kv_items[z].size());
-    if (split_tile_index(B) >= 0) append_split(L, split_tile_index(B), ki, weight);
+    if (split_tile_index(B) >= 0) append_split(L, split_tile_index(B), ki, weight, tmp);
   }
 }
 
@@ -164,9 +193,18 @@ size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 template <class T>
 size_t place(std::vector<char>& blob, const std::vector<T>& v) {
   const size_t off = align_up(blob.size());
-  blob.resize(off + v.size() * sizeof(T));
-  if (!v.empty()) std::memcpy(blob.data() + off, v.data(), v.size() * sizeof(T));
+  blob.resize(off);
+  if (!v.empty()) blob.insert(blob.end(), (const char*)v.data(), (const char*)(v.data() + v.size()));
   return off;
+}
+size_t list_bytes(const ScopeLists& L) {                     // at least what place() takes for one scope's lists
+  size_t n = L.segs.size() * sizeof(Seg) + 256;
+  for (int z = 0; z < kNumTileSizes; ++z) n += L.q_items[z].size() * sizeof(QItem) + L.kv_items[z].size() * sizeof(KvItem) + 512;
+  for (int ti = 0; ti < kNumSplitTiles; ++ti) {
+    n += L.split_items[ti].size() * sizeof(KvItem) + L.tile_items[ti].size() * sizeof(KvReduce) + 512;
+    for (int c = 0; c < kNumSplitClasses; ++c) n += L.reduce_items[ti][c].size() * sizeof(KvReduce) + 256;
+  }
+  return n;
 }
 
 }  // namespace
@@ -233,14 +271,11 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
     t->unit_slices[0].assign(fwd_unit_slices, fwd_unit_slices + n_slices);
     t->unit_ptr[1].assign(bwd_unit_ptr, bwd_unit_ptr + n_bwd_units + 1);
     t->unit_slices[1].assign(bwd_unit_slices, bwd_unit_slices + n_slices);
+    Scratch tmp;
     for (int pass = 0; pass < 2; ++pass) {
       for (int z = 0; z < kNumTileSizes; ++z) { t->per_unit[pass].q_off[z].push_back(0); t->per_unit[pass].kv_off[z].push_back(0); }
       for (int ti = 0; ti < kNumSplitTiles; ++ti)
-        for (int c = 0; c < kNumSplitClasses; ++c) {
-          t->per_unit[pass].split_off[ti][c].push_back(0);
-          t->per_unit[pass].reduce_off[ti][c].push_back(0);
-          t->per_unit[pass].tile_off[ti][c].push_back(0);
-        }
+        for (int c = 0; c < kNumSplitClasses; ++c) t->per_unit[pass].reduce_off[ti][c].push_back(0);
       // reach[s]: (unit, end of the unit's last query row in sample s), in list order.  A unit collects into the
       // key tiles of the sample that start before that end.
       std::vector<std::vector<std::pair<int32_t, int32_t>>> reach(n);
@@ -253,7 +288,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
         }
       for (int32_t u = 0; u < t->n_units[pass]; ++u) {
         const int32_t a = t->unit_ptr[pass][u], b = t->unit_ptr[pass][u + 1];
-        append_scope(t->per_unit[pass], merge_runs(slices, t->unit_slices[pass].data() + a, b - a), pass == 1,
+        append_scope(t->per_unit[pass], merge_runs(slices, t->unit_slices[pass].data() + a, b - a), pass == 1, tmp,
                      [&](int32_t sample) -> std::pair<int32_t, int32_t> {
                        int32_t before = 0, after = 0;      // furthest reach of an earlier / a later unit (0: none)
                        for (const auto& ur : reach[sample]) {
@@ -268,19 +303,17 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
     for (int32_t i = 0; i < n_slices; ++i) all[i] = i;
     for (int z = 0; z < kNumTileSizes; ++z) { t->fused.q_off[z].push_back(0); t->fused.kv_off[z].push_back(0); }
     for (int ti = 0; ti < kNumSplitTiles; ++ti)
-      for (int c = 0; c < kNumSplitClasses; ++c) {
-        t->fused.split_off[ti][c].push_back(0);
-        t->fused.reduce_off[ti][c].push_back(0);
-        t->fused.tile_off[ti][c].push_back(0);
-      }
-    append_scope(t->fused, merge_runs(slices, all.data(), n_slices), true,
+      for (int c = 0; c < kNumSplitClasses; ++c) t->fused.reduce_off[ti][c].push_back(0);
+    append_scope(t->fused, merge_runs(slices, all.data(), n_slices), true, tmp,
                  [](int32_t) -> std::pair<int32_t, int32_t> { return {0, 0}; });
 
     // one blob, one upload
     std::vector<char> blob;
+    blob.reserve(t->cu.size() * 4 + t->slices.size() * sizeof(slimattn_slice) + 2048 + list_bytes(t->per_unit[0]) +
+                 list_bytes(t->per_unit[1]) + list_bytes(t->fused));
     const size_t off_cu = place(blob, t->cu), off_sl = place(blob, t->slices);
-    size_t off_q[3][kNumTileSizes], off_kv[3][kNumTileSizes], off_seg[3], off_sp[3][kNumSplitTiles][kNumSplitClasses], off_rd[3][kNumSplitTiles][kNumSplitClasses],
-        off_ta[3][kNumSplitTiles][kNumSplitClasses];
+    size_t off_q[3][kNumTileSizes], off_kv[3][kNumTileSizes], off_seg[3], off_sp[3][kNumSplitTiles], off_rd[3][kNumSplitTiles][kNumSplitClasses],
+        off_ta[3][kNumSplitTiles];
     ScopeLists* lists[3] = {&t->per_unit[0], &t->per_unit[1], &t->fused};
     for (int s = 0; s < 3; ++s) {
       for (int z = 0; z < kNumTileSizes; ++z) {
@@ -288,12 +321,11 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
         off_kv[s][z] = place(blob, lists[s]->kv_items[z]);
       }
       off_seg[s] = place(blob, lists[s]->segs);
-      for (int ti = 0; ti < kNumSplitTiles; ++ti)
-        for (int c = 0; c < kNumSplitClasses; ++c) {
-          off_sp[s][ti][c] = place(blob, lists[s]->split_items[ti][c]);
-          off_rd[s][ti][c] = place(blob, lists[s]->reduce_items[ti][c]);
-          off_ta[s][ti][c] = place(blob, lists[s]->tile_items[ti][c]);
-        }
+      for (int ti = 0; ti < kNumSplitTiles; ++ti) {
+        off_sp[s][ti] = place(blob, lists[s]->split_items[ti]);
+        off_ta[s][ti] = place(blob, lists[s]->tile_items[ti]);
+        for (int c = 0; c < kNumSplitClasses; ++c) off_rd[s][ti][c] = place(blob, lists[s]->reduce_items[ti][c]);
+      }
     }
     blob.resize(align_up(blob.size()) + 256);
     hipError_t e = hipGetDevice(&t->device);
@@ -324,12 +356,11 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
         dl[s]->kv_items[z] = (const KvItem*)(base + off_kv[s][z]);
       }
       dl[s]->segs = (const Seg*)(base + off_seg[s]);
-      for (int ti = 0; ti < kNumSplitTiles; ++ti)
-        for (int c = 0; c < kNumSplitClasses; ++c) {
-          dl[s]->split_items[ti][c] = (const KvItem*)(base + off_sp[s][ti][c]);
-          dl[s]->reduce_items[ti][c] = (const KvReduce*)(base + off_rd[s][ti][c]);
-          dl[s]->tile_items[ti][c] = (const KvReduce*)(base + off_ta[s][ti][c]);
-        }
+      for (int ti = 0; ti < kNumSplitTiles; ++ti) {
+        dl[s]->split_items[ti] = (const KvItem*)(base + off_sp[s][ti]);
+        dl[s]->tile_items[ti] = (const KvReduce*)(base + off_ta[s][ti]);
+        for (int c = 0; c < kNumSplitClasses; ++c) dl[s]->reduce_items[ti][c] = (const KvReduce*)(base + off_rd[s][ti][c]);
+      }
     }
   } catch (const std::bad_alloc&) {
     delete t;
@@ -390,7 +421,7 @@ size_t slimattn_bwd_workspace_bytes(const slimattn_tables* t, int32_t hq, int32_
   size_t slots = row_slots(t, hkv);
   for (const ScopeLists* L : {&t->per_unit[1], &t->fused})
     for (size_t u = 0; u < L->longest[0][c].size(); ++u) {
-      const int n = L->split_off[0][c][u + 1] - L->split_off[0][c][u];
+      const int n = L->split_rng[0][c][u].end - L->split_rng[0][c][u].begin;
       const int hp = head_parts(n, hkv, hq / hkv, L->longest[0][c][u], max_blocks);
       if (hp > 1) slots = std::max(slots, (size_t)n * hp);
     }

@@ -156,11 +156,11 @@ static int fwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   int rc = SLIMATTN_OK;
   const int z = tile_index(fwd_q_tile(p->dtype, p->head_dim));
   const LaunchCtx ctx{p, stream, t->total_tokens};
-  auto run = [&](const QItem* items, int n) -> int {
+  auto run = [&](const QItem* items, int n, int divide_rows = 0) -> int {
     return timed(SLIMATTN_K_FWD, stream, [&] {
       return p->dtype == SLIMATTN_F32
                  ? launch_fwd_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (float*)o, lse, items, n)
-                 : launch_fwd_bf16(ctx, q, k, v, o, lse, items, n);
+                 : launch_fwd_bf16(ctx, q, k, v, o, lse, items, n, divide_rows);
     });
   };
   const bool whole = lo == 0 && hi == t->n_units[0];
@@ -169,8 +169,18 @@ static int fwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   if (whole && !(p->flags & SLIMATTN_FLAG_PER_UNIT_LAUNCH))
     return hip_rc(run(t->d_fused.q_items[z], (int)t->fused.q_items[z].size()));
   const auto& off = t->per_unit[0].q_off[z];
-  if (!(p->flags & SLIMATTN_FLAG_PER_UNIT_LAUNCH))
-    return hip_rc(run(t->d_per_unit[0].q_items[z] + off[lo], off[hi] - off[lo]));
+  if (!(p->flags & SLIMATTN_FLAG_PER_UNIT_LAUNCH)) {
+    // Part of the list in one launch (prefill by slices): the keys of long prefixes may be divided among blocks.  Whole-list
+    // and per-unit launches walk every row's keys in one block, so that those two give the same bits.
+    int longest = 0;
+    for (int u = lo; u < hi; ++u)
+      if (off[u + 1] > off[u]) {                            // a unit's items are in descending order of visible keys
+        const QItem& it = t->per_unit[0].q_items[z][off[u]];
+        const int rows = it.q_row0 + it.q_rows - it.kv_start;
+        longest = rows > longest ? rows : longest;
+      }
+    return hip_rc(run(t->d_per_unit[0].q_items[z] + off[lo], off[hi] - off[lo], longest));
+  }
   for (int u = lo; u < hi; ++u) {
     g_prof.cur_unit = u;
     rc = hip_rc(run(t->d_per_unit[0].q_items[z] + off[u], off[u + 1] - off[u]));

@@ -115,28 +115,39 @@ __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds
   }
 }
 
-template <int D>
+// Split: NoSplit, or FwdSplit for a launch whose items' keys are divided (block numbers: parts innermost, so that an XCD keeps
+// to the same runs of keys; then the heads that share them).
+template <int D, class Split>
 __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k,
                                                           const bf16* __restrict__ v, bf16* __restrict__ o,
                                                           float* __restrict__ lse, const QItem* __restrict__ items,
-                                                          int n_items, int T, int Hq, int Hkv, float scale) {
+                                                          int n_items, int T, int Hq, int Hkv, float scale, Split sp) {
   constexpr int NKS = D / 16;   // contraction steps over the head dimension
   constexpr int NDB = D / 32;   // 32-wide blocks of the head dimension
   constexpr int kTileBytes = kFwdBK * D * 2, kBufBytes = 2 * kTileBytes;
   __shared__ __attribute__((aligned(1024))) char smem[2 * kBufBytes];   // [buffer][K tile, V tile]
 
   const int g = Hq / Hkv;
-  int item_idx, hk, hg;
-  if (!map_block(blockIdx.x, g, Hkv, n_items, &item_idx, &hk, &hg)) return;
+  int item_idx, hk, hg, part = 0;
+  if constexpr (Split::on) {
+    part = blockIdx.x % sp.parts;
+    split_block(blockIdx.x / sp.parts, g, Hkv, &item_idx, &hk, &hg);
+  } else {
+    if (!map_block(blockIdx.x, g, Hkv, n_items, &item_idx, &hk, &hg)) return;
+  }
   const int h = hk * g + hg;
-  const QItem it = items[item_idx];
+  QItem it = items[item_idx];
+  int n_tiles = (it.q_row0 + it.q_rows - it.kv_start + kFwdBK - 1) / kFwdBK;
+  bool alone = true;
+  if constexpr (Split::on) {
+    if (!split_range(sp, it, part, &n_tiles, &alone)) return;
+  }
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int q0w = it.q_row0 + 32 * wave;          // first query row of this wave
   const int my_row = q0w + l32;                   // the query row this lane owns
   const int q_end = it.q_row0 + it.q_rows;
   LDS_PTR(char) lds = (LDS_PTR(char))smem;
 
-  const int n_tiles = (q_end - it.kv_start + kFwdBK - 1) / kFwdBK;
   const TileSource srcK = make_tile_source<D, 256>(k, it.kv_start, Hkv, hk, q_end, tid);
   const TileSource srcV = make_tile_source<D, 256>(v, it.kv_start, Hkv, hk, q_end, tid);
   stage_tile<D, kFwdBK, 256>(lds, srcK, 0, tid);
@@ -203,6 +214,12 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
   }
 
   const float l_tot = l_run + xor32(l_run);
+  if constexpr (Split::on) {
+    if (!alone) {
+      split_store<D>(sp, (item_idx * sp.parts + part) * Hq + h, wave, lane, oacc, m_ref, l_tot);
+      return;
+    }
+  }
   if (my_row < q_end) {
     const float inv = 1.f / l_tot;
     bf16* op = o + ((size_t)my_row * Hq + h) * D;
@@ -365,19 +382,29 @@ __device__ __forceinline__ void fwd_softmax(floatx16 (&sacc)[2], bf16x8 (&pf)[4]
   l_run += (ps[0] + ps[1]) + (ps[2] + ps[3]);
 }
 
-template <int D>
+template <int D, class Split>
 __global__ __launch_bounds__(512, 2) void fwd_pair_bf16_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k,
                                                                const bf16* __restrict__ v, bf16* __restrict__ o,
                                                                float* __restrict__ lse, const QItem* __restrict__ items,
-                                                               int n_items, int T, int Hq, int Hkv, float scale) {
+                                                               int n_items, int T, int Hq, int Hkv, float scale, Split sp) {
   constexpr int NKS = D / 16, NDB = D / 32;
   constexpr int kTileBytes = kFwdBK * D * 2, kBufBytes = 2 * kTileBytes;
   __shared__ __attribute__((aligned(1024))) char smem[2 * kBufBytes];   // [buffer][K tile, V tile]
 
   const int g = Hq / Hkv;
-  int item_idx, hk, hp;
-  if (!map_block(blockIdx.x, g >> 1, Hkv, n_items, &item_idx, &hk, &hp)) return;
-  const QItem it = items[item_idx];
+  int item_idx, hk, hp, part = 0;
+  if constexpr (Split::on) {
+    part = blockIdx.x % sp.parts;
+    split_block(blockIdx.x / sp.parts, g >> 1, Hkv, &item_idx, &hk, &hp);
+  } else {
+    if (!map_block(blockIdx.x, g >> 1, Hkv, n_items, &item_idx, &hk, &hp)) return;
+  }
+  QItem it = items[item_idx];
+  int n_tiles = (it.q_row0 + it.q_rows - it.kv_start + kFwdBK - 1) / kFwdBK;
+  bool alone = true;
+  if constexpr (Split::on) {
+    if (!split_range(sp, it, part, &n_tiles, &alone)) return;
+  }
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int grp = __builtin_amdgcn_readfirstlane(wave >> 2), w4 = __builtin_amdgcn_readfirstlane(wave & 3);
   const int h = hk * g + 2 * hp + grp;
@@ -386,7 +413,6 @@ __global__ __launch_bounds__(512, 2) void fwd_pair_bf16_kernel(const bf16* __res
   const int q_end = it.q_row0 + it.q_rows;
   LDS_PTR(char) lds = (LDS_PTR(char))smem;
 
-  const int n_tiles = (q_end - it.kv_start + kFwdBK - 1) / kFwdBK;
   // tiles this wave sees without a mask (a prefix of the tile sequence)
   const int n_full = max(0, (q0w - it.kv_start + 1) / kFwdBK);
   // The block's global loads are all issued before anything waits: the Q rows first, then the first
@@ -479,7 +505,9 @@ __global__ __launch_bounds__(512, 2) void fwd_pair_bf16_kernel(const bf16* __res
   else fwd_products<D, false, true, 0, 0>(pk, pv, qf, sacc, pf, oacc, m_ref);
 
   const float l_tot = l_run + xor32(l_run);
-  if (my_row < q_end) {
+  if (!alone) {
+    if constexpr (Split::on) split_store<D>(sp, (item_idx * sp.parts + part) * Hq + h, w4, lane, oacc, m_ref, l_tot);
+  } else if (my_row < q_end) {
     const float inv = 1.f / l_tot;
     bf16* op = o + ((size_t)my_row * Hq + h) * D;
 #pragma unroll
@@ -500,30 +528,34 @@ __global__ __launch_bounds__(512, 2) void fwd_pair_bf16_kernel(const bf16* __res
 
 int fwd_q_tile(int dtype, int) { return dtype == SLIMATTN_F32 ? 64 : kFwdBQ; }
 
-int launch_fwd_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse,
-                    const QItem* items, int n_items) {
-  if (n_items == 0) return 0;
+namespace {
+template <class Split>
+int launch_fwd_two_wave(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse, const QItem* items,
+                        int n_items, int parts, Split sp) {
   const slimattn_params& p = *c.p;
   const int g = p.n_q_heads / p.n_kv_heads;
-  if (g % 2 == 0 && p.head_dim == 128) return launch_fwd_wide_bf16(c, q, k, v, o, lse, items, n_items);
-  if (g % 2 == 0) {
-    const dim3 grid(mapped_grid(n_items, p.n_kv_heads, g / 2)), block(512);
-    if (p.head_dim == 128)
-      hipLaunchKernelGGL(fwd_pair_bf16_kernel<128>, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
-                         (const bf16*)v, (bf16*)o, lse, items, n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale);
-    else
-      hipLaunchKernelGGL(fwd_pair_bf16_kernel<64>, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
-                         (const bf16*)v, (bf16*)o, lse, items, n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale);
+  auto go = [&](auto kernel, int heads, int threads) -> int {      // heads per KV head and block: g / heads blocks share an item
+    const unsigned grid = Split::on ? (unsigned)(n_items * p.n_kv_heads * (g / heads) * parts) : (unsigned)mapped_grid(n_items, p.n_kv_heads, g / heads);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v,
+                       (bf16*)o, lse, items, n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, sp);
     return (int)hipGetLastError();
-  }
-  const dim3 grid(mapped_grid(n_items, p.n_kv_heads, g)), block(256);
-  if (p.head_dim == 128)
-    hipLaunchKernelGGL(fwd_bf16_kernel<128>, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
-                       (const bf16*)v, (bf16*)o, lse, items, n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale);
-  else
-    hipLaunchKernelGGL(fwd_bf16_kernel<64>, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
-                       (const bf16*)v, (bf16*)o, lse, items, n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale);
-  return (int)hipGetLastError();
+  };
+  if (g % 2 == 0) return go(fwd_pair_bf16_kernel<64, Split>, 2, 512);
+  return p.head_dim == 128 ? go(fwd_bf16_kernel<128, Split>, 1, 256) : go(fwd_bf16_kernel<64, Split>, 1, 256);
+}
+}  // namespace
+
+int launch_fwd_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse,
+                    const QItem* items, int n_items, int divide_rows) {
+  if (n_items == 0) return 0;
+  const slimattn_params& p = *c.p;
+  FwdSplit sp;
+  int e = split_begin(c, n_items, divide_rows, &sp);
+  if (e != 0) return e;
+  if (p.n_q_heads / p.n_kv_heads % 2 == 0 && p.head_dim == 128) e = launch_fwd_wide_bf16(c, q, k, v, o, lse, items, n_items, sp);
+  else if (sp.parts > 1) e = launch_fwd_two_wave(c, q, k, v, o, lse, items, n_items, sp.parts, sp);
+  else e = launch_fwd_two_wave(c, q, k, v, o, lse, items, n_items, 1, NoSplit{});
+  return e != 0 || sp.parts == 1 ? e : split_combine(c, sp, o, lse, items, n_items);
 }
 
 }  // namespace slimattn

@@ -134,10 +134,12 @@ __device__ __forceinline__ void ew_flush(uintx4 (&pf)[2][2][2], float& e0, float
   pf[1][KE][1][3] = w;
 }
 
-template <int D>
-__device__ __forceinline__ void fwd_wide_item(const QItem it, const int hk, const int hp, const bf16* __restrict__ q,
+// n_tiles: key tiles to walk.  unit >= 0 (FwdSplit only): the walk is one part of the item, its results go to partial results
+// unit (first head) and unit + 1.
+template <int D, class Split>
+__device__ __forceinline__ void fwd_wide_item(const QItem it, const int n_tiles, const int hk, const int hp, const bf16* __restrict__ q,
                                               const bf16* __restrict__ k, const bf16* __restrict__ v, bf16* __restrict__ o_out,
-                                              float* __restrict__ lse, int T, int Hq, int Hkv, float scale) {
+                                              float* __restrict__ lse, int T, int Hq, int Hkv, float scale, const Split& sp, int unit) {
   constexpr int NKS = kNKS<D>, NDB = kNDB<D>, NVF = kNVF<D>, PER = kPer<D>;
   // K and V buffers, then one transposition area per wave for the output rows (row stride padded by 16 bytes)
   constexpr int kOutStride = kRowBytes<D> + 16, kOutBytes = 32 * kOutStride;
@@ -148,7 +150,6 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int hk, cons
   const int h0 = hk * g + 2 * hp;
   const int q0w = it.q_row0 + 32 * wave, my_row = q0w + l32, q_end = it.q_row0 + it.q_rows;
   LDS_PTR(char) lds = (LDS_PTR(char))smem;
-  const int n_tiles = (q_end - it.kv_start + kKeys - 1) / kKeys;
   // tiles this wave sees without a mask (at most all: a wave past the end of a ragged query tile)
   const int n_full = min(max(0, (q0w - it.kv_start + 1) / kKeys), n_tiles);
 
@@ -213,7 +214,9 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int hk, cons
   floatx16 s[2][2];                                     // S^T [head][key block of the tile]
   uintx4 pf[2][2][2];                                   // packed P^T [head][key block][16-key step]
   float e0 = 0.f, e1 = 0.f, lr[2] = {0.f, 0.f}, lu[2] = {0.f, 0.f};
-  int rel_n = my_row - it.kv_start - 4 * half;          // of the tile whose scores come next
+  // of the tile whose scores come next.  (The last iteration also produces scores of the tile behind the walk, which the mask
+  // has to discard: the diagonal does, where the walk does not end before it.)
+  int rel_n = (Split::on ? min(my_row - it.kv_start, kKeys * n_tiles - 1) : my_row - it.kv_start) - 4 * half;
   int t = -1;
   int ksoff = kKeys * srcK.row_bytes;                   // byte offset of tile t + 2 in the sample's rows
   const int wave_off = wave * 1024;
@@ -416,6 +419,16 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int hk, cons
   while (t < n_tiles) iteration(IC<0>{}, IC<1>{});
   settle();
 
+  if constexpr (Split::on) {
+    if (unit >= 0) {
+#pragma unroll
+      for (int hb = 0; hb < 2; ++hb) {
+        const float l_run = lr[hb] + lu[hb];
+        split_store<D>(sp, unit + hb, wave, lane, o[hb], m_ref[hb], l_run + xor32(l_run));
+      }
+      return;
+    }
+  }
   // O = O^T / l, through the wave's own LDS area: a lane owns a row's values in pieces of 4 columns, and written as
   // they stand each store instruction would touch 32 rows with 16 bytes each; transposed, a store instruction
   // writes four whole rows.
@@ -480,7 +493,8 @@ __device__ __forceinline__ void fwd_wide_walk(const bf16* __restrict__ q, const 
     it.q_rows = __builtin_amdgcn_readfirstlane(cur[1]);
     it.kv_start = __builtin_amdgcn_readfirstlane(cur[2]);
     it.pad = 0;
-    if (it.q_rows > 0) fwd_wide_item<D>(it, hk, hp, q, k, v, o, lse, T, Hq, Hkv, scale);
+    if (it.q_rows > 0)
+      fwd_wide_item<D>(it, (it.q_row0 + it.q_rows - it.kv_start + kKeys - 1) / kKeys, hk, hp, q, k, v, o, lse, T, Hq, Hkv, scale, NoSplit{}, -1);
     cur = nxt;
     hk = hk_n;
     hp = hp_n;
@@ -494,13 +508,35 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_bf16_kernel_d128(const bf16* 
   fwd_wide_walk<128>(q, k, v, o, lse, items, n_items, T, Hq, Hkv, scale);
 }
 
+// The launch whose items' keys are divided: one block per (item, head pair, part), parts innermost, so that an XCD keeps to
+// the same runs of keys.
+__global__ __launch_bounds__(256, 1) void fwd_wide_bf16_split_kernel_d128(const bf16* __restrict__ q, const bf16* __restrict__ k,
+                                                                           const bf16* __restrict__ v, bf16* __restrict__ o,
+                                                                           float* __restrict__ lse, const QItem* __restrict__ items,
+                                                                           int T, int Hq, int Hkv, float scale, FwdSplit sp) {
+  const int part = blockIdx.x % sp.parts;
+  int idx, hk, hp, n_tiles;
+  const int g = Hq / Hkv;
+  split_block(blockIdx.x / sp.parts, g >> 1, Hkv, &idx, &hk, &hp);
+  QItem it = items[idx];
+  bool alone;
+  if (!split_range(sp, it, part, &n_tiles, &alone)) return;
+  fwd_wide_item<128>(it, n_tiles, hk, hp, q, k, v, o, lse, T, Hq, Hkv, scale, sp, alone ? -1 : (idx * sp.parts + part) * Hq + hk * g + 2 * hp);
+}
+
 }  // namespace
 
 int launch_fwd_wide_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse,
-                         const QItem* items, int n_items) {
+                         const QItem* items, int n_items, const FwdSplit& sp) {
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
   const int g = p.n_q_heads / p.n_kv_heads;
+  if (sp.parts > 1) {
+    hipLaunchKernelGGL(fwd_wide_bf16_split_kernel_d128, dim3((unsigned)(n_items * (p.n_q_heads / 2) * sp.parts)), dim3(256), 0,
+                       (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items, (int)c.T,
+                       p.n_q_heads, p.n_kv_heads, p.scale, sp);
+    return (int)hipGetLastError();
+  }
   // one block per compute unit is resident (512 registers per lane); the device's count, rounded to the mapping's 8
   static int n_cu = 0;
   if (n_cu == 0) {

@@ -138,6 +138,42 @@ struct LaunchCtx {
   int64_t T;
 };
 
+// ---- forward launches whose keys are divided among blocks ------------------------------------------------------------
+// A few query tiles against a long prefix (prefill by slices) are a launch of few blocks with a long serial walk: 1024 rows of
+// 8 heads after 31K keys are 32 blocks of 500 key tiles for 256 compute units.  The launch then has `parts` blocks per
+// (item, heads), each walking a run of the item's key tiles with a reference of its own, and stores unnormalised O, reference
+// and row sum in fp32; a second kernel adds the parts up in order.  Row sums and O are sums over fewer terms than before.
+//
+// The forward has no workspace argument and allocates nothing, so the partial results live in one of kSplitRegions arrays
+// (34 MB each) that the first tables with a sample long enough allocate on their device; they are held until the process ends.
+// A region belongs to a launch from its claim kernel to its last combining block, both on the caller's stream: the claim is an
+// atomic compare-and-swap of the region's owner from 0 to the launch's ticket (a process-wide counter), decided on the
+// device each time the launch runs, so calls on any streams and threads and replays of captured graphs never share a region.
+// A stream keeps to one region (a stream's launches run one after another: they never meet).  A launch that finds its region
+// taken, by one of more streams than there are regions, walks undivided (the blocks of part 0 take all keys): no waiting, and
+// the same result up to the order of its sums.
+constexpr int kSplitRegions = 4;
+constexpr int kSplitUnits = 512;                                // (item, part, head) results of 128 rows per region: 256 compute
+                                                                // units x 2 heads per block, or 2 blocks per unit x 1 head
+constexpr int kSplitMinRows = 48 * 64;                          // shortest prefix that is divided
+template <int D> constexpr int kSplitUnitFloats = 128 * D + 256;   // O^T, then per wave 32 references and 32 row sums
+struct FwdSplit {
+  static constexpr bool on = true;
+  float* data;                    // the region's partial results
+  unsigned long long* owner;
+  unsigned* done;                 // combining blocks that have finished
+  unsigned long long ticket;
+  int parts;                      // blocks per (item, heads): 1 = not divided
+  int target;                     // key tiles per part (at least; shorter items take fewer parts)
+};
+
+// Fills in `sp` for a launch of n_items query tiles and claims its region on the stream; parts = 1 where division does not pay.
+int split_begin(const LaunchCtx&, int n_items, int divide_rows, FwdSplit* sp);
+// Adds up the parts and gives the region back.
+int split_combine(const LaunchCtx&, const FwdSplit& sp, void* o, float* lse, const QItem* items, int n_items);
+// Allocates the arrays on the current device if it has none yet; where that fails, launches are not divided.
+int prepare_split_regions();
+
 // Kernel launchers (defined in the .hip files).  Each returns a hipError_t as int.
 int launch_fwd_f32(const LaunchCtx&, const float* q, const float* k, const float* v, float* o, float* lse,
                    const QItem* items, int n_items);
@@ -149,11 +185,12 @@ int launch_bwd_dkdv_f32(const LaunchCtx&, const float* q, const float* k, const 
                         const float* delta, float* acc_dk, float* acc_dv, float* dK, float* dV, const KvItem* items,
                         int n_items, const Seg* segs, int longest);
 
+// divide_rows: keys the longest item sees, if the keys of the items may be divided among blocks (below); 0: one block walks them
 int launch_fwd_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, void* o, float* lse,
-                    const QItem* items, int n_items);
+                    const QItem* items, int n_items, int divide_rows);
 // even group sizes at head dim 128: one wave per SIMD, two heads per wave (fwd_wide_bf16.hip); same arguments
 int launch_fwd_wide_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, void* o, float* lse,
-                         const QItem* items, int n_items);
+                         const QItem* items, int n_items, const FwdSplit& sp);
 // Row statistics of the bf16 backward (-lse*log2e and -delta = -dO.O per row and head, as bf16 triples):
 // either the dQ kernel computes and stores them for the rows it owns (own_stats != 0; `o`, `lse` read), or
 // the prepass below has stored them for the rows of the same query tiles and the dQ kernel reads them

@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "internal.h"
+
 namespace slimattn {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -358,5 +360,47 @@ __device__ __forceinline__ bool map_block(int block, int g, int Hkv, int n_items
   return true;
 }
 inline int mapped_grid(int n_items, int Hkv, int g) { return ((n_items * Hkv + 7) / 8) * 8 * g; }
+
+// ---- forward launches whose keys are divided (FwdSplit in internal.h) --------------------------------------
+struct NoSplit { static constexpr bool on = false; };
+
+// Block (without its part) -> item, KV head, head in group: the blocks that read the same keys are neighbours.
+__device__ __forceinline__ void split_block(int j, int g, int Hkv, int* item, int* hk, int* hg) {
+  *hg = j % g;
+  *hk = j / g % Hkv;
+  *item = j / (g * Hkv);
+}
+
+// Part `part` of an item: moves the item's first key and sets the tiles to walk; false: no such part.  Tiles whose first key is
+// visible to every row of the item are dealt evenly, so each part's first key can serve as its reference; the last part also
+// takes the (at most two) tiles behind.  *alone: the item is not divided and the block writes O and lse itself.
+__device__ __forceinline__ bool split_range(const FwdSplit& sp, QItem& it, int part, int* n_tiles, bool* alone) {
+  const int all = (it.q_row0 + it.q_rows - it.kv_start + 63) / 64, common = (it.q_row0 - it.kv_start) / 64 + 1;
+  const bool owned = __hip_atomic_load(sp.owner, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == sp.ticket;
+  const int n = __builtin_amdgcn_readfirstlane(owned ? min(sp.parts, (common + sp.target - 1) / sp.target) : 1);
+  if (part >= n) return false;
+  const int a = (int)((long long)common * part / n), b = part + 1 == n ? all : (int)((long long)common * (part + 1) / n);
+  it.kv_start += 64 * a;
+  *n_tiles = b - a;
+  *alone = n == 1;
+  return true;
+}
+
+// One wave's 32 rows of one head: O^T accumulators, reference (log2 units) and row sum of the part (stores of 1 KB per instruction).
+template <int D>
+__device__ __forceinline__ void split_store(const FwdSplit& sp, int unit, int wave4, int lane, const floatx16 (&o)[D / 32], float m, float l) {
+  float* base = sp.data + (size_t)unit * kSplitUnitFloats<D>;
+  floatx4* at = reinterpret_cast<floatx4*>(base + wave4 * 32 * D) + lane;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq)
+      at[(db * 4 + gq) * 64] = floatx4{o[db][4 * gq], o[db][4 * gq + 1], o[db][4 * gq + 2], o[db][4 * gq + 3]};
+  if (lane < 32) {
+    float* stat = base + 128 * D + wave4 * 64 + lane;
+    stat[0] = m;
+    stat[32] = l;
+  }
+}
 
 }  // namespace slimattn

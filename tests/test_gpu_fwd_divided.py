@@ -1,0 +1,132 @@
+"""Forward calls over a part of the unit list whose few query tiles see a long prefix: their keys are divided among blocks and
+the parts added up by a second kernel.  Against the CPU fp64 oracle on sampled rows (tolerance as in test_gpu_parity.py: 2e-2
+max-abs on O and lse), at the edges of the division, with rows behind the slice set to NaN, repeatable bit for bit, and with
+more streams at once than there are arrays for the partial results."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2509_26246_amd as S
+import workloads as W
+from oracle import attention as A
+from paper_2509_26246_amd import harness as H
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+
+
+def _slices(L, hq, hkv, d, slice_size, seed=3):
+    r = np.random.default_rng(seed)
+    T = int(sum(L))
+    arrs = [W.bf16_round(r.standard_normal((T, h, d), dtype=np.float32) * np.float32(f)) for h, f in ((hq, 0.5), (hkv, 0.5), (hkv, 0.5), (hq, 0.1))]
+    cu, sl = S.build_slices(L, slice_size)
+    units = (np.arange(len(sl) + 1), np.arange(len(sl)))
+    return H.make_problem(*arrs, cu, sl, units, units, bf16=True, scale=d ** -0.5), arrs, cu, sl
+
+
+def _check(prob, arrs, cu, first, end, got_o, got_lse, tag):
+    r = np.random.default_rng(1)
+    rows = np.unique(np.concatenate([[first, end - 1, min(end - 1, first + 63), min(end - 1, first + 128)], r.integers(first, end, 24)]))
+    rows = np.repeat(rows, 2)
+    heads = r.integers(0, prob.n_q_heads, len(rows))
+    ro, rl = A.fwd_rows(arrs[0], arrs[1], arrs[2], cu, prob.scale, rows, heads)
+    eo, el = np.max(np.abs(got_o[rows, heads] - ro)), np.max(np.abs(got_lse[heads, rows] - rl))
+    assert eo <= TOL and el <= TOL, f"{tag}: O {eo:.3e} lse {el:.3e}"
+
+
+# Last slice of the first sample.  Prefixes around the shortest that is divided (48 tiles of 64 keys), parts of unequal size, a
+# slice that starts inside a tile, one-row slices, several query tiles; the kernel for even groups at head dim 128, the one
+# for even groups at 64, the one for odd groups at both.
+@pytest.mark.parametrize("hq,hkv,d", [(8, 1, 128), (4, 2, 128), (6, 1, 64), (5, 5, 128), (3, 1, 64)])
+@pytest.mark.parametrize("length,slice_size", [(3071, 3000), (3073, 3072), (6145, 256), (7777, 1000), (9000, 999)])
+def test_last_slice_of_a_long_sample(hq, hkv, d, length, slice_size):
+    prob, arrs, cu, sl = _slices([length, 70], hq, hkv, d, slice_size)
+    last = [t for t in range(len(sl)) if sl[t][0] == 0][-1]
+    first, end = int(sl[last][2]), int(sl[last][2] + sl[last][3])
+    nan = float("nan")
+    for t in (prob.q, prob.k, prob.v):
+        t[end:] = nan                                     # the next sample has not arrived
+    runs = []
+    for _ in range(2):
+        prob.o.fill_(nan)
+        prob.lse.fill_(nan)
+        prob.forward(unit_lo=last, unit_hi=last + 1)
+        torch.cuda.synchronize()
+        runs.append((prob.o.clone(), prob.lse.clone()))
+    o, lse = H.device_to_f32(prob.o), prob.lse.cpu().numpy()
+    assert np.isfinite(o[first:end]).all() and np.isfinite(lse[:, first:end]).all()
+    assert np.isnan(o[:first]).all() and np.isnan(o[end:]).all() and np.isnan(lse[:, :first]).all() and np.isnan(lse[:, end:]).all()
+    _check(prob, arrs, cu, first, end, o, lse, f"{hq}/{hkv}/{d} {length}/{slice_size}")
+    assert torch.equal(runs[0][0][first:end].view(torch.int16), runs[1][0][first:end].view(torch.int16))
+    assert torch.equal(runs[0][1][:, first:end], runs[1][1][:, first:end])
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(4, 1, 128), (3, 1, 128), (4, 2, 64)])
+def test_long_and_short_prefixes_in_one_call(hq, hkv, d):
+    # the last slices of a long, a middling (fewer parts) and a short sample (not divided) in one launch
+    prob, arrs, cu, sl = _slices([6000, 2100, 40], hq, hkv, d, 500)
+    picks = [[t for t in range(len(sl)) if sl[t][0] == s][-1] for s in range(3)]
+    order = [t for t in range(len(sl)) if t not in picks] + picks
+    units = (np.concatenate([[0], np.arange(len(order) - 3, len(order) + 1)]), np.asarray(order))
+    prob.tables = S.tables_create(cu, sl, *units, *units)
+    prob.o.fill_(float("nan"))
+    prob.lse.fill_(float("nan"))
+    prob.forward(unit_lo=1, unit_hi=4)
+    torch.cuda.synchronize()
+    o, lse = H.device_to_f32(prob.o), prob.lse.cpu().numpy()
+    for t in picks:
+        _check(prob, arrs, cu, int(sl[t][2]), int(sl[t][2] + sl[t][3]), o, lse, f"{hq}/{hkv}/{d} slice {t}")
+
+
+def test_scores_that_climb_from_part_to_part():
+    # each part's scores lie far above the one before it (by more than fp32's exponent range over the sample): parts are
+    # weighted by their references
+    hq, hkv, d, n = 4, 1, 128, 5000
+    prob, arrs, cu, sl = _slices([n], hq, hkv, d, 500, 9)
+    q, k, v, _ = arrs
+    q[:, :, 0] = 4.0
+    k[:, 0, 0] = W.bf16_round(np.linspace(-300, 300, n).astype(np.float32) // 8 * 8)
+    prob = H.make_problem(*arrs, cu, sl, *[(np.arange(len(sl) + 1), np.arange(len(sl)))] * 2, bf16=True, scale=d ** -0.5)
+    u = len(sl) - 1
+    prob.forward(unit_lo=u, unit_hi=u + 1)
+    torch.cuda.synchronize()
+    rows, heads = np.arange(4500, 5000, 7), np.arange(72) % hq
+    rows = rows[:72]
+    ro, rl = A.fwd_rows(q, k, v, cu, prob.scale, rows, heads)
+    # (lse relative: the scaled query is rounded to bf16 once, a relative error of 2^-9 of each score)
+    assert np.max(np.abs(H.device_to_f32(prob.o)[rows, heads] - ro)) <= TOL
+    assert np.max(np.abs(prob.lse.cpu().numpy()[heads, rows] - rl) / (1.0 + np.abs(rl))) <= TOL
+
+
+def test_more_streams_than_arrays_and_graph_replays():
+    prob, arrs, cu, sl = _slices([8000], 8, 1, 128, 512)
+    u = len(sl) - 1
+    first, end = int(sl[u][2]), int(sl[u][2] + sl[u][3])
+    prob.forward(unit_lo=u, unit_hi=u + 1)
+    torch.cuda.synchronize()
+    _check(prob, arrs, cu, first, end, H.device_to_f32(prob.o), prob.lse.cpu().numpy(), "one stream")
+    want = (prob.o[first:end].clone(), prob.lse[:, first:end].clone())
+    streams = [torch.cuda.Stream() for _ in range(7)]
+    outs = [(torch.empty_like(prob.o), torch.empty_like(prob.lse)) for _ in streams]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for s, (o, lse) in zip(streams, outs):
+            with torch.cuda.stream(s):
+                S.fwd(prob.q, prob.k, prob.v, prob.tables, o, lse, **prob._kw(unit_lo=u, unit_hi=u + 1))
+    torch.cuda.synchronize()
+    for i, (o, lse) in enumerate(outs):                     # divided or, where the stream's array was taken, not: to tolerance
+        _check(prob, arrs, cu, first, end, H.device_to_f32(o), lse.cpu().numpy(), f"stream {i}")
+    side = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        prob.forward(unit_lo=u, unit_hi=u + 1)
+    for _ in range(3):
+        prob.o.fill_(float("nan"))
+        prob.lse.fill_(float("nan"))
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(prob.o[first:end].view(torch.int16), want[0].view(torch.int16)) and torch.equal(prob.lse[:, first:end], want[1])
+        S.fwd(prob.q, prob.k, prob.v, prob.tables, outs[0][0], outs[0][1], **prob._kw(unit_lo=u, unit_hi=u + 1))
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0][0][first:end].view(torch.int16), want[0].view(torch.int16))

@@ -173,7 +173,7 @@ static int fwd_impl(const slimattn_params* p, const void* q, const void* k, cons
     // Part of the list in one launch (prefill by slices): the keys of long prefixes may be divided among blocks.  Whole-list
     // and per-unit launches walk every row's keys in one block, so that those two give the same bits.
     int longest = 0;
-    for (int u = lo; u < hi; ++u)
+    for (int u = lo; u < hi && t->split_regions; ++u)
       if (off[u + 1] > off[u]) {                            // a unit's items are in descending order of visible keys
         const QItem& it = t->per_unit[0].q_items[z][off[u]];
         const int rows = it.q_row0 + it.q_rows - it.kv_start;

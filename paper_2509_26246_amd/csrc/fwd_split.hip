@@ -72,6 +72,7 @@ __global__ __launch_bounds__(256) void split_combine_kernel(FwdSplit sp, bf16* _
 constexpr int kMaxDevices = 64;
 float* g_data[kMaxDevices] = {};
 SplitState* g_state[kMaxDevices] = {};
+int g_holders[kMaxDevices] = {};          // handles whose launches may use the device's regions
 std::mutex g_mutex;
 std::atomic<unsigned long long> g_ticket{1};
 void* g_streams[kSplitRegions] = {};     // the streams the first regions were given to, in order of first use
@@ -91,22 +92,29 @@ constexpr size_t kRegionFloats = (size_t)kSplitUnits * kSplitUnitFloats<128>;
 
 }  // namespace
 
-int prepare_split_regions() {
-  int dev = -1;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess || dev < 0 || dev >= kMaxDevices) return e != hipSuccess ? (int)e : (int)hipErrorInvalidDevice;
+bool acquire_split_regions(int dev) {
+  if (dev < 0 || dev >= kMaxDevices) return false;
   std::lock_guard<std::mutex> lock(g_mutex);
-  if (g_data[dev]) return 0;
-  void *d = nullptr, *s = nullptr;
-  e = hipGetSymbolAddress(&s, HIP_SYMBOL(split_state));
-  if (e == hipSuccess) e = hipMalloc(&d, kSplitRegions * kRegionFloats * sizeof(float));
-  if (e != hipSuccess) {
-    (void)hipGetLastError();                             // launches report only their own errors
-    return (int)e;
+  if (!g_data[dev]) {
+    void *d = nullptr, *s = nullptr;
+    hipError_t e = hipGetSymbolAddress(&s, HIP_SYMBOL(split_state));
+    if (e == hipSuccess) e = hipMalloc(&d, kSplitRegions * kRegionFloats * sizeof(float));
+    if (e != hipSuccess) {
+      (void)hipGetLastError();                           // launches report only their own errors
+      return false;
+    }
+    g_state[dev] = (SplitState*)s;
+    g_data[dev] = (float*)d;
   }
-  g_state[dev] = (SplitState*)s;
-  g_data[dev] = (float*)d;
-  return 0;
+  ++g_holders[dev];
+  return true;
+}
+
+void release_split_regions(int dev) {
+  std::lock_guard<std::mutex> lock(g_mutex);
+  if (--g_holders[dev] > 0) return;
+  (void)hipFree(g_data[dev]);                            // (waits for work that may still use them, like the tables' own)
+  g_data[dev] = nullptr;
 }
 
 // As many parts as one round of blocks holds, of at least kMinPartTiles key tiles, if that is the faster way.  A tile takes about

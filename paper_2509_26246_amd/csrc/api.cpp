@@ -257,6 +257,8 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
     return timed(SLIMATTN_K_DKDV, stream, [&] {
       return f32 ? launch_bwd_dkdv_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (const float*)dO, lse,
                                        delta, acc_dk, acc_dv, (float*)dK, (float*)dV, items, n, segs, whole && !per_unit ? t->max_sample_len : 0)
+             : p->head_dim == 64
+                 ? launch_bwd_dkdv_d64_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp)
                  : launch_bwd_dkdv_wide_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp);
     });
   };

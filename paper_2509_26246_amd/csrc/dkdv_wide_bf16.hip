@@ -1,4 +1,4 @@
-// dK/dV for bf16 inputs at head dim 128 or 64: 256 key rows per block, one wave per SIMD, 64 key rows per wave.
+// dK/dV for bf16 inputs at head dim 128 (64: dkdv_d64_bf16.hip): 256 key rows per block, one wave per SIMD, 64 key rows per wave.
 //
 // What it computes is the dK/dV step of the backward (see bwd_bf16.hip): a block owns key rows of one
 // KV head and walks every query row of the launch scope at or after them, for every query head of the
@@ -144,7 +144,7 @@ __device__ __forceinline__ void score_products(const lds_cptr (&pq)[kNKS<D>], in
 }
 
 // Element-wise work, P = exp2(S - lse) and dS = P (dP - delta), as a stream of 32 values cut into slots,
-// one slot behind each gradient product (two at head dim 64).  Slot j: the exponential of value j, the dS
+// one slot behind each gradient product.  Slot j: the exponential of value j, the dS
 // product of value j - 1, and one packing to bf16: P of the pair (j - 1, j) in odd slots, dS of the pair
 // (j - 2, j - 1) in even ones; the last slot also finishes value 31.  One transcendental and two plain
 // vector instructions: with the product's own issue that fills, and does not exceed, the time the matrix
@@ -221,11 +221,8 @@ __device__ __forceinline__ void gradient_products(const lds_cptr (&pqt)[kNDB<D>]
   // batch b: head-dim block b % 4 of 16-row half b / 4 (first half first: its P, dS die early); its
   // four reads are issued one behind each product of batch b - 2, those of batches 0 and 1 behind the
   // last score products (by the caller)
-  constexpr int kPer = 32 / (4 * kGradBatches<D>);       // element-wise values per product slot (1 at d 128, 2 at d 64)
-  auto ew = [&](auto qc) {                              // the element-wise work behind product q of the phase
-    constexpr int q = decltype(qc)::value;
-    static_for<0, kPer>([&](auto ec) { ew_slot<kPer * q + decltype(ec)::value>(s, dp, pf, ds, tp, td); });
-  };
+  static_assert(4 * kGradBatches<D> == 32, "one element-wise value per product");
+  auto ew = [&](auto qc) { ew_slot<decltype(qc)::value>(s, dp, pf, ds, tp, td); };   // the element-wise work behind product q of the phase
   static_for<0, kGradBatches<D>>([&](auto ic) {
     constexpr int b = decltype(ic)::value, st = b / kNDB<D>, db = b % kNDB<D>;
     constexpr bool more = b + 2 < kGradBatches<D>;
@@ -427,11 +424,11 @@ __device__ __forceinline__ void dkdv_wide_block(
     int voff_n = 0, soff_n = 0;
     Tr2 tb[kGradBatches<D>];                               // the gradient phase's batches of transposed fragments
     const int m0_n = st_n * kStageBytes<D> + wave_off;     // where this wave's lines of the first pass go
-    // slots of the pieces (behind score product k): spread out at d 128 (32 slots), packed at d 64 (16).
+    // slots of the pieces (behind score product k, of 32), spread out.
     // A piece is a handful of instructions: what does not fit behind its product delays the next one.
-    constexpr int kSlotWalkA = D == 128 ? 4 : 2, kSlotWalkB = D == 128 ? 5 : 3, kSlotWalkC = D == 128 ? 6 : 3;
-    constexpr int kSlotStatA = D == 128 ? 7 : 4, kSlotStat = D == 128 ? 8 : 5, kSlotAddr = D == 128 ? 9 : 4;
-    constexpr int kSlotLoad = D == 128 ? 10 : 6, kLoadStride = D == 128 ? 2 : 1, kSlotMask = D == 128 ? 18 : 7;
+    constexpr int kSlotWalkA = 4, kSlotWalkB = 5, kSlotWalkC = 6;
+    constexpr int kSlotStatA = 7, kSlotStat = 8, kSlotAddr = 9;
+    constexpr int kSlotLoad = 10, kLoadStride = 2, kSlotMask = 18;
     constexpr int kSlotGrad = 4 * (kNKS<D> - 2);
     constexpr int kPasses = kTileBytes<D> / 4096;         // staging loads per tile (256 threads x 16 bytes each)
     bool ok_n = false;
@@ -568,20 +565,12 @@ __device__ __forceinline__ void dkdv_wide_block(
   }
 }
 
-// One kernel per head dim (plain functions: the launch below names them).
 __global__ __launch_bounds__(256, 1) void dkdv_wide_bf16_kernel_d128(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ dO,
     const bf16x8* __restrict__ stat3, float* __restrict__ acc_dk, float* __restrict__ acc_dv, bf16* __restrict__ dK,
     bf16* __restrict__ dV, const KvItem* __restrict__ items, int n_items, const Seg* __restrict__ segs, int T, int Hq, int Hkv,
     float scale, float* __restrict__ parts, int head_parts) {
   dkdv_wide_block<128>(q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n_items, segs, T, Hq, Hkv, scale, parts, head_parts);
-}
-__global__ __launch_bounds__(256, 1) void dkdv_wide_bf16_kernel_d64(
-    const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ dO,
-    const bf16x8* __restrict__ stat3, float* __restrict__ acc_dk, float* __restrict__ acc_dv, bf16* __restrict__ dK,
-    bf16* __restrict__ dV, const KvItem* __restrict__ items, int n_items, const Seg* __restrict__ segs, int T, int Hq, int Hkv,
-    float scale, float* __restrict__ parts, int head_parts) {
-  dkdv_wide_block<64>(q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n_items, segs, T, Hq, Hkv, scale, parts, head_parts);
 }
 
 }  // namespace
@@ -592,14 +581,9 @@ int launch_bwd_dkdv_wide_bf16(const LaunchCtx& c, const void* q, const void* k, 
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
   const dim3 grid((unsigned)(n_items * p.n_kv_heads * head_parts)), block(256);
-  if (p.head_dim == 128)
-    hipLaunchKernelGGL(dkdv_wide_bf16_kernel_d128, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
-                       (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv, (bf16*)dK, (bf16*)dV, items, n_items,
-                       segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, head_parts);
-  else
-    hipLaunchKernelGGL(dkdv_wide_bf16_kernel_d64, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
-                       (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv, (bf16*)dK, (bf16*)dV, items, n_items,
-                       segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, head_parts);
+  hipLaunchKernelGGL(dkdv_wide_bf16_kernel_d128, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
+                     (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv, (bf16*)dK, (bf16*)dV, items, n_items,
+                     segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, head_parts);
   return (int)hipGetLastError();
 }
 

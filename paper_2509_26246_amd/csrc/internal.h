@@ -208,6 +208,10 @@ int launch_bwd_dq_bf16(const LaunchCtx&, const void* q, const void* k, const voi
 int launch_bwd_dkdv_wide_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
                             float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
                             float* parts, int head_parts);
+// head_dim 64: two waves per SIMD (dkdv_d64_bf16.hip); same arguments
+int launch_bwd_dkdv_d64_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
+                             float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
+                             float* parts, int head_parts);
 // adds up the partial tiles (tile_rows rows each) of divided key tiles, in slot order, into dK/dV or the
 // fp32 accumulators; per_slot: partial tiles per slot (the blocks that share an item by query heads)
 int launch_bwd_reduce_bf16(const LaunchCtx&, const float* parts, float* acc_dk, float* acc_dv, void* dK, void* dV,

@@ -403,4 +403,32 @@ __device__ __forceinline__ void split_store(const FwdSplit& sp, int unit, int wa
   }
 }
 
+// ---- output rows ------------------------------------------------------------------------------
+// A wave's 32 rows of one head from its transposed accumulators times `factor`, rows row0 .. min(row0 + 32, row_end), through the wave's LDS area `ep`
+// (kOutAreaBytes<D>): a lane owns a row's values in pieces of 4 columns, and written as they stand each store
+// instruction would touch 32 rows with 16 bytes each; transposed, a store instruction writes whole rows.
+template <int D> constexpr int kOutStride = D * 2 + 16;
+template <int D> constexpr int kOutAreaBytes = 32 * kOutStride<D>;
+template <int D>
+__device__ __forceinline__ void store_rows(LDS_PTR(char) ep, const floatx16 (&acc)[D / 32], float factor, bf16* __restrict__ out, int Hq, int h,
+                                           int row0, int row_end, int lane) {
+  constexpr int kChunks = D * 2 / 16, kRowsPerStore = 64 / kChunks;      // 16-byte chunks per row; rows per store
+  const int half = lane >> 5, l32 = lane & 31, st_row = lane / kChunks, st_chunk = lane % kChunks;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+      bf16x4 w;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) w[x] = (bf16)(acc[db][4 * gq + x] * factor);
+      *reinterpret_cast<LDS_PTR(bf16x4)>(ep + l32 * kOutStride<D> + (32 * db + 8 * gq + 4 * half) * 2) = w;
+    }
+#pragma unroll
+  for (int j = 0; j < 32 / kRowsPerStore; ++j) {
+    const int r = j * kRowsPerStore + st_row;
+    const bf16x8 w = *reinterpret_cast<LDS_PTR(const bf16x8)>(ep + r * kOutStride<D> + st_chunk * 16);
+    if (row0 + r < row_end) *reinterpret_cast<bf16x8*>(out + ((size_t)(row0 + r) * Hq + h) * D + st_chunk * 8) = w;
+  }
+}
+
 }  // namespace slimattn

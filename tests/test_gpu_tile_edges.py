@@ -87,3 +87,11 @@ def test_bf16_head_parts_leave_the_static_scratch_enough():
     S.bwd_static(prob.q, prob.k, prob.v, prob.o, prob.lse, prob.dO, prob.tables, prob.dQ, prob.dK, prob.dV, **prob._kw())
     torch.cuda.synchronize()
     _check(prob, ref, True, "static scratch")
+
+
+# Head dim 64, 32 keys per wave and query steps in pairs: tiles with few waves in use, one step alone, odd and even numbers of
+# steps (odd groups), steps that end inside a run, runs that start inside a wave's keys
+@pytest.mark.parametrize("L", [[1, 31, 32, 33], [63, 65, 224, 225], [255, 257, 300]], ids=["wave", "waves", "tile"])
+@pytest.mark.parametrize("hq,hkv,slice_size", [(1, 1, 1000), (3, 1, 97), (4, 2, 64)])
+def test_bf16_dkdv_head_dim_64(L, hq, hkv, slice_size):
+    _fused_and_per_unit(L, hq, hkv, 64, True, slice_size)

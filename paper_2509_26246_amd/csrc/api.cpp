@@ -155,7 +155,7 @@ static int fwd_impl(const slimattn_params* p, const void* q, const void* k, cons
                     float* lse, void* stream, int lo, int hi) {
   int rc = SLIMATTN_OK;
   const int z = tile_index(fwd_q_tile(p->dtype, p->head_dim));
-  const LaunchCtx ctx{p, stream, t->total_tokens};
+  const LaunchCtx ctx{p, stream, t->total_tokens, t->mean_keys};
   auto run = [&](const QItem* items, int n, int divide_rows = 0) -> int {
     return timed(SLIMATTN_K_FWD, stream, [&] {
       return p->dtype == SLIMATTN_F32
@@ -227,7 +227,7 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   const bool whole = lo == 0 && hi == n_units;
   const bool per_unit = (p->flags & SLIMATTN_FLAG_PER_UNIT_LAUNCH) != 0;
 
-  const LaunchCtx ctx{p, stream, t->total_tokens};
+  const LaunchCtx ctx{p, stream, t->total_tokens, t->mean_keys};
 
   // Row statistic delta_i = dO_i . o_i, always for the query rows of the launch scope only (a caller that runs the
   // list one unit at a time need not have o, lse and dO of later units yet): the dQ kernel computes it for the rows it

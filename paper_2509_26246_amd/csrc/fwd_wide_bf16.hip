@@ -100,7 +100,7 @@ __device__ __forceinline__ void lds_ptr_add(lds_cptr& p, int d) {
 // rounding to bf16), and in even slots the packing of the pair (J-2, J-1).  Slots 0 and 1 also add the
 // previous unit's row sums to the running ones.  No instruction reads the result of the
 // exponential right in front of it (a transcendental's result is not forwarded to the next instruction).
-// (Row sums over the packed values with the dot-product instruction, as the two-wave kernel takes them,
+// (Row sums over the packed values with the dot-product instruction, as the kernel of fwd_bf16.hip takes them,
 // are not used here: that instruction did not overlap with a running matrix product.)
 template <int KE, int J>
 __device__ __forceinline__ void ew_slot(floatx16 (&s)[2][2], uintx4 (&pf)[2][2][2], float& e0, float& e1, float (&lr)[2],
@@ -141,9 +141,8 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int n_tiles,
                                               const bf16* __restrict__ k, const bf16* __restrict__ v, bf16* __restrict__ o_out,
                                               float* __restrict__ lse, int T, int Hq, int Hkv, float scale, const Split& sp, int unit) {
   constexpr int NKS = kNKS<D>, NDB = kNDB<D>, NVF = kNVF<D>, PER = kPer<D>;
-  // K and V buffers, then one transposition area per wave for the output rows (row stride padded by 16 bytes)
-  constexpr int kOutStride = kRowBytes<D> + 16, kOutBytes = 32 * kOutStride;
-  __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes<D> + 4 * kOutBytes];
+  // K and V buffers, then one transposition area per wave for the output rows
+  __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes<D> + 4 * kOutAreaBytes<D>];
 
   const int g = Hq / Hkv;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
@@ -429,34 +428,12 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int n_tiles,
       return;
     }
   }
-  // O = O^T / l, through the wave's own LDS area: a lane owns a row's values in pieces of 4 columns, and written as
-  // they stand each store instruction would touch 32 rows with 16 bytes each; transposed, a store instruction
-  // writes four whole rows.
-  LDS_PTR(char) ep = lds + 4 * kTileBytes<D> + wave * kOutBytes;
-  constexpr int kChunks = kRowBytes<D> / 16, kRowsPerStore = 64 / kChunks;   // 16-byte chunks per row; rows per store
-  const int st_row = lane / kChunks, st_chunk = lane % kChunks;
 #pragma unroll
   for (int hb = 0; hb < 2; ++hb) {
     const float l_run = lr[hb] + lu[hb];
     const float l_tot = l_run + xor32(l_run);
-    const float inv = 1.f / l_tot;
-    const int h = h0 + hb;
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        bf16x4 w;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) w[x] = (bf16)(o[hb][db][4 * gq + x] * inv);
-        *reinterpret_cast<LDS_PTR(bf16x4)>(ep + l32 * kOutStride + (32 * db + 8 * gq + 4 * half) * 2) = w;
-      }
-    if (half == 0 && my_row < q_end) lse[(size_t)h * T + my_row] = (m_ref[hb] + __builtin_amdgcn_logf(l_tot)) * kLn2;
-#pragma unroll
-    for (int j = 0; j < 32 / kRowsPerStore; ++j) {
-      const int r = j * kRowsPerStore + st_row;
-      const bf16x8 w = *reinterpret_cast<LDS_PTR(const bf16x8)>(ep + r * kOutStride + st_chunk * 16);
-      if (q0w + r < q_end) *reinterpret_cast<bf16x8*>(o_out + ((size_t)(q0w + r) * Hq + h) * D + st_chunk * 8) = w;
-    }
+    store_rows<D>(lds + 4 * kTileBytes<D> + wave * kOutAreaBytes<D>, o[hb], 1.f / l_tot, o_out, Hq, h0 + hb, q0w, q_end, lane);
+    if (half == 0 && my_row < q_end) lse[(size_t)(h0 + hb) * T + my_row] = (m_ref[hb] + __builtin_amdgcn_logf(l_tot)) * kLn2;
   }
 }
 
@@ -546,8 +523,8 @@ int launch_fwd_wide_bf16(const LaunchCtx& c, const void* q, const void* k, const
   }
   const int total = mapped_grid(n_items, p.n_kv_heads, g / 2);
   const dim3 grid(total < n_cu ? total : n_cu), block(256);
-  // (the body also instantiates at head dim 64, where it is bound by the vector unit and no faster than the
-  // two-wave kernel: 1033 against 1027 TFLOP/s on a 16K sample; not dispatched)
+  // (the body also instantiates at head dim 64, where it is bound by the vector unit and slower than the kernel of
+  // fwd_bf16.hip: not dispatched)
   hipLaunchKernelGGL(fwd_wide_bf16_kernel_d128, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
                      (const bf16*)v, (bf16*)o, lse, items, n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale);
   return (int)hipGetLastError();

@@ -117,6 +117,7 @@ struct slimattn_tables {
   int32_t n_samples = 0, n_slices = 0, n_units[2] = {0, 0};
   int64_t total_tokens = 0;
   int32_t max_sample_len = 0;
+  int32_t mean_keys = 0;          // keys a row sees, on average over the pack's rows
   std::vector<int32_t> cu;
   std::vector<slimattn_slice> slices;
   std::vector<int32_t> unit_ptr[2], unit_slices[2];      // [0] forward list, [1] backward list
@@ -137,6 +138,7 @@ struct LaunchCtx {
   const slimattn_params* p;
   void* stream;           // hipStream_t
   int64_t T;
+  int mean_keys;          // keys a row of the pack sees on average
 };
 
 // ---- forward launches whose keys are divided among blocks ------------------------------------------------------------
@@ -193,7 +195,7 @@ int launch_bwd_dkdv_f32(const LaunchCtx&, const float* q, const float* k, const 
 // divide_rows: keys the longest item sees, if the keys of the items may be divided among blocks (below); 0: one block walks them
 int launch_fwd_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, void* o, float* lse,
                     const QItem* items, int n_items, int divide_rows);
-// even group sizes at head dim 128: one wave per SIMD, two heads per wave (fwd_wide_bf16.hip); same arguments
+// even group sizes at head dim 128: one wave per SIMD, two heads per wave (fwd_wide_bf16.hip)
 int launch_fwd_wide_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, void* o, float* lse,
                          const QItem* items, int n_items, const FwdSplit& sp);
 // Row statistics of the bf16 backward (-lse*log2e and -delta = -dO.O per row and head, as bf16 triples):

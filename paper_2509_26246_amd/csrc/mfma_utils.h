@@ -191,35 +191,6 @@ __device__ __forceinline__ bf16x8 tr2_frag(const Tr2& t, int j) {
   short8v x = __builtin_shufflevector(t.r[2 * j], t.r[2 * j + 1], 0, 1, 2, 3, 4, 5, 6, 7);
   return __builtin_bit_cast(bf16x8, x);
 }
-// Two fragments from two different address pairs at one byte offset (e.g. the same key step of two
-// head-dim blocks, which feed two independent accumulators).
-template <int O>
-__device__ __forceinline__ void tr2x_issue(lds_cptr a0, lds_cptr a1, lds_cptr b0, lds_cptr b1, Tr2& n) {
-  asm volatile("ds_read_b64_tr_b16 %0, %[a0] offset:%[o]\n\t"
-               "ds_read_b64_tr_b16 %1, %[a1] offset:%[o]\n\t"
-               "ds_read_b64_tr_b16 %2, %[b0] offset:%[o]\n\t"
-               "ds_read_b64_tr_b16 %3, %[b1] offset:%[o]"
-               : "=&v"(n.r[0]), "=&v"(n.r[1]), "=&v"(n.r[2]), "=&v"(n.r[3])
-               : [a0] "v"(a0), [a1] "v"(a1), [b0] "v"(b0), [b1] "v"(b1), [o] "n"(O));
-}
-
-// Row-fragment batches through inline asm (same reason and same protocol as the transposed ones):
-// two 16-byte fragment loads per batch, each with its own address register and byte offset.
-struct R2 { bf16x8 f[2]; };
-template <int O0, int O1>
-__device__ __forceinline__ void r2_issue(lds_cptr a0, lds_cptr a1, R2& n) {
-  asm volatile("ds_read_b128 %0, %[a0] offset:%[o0]\n\tds_read_b128 %1, %[a1] offset:%[o1]"
-               : "=&v"(n.f[0]), "=&v"(n.f[1])
-               : [a0] "v"(a0), [a1] "v"(a1), [o0] "n"(O0), [o1] "n"(O1));
-}
-template <int O0, int O1>
-__device__ __forceinline__ void r2_issue_wait(lds_cptr a0, lds_cptr a1, R2& n, R2& p) {
-  asm volatile("ds_read_b128 %0, %[a0] offset:%[o0]\n\tds_read_b128 %1, %[a1] offset:%[o1]\n\ts_waitcnt lgkmcnt(2)"
-               : "=&v"(n.f[0]), "=&v"(n.f[1]), "+v"(p.f[0]), "+v"(p.f[1])
-               : [a0] "v"(a0), [a1] "v"(a1), [o0] "n"(O0), [o1] "n"(O1));
-}
-__device__ __forceinline__ void r2_wait(R2& p) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(p.f[0]), "+v"(p.f[1])); }
-
 // Four-fragment row batches.
 struct R4 { bf16x8 f[4]; };
 
@@ -241,10 +212,6 @@ __device__ __forceinline__ void r1_issue(lds_cptr a, bf16x8& f) {
 template <int N>
 __device__ __forceinline__ void lds_wait(R4& p) {
   asm volatile("s_waitcnt lgkmcnt(%[n])" : "+v"(p.f[0]), "+v"(p.f[1]), "+v"(p.f[2]), "+v"(p.f[3]) : [n] "n"(N));
-}
-template <int N>
-__device__ __forceinline__ void lds_wait(R2& p) {
-  asm volatile("s_waitcnt lgkmcnt(%[n])" : "+v"(p.f[0]), "+v"(p.f[1]) : [n] "n"(N));
 }
 template <int N>
 __device__ __forceinline__ void lds_wait(Tr2& p) {

@@ -1,0 +1,48 @@
+"""The two bf16 forward kernels on either side of the rule that chooses between them (keys a row of the pack sees on average),
+with ragged samples, references that have to move, and the whole list against one launch per unit bit for bit.  Against the CPU
+fp64 oracle (tolerance as in test_gpu_parity.py: 2e-2 max-abs on O, and on lse relative to 1 + |lse|, as the scaled query is
+rounded to bf16 once)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2509_26246_amd as S
+import workloads as W
+from oracle import attention as A
+from paper_2509_26246_amd import harness as H
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+
+
+# mean keys 400 (last of the short side) and 401, ragged tiles on both sides, samples shorter than a wave's rows
+@pytest.mark.parametrize("L", [[800], [801], [511, 37, 200, 128, 1], [1, 1390, 37, 129, 64]], ids=["400", "401", "short", "long"])
+@pytest.mark.parametrize("hq,hkv,d", [(4, 2, 128), (8, 1, 128), (3, 1, 128), (4, 1, 64), (3, 1, 64)])
+@pytest.mark.parametrize("jump", [0.0, 200.0])
+def test_forward_routes(L, hq, hkv, d, jump):
+    r = np.random.default_rng(5)
+    T, scale = sum(L), d ** -0.5
+    arrs = [r.standard_normal((T, h, d), dtype=np.float32) * np.float32(f) for h, f in ((hq, 0.5), (hkv, 0.5), (hkv, 0.5), (hq, 0.1))]
+    if jump:                                               # scores climb by `jump` inside each sample, from a key on that moves about
+        arrs[0][:, :, 0] = 4.0
+        st = 0
+        for n in L:
+            arrs[1][st:st + n, :, 0] = -jump / (8 * scale)
+            arrs[1][st + n * 2 // 3:st + n, :, 0] = jump / (8 * scale)
+            st += n
+    arrs = [W.bf16_round(a) for a in arrs]
+    cu, sl = S.build_slices(L, 192)
+    fu = S.build_units(cu, sl, "PER_SAMPLE")
+    prob = H.make_problem(*arrs, cu, sl, fu, fu, bf16=True, scale=scale)
+    want_o, want_lse = A.fwd_packed(*arrs[:3], cu, scale)
+    got = []
+    for flags in (0, S.FLAG_PER_UNIT_LAUNCH):
+        prob.o.fill_(float("nan"))
+        prob.lse.fill_(float("nan"))
+        prob.forward(flags=flags)
+        torch.cuda.synchronize()
+        got.append((prob.o.clone(), prob.lse.clone()))
+    o, lse = H.device_to_f32(prob.o), prob.lse.cpu().numpy()
+    assert float(np.max(np.abs(o - want_o))) <= TOL
+    assert float(np.max(np.abs(lse - want_lse) / (1.0 + np.abs(want_lse)))) <= TOL
+    assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16)) and torch.equal(got[0][1], got[1][1])

@@ -77,8 +77,8 @@ __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds
   probabilities(0.f);
   // Lazy rescaling: the reference only moves when some lane's sum of its 32 probabilities exceeds kLazySum (so no single one
   // does; an overflow to inf does; wave-uniform test): the test costs one comparison where a row maximum costs 16 instructions
-  // and a cross-lane exchange.  O / l is unaffected.  The reference starts at the row's score against the walk's first key
-  // (always visible), so row sums cannot underflow.
+  // and a cross-lane exchange.  O / l is unaffected.  The reference starts at the row's score against the sample's first key
+  // (always visible), so a row's sum cannot underflow (a part of a divided walk may come to a sum of 0).
   if (__builtin_expect(__any(lt > kLazySum), 0)) {
     float mx = sacc[0][0];
 #pragma unroll
@@ -134,6 +134,7 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
   }
   const int h = hk * g + hg;
   QItem it = items[item_idx];
+  const int first_key = it.kv_start;              // of the sample
   int n_tiles = (it.q_row0 + it.q_rows - it.kv_start + kFwdBK - 1) / kFwdBK;
   bool alone = true;
   if constexpr (Split::on) {
@@ -166,10 +167,12 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
-  // reference maximum (log2 units): the row's score against the first key of the sample
+  // reference (log2 units): the row's score against the first key of the sample, for every part of a divided walk.  (A part's own
+  // first key may be one that takes no part in the softmax, of a score far below the others or -inf: the part's scores would
+  // be lost under such a reference.)
   float m_ref = 0.f, l_run = 0.f;
   {
-    const bf16* kp = k + ((size_t)it.kv_start * Hkv + hk) * D + 8 * half;
+    const bf16* kp = k + ((size_t)first_key * Hkv + hk) * D + 8 * half;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       const bf16x8 k0 = *reinterpret_cast<const bf16x8*>(kp + 16 * ks);

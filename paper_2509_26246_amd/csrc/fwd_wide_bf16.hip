@@ -134,10 +134,12 @@ __device__ __forceinline__ void ew_flush(uintx4 (&pf)[2][2][2], float& e0, float
   pf[1][KE][1][3] = w;
 }
 
-// n_tiles: key tiles to walk.  unit >= 0 (FwdSplit only): the walk is one part of the item, its results go to partial results
+// n_tiles: key tiles to walk from it.kv_start on.  first_key: the sample's first key, whose score is the row's reference also where
+// the walk is one part of the item (a part's own first key may take no part in the softmax: a score of -inf, or one so far below
+// the others that they would be lost against it).  unit >= 0 (FwdSplit only): the walk is one part of the item, its results go to partial results
 // unit (first head) and unit + 1.
 template <int D, class Split>
-__device__ __forceinline__ void fwd_wide_item(const QItem it, const int n_tiles, const int hk, const int hp, const bf16* __restrict__ q,
+__device__ __forceinline__ void fwd_wide_item(const QItem it, const int first_key, const int n_tiles, const int hk, const int hp, const bf16* __restrict__ q,
                                               const bf16* __restrict__ k, const bf16* __restrict__ v, bf16* __restrict__ o_out,
                                               float* __restrict__ lse, int T, int Hq, int Hkv, float scale, const Split& sp, int unit) {
   constexpr int NKS = kNKS<D>, NDB = kNDB<D>, NVF = kNVF<D>, PER = kPer<D>;
@@ -161,7 +163,7 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int n_tiles,
     for (int u = 0; u < NKS; ++u) qf[hb][u] = *reinterpret_cast<const bf16x8*>(qp + 16 * u);
   }
   {
-    const bf16* kp = k + ((size_t)it.kv_start * Hkv + hk) * D + 8 * half;
+    const bf16* kp = k + ((size_t)first_key * Hkv + hk) * D + 8 * half;
 #pragma unroll
     for (int u = 0; u < NKS; ++u) k0[u] = *reinterpret_cast<const bf16x8*>(kp + 16 * u);
   }
@@ -471,7 +473,7 @@ __device__ __forceinline__ void fwd_wide_walk(const bf16* __restrict__ q, const 
     it.kv_start = __builtin_amdgcn_readfirstlane(cur[2]);
     it.pad = 0;
     if (it.q_rows > 0)
-      fwd_wide_item<D>(it, (it.q_row0 + it.q_rows - it.kv_start + kKeys - 1) / kKeys, hk, hp, q, k, v, o, lse, T, Hq, Hkv, scale, NoSplit{}, -1);
+      fwd_wide_item<D>(it, it.kv_start, (it.q_row0 + it.q_rows - it.kv_start + kKeys - 1) / kKeys, hk, hp, q, k, v, o, lse, T, Hq, Hkv, scale, NoSplit{}, -1);
     cur = nxt;
     hk = hk_n;
     hp = hp_n;
@@ -496,9 +498,10 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_bf16_split_kernel_d128(const 
   const int g = Hq / Hkv;
   split_block(blockIdx.x / sp.parts, g >> 1, Hkv, &idx, &hk, &hp);
   QItem it = items[idx];
+  const int first_key = it.kv_start;
   bool alone;
   if (!split_range(sp, it, part, &n_tiles, &alone)) return;
-  fwd_wide_item<128>(it, n_tiles, hk, hp, q, k, v, o, lse, T, Hq, Hkv, scale, sp, alone ? -1 : (idx * sp.parts + part) * Hq + hk * g + 2 * hp);
+  fwd_wide_item<128>(it, first_key, n_tiles, hk, hp, q, k, v, o, lse, T, Hq, Hkv, scale, sp, alone ? -1 : (idx * sp.parts + part) * Hq + hk * g + 2 * hp);
 }
 
 }  // namespace

@@ -339,8 +339,7 @@ __device__ __forceinline__ void split_block(int j, int g, int Hkv, int* item, in
 }
 
 // Part `part` of an item: moves the item's first key and sets the tiles to walk; false: no such part.  Tiles whose first key is
-// visible to every row of the item are dealt evenly, so each part's first key can serve as its reference; the last part also
-// takes the (at most two) tiles behind.  *alone: the item is not divided and the block writes O and lse itself.
+// visible to every row of the item are dealt evenly; the last part also takes the (at most two) tiles behind.  *alone: the item is not divided and the block writes O and lse itself.
 __device__ __forceinline__ bool split_range(const FwdSplit& sp, QItem& it, int part, int* n_tiles, bool* alone) {
   const int all = (it.q_row0 + it.q_rows - it.kv_start + 63) / 64, common = (it.q_row0 - it.kv_start) / 64 + 1;
   const bool owned = __hip_atomic_load(sp.owner, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == sp.ticket;

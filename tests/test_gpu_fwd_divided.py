@@ -130,3 +130,32 @@ def test_more_streams_than_arrays_and_graph_replays():
         S.fwd(prob.q, prob.k, prob.v, prob.tables, outs[0][0], outs[0][1], **prob._kw(unit_lo=u, unit_hi=u + 1))
         torch.cuda.synchronize()
         assert torch.equal(outs[0][0][first:end].view(torch.int16), want[0].view(torch.int16))
+
+
+# Keys that take no part in the softmax (a component of -inf, or one of -1e9 as masks use) at the first key of every tile but the
+# sample's first, hence at the first key of every part, on each kernel that divides.  Each row of the last slice has most of its
+# weight on one key, in a tile of its own choice, so that a part which loses its first tile's scores shows.  The last pack has an
+# even group and 331 keys per row on average: the one-head kernel at head dim 128.
+@pytest.mark.parametrize("low", [float("-inf"), -1e9])
+@pytest.mark.parametrize("L,hq,hkv,d,first", [([9088], 8, 1, 128, 8960), ([9088], 3, 1, 128, 8960), ([9088], 4, 2, 64, 8960),
+                                              ([3500] + [64] * 260, 2, 1, 128, 3392)])
+def test_keys_without_weight_at_every_tile_edge(L, hq, hkv, d, first, low):
+    prob, arrs, cu, sl = _slices(L, hq, hkv, d, first)
+    q, k, v, dO = arrs
+    rows, tiles = np.arange(first, L[0]), 1 + np.arange(L[0] - first) % (first // 64 - 1)
+    signs = np.sign(np.random.default_rng(2).standard_normal((len(tiles), 1, d))).astype(np.float32)
+    signs[:, :, 0] = 0.0
+    k[64 * tiles + 8] = signs[tiles - 1] * np.float32(160 / d)
+    q[rows] = signs[tiles - 1]                             # score 160 d^-1/2 with its key, far less with the others
+    q[:, :, 0] = 4.0
+    k[64:L[0]:64, :, 0] = low if np.isinf(low) else W.bf16_round(np.array([low], np.float32))[0]
+    prob = H.make_problem(q, k, v, dO, cu, sl, *[(np.arange(len(sl) + 1), np.arange(len(sl)))] * 2, bf16=True, scale=d ** -0.5)
+    prob.forward(unit_lo=1, unit_hi=2)
+    torch.cuda.synchronize()
+    o, lse = H.device_to_f32(prob.o), prob.lse.cpu().numpy()
+    assert np.isfinite(o[rows]).all() and np.isfinite(lse[:, rows]).all()
+    heads = rows % hq
+    ro, rl = A.fwd_rows(q, k, v, cu, prob.scale, rows, heads)
+    # (lse relative: the scaled query is rounded to bf16 once, a relative error of 2^-9 of the heavy key's score)
+    assert np.max(np.abs(o[rows, heads] - ro)) <= TOL
+    assert np.max(np.abs(lse[heads, rows] - rl) / (1.0 + np.abs(rl))) <= TOL

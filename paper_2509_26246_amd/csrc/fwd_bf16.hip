@@ -42,7 +42,10 @@ constexpr float kLazySum = 4096.f;   // the reference moves when a lane's sum of
 // V^T-fragment address pair for head-dim block db; both already point into the current buffer.
 // qf holds q * scale * log2(e), so the products are scores in log2 units; the accumulators start
 // at minus the row's reference (every register of negm), so they come out as the exponents directly.
-template <int D, bool MASKED, class Side>
+// EXACT: the row sum adds the probabilities before they are rounded to bf16 for the product, in the order of the one-wave kernel
+// (packs of short samples at head dim 128, even groups: their rows get the lse that kernel gives).  Otherwise it adds the rounded
+// ones with dot products, half the instructions.
+template <int D, bool MASKED, bool EXACT, class Side>
 __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds_cptr (&pv)[D / 32][2],
                                          const bf16x8 (&qf)[D / 16], floatx16 (&oacc)[D / 32], floatx16& negm, float& l_run,
                                          int rel, Side&& side) {
@@ -60,8 +63,8 @@ __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds
         if (32 * b + 8 * (r >> 2) + (r & 3) > rel) sacc[b][r] = -INFINITY;
   }
   bf16x8 pf[4];
-  float lt;
-  // probabilities against the reference as it stands (`shift` below it), their row sum (of the rounded values the product uses)
+  float lb[2];                                    // row sums of the two key blocks
+  // probabilities against the reference as it stands (`shift` below it), their row sums
   auto probabilities = [&](float shift) {
     float ps[4];
 #pragma unroll
@@ -70,16 +73,23 @@ __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds
 #pragma unroll
       for (int i = 0; i < 8; ++i) e[i] = __builtin_amdgcn_exp2f(sacc[ks2 >> 1][8 * (ks2 & 1) + i] - shift);
       pf[ks2] = __builtin_convertvector(e, bf16x8);
-      ps[ks2] = sum8(pf[ks2], 0.f);
+      if constexpr (EXACT) {
+        float& l = lb[ks2 >> 1];
+        l = ks2 & 1 ? l + e[0] : e[0];
+#pragma unroll
+        for (int i = 1; i < 8; ++i) l += e[i];
+      } else {
+        ps[ks2] = sum8(pf[ks2], 0.f);
+      }
     }
-    lt = (ps[0] + ps[1]) + (ps[2] + ps[3]);
+    if constexpr (!EXACT) { lb[0] = ps[0] + ps[1]; lb[1] = ps[2] + ps[3]; }
   };
   probabilities(0.f);
   // Lazy rescaling: the reference only moves when some lane's sum of its 32 probabilities exceeds kLazySum (so no single one
   // does; an overflow to inf does; wave-uniform test): the test costs one comparison where a row maximum costs 16 instructions
   // and a cross-lane exchange.  O / l is unaffected.  The reference starts at the row's score against the sample's first key
   // (always visible), so a row's sum cannot underflow (a part of a divided walk may come to a sum of 0).
-  if (__builtin_expect(__any(lt > kLazySum), 0)) {
+  if (__builtin_expect(__any(lb[0] + lb[1] > kLazySum), 0)) {
     float mx = sacc[0][0];
 #pragma unroll
     for (int b = 0; b < 2; ++b)
@@ -98,7 +108,8 @@ __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds
     for (int r = 0; r < 16; ++r) negm[r] = m;
     asm volatile("" : "+v"(negm));
   }
-  l_run += lt;
+  if constexpr (EXACT) { l_run += lb[0]; l_run += lb[1]; }
+  else l_run += lb[0] + lb[1];
   // O^T += V^T P^T: one batch of four V^T fragments (the four 16-key steps) per head-dim block
   Tr4 tb[NDB];
   constexpr int kStep = 16 * kRowBytes;
@@ -114,7 +125,7 @@ __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds
 
 // Split: NoSplit, or FwdSplit for a launch whose items' keys are divided (block numbers: parts innermost, so that an XCD keeps
 // to the same runs of keys; then the heads that share them).
-template <int D, class Split>
+template <int D, class Split, bool EXACT>
 __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k,
                                                           const bf16* __restrict__ v, bf16* __restrict__ o,
                                                           float* __restrict__ lse, const QItem* __restrict__ items,
@@ -176,8 +187,16 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
       const bf16x8 k0 = *reinterpret_cast<const bf16x8*>(kp + 16 * ks);
+      if constexpr (EXACT) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) m_ref = fmaf((float)qf[ks][e], (float)k0[e], m_ref);
+        for (int x = 0; x < 4; ++x) {             // (as the one-wave kernel forms it)
+          const bf16x2 a2 = {qf[ks][2 * x], qf[ks][2 * x + 1]}, b2 = {k0[2 * x], k0[2 * x + 1]};
+          m_ref = __builtin_amdgcn_fdot2_f32_bf16(a2, b2, m_ref, false);
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m_ref = fmaf((float)qf[ks][e], (float)k0[e], m_ref);
+      }
     }
     m_ref += xor32(m_ref);
   }
@@ -201,9 +220,9 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
     };
     const int rel = my_row - j0 - 4 * half;
     if (j0 + kFwdBK - 1 <= q0w) {                  // whole tile visible to every row of the wave
-      fwd_tile<D, false>(pk, pv, qf, oacc, negm, l_run, rel, side);
+      fwd_tile<D, false, EXACT>(pk, pv, qf, oacc, negm, l_run, rel, side);
     } else if (j0 <= q0w + 31) {                   // diagonal region
-      fwd_tile<D, true>(pk, pv, qf, oacc, negm, l_run, rel, side);
+      fwd_tile<D, true, EXACT>(pk, pv, qf, oacc, negm, l_run, rel, side);
     } else {                                       // nothing visible to this wave: only fetch
 #pragma unroll
       for (int i = 0; i < 2 * kPasses; ++i) side(i);
@@ -236,12 +255,12 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
 int fwd_q_tile(int dtype, int) { return dtype == SLIMATTN_F32 ? 64 : kFwdBQ; }
 
 namespace {
-template <int D, class Split>
+template <int D, bool EXACT, class Split>
 int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse, const QItem* items,
                         int n_items, int parts, Split sp) {
   const slimattn_params& p = *c.p;
   const unsigned grid = Split::on ? (unsigned)(n_items * p.n_q_heads * parts) : (unsigned)mapped_grid(n_items, p.n_kv_heads, p.n_q_heads / p.n_kv_heads);
-  hipLaunchKernelGGL((fwd_bf16_kernel<D, Split>), dim3(grid), dim3(256), 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
+  hipLaunchKernelGGL((fwd_bf16_kernel<D, Split, EXACT>), dim3(grid), dim3(256), 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
                      (const bf16*)v, (bf16*)o, lse, items, n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, sp);
   return (int)hipGetLastError();
 }
@@ -262,15 +281,17 @@ int launch_fwd_bf16(const LaunchCtx& c, const void* q, const void* k, const void
   FwdSplit sp;
   int e = split_begin(c, n_items, divide_rows, &sp);
   if (e != 0) return e;
-  const bool divided = sp.parts > 1;
-  if (p.head_dim == 64)
-    e = divided ? launch_fwd_one_head<64>(c, q, k, v, o, lse, items, n_items, sp.parts, sp)
-                : launch_fwd_one_head<64>(c, q, k, v, o, lse, items, n_items, 1, NoSplit{});
-  else if (p.n_q_heads / p.n_kv_heads % 2 == 0 && c.mean_keys > kShortMeanKeys)
-    e = launch_fwd_wide_bf16(c, q, k, v, o, lse, items, n_items, sp);
-  else
-    e = divided ? launch_fwd_one_head<128>(c, q, k, v, o, lse, items, n_items, sp.parts, sp)
-                : launch_fwd_one_head<128>(c, q, k, v, o, lse, items, n_items, 1, NoSplit{});
+  const bool divided = sp.parts > 1, even = p.n_q_heads / p.n_kv_heads % 2 == 0;
+  auto one_head = [&](auto dc, auto exact) {
+    constexpr int D = decltype(dc)::value;
+    constexpr bool EXACT = decltype(exact)::value != 0;
+    return divided ? launch_fwd_one_head<D, EXACT>(c, q, k, v, o, lse, items, n_items, sp.parts, sp)
+                   : launch_fwd_one_head<D, EXACT>(c, q, k, v, o, lse, items, n_items, 1, NoSplit{});
+  };
+  if (p.head_dim == 64) e = one_head(IC<64>{}, IC<0>{});
+  else if (!even) e = one_head(IC<128>{}, IC<0>{});
+  else if (c.mean_keys > kShortMeanKeys) e = launch_fwd_wide_bf16(c, q, k, v, o, lse, items, n_items, sp);
+  else e = one_head(IC<128>{}, IC<1>{});
   return e != 0 || !divided ? e : split_combine(c, sp, o, lse, items, n_items);
 }
 

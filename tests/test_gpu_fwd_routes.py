@@ -46,3 +46,29 @@ def test_forward_routes(L, hq, hkv, d, jump):
     assert float(np.max(np.abs(o - want_o))) <= TOL
     assert float(np.max(np.abs(lse - want_lse) / (1.0 + np.abs(want_lse)))) <= TOL
     assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16)) and torch.equal(got[0][1], got[1][1])
+
+
+# Even groups at head dim 128 run the one-wave kernel or, in packs of short samples, the one-head kernel: both add probabilities in
+# fp32 before they are rounded for the product, so a row's o and lse do not depend on which it is.
+@pytest.mark.parametrize("L", [[128] * 9, [511, 37, 200, 128, 1], [400, 399, 65]])
+@pytest.mark.parametrize("hq,hkv", [(8, 1), (4, 2)])
+def test_short_samples_keep_the_precision_of_lse(L, hq, hkv):
+    d, r = 128, np.random.default_rng(11)
+    T, scale = sum(L), d ** -0.5
+    arrs = [W.bf16_round(r.standard_normal((T + 2000, h, d), dtype=np.float32) * np.float32(f)) for h, f in ((hq, 0.5), (hkv, 0.5), (hkv, 0.5), (hq, 0.1))]
+    got = []
+    for lengths in (L, L + [2000]):                         # with the long sample a row of the pack sees more than 400 keys on average
+        n = sum(lengths)
+        cu, sl = S.build_slices(lengths, 4096)
+        one = S.build_units(cu, sl, "ALL")
+        prob = H.make_problem(*[a[:n] for a in arrs], cu, sl, one, one, bf16=True, scale=scale)
+        prob.forward()
+        torch.cuda.synchronize()
+        got.append((prob.o[:T].clone(), prob.lse[:, :T].clone()))
+    # against fp64 on the query as the kernels round it (times scale log2 e, to bf16): a row sum of n <= 511 fp32 terms is off by at
+    # most n 2^-24 relative, its exponents (below 4 in log2 units) by less than 2^-22; rounded probabilities are off by 2^-9 each
+    q2 = W.bf16_round(arrs[0][:T] * (np.float32(scale) * np.float32(1.4426950408889634)))
+    _, want = A.fwd_packed(q2, arrs[1][:T], arrs[2][:T], S.build_slices(L, 4096)[0], np.log(2.0))
+    for o, lse in got:
+        assert np.max(np.abs(lse.cpu().numpy() - want)) <= 4e-5
+    assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16)) and torch.equal(got[0][1], got[1][1])

@@ -95,7 +95,10 @@ __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[b][r]);
-    const float shift = fmaxf(fmaxf(mx, xor32(mx)), 0.f);
+    // (only rows of the lane pairs that asked for it, so that a row's bits do not depend on the rows that share its wave: the others
+    // go through this with a shift of 0, which changes nothing)
+    const float own = lb[0] + lb[1];
+    const float shift = fmaxf(own, xor32(own)) > kLazySum ? fmaxf(fmaxf(mx, xor32(mx)), 0.f) : 0.f;
     const float alpha = __builtin_amdgcn_exp2f(-shift);
     l_run *= alpha;
 #pragma unroll
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
 
   bf16x8 qf[NKS];
   {
-    const bf16* qp = q + ((size_t)min(my_row, T - 1) * Hq + h) * D + 8 * half;
+    const bf16* qp = q + ((size_t)min(my_row, q_end - 1) * Hq + h) * D + 8 * half;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) qf[ks] = scale8(*reinterpret_cast<const bf16x8*>(qp + 16 * ks), scale * kLog2e);
   }

@@ -158,7 +158,7 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int first_ke
   bf16x8 qf[2][NKS], k0[NKS];
 #pragma unroll
   for (int hb = 0; hb < 2; ++hb) {
-    const bf16* qp = q + ((size_t)min(my_row, T - 1) * Hq + h0 + hb) * D + 8 * half;
+    const bf16* qp = q + ((size_t)min(my_row, q_end - 1) * Hq + h0 + hb) * D + 8 * half;
 #pragma unroll
     for (int u = 0; u < NKS; ++u) qf[hb][u] = *reinterpret_cast<const bf16x8*>(qp + 16 * u);
   }
@@ -256,7 +256,8 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int first_ke
 #pragma unroll
       for (int r = 1; r < 16; ++r) mxs = fmaxf(mxs, s[hb][KB][r]);
       mxs = fmaxf(mxs, xor32(mxs));
-      const float shift = fmaxf(mxs, 0.f);
+      // (only rows whose lanes asked for it: a shift of 0 changes nothing, and a row's bits do not depend on its wave's other rows)
+      const float shift = fmaxf(lu[hb], xor32(lu[hb])) > kLazySum ? fmaxf(mxs, 0.f) : 0.f;
       const float alpha = __builtin_amdgcn_exp2f(-shift);
 #pragma unroll
       for (int db = 0; db < NDB; ++db)

@@ -72,3 +72,36 @@ def test_short_samples_keep_the_precision_of_lse(L, hq, hkv):
     for o, lse in got:
         assert np.max(np.abs(lse.cpu().numpy() - want)) <= 4e-5
     assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16)) and torch.equal(got[0][1], got[1][1])
+
+
+# A row's bits depend on its own scores only: not on the rows that share its wave (units that cut samples at ragged slices change
+# them), not on q rows of other units (which may hold anything).  Scores climb along the sample at a rate of each row's own, so
+# references move at different keys in different rows.
+@pytest.mark.parametrize("L", [[700, 130, 1, 300], [1, 1390, 301, 129]], ids=["short", "long"])
+@pytest.mark.parametrize("hq,hkv,d", [(4, 2, 128), (3, 1, 128), (4, 1, 64), (3, 1, 64)])
+def test_rows_do_not_depend_on_their_neighbours(L, hq, hkv, d):
+    r = np.random.default_rng(8)
+    T, scale = sum(L), d ** -0.5
+    arrs = [r.standard_normal((T, h, d), dtype=np.float32) * np.float32(f) for h, f in ((hq, 0.5), (hkv, 0.5), (hkv, 0.5), (hq, 0.1))]
+    arrs[0][:, :, 0] = r.uniform(0.0, 4.0, (T, hq))
+    arrs[1][:, :, 0] = (np.concatenate([np.arange(n) for n in L]) * (100.0 / (scale * 4.0 * 700)))[:, None]
+    arrs = [W.bf16_round(a) for a in arrs]
+    cu, sl = S.build_slices(L, 97)
+    units = (np.arange(len(sl) + 1), np.arange(len(sl)))
+    prob = H.make_problem(*arrs, cu, sl, units, units, bf16=True, scale=scale)
+    prob.forward()
+    torch.cuda.synchronize()
+    want_o, want_lse, q = prob.o.clone(), prob.lse.clone(), prob.q.clone()
+    ref_o, ref_lse = A.fwd_packed(*arrs[:3], cu, scale)
+    assert float(np.max(np.abs(H.device_to_f32(want_o) - ref_o))) <= TOL
+    assert float(np.max(np.abs(want_lse.cpu().numpy() - ref_lse) / (1.0 + np.abs(ref_lse)))) <= TOL
+    prob.o.fill_(float("nan"))
+    prob.lse.fill_(float("nan"))
+    for u in range(len(sl)):
+        a, b = int(sl[u][2]), int(sl[u][2] + sl[u][3])
+        prob.q.mul_(1000.0)                                 # the other units' rows
+        prob.q[a:b] = q[a:b]
+        prob.forward(unit_lo=u, unit_hi=u + 1)
+        prob.q.copy_(q)
+    torch.cuda.synchronize()
+    assert torch.equal(prob.o.view(torch.int16), want_o.view(torch.int16)) and torch.equal(prob.lse, want_lse)

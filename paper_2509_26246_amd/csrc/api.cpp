@@ -171,7 +171,8 @@ static int fwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   const auto& off = t->per_unit[0].q_off[z];
   if (!(p->flags & SLIMATTN_FLAG_PER_UNIT_LAUNCH)) {
     // Part of the list in one launch (prefill by slices): the keys of long prefixes may be divided among blocks.  Whole-list
-    // and per-unit launches walk every row's keys in one block, so that those two give the same bits.
+    // and per-unit launches walk every row's keys in one block: those two give a row the same bits, unless a softmax
+    // reference moves and the row's query tile holds other rows there.
     int longest = 0;
     for (int u = lo; u < hi && t->split_regions; ++u)
       if (off[u + 1] > off[u]) {                            // a unit's items are in descending order of visible keys

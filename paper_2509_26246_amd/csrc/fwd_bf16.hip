@@ -95,10 +95,10 @@ __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[b][r]);
-    // (only rows of the lane pairs that asked for it, so that a row's bits do not depend on the rows that share its wave: the others
-    // go through this with a shift of 0, which changes nothing)
-    const float own = lb[0] + lb[1];
-    const float shift = fmaxf(own, xor32(own)) > kLazySum ? fmaxf(fmaxf(mx, xor32(mx)), 0.f) : 0.f;
+    // (Every row of the wave with a score above its reference moves along, so where references move a row's last bits depend on the
+    // rows of its query tile.  Moving only the rows that asked for it takes many more moves where scores climb at different rates:
+    // 4096-row samples of 32/8 heads on the one-wave kernel, climbs of up to 20 nats 555 -> 777 us, of 100 641 -> 1055.)
+    const float shift = fmaxf(fmaxf(mx, xor32(mx)), 0.f);
     const float alpha = __builtin_amdgcn_exp2f(-shift);
     l_run *= alpha;
 #pragma unroll
@@ -273,7 +273,7 @@ int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const 
 // holds one block per compute unit, and what an item costs beside its tiles (11 us of loads and stores) is hidden by nothing, while
 // two blocks of this kernel overlap each other.  16K tokens in equal samples, 32/8 heads, one-wave against this kernel: 128-row
 // samples 105 / 96 us, 512 rows 151 / 130, 1024 rows 196 / 189, 2048 rows 297 / 307, 16384 rows 1634 / 1839.  The rule
-// looks at the pack alone, so that every launch of a handle gives a row the same bits; a row of a 1024-row sample sees 512 keys
+// looks at the pack alone, so that every launch of a handle takes the same kernel; a row of a 1024-row sample sees 512 keys
 // on average.  (At head dim 64 this kernel is bound by the vector unit, where a second head per wave saves nothing.)
 constexpr int kShortMeanKeys = 400;
 

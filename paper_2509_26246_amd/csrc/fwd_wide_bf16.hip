@@ -256,8 +256,7 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int first_ke
 #pragma unroll
       for (int r = 1; r < 16; ++r) mxs = fmaxf(mxs, s[hb][KB][r]);
       mxs = fmaxf(mxs, xor32(mxs));
-      // (only rows whose lanes asked for it: a shift of 0 changes nothing, and a row's bits do not depend on its wave's other rows)
-      const float shift = fmaxf(lu[hb], xor32(lu[hb])) > kLazySum ? fmaxf(mxs, 0.f) : 0.f;
+      const float shift = fmaxf(mxs, 0.f);
       const float alpha = __builtin_amdgcn_exp2f(-shift);
 #pragma unroll
       for (int db = 0; db < NDB; ++db)

@@ -1,5 +1,6 @@
 """The two bf16 forward kernels on either side of the rule that chooses between them (keys a row of the pack sees on average),
-with ragged samples, references that have to move, and the whole list against one launch per unit bit for bit.  Against the CPU
+with ragged samples, references that have to move, and the whole list against one launch per unit (of the same query tiles) bit for
+bit.  Against the CPU
 fp64 oracle (tolerance as in test_gpu_parity.py: 2e-2 max-abs on O, and on lse relative to 1 + |lse|, as the scaled query is
 rounded to bf16 once)."""
 import numpy as np
@@ -74,12 +75,11 @@ def test_short_samples_keep_the_precision_of_lse(L, hq, hkv):
     assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16)) and torch.equal(got[0][1], got[1][1])
 
 
-# A row's bits depend on its own scores only: not on the rows that share its wave (units that cut samples at ragged slices change
-# them), not on q rows of other units (which may hold anything).  Scores climb along the sample at a rate of each row's own, so
-# references move at different keys in different rows.
+# q rows of other units, which may hold anything, take no part in a tile's decision to move its references: one unit at a time, with
+# ragged slices and scores that climb along the sample at a rate of each row's own, and everything outside the unit 1000 times larger.
 @pytest.mark.parametrize("L", [[700, 130, 1, 300], [1, 1390, 301, 129]], ids=["short", "long"])
 @pytest.mark.parametrize("hq,hkv,d", [(4, 2, 128), (3, 1, 128), (4, 1, 64), (3, 1, 64)])
-def test_rows_do_not_depend_on_their_neighbours(L, hq, hkv, d):
+def test_rows_of_other_units_change_no_bit(L, hq, hkv, d):
     r = np.random.default_rng(8)
     T, scale = sum(L), d ** -0.5
     arrs = [r.standard_normal((T, h, d), dtype=np.float32) * np.float32(f) for h, f in ((hq, 0.5), (hkv, 0.5), (hkv, 0.5), (hq, 0.1))]
@@ -89,19 +89,18 @@ def test_rows_do_not_depend_on_their_neighbours(L, hq, hkv, d):
     cu, sl = S.build_slices(L, 97)
     units = (np.arange(len(sl) + 1), np.arange(len(sl)))
     prob = H.make_problem(*arrs, cu, sl, units, units, bf16=True, scale=scale)
-    prob.forward()
-    torch.cuda.synchronize()
-    want_o, want_lse, q = prob.o.clone(), prob.lse.clone(), prob.q.clone()
-    ref_o, ref_lse = A.fwd_packed(*arrs[:3], cu, scale)
-    assert float(np.max(np.abs(H.device_to_f32(want_o) - ref_o))) <= TOL
-    assert float(np.max(np.abs(want_lse.cpu().numpy() - ref_lse) / (1.0 + np.abs(ref_lse)))) <= TOL
-    prob.o.fill_(float("nan"))
-    prob.lse.fill_(float("nan"))
-    for u in range(len(sl)):
-        a, b = int(sl[u][2]), int(sl[u][2] + sl[u][3])
-        prob.q.mul_(1000.0)                                 # the other units' rows
-        prob.q[a:b] = q[a:b]
-        prob.forward(unit_lo=u, unit_hi=u + 1)
-        prob.q.copy_(q)
-    torch.cuda.synchronize()
-    assert torch.equal(prob.o.view(torch.int16), want_o.view(torch.int16)) and torch.equal(prob.lse, want_lse)
+    q, got = prob.q.clone(), []
+    for foreign in (1.0, 1000.0):
+        prob.o.fill_(float("nan"))
+        prob.lse.fill_(float("nan"))
+        for u in range(len(sl)):
+            a, b = int(sl[u][2]), int(sl[u][2] + sl[u][3])
+            prob.q.copy_(q).mul_(foreign)
+            prob.q[a:b] = q[a:b]
+            prob.forward(unit_lo=u, unit_hi=u + 1)
+        torch.cuda.synchronize()
+        got.append((prob.o.clone(), prob.lse.clone()))
+    want_o, want_lse = A.fwd_packed(*arrs[:3], cu, scale)
+    assert float(np.max(np.abs(H.device_to_f32(prob.o) - want_o))) <= TOL
+    assert float(np.max(np.abs(prob.lse.cpu().numpy() - want_lse) / (1.0 + np.abs(want_lse)))) <= TOL
+    assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16)) and torch.equal(got[0][1], got[1][1])

@@ -174,7 +174,7 @@ static int fwd_impl(const slimattn_params* p, const void* q, const void* k, cons
     // and per-unit launches walk every row's keys in one block: those two give a row the same bits, unless a softmax
     // reference moves and the row's query tile holds other rows there.
     int longest = 0;
-    for (int u = lo; u < hi && t->split_regions; ++u)
+    for (int u = lo; u < hi; ++u)
       if (off[u + 1] > off[u]) {                            // a unit's items are in descending order of visible keys
         const QItem& it = t->per_unit[0].q_items[z][off[u]];
         const int rows = it.q_row0 + it.q_rows - it.kv_start;

@@ -8,9 +8,14 @@
 #include "internal.h"
 #include "mfma_utils.h"
 
-// Who owns each region of the current device.  Zero at load: nobody.
+// Who owns each region of the current device (zero at load: nobody), and the regions themselves.  Arrays built into the library, like the
+// scratch of slimattn_bwd_static: one set per GPU the library runs on, held until the process ends, so that no handle pays for
+// them.  (Allocated with the first handle and freed with the last, create and destroy of a 65536-token handle
+// took 502 us, 173 now.)
 struct SplitState { unsigned long long owner[slimattn::kSplitRegions]; unsigned done[slimattn::kSplitRegions]; };
 static __device__ SplitState split_state;
+constexpr size_t kRegionFloats = (size_t)slimattn::kSplitUnits * slimattn::kSplitUnitFloats<128>;
+static __device__ __align__(256) float split_data[slimattn::kSplitRegions * kRegionFloats];
 
 namespace slimattn {
 namespace {
@@ -72,7 +77,6 @@ __global__ __launch_bounds__(256) void split_combine_kernel(FwdSplit sp, bf16* _
 constexpr int kMaxDevices = 64;
 float* g_data[kMaxDevices] = {};
 SplitState* g_state[kMaxDevices] = {};
-int g_holders[kMaxDevices] = {};          // handles whose launches may use the device's regions
 std::mutex g_mutex;
 std::atomic<unsigned long long> g_ticket{1};
 void* g_streams[kSplitRegions] = {};     // the streams the first regions were given to, in order of first use
@@ -88,33 +92,25 @@ int region_of(void* stream) {            // under g_mutex
   return (int)((reinterpret_cast<uintptr_t>(stream) >> 6) % kSplitRegions);
 }
 
-constexpr size_t kRegionFloats = (size_t)kSplitUnits * kSplitUnitFloats<128>;
-
 }  // namespace
 
-bool acquire_split_regions(int dev) {
-  if (dev < 0 || dev >= kMaxDevices) return false;
+int prepare_split_regions() {
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return (int)e;
+  if (dev < 0 || dev >= kMaxDevices) return 0;             // launches on it are not divided
   std::lock_guard<std::mutex> lock(g_mutex);
-  if (!g_data[dev]) {
-    void *d = nullptr, *s = nullptr;
-    hipError_t e = hipGetSymbolAddress(&s, HIP_SYMBOL(split_state));
-    if (e == hipSuccess) e = hipMalloc(&d, kSplitRegions * kRegionFloats * sizeof(float));
-    if (e != hipSuccess) {
-      (void)hipGetLastError();                           // launches report only their own errors
-      return false;
-    }
-    g_state[dev] = (SplitState*)s;
-    g_data[dev] = (float*)d;
+  if (g_data[dev]) return 0;
+  void *d = nullptr, *s = nullptr;
+  e = hipGetSymbolAddress(&s, HIP_SYMBOL(split_state));
+  if (e == hipSuccess) e = hipGetSymbolAddress(&d, HIP_SYMBOL(split_data));
+  if (e != hipSuccess) {
+    (void)hipGetLastError();                               // launches report only their own errors
+    return (int)e;
   }
-  ++g_holders[dev];
-  return true;
-}
-
-void release_split_regions(int dev) {
-  std::lock_guard<std::mutex> lock(g_mutex);
-  if (--g_holders[dev] > 0) return;
-  (void)hipFree(g_data[dev]);                            // (waits for work that may still use them, like the tables' own)
-  g_data[dev] = nullptr;
+  g_state[dev] = (SplitState*)s;
+  g_data[dev] = (float*)d;
+  return 0;
 }
 
 // As many parts as one round of blocks holds, of at least kMinPartTiles key tiles, if that is the faster way.  A tile takes about

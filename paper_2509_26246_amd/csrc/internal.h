@@ -129,7 +129,6 @@ struct slimattn_tables {
   void* d_blob = nullptr;
   void* h_staging = nullptr;      // pinned copy of the tables for an upload queued on a stream (kept until destroy)
   int device = -1;
-  bool split_regions = false;     // holds the device's arrays for divided forward launches
 };
 
 namespace slimattn {
@@ -148,8 +147,7 @@ struct LaunchCtx {
 // the sample's first key), and stores unnormalised O, reference and row sum in fp32; a second kernel adds the parts up in order.  Row sums and O are sums over fewer terms than before.
 //
 // The forward has no workspace argument and allocates nothing, so the partial results live in one of kSplitRegions arrays
-// (34 MB each) per device.  Every handle with a sample long enough holds them: the first allocates them, destroying the last gives
-// them back.
+// (34 MB each) built into the library, one set per device.
 // A region belongs to a launch from its claim kernel to its last combining block, both on the caller's stream: the claim is an
 // atomic compare-and-swap of the region's owner from 0 to the launch's ticket (a process-wide counter), decided on the
 // device each time the launch runs, so calls on any streams and threads and replays of captured graphs never share a region.
@@ -157,7 +155,7 @@ struct LaunchCtx {
 // taken, by one of more streams than there are regions, walks undivided (the blocks of part 0 take all keys): no waiting, and
 // the same result up to the order of its sums.  (Two executable graphs made from one capture carry one ticket; they also write
 // the same o and lse, so they may not run at the same time in any case.)
-constexpr int kSplitRegions = 4;
+constexpr int kSplitRegions = 2;
 constexpr int kSplitUnits = 512;                                // (item, part, head) results of 128 rows per region: 256 compute
                                                                 // units x 2 heads per block, or 2 blocks per unit x 1 head
 constexpr int kSplitMinRows = 48 * 64;                          // shortest prefix that is divided
@@ -176,10 +174,8 @@ struct FwdSplit {
 int split_begin(const LaunchCtx&, int n_items, int divide_rows, FwdSplit* sp);
 // Adds up the parts and gives the region back.
 int split_combine(const LaunchCtx&, const FwdSplit& sp, void* o, float* lse, const QItem* items, int n_items);
-// A handle's hold on the regions of the current device `dev`: allocated with the first, freed with the last.  False where there is
-// no memory for them: the handle's launches are then not divided.
-bool acquire_split_regions(int dev);
-void release_split_regions(int dev);
+// Looks up the current device's regions (at table creation, so that launches find them ready, also under stream capture); hipError_t.
+int prepare_split_regions();
 
 // Kernel launchers (defined in the .hip files).  Each returns a hipError_t as int.
 int launch_fwd_f32(const LaunchCtx&, const float* q, const float* k, const float* v, float* o, float* lse,

@@ -336,7 +336,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
     blob.resize(align_up(blob.size()) + 256);
     hipError_t e = hipGetDevice(&t->device);
     if (e == hipSuccess) (void)prepare_static_scratch();    // set-up for slimattn_bwd_static on this device; its own call reports a failure
-    if (e == hipSuccess && n_fwd_units > 1 && t->max_sample_len >= kSplitMinRows) t->split_regions = acquire_split_regions(t->device);
+    if (e == hipSuccess) (void)prepare_split_regions();     // likewise for slimattn_fwd: without them its launches are not divided
     if (e == hipSuccess) e = hipMalloc(&t->d_blob, blob.size());
     if (e == hipSuccess && !use_stream) e = hipMemcpy(t->d_blob, blob.data(), blob.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess && use_stream) {
@@ -381,7 +381,6 @@ void slimattn_tables_destroy(slimattn_tables* t) {
   if (!t) return;
   if (t->d_blob) (void)hipFree(t->d_blob);      // (waits for work that may still read the tables)
   if (t->h_staging) (void)hipHostFree(t->h_staging);
-  if (t->split_regions) release_split_regions(t->device);
   delete t;
 }
 

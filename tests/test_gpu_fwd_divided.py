@@ -159,3 +159,16 @@ def test_keys_without_weight_at_every_tile_edge(L, hq, hkv, d, first, low):
     # (lse relative: the scaled query is rounded to bf16 once, a relative error of 2^-9 of the heavy key's score)
     assert np.max(np.abs(o[rows, heads] - ro)) <= TOL
     assert np.max(np.abs(lse[heads, rows] - rl) / (1.0 + np.abs(rl))) <= TOL
+
+
+def test_handles_hold_their_tables_only():
+    """The arrays for partial results belong to the library: a handle with a long sample in several units takes no more device memory
+    than its tables, also where it is the process's only one."""
+    cu, sl = S.build_slices([40000], 2048)
+    units = (np.arange(len(sl) + 1), np.arange(len(sl)))
+    S.tables_create(cu, sl, *units, *units).destroy()         # the library's own set-up
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    t = S.tables_create(cu, sl, *units, *units)
+    assert free - torch.cuda.mem_get_info()[0] <= 8 << 20     # 20 units' lists: far below 1 MB, in whole allocation blocks
+    t.destroy()

@@ -330,8 +330,10 @@ int slimattn_shape_supported(int64_t total_tokens, int32_t max_sample_len, int32
  * K/V need not exist yet), and o/lse rows of slices outside the range are not written.  A runtime can
  * therefore call it one unit at a time as K/V arrive slice by slice.
  * A call over a part of the list (without SLIMATTN_FLAG_PER_UNIT_LAUNCH) may divide the keys of a long prefix among blocks: its
- * o and lse then equal those of the whole list up to the order of fp32 sums.  The partial results live in arrays
- * built into the library (2 x 34 MB of device memory per GPU the library runs on, held until the process ends).
+ * o and lse then equal those of the whole list, or of the units' own launches with that flag, up to the order of fp32 sums.  The same
+ * call on the same inputs gives the same bits each time, whatever runs beside it.  The partial results live in arrays
+ * built into the library (2 x 34 MB of device memory per GPU the library runs on, held until the process ends); launches that find
+ * both in use take longer.  Graphs instantiated from one capture of such a call must not run at the same time.
  * q, k, v DEVICE (read), o, lse DEVICE (written), 16-byte aligned.
  * stream: a hipStream_t (NULL = default stream).  Allocates nothing, does not synchronise, issues kernel
  * launches only (no memset, no copy): the call -- and slimattn_bwd likewise -- may be recorded by a stream

@@ -33,6 +33,7 @@ namespace {
 
 constexpr int kFwdBQ = 128;   // query rows per block: 4 waves x 32 rows
 constexpr int kFwdBK = 64;    // keys per step
+template <int D> constexpr int kFwdLdsBytes = 4 * kFwdBK * D * 2;   // K and V tiles, two buffers of each
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kLazySum = 4096.f;   // the reference moves when a lane's sum of the 32 probabilities of a tile exceeds this
@@ -126,42 +127,22 @@ __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds
   }
 }
 
-// Split: NoSplit, or FwdSplit for a launch whose items' keys are divided (block numbers: parts innermost, so that an XCD keeps
-// to the same runs of keys; then the heads that share them).
-template <int D, class Split, bool EXACT>
-__global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k,
-                                                          const bf16* __restrict__ v, bf16* __restrict__ o,
-                                                          float* __restrict__ lse, const QItem* __restrict__ items,
-                                                          int n_items, int T, int Hq, int Hkv, float scale, Split sp) {
+// The walk of one block: rows q_row0 .. q_end - 1 of head h (at most 128) over n_tiles key tiles from kv_start on, up to row q_end - 1.
+// first_key: of the sample.  Leaves O^T, the reference (log2 units) and the row sum of this thread's row; all of the block's
+// threads are behind a barrier and done with the LDS.
+template <int D, bool EXACT>
+__device__ __forceinline__ void fwd_walk(LDS_PTR(char) lds, const bf16* __restrict__ q, const bf16* __restrict__ k,
+                                         const bf16* __restrict__ v, int q_row0, int q_end, int first_key, int kv_start, int n_tiles,
+                                         int h, int hk, int Hq, int Hkv, float scale, floatx16 (&oacc)[D / 32], float& m_ref, float& l_tot) {
   constexpr int NKS = D / 16;   // contraction steps over the head dimension
   constexpr int NDB = D / 32;   // 32-wide blocks of the head dimension
-  constexpr int kTileBytes = kFwdBK * D * 2, kBufBytes = 2 * kTileBytes;
-  __shared__ __attribute__((aligned(1024))) char smem[2 * kBufBytes];   // [buffer][K tile, V tile]
-
-  const int g = Hq / Hkv;
-  int item_idx, hk, hg, part = 0;
-  if constexpr (Split::on) {
-    part = blockIdx.x % sp.parts;
-    split_block(blockIdx.x / sp.parts, g, Hkv, &item_idx, &hk, &hg);
-  } else {
-    if (!map_block(blockIdx.x, g, Hkv, n_items, &item_idx, &hk, &hg)) return;
-  }
-  const int h = hk * g + hg;
-  QItem it = items[item_idx];
-  const int first_key = it.kv_start;              // of the sample
-  int n_tiles = (it.q_row0 + it.q_rows - it.kv_start + kFwdBK - 1) / kFwdBK;
-  bool alone = true;
-  if constexpr (Split::on) {
-    if (!split_range(sp, it, part, &n_tiles, &alone)) return;
-  }
+  constexpr int kTileBytes = kFwdBK * D * 2, kBufBytes = 2 * kTileBytes;   // LDS: [buffer][K tile, V tile]
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-  const int q0w = it.q_row0 + 32 * wave;          // first query row of this wave
+  const int q0w = q_row0 + 32 * wave;             // first query row of this wave
   const int my_row = q0w + l32;                   // the query row this lane owns
-  const int q_end = it.q_row0 + it.q_rows;
-  LDS_PTR(char) lds = (LDS_PTR(char))smem;
 
-  const TileSource srcK = make_tile_source<D, 256>(k, it.kv_start, Hkv, hk, q_end, tid);
-  const TileSource srcV = make_tile_source<D, 256>(v, it.kv_start, Hkv, hk, q_end, tid);
+  const TileSource srcK = make_tile_source<D, 256>(k, kv_start, Hkv, hk, q_end, tid);
+  const TileSource srcV = make_tile_source<D, 256>(v, kv_start, Hkv, hk, q_end, tid);
   stage_tile<D, kFwdBK, 256>(lds, srcK, 0, tid);
   stage_tile<D, kFwdBK, 256>(lds + kTileBytes, srcV, 0, tid);
 
@@ -176,7 +157,6 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
   for (int ks = 0; ks < NKS; ++ks) pk[ks] = lds_row_ptr<D>(lds, l32, 16 * ks + 8 * half);
 #pragma unroll
   for (int db = 0; db < NDB; ++db) lds_tr_ptrs<D>(lds + kTileBytes, 32 * db, lane, pv[db][0], pv[db][1]);
-  floatx16 oacc[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -184,7 +164,8 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
   // reference (log2 units): the row's score against the first key of the sample, for every part of a divided walk.  (A part's own
   // first key may be one that takes no part in the softmax, of a score far below the others or -inf: the part's scores would
   // be lost under such a reference.)
-  float m_ref = 0.f, l_run = 0.f;
+  float l_run = 0.f;
+  m_ref = 0.f;
   {
     const bf16* kp = k + ((size_t)first_key * Hkv + hk) * D + 8 * half;
 #pragma unroll
@@ -211,7 +192,7 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
   __syncthreads();
 
   for (int t = 0; t < n_tiles; ++t) {
-    const int j0 = it.kv_start + t * kFwdBK;
+    const int j0 = kv_start + t * kFwdBK;
     // next tile straight into the other buffer (its last readers passed the barrier below); past
     // the end of the tensor the loads return zeros that nobody uses.  kPasses loads per tensor,
     // spread over the first products of the tile.
@@ -240,17 +221,104 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
   }
 
   m_ref = -negm[0];
-  const float l_tot = l_run + xor32(l_run);
-  if constexpr (Split::on) {
-    if (!alone) {
-      split_store<D>(sp, (item_idx * sp.parts + part) * Hq + h, wave, lane, oacc, m_ref, l_tot);
-      return;
-    }
-  }
-  // (the tile buffers are free behind the loop's last barrier; each wave uses a part of its own)
-  static_assert(4 * kOutAreaBytes<D> <= 2 * kBufBytes, "the transposition areas must fit the tile buffers");
+  l_tot = l_run + xor32(l_run);
+}
+
+// Rows of the block out: O = O^T / l through LDS, lse.
+template <int D>
+__device__ __forceinline__ void fwd_out(LDS_PTR(char) lds, const floatx16 (&oacc)[D / 32], float m_ref, float l_tot, bf16* __restrict__ o,
+                                        float* __restrict__ lse, int q_row0, int q_end, int h, int T, int Hq) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q0w = q_row0 + 32 * wave, my_row = q0w + (lane & 31);
+  // (the tile buffers are free behind the walk's last barrier; each wave uses a part of its own)
+  static_assert(4 * kOutAreaBytes<D> <= kFwdLdsBytes<D>, "the transposition areas must fit the tile buffers");
   store_rows<D>(lds + __builtin_amdgcn_readfirstlane(wave) * kOutAreaBytes<D>, oacc, 1.f / l_tot, o, Hq, h, q0w, q_end, lane);
-  if (half == 0 && my_row < q_end) lse[(size_t)h * T + my_row] = (m_ref + __builtin_amdgcn_logf(l_tot)) * kLn2;
+  if (lane < 32 && my_row < q_end) lse[(size_t)h * T + my_row] = (m_ref + __builtin_amdgcn_logf(l_tot)) * kLn2;
+}
+
+template <int D, bool EXACT>
+__global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k,
+                                                          const bf16* __restrict__ v, bf16* __restrict__ o,
+                                                          float* __restrict__ lse, const QItem* __restrict__ items,
+                                                          int n_items, int T, int Hq, int Hkv, float scale) {
+  __shared__ __attribute__((aligned(1024))) char smem[kFwdLdsBytes<D>];
+  const int g = Hq / Hkv;
+  int item_idx, hk, hg;
+  if (!map_block(blockIdx.x, g, Hkv, n_items, &item_idx, &hk, &hg)) return;
+  const QItem it = items[item_idx];
+  const int q_end = it.q_row0 + it.q_rows;
+  floatx16 oacc[D / 32];
+  float m, l;
+  fwd_walk<D, EXACT>((LDS_PTR(char))smem, q, k, v, it.q_row0, q_end, it.kv_start, it.kv_start,
+                     (q_end - it.kv_start + kFwdBK - 1) / kFwdBK, hk * g + hg, hk, Hq, Hkv, scale, oacc, m, l);
+  fwd_out<D>((LDS_PTR(char))smem, oacc, m, l, o, lse, it.q_row0, q_end, hk * g + hg, T, Hq);
+}
+
+// The launch whose items' keys are divided: one block per (item, head, part), parts innermost, so that an XCD keeps to the same runs
+// of keys; then the heads that share them.
+template <int D, bool EXACT>
+__global__ __launch_bounds__(256, 2) void fwd_bf16_split_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k,
+                                                                const bf16* __restrict__ v, bf16* __restrict__ o,
+                                                                float* __restrict__ lse, const QItem* __restrict__ items, int T,
+                                                                int Hq, int Hkv, float scale, FwdSplit sp) {
+  __shared__ __attribute__((aligned(1024))) char smem[kFwdLdsBytes<D>];
+  const int part = blockIdx.x % sp.parts, g = Hq / Hkv;
+  int item_idx, hk, hg;
+  split_block(blockIdx.x / sp.parts, g, Hkv, &item_idx, &hk, &hg);
+  QItem it = items[item_idx];
+  const int first_key = it.kv_start, q_end = it.q_row0 + it.q_rows, h = hk * g + hg, n = split_parts(sp, it);
+  if (part >= n) return;
+  const int region = n > 1 ? split_region(sp) : 0;
+  if (region < 0) return;                         // the finishing kernel walks the parts
+  const int n_tiles = split_range(it, part, n);
+  floatx16 oacc[D / 32];
+  float m, l;
+  fwd_walk<D, EXACT>((LDS_PTR(char))smem, q, k, v, it.q_row0, q_end, first_key, it.kv_start, n_tiles, h, hk, Hq, Hkv, scale, oacc, m, l);
+  if (n > 1)
+    split_store<D>(split_unit<D>(sp, region, (item_idx * sp.parts + part) * Hq + h), threadIdx.x >> 6, threadIdx.x & 63, oacc, m, l);
+  else
+    fwd_out<D>((LDS_PTR(char))smem, oacc, m, l, o, lse, it.q_row0, q_end, h, T, Hq);
+}
+
+// Adds the parts up, grid (items, heads, head-dim blocks).  Without a region the blocks of the first head-dim block walk them, with the
+// sums of the parts so far in LDS.
+template <int D, bool EXACT>
+__global__ __launch_bounds__(256, D == 128 ? 1 : 2) void fwd_bf16_finish_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k,
+                                                                 const bf16* __restrict__ v, bf16* __restrict__ o,
+                                                                 float* __restrict__ lse, const QItem* __restrict__ items, int T,
+                                                                 int Hq, int Hkv, float scale, FwdSplit sp) {
+  __shared__ __attribute__((aligned(1024))) char smem[kFwdLdsBytes<D> + kFwdBQ * D * 4];
+  const QItem it = items[blockIdx.x];
+  const int n = split_parts(sp, it), region = split_region(sp);
+  if (n > 1 && region >= 0) {
+    split_combine<D>(sp, region, n, it, o, lse, T, Hq);
+  } else if (n > 1 && blockIdx.z == 0) {
+    const int h = blockIdx.y, q_end = it.q_row0 + it.q_rows;
+    LDS_PTR(floatx4) sum = (LDS_PTR(floatx4))(smem + kFwdLdsBytes<D>) + threadIdx.x;     // D / 8 vectors of a row, 256 apart
+    floatx16 oacc[D / 32];
+    float m = 0.f, l = 0.f;
+    for (int part = 0; part < n; ++part) {
+      QItem run = it;
+      const int n_tiles = split_range(run, part, n);
+      float mp, lp;
+      fwd_walk<D, EXACT>((LDS_PTR(char))smem, q, k, v, it.q_row0, q_end, it.kv_start, run.kv_start, n_tiles, h, h / (Hq / Hkv), Hq, Hkv,
+                         scale, oacc, mp, lp);
+      const bool first = part == 0;
+      if (first) m = mp;
+      const SplitAdd add(m, l, mp, lp);
+      if (first) l = lp;
+#pragma unroll
+      for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+          floatx4 x = sum[(db * 4 + gq) * 256];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = oacc[db][4 * gq + e] = first ? oacc[db][4 * gq + e] : add(x[e], oacc[db][4 * gq + e]);
+          sum[(db * 4 + gq) * 256] = x;
+        }
+    }
+    fwd_out<D>((LDS_PTR(char))smem, oacc, m, l, o, lse, it.q_row0, q_end, h, T, Hq);
+  }
+  split_release(sp, region);
 }
 
 }  // namespace
@@ -258,13 +326,24 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict
 int fwd_q_tile(int dtype, int) { return dtype == SLIMATTN_F32 ? 64 : kFwdBQ; }
 
 namespace {
-template <int D, bool EXACT, class Split>
+template <int D, bool EXACT>
 int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse, const QItem* items,
-                        int n_items, int parts, Split sp) {
+                        int n_items, const FwdSplit& sp) {
   const slimattn_params& p = *c.p;
-  const unsigned grid = Split::on ? (unsigned)(n_items * p.n_q_heads * parts) : (unsigned)mapped_grid(n_items, p.n_kv_heads, p.n_q_heads / p.n_kv_heads);
-  hipLaunchKernelGGL((fwd_bf16_kernel<D, Split, EXACT>), dim3(grid), dim3(256), 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
-                     (const bf16*)v, (bf16*)o, lse, items, n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, sp);
+  const dim3 block(256);
+  if (sp.parts > 1) {
+    hipLaunchKernelGGL((fwd_bf16_split_kernel<D, EXACT>), dim3((unsigned)(n_items * p.n_q_heads * sp.parts)), block, 0, (hipStream_t)c.stream,
+                       (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, sp);
+    const int e = (int)hipGetLastError();
+    if (e != 0) return e;
+    hipLaunchKernelGGL((fwd_bf16_finish_kernel<D, EXACT>), dim3((unsigned)n_items, (unsigned)p.n_q_heads, D / 32), block, 0,
+                       (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items, (int)c.T, p.n_q_heads,
+                       p.n_kv_heads, p.scale, sp);
+    return (int)hipGetLastError();
+  }
+  hipLaunchKernelGGL((fwd_bf16_kernel<D, EXACT>), dim3((unsigned)mapped_grid(n_items, p.n_kv_heads, p.n_q_heads / p.n_kv_heads)), block, 0,
+                     (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items, n_items, (int)c.T,
+                     p.n_q_heads, p.n_kv_heads, p.scale);
   return (int)hipGetLastError();
 }
 }  // namespace
@@ -282,20 +361,13 @@ int launch_fwd_bf16(const LaunchCtx& c, const void* q, const void* k, const void
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
   FwdSplit sp;
-  int e = split_begin(c, n_items, divide_rows, &sp);
+  const int e = split_begin(c, n_items, divide_rows, &sp);
   if (e != 0) return e;
-  const bool divided = sp.parts > 1, even = p.n_q_heads / p.n_kv_heads % 2 == 0;
-  auto one_head = [&](auto dc, auto exact) {
-    constexpr int D = decltype(dc)::value;
-    constexpr bool EXACT = decltype(exact)::value != 0;
-    return divided ? launch_fwd_one_head<D, EXACT>(c, q, k, v, o, lse, items, n_items, sp.parts, sp)
-                   : launch_fwd_one_head<D, EXACT>(c, q, k, v, o, lse, items, n_items, 1, NoSplit{});
-  };
-  if (p.head_dim == 64) e = one_head(IC<64>{}, IC<0>{});
-  else if (!even) e = one_head(IC<128>{}, IC<0>{});
-  else if (c.mean_keys > kShortMeanKeys) e = launch_fwd_wide_bf16(c, q, k, v, o, lse, items, n_items, sp);
-  else e = one_head(IC<128>{}, IC<1>{});
-  return e != 0 || !divided ? e : split_combine(c, sp, o, lse, items, n_items);
+  const bool even = p.n_q_heads / p.n_kv_heads % 2 == 0;
+  if (p.head_dim == 64) return launch_fwd_one_head<64, false>(c, q, k, v, o, lse, items, n_items, sp);
+  if (!even) return launch_fwd_one_head<128, false>(c, q, k, v, o, lse, items, n_items, sp);
+  if (c.mean_keys > kShortMeanKeys) return launch_fwd_wide_bf16(c, q, k, v, o, lse, items, n_items, sp);
+  return launch_fwd_one_head<128, true>(c, q, k, v, o, lse, items, n_items, sp);
 }
 
 }  // namespace slimattn

@@ -136,21 +136,17 @@ __device__ __forceinline__ void ew_flush(uintx4 (&pf)[2][2][2], float& e0, float
 
 // n_tiles: key tiles to walk from it.kv_start on.  first_key: the sample's first key, whose score is the row's reference also where
 // the walk is one part of the item (a part's own first key may take no part in the softmax: a score of -inf, or one so far below
-// the others that they would be lost against it).  unit >= 0 (FwdSplit only): the walk is one part of the item, its results go to partial results
-// unit (first head) and unit + 1.
-template <int D, class Split>
-__device__ __forceinline__ void fwd_wide_item(const QItem it, const int first_key, const int n_tiles, const int hk, const int hp, const bf16* __restrict__ q,
-                                              const bf16* __restrict__ k, const bf16* __restrict__ v, bf16* __restrict__ o_out,
-                                              float* __restrict__ lse, int T, int Hq, int Hkv, float scale, const Split& sp, int unit) {
+// the others that they would be lost against it).  PART: the walk may end before the diagonal.  out(head, O^T, reference, row
+// sum) takes the results of the wave's two heads.
+template <int D, bool PART, class Out>
+__device__ __forceinline__ void fwd_wide_item(LDS_PTR(char) lds, const QItem it, const int first_key, const int n_tiles, const int hk,
+                                              const int hp, const bf16* __restrict__ q, const bf16* __restrict__ k,
+                                              const bf16* __restrict__ v, int Hq, int Hkv, float scale, Out&& out) {
   constexpr int NKS = kNKS<D>, NDB = kNDB<D>, NVF = kNVF<D>, PER = kPer<D>;
-  // K and V buffers, then one transposition area per wave for the output rows
-  __shared__ __attribute__((aligned(1024))) char smem[4 * kTileBytes<D> + 4 * kOutAreaBytes<D>];
-
   const int g = Hq / Hkv;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int h0 = hk * g + 2 * hp;
   const int q0w = it.q_row0 + 32 * wave, my_row = q0w + l32, q_end = it.q_row0 + it.q_rows;
-  LDS_PTR(char) lds = (LDS_PTR(char))smem;
   // tiles this wave sees without a mask (at most all: a wave past the end of a ragged query tile)
   const int n_full = min(max(0, (q0w - it.kv_start + 1) / kKeys), n_tiles);
 
@@ -217,7 +213,7 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int first_ke
   float e0 = 0.f, e1 = 0.f, lr[2] = {0.f, 0.f}, lu[2] = {0.f, 0.f};
   // of the tile whose scores come next.  (The last iteration also produces scores of the tile behind the walk, which the mask
   // has to discard: the diagonal does, where the walk does not end before it.)
-  int rel_n = (Split::on ? min(my_row - it.kv_start, kKeys * n_tiles - 1) : my_row - it.kv_start) - 4 * half;
+  int rel_n = (PART ? min(my_row - it.kv_start, kKeys * n_tiles - 1) : my_row - it.kv_start) - 4 * half;
   int t = -1;
   int ksoff = kKeys * srcK.row_bytes;                   // byte offset of tile t + 2 in the sample's rows
   const int wave_off = wave * 1024;
@@ -420,23 +416,24 @@ __device__ __forceinline__ void fwd_wide_item(const QItem it, const int first_ke
   while (t < n_tiles) iteration(IC<0>{}, IC<1>{});
   settle();
 
-  if constexpr (Split::on) {
-    if (unit >= 0) {
-#pragma unroll
-      for (int hb = 0; hb < 2; ++hb) {
-        const float l_run = lr[hb] + lu[hb];
-        split_store<D>(sp, unit + hb, wave, lane, o[hb], m_ref[hb], l_run + xor32(l_run));
-      }
-      return;
-    }
-  }
 #pragma unroll
   for (int hb = 0; hb < 2; ++hb) {
     const float l_run = lr[hb] + lu[hb];
-    const float l_tot = l_run + xor32(l_run);
-    store_rows<D>(lds + 4 * kTileBytes<D> + wave * kOutAreaBytes<D>, o[hb], 1.f / l_tot, o_out, Hq, h0 + hb, q0w, q_end, lane);
-    if (half == 0 && my_row < q_end) lse[(size_t)(h0 + hb) * T + my_row] = (m_ref[hb] + __builtin_amdgcn_logf(l_tot)) * kLn2;
+    out(hb, o[hb], m_ref[hb], l_run + xor32(l_run));
   }
+}
+
+// LDS of a block: K and V buffers, then one transposition area per wave for the output rows
+template <int D> constexpr int kLdsBytes = 4 * kTileBytes<D> + 4 * kOutAreaBytes<D>;
+
+// One wave's rows of head h: O = O^T / l, through the block's transposition areas, and lse.
+template <int D>
+__device__ __forceinline__ void fwd_wide_out(LDS_PTR(char) areas, const QItem& it, const floatx16 (&acc)[kNDB<D>], float m, float l,
+                                             bf16* __restrict__ o, float* __restrict__ lse, int h, int T, int Hq) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int q0w = it.q_row0 + 32 * wave, my_row = q0w + (lane & 31), q_end = it.q_row0 + it.q_rows;
+  store_rows<D>(areas + wave * kOutAreaBytes<D>, acc, 1.f / l, o, Hq, h, q0w, q_end, lane);
+  if (lane < 32 && my_row < q_end) lse[(size_t)h * T + my_row] = (m + __builtin_amdgcn_logf(l)) * kLn2;
 }
 
 // A block walks the work list in rounds of the grid's size (the launch has as many blocks as the chip holds at
@@ -449,6 +446,7 @@ template <int D>
 __device__ __forceinline__ void fwd_wide_walk(const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
                                               bf16* __restrict__ o, float* __restrict__ lse, const QItem* __restrict__ items,
                                               int n_items, int T, int Hq, int Hkv, float scale) {
+  __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes<D>];
   const int g2 = (Hq / Hkv) >> 1;
   const int total = ((n_items * Hkv + 7) / 8) * 8 * g2;   // block numbers of the mapping, padding included
   const __amdgpu_buffer_rsrc_t irsrc = __builtin_amdgcn_make_buffer_rsrc((void*)items, 0, n_items * (int)sizeof(QItem), 0x00020000);
@@ -473,7 +471,10 @@ __device__ __forceinline__ void fwd_wide_walk(const bf16* __restrict__ q, const 
     it.kv_start = __builtin_amdgcn_readfirstlane(cur[2]);
     it.pad = 0;
     if (it.q_rows > 0)
-      fwd_wide_item<D>(it, it.kv_start, (it.q_row0 + it.q_rows - it.kv_start + kKeys - 1) / kKeys, hk, hp, q, k, v, o, lse, T, Hq, Hkv, scale, NoSplit{}, -1);
+      fwd_wide_item<D, false>((LDS_PTR(char))smem, it, it.kv_start, (it.q_row0 + it.q_rows - it.kv_start + kKeys - 1) / kKeys, hk, hp, q, k, v, Hq,
+                              Hkv, scale, [&](int hb, const floatx16 (&acc)[kNDB<D>], float m, float l) {
+                                fwd_wide_out<D>((LDS_PTR(char))smem + 4 * kTileBytes<D>, it, acc, m, l, o, lse, hk * (Hq / Hkv) + 2 * hp + hb, T, Hq);
+                              });
     cur = nxt;
     hk = hk_n;
     hp = hp_n;
@@ -493,15 +494,83 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_bf16_split_kernel_d128(const 
                                                                            const bf16* __restrict__ v, bf16* __restrict__ o,
                                                                            float* __restrict__ lse, const QItem* __restrict__ items,
                                                                            int T, int Hq, int Hkv, float scale, FwdSplit sp) {
-  const int part = blockIdx.x % sp.parts;
-  int idx, hk, hp, n_tiles;
-  const int g = Hq / Hkv;
+  __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes<128>];
+  const int part = blockIdx.x % sp.parts, g = Hq / Hkv;
+  int idx, hk, hp;
   split_block(blockIdx.x / sp.parts, g >> 1, Hkv, &idx, &hk, &hp);
   QItem it = items[idx];
-  const int first_key = it.kv_start;
-  bool alone;
-  if (!split_range(sp, it, part, &n_tiles, &alone)) return;
-  fwd_wide_item<128>(it, first_key, n_tiles, hk, hp, q, k, v, o, lse, T, Hq, Hkv, scale, sp, alone ? -1 : (idx * sp.parts + part) * Hq + hk * g + 2 * hp);
+  const int first_key = it.kv_start, n = split_parts(sp, it);
+  if (part >= n) return;
+  const int region = n > 1 ? split_region(sp) : 0;
+  if (region < 0) return;                               // the finishing kernel walks the parts
+  const int n_tiles = split_range(it, part, n);
+  fwd_wide_item<128, true>((LDS_PTR(char))smem, it, first_key, n_tiles, hk, hp, q, k, v, Hq, Hkv, scale,
+                           [&](int hb, const floatx16 (&acc)[4], float m, float l) {
+                             const int h = hk * g + 2 * hp + hb;
+                             if (n > 1)
+                               split_store<128>(split_unit<128>(sp, region, (idx * sp.parts + part) * Hq + h), threadIdx.x >> 6, threadIdx.x & 63, acc, m, l);
+                             else
+                               fwd_wide_out<128>((LDS_PTR(char))smem + 4 * kTileBytes<128>, it, acc, m, l, o, lse, h, T, Hq);
+                           });
+}
+
+// Adds the parts up, grid (items, heads, head-dim blocks).  Without a region one block per head pair walks them; the sums of the parts so
+// far wait in accumulation registers the walk leaves free (first head) and in LDS (second).
+__global__ __launch_bounds__(256, 1) void fwd_wide_bf16_finish_kernel_d128(const bf16* __restrict__ q, const bf16* __restrict__ k,
+                                                                            const bf16* __restrict__ v, bf16* __restrict__ o,
+                                                                            float* __restrict__ lse, const QItem* __restrict__ items,
+                                                                            int T, int Hq, int Hkv, float scale, FwdSplit sp) {
+  // K and V buffers (the transposition areas behind the last walk), then the second head's sums
+  constexpr int kWalkBytes = 4 * kTileBytes<128>;
+  static_assert(4 * kOutAreaBytes<128> <= kWalkBytes, "the transposition areas must fit the tile buffers");
+  __shared__ __attribute__((aligned(1024))) char smem[kWalkBytes + 128 * 128 * 4];
+  const QItem it = items[blockIdx.x];
+  const int n = split_parts(sp, it), region = split_region(sp);
+  if (n > 1 && region >= 0) {
+    split_combine<128>(sp, region, n, it, o, lse, T, Hq);
+  } else if (n > 1 && blockIdx.z == 0 && blockIdx.y % 2 == 0) {
+    const int g = Hq / Hkv, h0 = blockIdx.y;
+    floatx16 sum0[4];
+    LDS_PTR(floatx4) sum1 = (LDS_PTR(floatx4))(smem + kWalkBytes) + threadIdx.x;      // 16 vectors, 256 apart
+    float m[2] = {0.f, 0.f}, l[2] = {0.f, 0.f};
+    for (int part = 0; part < n; ++part) {
+      QItem run = it;
+      const int n_tiles = split_range(run, part, n);
+      auto take = [&](int hb, const floatx16 (&acc)[4], float mp, float lp) {
+        const bool first = part == 0;
+        if (first) {
+          m[hb] = mp;
+          l[hb] = 0.f;
+        }
+        const SplitAdd add(m[hb], l[hb], mp, lp);
+        if (first) l[hb] = lp;
+#pragma unroll
+        for (int db = 0; db < 4; ++db) {
+          if (hb == 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum0[db][r] = first ? acc[db][r] : add(sum0[db][r], acc[db][r]);
+            asm volatile("" : "+a"(sum0[db]));
+          } else {
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq) {
+              floatx4 x = sum1[(db * 4 + gq) * 256];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) x[e] = first ? acc[db][4 * gq + e] : add(x[e], acc[db][4 * gq + e]);
+              sum1[(db * 4 + gq) * 256] = x;
+            }
+          }
+        }
+      };
+      fwd_wide_item<128, true>((LDS_PTR(char))smem, run, it.kv_start, n_tiles, h0 / g, h0 % g / 2, q, k, v, Hq, Hkv, scale, take);
+    }
+    fwd_wide_out<128>((LDS_PTR(char))smem, it, sum0, m[0], l[0], o, lse, h0, T, Hq);
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum0[db][r] = sum1[(db * 4 + r / 4) * 256][r % 4];
+    fwd_wide_out<128>((LDS_PTR(char))smem, it, sum0, m[1], l[1], o, lse, h0 + 1, T, Hq);
+  }
+  split_release(sp, region);
 }
 
 }  // namespace
@@ -515,6 +584,10 @@ int launch_fwd_wide_bf16(const LaunchCtx& c, const void* q, const void* k, const
     hipLaunchKernelGGL(fwd_wide_bf16_split_kernel_d128, dim3((unsigned)(n_items * (p.n_q_heads / 2) * sp.parts)), dim3(256), 0,
                        (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items, (int)c.T,
                        p.n_q_heads, p.n_kv_heads, p.scale, sp);
+    const int e = (int)hipGetLastError();
+    if (e != 0) return e;
+    hipLaunchKernelGGL(fwd_wide_bf16_finish_kernel_d128, dim3((unsigned)n_items, (unsigned)p.n_q_heads, 4), dim3(256), 0, (hipStream_t)c.stream,
+                       (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, sp);
     return (int)hipGetLastError();
   }
   // one block per compute unit is resident (512 registers per lane); the device's count, rounded to the mapping's 8

@@ -148,32 +148,33 @@ struct LaunchCtx {
 //
 // The forward has no workspace argument and allocates nothing, so the partial results live in one of kSplitRegions arrays
 // (34 MB each) built into the library, one set per device.
-// A region belongs to a launch from its claim kernel to its last combining block, both on the caller's stream: the claim is an
-// atomic compare-and-swap of the region's owner from 0 to the launch's ticket (a process-wide counter), decided on the
+// A region belongs to a launch from its claim kernel to its last finishing block, both on the caller's stream: the claim is an
+// atomic compare-and-swap of a region's owner from 0 to the launch's ticket (a process-wide counter), decided on the
 // device each time the launch runs, so calls on any streams and threads and replays of captured graphs never share a region.
-// A stream keeps to one region (a stream's launches run one after another: they never meet).  A launch that finds its region
-// taken, by one of more streams than there are regions, walks undivided (the blocks of part 0 take all keys): no waiting, and
-// the same result up to the order of its sums.  (Two executable graphs made from one capture carry one ticket; they also write
-// the same o and lse, so they may not run at the same time in any case.)
+// A launch that finds all of them taken, by launches that run at the same time, is not divided among blocks: its parts are
+// walked one after another by the finishing kernel's blocks and added up in the same order by the same operations, so that
+// o and lse have the same bits either way.  No launch waits for another.  (Executable graphs made from one capture carry
+// one ticket; they also write the same o and lse, and may not run at the same time.)
 constexpr int kSplitRegions = 2;
 constexpr int kSplitUnits = 512;                                // (item, part, head) results of 128 rows per region: 256 compute
                                                                 // units x 2 heads per block, or 2 blocks per unit x 1 head
 constexpr int kSplitMinRows = 48 * 64;                          // shortest prefix that is divided
 template <int D> constexpr int kSplitUnitFloats = 128 * D + 256;   // O^T, then per wave 32 references and 32 row sums
+constexpr size_t kSplitRegionFloats = (size_t)kSplitUnits * kSplitUnitFloats<128>;
+struct SplitState {
+  unsigned long long owner[kSplitRegions];
+  unsigned done[kSplitRegions];   // finishing blocks that are through
+};
 struct FwdSplit {
-  static constexpr bool on = true;
-  float* data;                    // the region's partial results
-  unsigned long long* owner;
-  unsigned* done;                 // combining blocks that have finished
+  float* data;                    // the device's regions
+  SplitState* state;
   unsigned long long ticket;
   int parts;                      // blocks per (item, heads): 1 = not divided
   int target;                     // key tiles per part (at least; shorter items take fewer parts)
 };
 
-// Fills in `sp` for a launch of n_items query tiles and claims its region on the stream; parts = 1 where division does not pay.
+// Fills in `sp` for a launch of n_items query tiles and claims a region on the stream; parts = 1 where division does not pay.
 int split_begin(const LaunchCtx&, int n_items, int divide_rows, FwdSplit* sp);
-// Adds up the parts and gives the region back.
-int split_combine(const LaunchCtx&, const FwdSplit& sp, void* o, float* lse, const QItem* items, int n_items);
 // Looks up the current device's regions (at table creation, so that launches find them ready, also under stream capture); hipError_t.
 int prepare_split_regions();
 

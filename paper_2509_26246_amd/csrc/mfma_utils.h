@@ -329,8 +329,6 @@ __device__ __forceinline__ bool map_block(int block, int g, int Hkv, int n_items
 inline int mapped_grid(int n_items, int Hkv, int g) { return ((n_items * Hkv + 7) / 8) * 8 * g; }
 
 // ---- forward launches whose keys are divided (FwdSplit in internal.h) --------------------------------------
-struct NoSplit { static constexpr bool on = false; };
-
 // Block (without its part) -> item, KV head, head in group: the blocks that read the same keys are neighbours.
 __device__ __forceinline__ void split_block(int j, int g, int Hkv, int* item, int* hk, int* hg) {
   *hg = j % g;
@@ -338,24 +336,37 @@ __device__ __forceinline__ void split_block(int j, int g, int Hkv, int* item, in
   *item = j / (g * Hkv);
 }
 
-// Part `part` of an item: moves the item's first key and sets the tiles to walk; false: no such part.  Tiles whose first key is
-// visible to every row of the item are dealt evenly; the last part also takes the (at most two) tiles behind.  *alone: the item is not divided and the block writes O and lse itself.
-__device__ __forceinline__ bool split_range(const FwdSplit& sp, QItem& it, int part, int* n_tiles, bool* alone) {
+// Parts of an item, and part `part` of n: moves the item's first key and returns the tiles to walk.  Tiles whose first key is
+// visible to every row of the item are dealt evenly; the last part also takes the (at most two) tiles behind.
+__device__ __forceinline__ int split_parts(const FwdSplit& sp, const QItem& it) {
+  const int common = (it.q_row0 - it.kv_start) / 64 + 1;
+  return min(sp.parts, (common + sp.target - 1) / sp.target);
+}
+__device__ __forceinline__ int split_range(QItem& it, int part, int n) {
   const int all = (it.q_row0 + it.q_rows - it.kv_start + 63) / 64, common = (it.q_row0 - it.kv_start) / 64 + 1;
-  const bool owned = __hip_atomic_load(sp.owner, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == sp.ticket;
-  const int n = __builtin_amdgcn_readfirstlane(owned ? min(sp.parts, (common + sp.target - 1) / sp.target) : 1);
-  if (part >= n) return false;
   const int a = (int)((long long)common * part / n), b = part + 1 == n ? all : (int)((long long)common * (part + 1) / n);
   it.kv_start += 64 * a;
-  *n_tiles = b - a;
-  *alone = n == 1;
-  return true;
+  return b - a;
+}
+
+// The region the launch has claimed; -1: it found none free.
+__device__ __forceinline__ int split_region(const FwdSplit& sp) {
+  int region = -1;
+#pragma unroll
+  for (int r = 0; r < kSplitRegions; ++r)
+    if (__hip_atomic_load(&sp.state->owner[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == sp.ticket) region = r;
+  return __builtin_amdgcn_readfirstlane(region);
+}
+
+// Results of one (item, part, head): `unit` counts them as (item * parts + part) * Hq + head.
+template <int D>
+__device__ __forceinline__ float* split_unit(const FwdSplit& sp, int region, int unit) {
+  return sp.data + region * kSplitRegionFloats + (size_t)unit * kSplitUnitFloats<D>;
 }
 
 // One wave's 32 rows of one head: O^T accumulators, reference (log2 units) and row sum of the part (stores of 1 KB per instruction).
 template <int D>
-__device__ __forceinline__ void split_store(const FwdSplit& sp, int unit, int wave4, int lane, const floatx16 (&o)[D / 32], float m, float l) {
-  float* base = sp.data + (size_t)unit * kSplitUnitFloats<D>;
+__device__ __forceinline__ void split_store(float* base, int wave4, int lane, const floatx16 (&o)[D / 32], float m, float l) {
   floatx4* at = reinterpret_cast<floatx4*>(base + wave4 * 32 * D) + lane;
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
@@ -366,6 +377,74 @@ __device__ __forceinline__ void split_store(const FwdSplit& sp, int unit, int wa
     float* stat = base + 128 * D + wave4 * 64 + lane;
     stat[0] = m;
     stat[32] = l;
+  }
+}
+
+// Adds a part to the sum of those before it, each weighted by its reference: constructed from the two references and row sums,
+// then called for each value of O.  (One operation for a multiplication and the addition, written out: the two ways a
+// launch is finished must round alike.)
+struct SplitAdd {
+  float a, b;
+  __device__ __forceinline__ SplitAdd(float& m, float& l, float m_part, float l_part) {
+    const float top = fmaxf(m, m_part);
+    a = __builtin_amdgcn_exp2f(m - top);
+    b = __builtin_amdgcn_exp2f(m_part - top);
+    m = top;
+    l = (*this)(l, l_part);
+  }
+  __device__ __forceinline__ float operator()(float sum, float part) const { return __builtin_fmaf(b, part, a * sum); }
+};
+
+// The finishing kernel of a launch that owns a region, grid (items, heads, head-dim blocks of 32): a wave adds up the n parts of 32 rows, a
+// lane 16 columns of one row.  Bound by reading the partial results once; the head-dim blocks give enough blocks to cover
+// that latency (1024 rows x 8 heads in 8 parts: 256 blocks).
+template <int D>
+__device__ __forceinline__ void split_combine(const FwdSplit& sp, int region, int n, const QItem& it, bf16* __restrict__ o,
+                                              float* __restrict__ lse, int T, int Hq) {
+  const int h = blockIdx.y, db = blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+  const int r = 32 * wave + l32;
+  if (r >= it.q_rows) return;
+  float m = 0.f, l = 0.f;
+  floatx4 sum[4];
+#pragma unroll 2
+  for (int p = 0; p < n; ++p) {
+    const float* u = split_unit<D>(sp, region, ((int)blockIdx.x * sp.parts + p) * Hq + h);
+    const float mp = u[128 * D + wave * 64 + l32], lp = u[128 * D + wave * 64 + 32 + l32];
+    const floatx4* at = reinterpret_cast<const floatx4*>(u + wave * 32 * D) + db * 256 + lane;
+    if (p == 0) {
+      m = mp;
+      l = lp;
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) sum[gq] = at[gq * 64];
+    } else {
+      const SplitAdd add(m, l, mp, lp);
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) {
+        const floatx4 x = at[gq * 64];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[gq][e] = add(sum[gq][e], x[e]);
+      }
+    }
+  }
+  const float inv = 1.f / l;
+  bf16* op = o + ((size_t)(it.q_row0 + r) * Hq + h) * D + 32 * db + 4 * half;
+#pragma unroll
+  for (int gq = 0; gq < 4; ++gq) {
+    bf16x4 w;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) w[x] = (bf16)(sum[gq][x] * inv);
+    *reinterpret_cast<bf16x4*>(op + 8 * gq) = w;
+  }
+  if (db == 0 && half == 0) lse[(size_t)h * T + it.q_row0 + r] = (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+}
+// The end of a finishing kernel's block: the last one to get here gives the region back.
+__device__ __forceinline__ void split_release(const FwdSplit& sp, int region) {
+  __syncthreads();
+  if (region < 0 || threadIdx.x != 0) return;
+  __threadfence();
+  if (atomicAdd(&sp.state->done[region], 1u) == gridDim.x * gridDim.y * gridDim.z - 1) {
+    __threadfence();
+    atomicExch(&sp.state->owner[region], 0ull);
   }
 }
 

@@ -172,3 +172,36 @@ def test_handles_hold_their_tables_only():
     t = S.tables_create(cu, sl, *units, *units)
     assert free - torch.cuda.mem_get_info()[0] <= 8 << 20     # 20 units' lists: far below 1 MB, in whole allocation blocks
     t.destroy()
+
+
+# More launches at once than there are arrays: those that find none free walk their parts one after another, to the same bits.  Every
+# kernel that divides; eager calls on many streams beside replays of a graph.
+@pytest.mark.parametrize("L,hq,hkv,d", [([32768], 8, 1, 128), ([20000], 3, 1, 128), ([20000], 4, 2, 64), ([9000] + [64] * 3000, 2, 1, 128)])
+def test_concurrent_launches_have_the_bits_of_one_alone(L, hq, hkv, d):
+    prob, arrs, cu, sl = _slices(L, hq, hkv, d, 1024)
+    u = [t for t in range(len(sl)) if sl[t][0] == 0][-1]
+    first, end = int(sl[u][2]), int(sl[u][2] + sl[u][3])
+    prob.forward(unit_lo=u, unit_hi=u + 1)
+    torch.cuda.synchronize()
+    _check(prob, arrs, cu, first, end, H.device_to_f32(prob.o), prob.lse.cpu().numpy(), "alone")
+    want = (prob.o[first:end].clone(), prob.lse[:, first:end].clone())
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        prob.forward(unit_lo=u, unit_hi=u + 1)
+    streams = [torch.cuda.Stream() for _ in range(8)]
+    outs = [(torch.empty_like(prob.o), torch.empty_like(prob.lse)) for _ in streams]
+    for _ in range(4):
+        for t in [prob.o, prob.lse] + [t for pair in outs for t in pair]:
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for _ in range(3):
+            for s, (o, lse) in zip(streams, outs):
+                with torch.cuda.stream(s):
+                    S.fwd(prob.q, prob.k, prob.v, prob.tables, o, lse, **prob._kw(unit_lo=u, unit_hi=u + 1))
+            with torch.cuda.stream(side):
+                g.replay()
+        torch.cuda.synchronize()
+        for i, (o, lse) in enumerate(outs + [(prob.o, prob.lse)]):
+            assert torch.equal(o[first:end].view(torch.int16), want[0].view(torch.int16)), f"stream {i}: O"
+            assert torch.equal(lse[:, first:end], want[1]), f"stream {i}: lse"
+            assert torch.isnan(o[:first]).all() and torch.isnan(o[end:]).all()

@@ -341,6 +341,11 @@ int slimattn_shape_supported(int64_t total_tokens, int32_t max_sample_len, int32
 int slimattn_fwd(const slimattn_params* p, const void* q, const void* k, const void* v,
                  const slimattn_tables* t, void* o, float* lse, void* stream);
 
+/* How slimattn_fwd calls over a part of the list ran on the current device so far (informational; waits for the device's default
+ * stream): counts [3], HOST: launches whose keys were divided among blocks, launches whose parts were walked one after
+ * another because the arrays were in use, arrays in use now. */
+int slimattn_fwd_divided_counts(int64_t* counts);
+
 /* Backward over units [unit_lo, unit_hi) of the backward list, with the scores recomputed from q, k
  * and lse (paper: Asymmetric Cost Profile -- the recomputation is why backward costs 2.5 x forward;
  * Asymmetric Partition -- hence a unit list of its own): P_ij = exp(S_ij - lse_i), dP_ij = dO_i . v_j,

@@ -19,7 +19,7 @@ POLICY_KINDS = {"ALL": 0, "PER_SAMPLE": 1, "ROUND_ROBIN": 2, "PREFIX_FILL": 3, "
 EXPORTED_SYMBOLS = [
     "slimattn_build_slices", "slimattn_build_slices_from_bounds", "slimattn_build_units", "slimattn_validate",
     "slimattn_solve_partition", "slimattn_solve_bottlenecks", "slimattn_dag_timeline", "slimattn_dag_build_1f1b", "slimattn_dag_memory", "slimattn_dag_buffers_1f1b", "slimattn_candidate_unit_counts", "slimattn_search_unit_count", "slimattn_shape_supported", "slimattn_slice_pairs", "slimattn_flops_fwd", "slimattn_flops_bwd", "slimattn_tables_create", "slimattn_tables_create_async",
-    "slimattn_tables_destroy", "slimattn_tables_count", "slimattn_bwd_workspace_bytes", "slimattn_fwd",
+    "slimattn_tables_destroy", "slimattn_tables_count", "slimattn_bwd_workspace_bytes", "slimattn_fwd", "slimattn_fwd_divided_counts",
     "slimattn_bwd", "slimattn_bwd_static", "slimattn_bwd_released_rows", "slimattn_strerror", "slimattn_last_hip_error", "slimattn_version", "slimattn_profile_enable",
     "slimattn_profile_read", "slimattn_profile_read_launches"]
 KERNEL_CLASSES = ["fwd", "delta", "dq", "dkdv", "reduce", "unused", "fwd_call", "bwd_call"]
@@ -98,6 +98,7 @@ def load_library():
     lib.slimattn_bwd.argtypes = [C.POINTER(_Params)] + [vp] * 12
     lib.slimattn_bwd_static.argtypes = [C.POINTER(_Params)] + [vp] * 11
     lib.slimattn_bwd_released_rows.argtypes = [vp, C.c_int32, i32p, C.c_int32, i32p]
+    lib.slimattn_fwd_divided_counts.argtypes = [C.POINTER(C.c_int64)]
     lib.slimattn_strerror.argtypes = [C.c_int]
     lib.slimattn_strerror.restype = C.c_char_p
     lib.slimattn_last_hip_error.restype = C.c_int
@@ -478,6 +479,16 @@ def profile_enable(max_launches: int) -> None:
     rc = load_library().slimattn_profile_enable(max_launches)
     if rc != 0:
         raise SlimAttnError(rc, "slimattn_profile_enable")
+
+
+def fwd_divided_counts():
+    """Forward calls over a part of the list on the current device so far: (launches divided among blocks, launches whose parts were
+    walked one after another, arrays for partial results in use now)."""
+    n = (C.c_int64 * 3)()
+    rc = load_library().slimattn_fwd_divided_counts(n)
+    if rc != 0:
+        raise SlimAttnError(rc, "slimattn_fwd_divided_counts")
+    return tuple(n)
 
 
 def profile_read():

@@ -15,6 +15,8 @@ static __device__ slimattn::SplitState split_state;
 static __device__ __align__(256) float split_data[slimattn::kSplitRegions * slimattn::kSplitRegionFloats];
 
 namespace slimattn {
+int& last_hip_error();
+
 namespace {
 
 __global__ void split_claim_kernel(SplitState* state, unsigned long long ticket) {
@@ -83,3 +85,21 @@ int split_begin(const LaunchCtx& c, int n_items, int divide_rows, FwdSplit* sp) 
 }
 
 }  // namespace slimattn
+
+using namespace slimattn;
+
+extern "C" int slimattn_fwd_divided_counts(int64_t* counts) {
+  if (!counts) return SLIMATTN_EINVAL;
+  SplitState now;
+  hipError_t e = (hipError_t)prepare_split_regions();
+  if (e == hipSuccess) e = hipMemcpyFromSymbol(&now, HIP_SYMBOL(split_state), sizeof(now));
+  if (e != hipSuccess) {
+    last_hip_error() = (int)e;
+    return SLIMATTN_EHIP;
+  }
+  counts[0] = (int64_t)now.launches[0];
+  counts[1] = (int64_t)now.launches[1];
+  counts[2] = 0;
+  for (unsigned long long owner : now.owner) counts[2] += owner != 0;
+  return SLIMATTN_OK;
+}

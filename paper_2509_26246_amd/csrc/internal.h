@@ -164,6 +164,7 @@ constexpr size_t kSplitRegionFloats = (size_t)kSplitUnits * kSplitUnitFloats<128
 struct SplitState {
   unsigned long long owner[kSplitRegions];
   unsigned done[kSplitRegions];   // finishing blocks that are through
+  unsigned long long launches[2]; // launches so far: added up from a region, walked part by part (slimattn_fwd_divided_counts)
 };
 struct FwdSplit {
   float* data;                    // the device's regions

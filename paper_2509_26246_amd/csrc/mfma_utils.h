@@ -440,9 +440,14 @@ __device__ __forceinline__ void split_combine(const FwdSplit& sp, int region, in
 // The end of a finishing kernel's block: the last one to get here gives the region back.
 __device__ __forceinline__ void split_release(const FwdSplit& sp, int region) {
   __syncthreads();
-  if (region < 0 || threadIdx.x != 0) return;
+  if (threadIdx.x != 0) return;
+  if (region < 0) {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) atomicAdd(&sp.state->launches[1], 1ull);
+    return;
+  }
   __threadfence();
   if (atomicAdd(&sp.state->done[region], 1u) == gridDim.x * gridDim.y * gridDim.z - 1) {
+    atomicAdd(&sp.state->launches[0], 1ull);
     __threadfence();
     atomicExch(&sp.state->owner[region], 0ull);
   }

@@ -190,6 +190,7 @@ def test_concurrent_launches_have_the_bits_of_one_alone(L, hq, hkv, d):
         prob.forward(unit_lo=u, unit_hi=u + 1)
     streams = [torch.cuda.Stream() for _ in range(8)]
     outs = [(torch.empty_like(prob.o), torch.empty_like(prob.lse)) for _ in streams]
+    before = S.fwd_divided_counts()
     for _ in range(4):
         for t in [prob.o, prob.lse] + [t for pair in outs for t in pair]:
             t.fill_(float("nan"))
@@ -201,7 +202,32 @@ def test_concurrent_launches_have_the_bits_of_one_alone(L, hq, hkv, d):
             with torch.cuda.stream(side):
                 g.replay()
         torch.cuda.synchronize()
+        after = S.fwd_divided_counts()
+        assert after[0] + after[1] - before[0] - before[1] == 27 and after[1] > before[1] and after[2] == 0, (before, after)
+        before = after
         for i, (o, lse) in enumerate(outs + [(prob.o, prob.lse)]):
             assert torch.equal(o[first:end].view(torch.int16), want[0].view(torch.int16)), f"stream {i}: O"
             assert torch.equal(lse[:, first:end], want[1]), f"stream {i}: lse"
             assert torch.isnan(o[:first]).all() and torch.isnan(o[end:]).all()
+
+
+@pytest.mark.parametrize("L,hq,hkv,d", [([9000], 8, 1, 128), ([9000], 3, 1, 128), ([9000], 4, 2, 64), ([3500] + [64] * 260, 2, 1, 128),
+                                        ([3073], 8, 1, 128), ([3071], 8, 1, 128)])
+def test_divided_launches_are_counted(L, hq, hkv, d):
+    """A call over part of the list with a long prefix is divided, each time; per-unit and whole-list launches are not, nor is a prefix
+    below 3072 keys."""
+    prob, _, _, sl = _slices(L, hq, hkv, d, 400)
+    u = [t for t in range(len(sl)) if sl[t][0] == 0][-1]
+
+    def counted(**kw):
+        before = S.fwd_divided_counts()
+        prob.forward(**kw)
+        torch.cuda.synchronize()
+        after = S.fwd_divided_counts()
+        assert after[2] == 0
+        return after[0] - before[0], after[1] - before[1]
+
+    for _ in range(3):
+        assert counted(unit_lo=u, unit_hi=u + 1) == ((1, 0) if L[0] > 3071 else (0, 0))
+    assert counted(unit_lo=u, unit_hi=u + 1, flags=S.FLAG_PER_UNIT_LAUNCH) == (0, 0)
+    assert counted() == (0, 0)

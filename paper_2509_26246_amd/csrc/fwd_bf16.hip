@@ -336,7 +336,7 @@ int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const 
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, sp);
     const int e = (int)hipGetLastError();
     if (e != 0) return e;
-    hipLaunchKernelGGL((fwd_bf16_finish_kernel<D, EXACT>), dim3((unsigned)n_items, (unsigned)p.n_q_heads, D / 32), block, 0,
+    hipLaunchKernelGGL((fwd_bf16_finish_kernel<D, EXACT>), dim3((unsigned)n_items, (unsigned)p.n_q_heads, split_finish_z(n_items, p.n_q_heads, D)), block, 0,
                        (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items, (int)c.T, p.n_q_heads,
                        p.n_kv_heads, p.scale, sp);
     return (int)hipGetLastError();

@@ -56,11 +56,11 @@ int prepare_split_regions() {
 }
 
 // As many parts as one round of blocks holds, of at least kMinPartTiles key tiles, if that is the faster way.  A tile takes about
-// 1.15 us while most compute units idle and 1.65 us when all work; claim and combining take 20 us, and up to 25 more for
-// writing and reading a full region.  Measured, undivided -> divided: 1024 rows of 8/1 heads after 31K keys (8 parts) 569 ->
-// 132 us, 256 rows after 7.9K 147 -> 43, after 2.8K (3 parts) 61 -> 37; 512 rows of 32/8 heads after 3.6K (4 parts) 80 -> 68.
-// With 1024 rows of 32/8 heads only two parts fit: 82 -> 108 after 3K keys, 157 -> 156 after 7K (both stay undivided), 583 -> 441
-// after 31K.
+// 1.15 us while most compute units idle and 1.65 us when all work; claim and adding up were taken at 20 us, and up to 25 more for
+// writing and reading a full region (they take less since).  Measured, undivided -> divided: 1024 rows of 8/1 heads after 31K keys
+// (8 parts) 569 -> 129 us, 256 rows after 7.9K 150 -> 39, after 2.8K (3 parts) 61 -> 35; 512 rows of 32/8 heads after 3.6K (4 parts)
+// 82 -> 59.  With 1024 rows of 32/8 heads only two parts fit: after 3K and 7K keys they stay undivided (82, 157 us), after 31K
+// 607 -> 459.
 int split_begin(const LaunchCtx& c, int n_items, int divide_rows, FwdSplit* sp) {
   constexpr int kMinPartTiles = 16;
   *sp = FwdSplit{nullptr, nullptr, 0, 1, 1};

@@ -586,7 +586,7 @@ int launch_fwd_wide_bf16(const LaunchCtx& c, const void* q, const void* k, const
                        p.n_q_heads, p.n_kv_heads, p.scale, sp);
     const int e = (int)hipGetLastError();
     if (e != 0) return e;
-    hipLaunchKernelGGL(fwd_wide_bf16_finish_kernel_d128, dim3((unsigned)n_items, (unsigned)p.n_q_heads, 4), dim3(256), 0, (hipStream_t)c.stream,
+    hipLaunchKernelGGL(fwd_wide_bf16_finish_kernel_d128, dim3((unsigned)n_items, (unsigned)p.n_q_heads, split_finish_z(n_items, p.n_q_heads, 128)), dim3(256), 0, (hipStream_t)c.stream,
                        (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, sp);
     return (int)hipGetLastError();
   }

@@ -395,47 +395,62 @@ struct SplitAdd {
   __device__ __forceinline__ float operator()(float sum, float part) const { return __builtin_fmaf(b, part, a * sum); }
 };
 
-// The finishing kernel of a launch that owns a region, grid (items, heads, head-dim blocks of 32): a wave adds up the n parts of 32 rows, a
-// lane 16 columns of one row.  Bound by reading the partial results once; the head-dim blocks give enough blocks to cover
-// that latency (1024 rows x 8 heads in 8 parts: 256 blocks).
-template <int D>
-__device__ __forceinline__ void split_combine(const FwdSplit& sp, int region, int n, const QItem& it, bf16* __restrict__ o,
-                                              float* __restrict__ lse, int T, int Hq) {
-  const int h = blockIdx.y, db = blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+// The finishing kernel of a launch that owns a region, grid (items, heads, 1 .. D / 32): a wave adds up the n parts of 32 rows over N
+// head-dim blocks of 32, a lane 16 columns of one row in each.  Bound by reading the partial results once; as the walk in the
+// same kernel leaves room for few blocks per compute unit, a launch takes as many head-dim blocks per block as keep it to one
+// round (split_finish_z; 1024 rows of 32/8 heads after 31K keys, in 2 parts: whole call 506 us with one each, 459 with four; 512 rows after 3.6K,
+// in 4 parts: 78 and 59).
+template <int D, int N>
+__device__ __forceinline__ void split_combine_blocks(const FwdSplit& sp, int region, int n, const QItem& it, bf16* __restrict__ o,
+                                                     float* __restrict__ lse, int T, int Hq) {
+  const int h = blockIdx.y, db0 = N * blockIdx.z, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
   const int r = 32 * wave + l32;
   if (r >= it.q_rows) return;
   float m = 0.f, l = 0.f;
-  floatx4 sum[4];
+  floatx4 sum[N][4];
 #pragma unroll 2
   for (int p = 0; p < n; ++p) {
     const float* u = split_unit<D>(sp, region, ((int)blockIdx.x * sp.parts + p) * Hq + h);
     const float mp = u[128 * D + wave * 64 + l32], lp = u[128 * D + wave * 64 + 32 + l32];
-    const floatx4* at = reinterpret_cast<const floatx4*>(u + wave * 32 * D) + db * 256 + lane;
+    const floatx4* at = reinterpret_cast<const floatx4*>(u + wave * 32 * D) + db0 * 256 + lane;
+    floatx4 x[N][4];
+#pragma unroll
+    for (int i = 0; i < 4 * N; ++i) x[i / 4][i % 4] = at[i * 64];
     if (p == 0) {
       m = mp;
       l = lp;
 #pragma unroll
-      for (int gq = 0; gq < 4; ++gq) sum[gq] = at[gq * 64];
+      for (int i = 0; i < 4 * N; ++i) sum[i / 4][i % 4] = x[i / 4][i % 4];
     } else {
       const SplitAdd add(m, l, mp, lp);
 #pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        const floatx4 x = at[gq * 64];
+      for (int i = 0; i < 4 * N; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[gq][e] = add(sum[gq][e], x[e]);
-      }
+        for (int e = 0; e < 4; ++e) sum[i / 4][i % 4][e] = add(sum[i / 4][i % 4][e], x[i / 4][i % 4][e]);
     }
   }
   const float inv = 1.f / l;
-  bf16* op = o + ((size_t)(it.q_row0 + r) * Hq + h) * D + 32 * db + 4 * half;
+  bf16* op = o + ((size_t)(it.q_row0 + r) * Hq + h) * D + 32 * db0 + 4 * half;
 #pragma unroll
-  for (int gq = 0; gq < 4; ++gq) {
+  for (int i = 0; i < 4 * N; ++i) {
     bf16x4 w;
 #pragma unroll
-    for (int x = 0; x < 4; ++x) w[x] = (bf16)(sum[gq][x] * inv);
-    *reinterpret_cast<bf16x4*>(op + 8 * gq) = w;
+    for (int x = 0; x < 4; ++x) w[x] = (bf16)(sum[i / 4][i % 4][x] * inv);
+    *reinterpret_cast<bf16x4*>(op + 8 * i) = w;
   }
-  if (db == 0 && half == 0) lse[(size_t)h * T + it.q_row0 + r] = (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+  if (db0 == 0 && half == 0) lse[(size_t)h * T + it.q_row0 + r] = (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+}
+template <int D>
+__device__ __forceinline__ void split_combine(const FwdSplit& sp, int region, int n, const QItem& it, bf16* __restrict__ o,
+                                              float* __restrict__ lse, int T, int Hq) {
+  if (gridDim.z == D / 32) split_combine_blocks<D, 1>(sp, region, n, it, o, lse, T, Hq);
+  else if (gridDim.z == D / 64) split_combine_blocks<D, 2>(sp, region, n, it, o, lse, T, Hq);
+  else split_combine_blocks<D, D / 32>(sp, region, n, it, o, lse, T, Hq);
+}
+inline unsigned split_finish_z(int n_items, int n_heads, int head_dim) {
+  unsigned z = head_dim / 32;
+  while (z > 1 && (int64_t)n_items * n_heads * z > 256) z /= 2;
+  return z;
 }
 // The end of a finishing kernel's block: the last one to get here gives the region back.
 __device__ __forceinline__ void split_release(const FwdSplit& sp, int region) {

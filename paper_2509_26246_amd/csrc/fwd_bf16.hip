@@ -360,14 +360,17 @@ int launch_fwd_bf16(const LaunchCtx& c, const void* q, const void* k, const void
                     const QItem* items, int n_items, int divide_rows) {
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
-  FwdSplit sp;
-  const int e = split_begin(c, n_items, divide_rows, &sp);
-  if (e != 0) return e;
   const bool even = p.n_q_heads / p.n_kv_heads % 2 == 0;
-  if (p.head_dim == 64) return launch_fwd_one_head<64, false>(c, q, k, v, o, lse, items, n_items, sp);
-  if (!even) return launch_fwd_one_head<128, false>(c, q, k, v, o, lse, items, n_items, sp);
-  if (c.mean_keys > kShortMeanKeys) return launch_fwd_wide_bf16(c, q, k, v, o, lse, items, n_items, sp);
-  return launch_fwd_one_head<128, true>(c, q, k, v, o, lse, items, n_items, sp);
+  FwdSplit sp;
+  int e = split_begin(c, n_items, divide_rows, &sp);
+  if (e == 0) {
+    if (p.head_dim == 64) e = launch_fwd_one_head<64, false>(c, q, k, v, o, lse, items, n_items, sp);
+    else if (!even) e = launch_fwd_one_head<128, false>(c, q, k, v, o, lse, items, n_items, sp);
+    else if (c.mean_keys > kShortMeanKeys) e = launch_fwd_wide_bf16(c, q, k, v, o, lse, items, n_items, sp);
+    else e = launch_fwd_one_head<128, true>(c, q, k, v, o, lse, items, n_items, sp);
+  }
+  if (e != 0) split_abandon(c, sp);
+  return e;
 }
 
 }  // namespace slimattn

@@ -28,6 +28,10 @@ __global__ void split_claim_kernel(SplitState* state, unsigned long long ticket)
     }
 }
 
+__global__ void split_abandon_kernel(SplitState* state, unsigned long long ticket) {
+  if (threadIdx.x < kSplitRegions) atomicCAS(&state->owner[threadIdx.x], ticket, 0ull);
+}
+
 constexpr int kMaxDevices = 64;
 float* g_data[kMaxDevices] = {};
 SplitState* g_state[kMaxDevices] = {};
@@ -82,6 +86,12 @@ int split_begin(const LaunchCtx& c, int n_items, int divide_rows, FwdSplit* sp) 
   }
   hipLaunchKernelGGL(split_claim_kernel, dim3(1), dim3(64), 0, (hipStream_t)c.stream, sp->state, sp->ticket);
   return (int)hipGetLastError();
+}
+
+void split_abandon(const LaunchCtx& c, const FwdSplit& sp) {
+  if (sp.parts < 2) return;
+  hipLaunchKernelGGL(split_abandon_kernel, dim3(1), dim3(64), 0, (hipStream_t)c.stream, sp.state, sp.ticket);
+  (void)hipGetLastError();                                 // the caller reports the error that led here
 }
 
 }  // namespace slimattn

@@ -176,6 +176,8 @@ struct FwdSplit {
 
 // Fills in `sp` for a launch of n_items query tiles and claims a region on the stream; parts = 1 where division does not pay.
 int split_begin(const LaunchCtx&, int n_items, int divide_rows, FwdSplit* sp);
+// For a launch that fails behind split_begin: gives back, on the stream, what its claim may have taken.
+void split_abandon(const LaunchCtx&, const FwdSplit& sp);
 // Looks up the current device's regions (at table creation, so that launches find them ready, also under stream capture); hipError_t.
 int prepare_split_regions();
 

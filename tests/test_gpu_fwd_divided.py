@@ -231,3 +231,21 @@ def test_divided_launches_are_counted(L, hq, hkv, d):
         assert counted(unit_lo=u, unit_hi=u + 1) == ((1, 0) if L[0] > 3071 else (0, 0))
     assert counted(unit_lo=u, unit_hi=u + 1, flags=S.FLAG_PER_UNIT_LAUNCH) == (0, 0)
     assert counted() == (0, 0)
+
+
+def test_a_call_that_fails_gives_its_array_back():
+    """A launch reports an earlier error of the thread's HIP calls as its own: such a call fails behind its claim."""
+    prob, _, _, sl = _slices([9000], 8, 1, 128, 400)
+    u = len(sl) - 1
+    prob.forward(unit_lo=u, unit_hi=u + 1)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        assert S.load_library().hipSetDevice(999) != 0        # refused, and remembered by the runtime; the device stays
+        with pytest.raises(S.SlimAttnError):
+            prob.forward(unit_lo=u, unit_hi=u + 1)
+    torch.cuda.synchronize()
+    before = S.fwd_divided_counts()
+    assert before[2] == 0
+    prob.forward(unit_lo=u, unit_hi=u + 1)
+    torch.cuda.synchronize()
+    assert S.fwd_divided_counts() == (before[0] + 1, before[1], 0)

@@ -341,10 +341,12 @@ int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const 
                        p.n_kv_heads, p.scale, sp);
     return (int)hipGetLastError();
   }
-  hipLaunchKernelGGL((fwd_bf16_kernel<D, EXACT>), dim3((unsigned)mapped_grid(n_items, p.n_kv_heads, p.n_q_heads / p.n_kv_heads)), block, 0,
-                     (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items, n_items, (int)c.T,
-                     p.n_q_heads, p.n_kv_heads, p.scale);
-  return (int)hipGetLastError();
+  return in_runs(n_items, p.n_q_heads, [&](int first, int n) {
+    hipLaunchKernelGGL((fwd_bf16_kernel<D, EXACT>), dim3((unsigned)mapped_grid(n, p.n_kv_heads, p.n_q_heads / p.n_kv_heads)), block, 0,
+                       (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items + first, n, (int)c.T,
+                       p.n_q_heads, p.n_kv_heads, p.scale);
+    return (int)hipGetLastError();
+  });
 }
 }  // namespace
 

@@ -133,6 +133,17 @@ struct slimattn_tables {
 
 namespace slimattn {
 
+// A launch may have at most 2^32 - 1 threads in a dimension, and the kernels' lists one item per sample: packs of very many short
+// samples are launched in runs of the list.  f(first, count) launches a run and returns a hipError_t.
+constexpr int64_t kMaxBlocks = int64_t(1) << 22;
+template <class F>
+int in_runs(int n_items, int64_t blocks_per_item, F&& f) {
+  const int run = (int)(kMaxBlocks / blocks_per_item > 0 ? kMaxBlocks / blocks_per_item : 1);
+  int e = 0;
+  for (int a = 0; a < n_items && e == 0; a += run) e = f(a, n_items - a < run ? n_items - a : run);
+  return e;
+}
+
 struct LaunchCtx {
   const slimattn_params* p;
   void* stream;           // hipStream_t

@@ -428,20 +428,24 @@ int launch_fwd_f32(const LaunchCtx& c, const float* q, const float* k, const flo
                    const QItem* items, int n_items) {
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
-  const dim3 grid((unsigned)mapped_grid(2 * n_items, p.n_kv_heads, p.n_q_heads / p.n_kv_heads)), block(64 * kWaves);
-  DISPATCH_D(p.head_dim, hipLaunchKernelGGL(fwd_f32_kernel<D>, grid, block, 0, (hipStream_t)c.stream, q, k, v, o, lse, items,
-                                            n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale));
-  return (int)hipGetLastError();
+  return in_runs(n_items, 2 * (int64_t)p.n_q_heads, [&](int first, int n) -> int {
+    const dim3 grid((unsigned)mapped_grid(2 * n, p.n_kv_heads, p.n_q_heads / p.n_kv_heads)), block(64 * kWaves);
+    DISPATCH_D(p.head_dim, hipLaunchKernelGGL(fwd_f32_kernel<D>, grid, block, 0, (hipStream_t)c.stream, q, k, v, o, lse, items + first,
+                                              n, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale));
+    return (int)hipGetLastError();
+  });
 }
 
 int launch_bwd_dq_f32(const LaunchCtx& c, const float* q, const float* k, const float* v, const float* o, const float* dO,
                       const float* lse, float* delta, float* dQ, const QItem* items, int n_items) {
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
-  const dim3 grid((unsigned)mapped_grid(2 * n_items, p.n_kv_heads, p.n_q_heads / p.n_kv_heads)), block(64 * kWaves);
-  DISPATCH_D(p.head_dim, hipLaunchKernelGGL(dq_f32_kernel<D>, grid, block, 0, (hipStream_t)c.stream, q, k, v, o, dO, lse, delta,
-                                            dQ, items, n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale));
-  return (int)hipGetLastError();
+  return in_runs(n_items, 2 * (int64_t)p.n_q_heads, [&](int first, int n) -> int {
+    const dim3 grid((unsigned)mapped_grid(2 * n, p.n_kv_heads, p.n_q_heads / p.n_kv_heads)), block(64 * kWaves);
+    DISPATCH_D(p.head_dim, hipLaunchKernelGGL(dq_f32_kernel<D>, grid, block, 0, (hipStream_t)c.stream, q, k, v, o, dO, lse, delta,
+                                              dQ, items + first, n, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale));
+    return (int)hipGetLastError();
+  });
 }
 
 int launch_bwd_dkdv_f32(const LaunchCtx& c, const float* q, const float* k, const float* v, const float* dO,
@@ -449,14 +453,18 @@ int launch_bwd_dkdv_f32(const LaunchCtx& c, const float* q, const float* k, cons
                         const KvItem* items, int n_items, const Seg* segs, int longest) {
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
-  const int blocks = 2 * n_items * p.n_kv_heads;
+  const int64_t blocks = 2 * (int64_t)n_items * p.n_kv_heads;
   // Few long walks (up to three rounds of the chip's compute units): the first tiles of the longest sample decide the
   // launch, so every walk is divided in two (the pack above: 634 -> 381 us with the addition).  A wave's longest walk has
   // to be worth the second launch (about 7 us): from 16 steps on (a step is 4 to 8 us at head dims 64 to 128).
   const int parts = longest * (p.n_q_heads / p.n_kv_heads) >= 16 * kSub * kWaves && blocks <= 768 ? 2 : 1;
-  const dim3 grid((unsigned)blocks, parts), block(64 * kWaves);
-  DISPATCH_D(p.head_dim, hipLaunchKernelGGL(dkdv_f32_kernel<D>, grid, block, 0, (hipStream_t)c.stream, q, k, v, dO, lse, delta,
-                                            acc_dk, acc_dv, dK, dV, items, segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale));
+  const int e = in_runs(n_items, 2 * (int64_t)p.n_kv_heads, [&](int first, int n) -> int {
+    const dim3 grid((unsigned)(2 * n * p.n_kv_heads), parts), block(64 * kWaves);
+    DISPATCH_D(p.head_dim, hipLaunchKernelGGL(dkdv_f32_kernel<D>, grid, block, 0, (hipStream_t)c.stream, q, k, v, dO, lse, delta,
+                                              acc_dk, acc_dv, dK, dV, items + first, segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale));
+    return (int)hipGetLastError();
+  });
+  if (e != 0) return e;
   if (parts == 2) {
     const size_t n4 = (size_t)c.T * p.n_kv_heads * p.head_dim / 4;
     hipLaunchKernelGGL(add_parts_f32_kernel, dim3((unsigned)(n4 / 256 < 512 ? n4 / 256 + 1 : 512), 2), dim3(256), 0,

@@ -126,6 +126,32 @@ template <int D> __device__ __forceinline__ void load_rows(RowFrag<D>& f, const 
   for (int c = 0; c < kNC<D>; ++c) f.x[c] = load_row<D>(t, voff, c);
 }
 
+// Keys of the diagonal's tile with a NaN or an infinity: the product over the tile would carry them, times a probability of 0, into
+// the rows in front of them, which do not see them.  If there are any (kr and kc hold the same keys), their values become 0 in kc
+// and NaN goes to the rows that do see them, which is what the product would have given those (their scores are NaN or infinite).
+template <int D>
+__device__ __forceinline__ void unseen_keys(floatx16 (&acc)[kNB<D>], const RowFrag<D>& kr, ColFrag<D>& kc, int rel) {
+  float odd = 0.f;
+#pragma unroll
+  for (int c = 0; c < kNC<D>; ++c)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) odd = fmaf(kr.x[c][j], 0.f, odd);     // stays 0 unless one is not finite
+  if (__builtin_expect(!__any(odd != 0.f), 1)) return;
+#pragma unroll
+  for (int b = 0; b < kNB<D>; ++b) {
+    floatx16 seen = {};                                               // how many such keys a row sees, per dim
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float x = elem<kNB<D>>(kc.x[r], b);
+      const bool bad = !(fabsf(x) < INFINITY);
+      seen = mfma_f32(bad ? 1.f : 0.f, c_row(r) > rel ? 0.f : 1.f, seen);
+      if constexpr (kNB<D> == 1) kc.x[r] = bad ? 0.f : x; else kc.x[r][b] = bad ? 0.f : x;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[b][r] = seen[r] > 0.f ? __builtin_nanf("") : acc[b][r];
+  }
+}
+
 // A wave's accumulator (C layout, lane = row l32) into its LDS area, one row of D floats per lane pair.
 template <int D>
 __device__ __forceinline__ void put_partial(float (*area)[kPad<D>], const floatx16 (&acc)[kNB<D>], int l32, int half) {
@@ -258,21 +284,24 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void dq_f32_kernel(
   floatx16 acc[kNB<D>];
 #pragma unroll
   for (int b = 0; b < kNB<D>; ++b) acc[b] = floatx16{};
-  for (int kb = wave; kb < n; kb += kWaves) {
-    const int key0 = it.kv_start + kSub * kb;
+  auto step = [&](int kb, auto masked_c) {
+    constexpr bool masked = decltype(masked_c)::value != 0;      // the tile touches the diagonal of some row
     const Rows32<D> tk = tile(k, kb), tv = tile(v, kb), tn = tile(k, kb + kWaves);
     floatx16 s = {}, dp = {};
     row_products<D>(s, kr, qf, [&](auto cc) { constexpr int c = decltype(cc)::value; vr.x[c] = load_row<D>(tv, rvoff, c); });
     row_products<D>(dp, vr, dof, [&](auto cc) { cols_by_chunk<D, decltype(cc)::value>(kc, tk, cvoff); });
-    const bool masked = key0 + kSub - 1 > q0;
-    const int rel = masked ? q0 + l32 - key0 - 4 * half : kSub;
+    const int rel = q0 + l32 - it.kv_start - kSub * kb - 4 * half;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float ds = __builtin_amdgcn_exp2f(fmaf(row_lse, -kLog2e, s[r])) * (dp[r] - dlt);
-      s[r] = c_row(r) > rel ? 0.f : ds;
+      s[r] = masked && c_row(r) > rel ? 0.f : ds;
     }
+    if constexpr (masked) unseen_keys<D>(acc, kr, kc, rel);
     col_products<D>(acc, kc, s, [&](auto rc) { rows_by_reg<D, decltype(rc)::value>(kr, tn, rvoff); });
-  }
+  };
+  int kb = wave;
+  for (const int n_full = (q0 + 1 - it.kv_start) / kSub; kb < n_full; kb += kWaves) step(kb, IC<0>{});
+  for (; kb < n; kb += kWaves) step(kb, IC<1>{});
   put_partial<D>(part[wave], acc, l32, half);
   __syncthreads();
   const int row = tid >> 3;

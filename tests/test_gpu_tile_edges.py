@@ -95,3 +95,30 @@ def test_bf16_head_parts_leave_the_static_scratch_enough():
 @pytest.mark.parametrize("hq,hkv,slice_size", [(1, 1, 1000), (3, 1, 97), (4, 2, 64)])
 def test_bf16_dkdv_head_dim_64(L, hq, hkv, slice_size):
     _fused_and_per_unit(L, hq, hkv, 64, True, slice_size)
+
+
+# fp32 dQ: a key with a NaN or an infinity reaches the rows that see it and no row in front of it, in the middle of a tile too; a key of
+# -inf (score -inf, probability 0) spoils only its own dim of those rows
+@pytest.mark.parametrize("d", [16, 32, 64, 128])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+def test_fp32_dq_of_rows_in_front_of_a_key_that_is_not_finite(d, value):
+    at = 90
+    prob, ref = _problem([37, 130], 2, 1, d, False, 1000)
+    prob.q[:, :, 3] = prob.q[:, :, 3].abs() + 0.5
+    prob.dO.mul_(0.1)
+    prob.forward()
+    prob.backward()
+    torch.cuda.synchronize()
+    want = prob.dQ.clone()
+    prob.k[at, 0, 3] = value
+    prob.dQ.fill_(7.0)
+    prob.forward()
+    prob.backward()
+    torch.cuda.synchronize()
+    assert torch.equal(prob.dQ[:at], want[:at])
+    assert not torch.isfinite(prob.dQ[at:, :, 3]).any()
+    if value < 0:
+        dims = [c for c in range(d) if c != 3]
+        assert torch.isfinite(prob.dQ[at:][:, :, dims]).all()
+    else:
+        assert torch.isnan(prob.dQ[at:]).all()

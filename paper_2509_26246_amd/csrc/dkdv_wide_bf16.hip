@@ -45,14 +45,15 @@ namespace {
 constexpr int kKeys = 256;                              // key rows per block: 4 waves x 64
 constexpr int kQStep = 32;
 constexpr int kStages = 3;
-template <int D> constexpr int kNKS = D / 16;           // head-dim steps of a score product
-template <int D> constexpr int kNDB = D / 32;           // head-dim blocks of a gradient accumulator
-template <int D> constexpr int kRowBytes = D * 2;
-template <int D> constexpr int kTileBytes = kQStep * kRowBytes<D>;   // one Q or dO tile
-template <int D> constexpr int kStageBytes = 2 * kTileBytes<D>;      // [Q tile, dO tile]
-template <int D> constexpr int kVBase = kStages * kStageBytes<D>;
-template <int D> constexpr int kVBytes = kKeys * kRowBytes<D>;
-template <int D> constexpr int kGradBatches = 2 * kNDB<D>;           // batches of transposed reads in the gradient phase
+constexpr int D = 128;                                  // head dim
+constexpr int kNKS = D / 16;                            // head-dim steps of a score product
+constexpr int kNDB = D / 32;                            // head-dim blocks of a gradient accumulator
+constexpr int kRowBytes = D * 2;
+constexpr int kTileBytes = kQStep * kRowBytes;          // one Q or dO tile
+constexpr int kStageBytes = 2 * kTileBytes;             // [Q tile, dO tile]
+constexpr int kVBase = kStages * kStageBytes;
+constexpr int kVBytes = kKeys * kRowBytes;
+constexpr int kGradBatches = 2 * kNDB;                  // batches of transposed reads in the gradient phase
 constexpr float kLog2e = 1.4426950408889634f;
 
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned uintx4;   // a packed bf16x8 fragment, by dword
@@ -82,22 +83,22 @@ __device__ __forceinline__ void mfma_acc(floatx16& acc, bf16x8 a, bf16x8 b) {
 // (local row - 4*half outside [rel_lo[kb], rel_hi): before the lane's key, or past the end of the query
 // run) are then set to -inf, so that their probability and dS come out as zero.
 // One batch of LDS reads per head-dim step: the Q and dO fragments and the two V fragments.
-template <int D, class Between>
-__device__ __forceinline__ void score_products(const lds_cptr (&pq)[kNKS<D>], int v_rel, bf16x8 stat, uintx4 ones_l, uintx4 ones_d,
-                                               const bf16x8 (&kf)[2][kNKS<D>], floatx16 (&s)[2], floatx16 (&dp)[2],
+template <class Between>
+__device__ __forceinline__ void score_products(const lds_cptr (&pq)[kNKS], int v_rel, bf16x8 stat, uintx4 ones_l, uintx4 ones_d,
+                                               const bf16x8 (&kf)[2][kNKS], floatx16 (&s)[2], floatx16 (&dp)[2],
                                                bool masked, const int (&rel_lo)[2], int rel_hi, Between&& between) {
   // Fragment i of head-dim step u: 0 Q rows, 1 dO rows, 2/3 the V rows of the two key blocks.  The
   // reads of step u + 2 are issued one behind each product of step u (an LDS read takes about twice the
   // issue time of a plain instruction: four in a row would outlast the product they follow); those of
   // the first two steps run while the accumulators are started.
-  R4 g[kNKS<D>];
+  R4 g[kNKS];
   lds_cptr pv = pq[0];
   auto issue_one = [&](auto uc, auto ic) {
     constexpr int u = decltype(uc)::value, i = decltype(ic)::value;
     if constexpr (i == 0) r1_issue<0>(pq[u], g[u].f[0]);
-    if constexpr (i == 1) { r1_issue<kTileBytes<D>>(pq[u], g[u].f[1]); pv = pq[u] + v_rel; }
+    if constexpr (i == 1) { r1_issue<kTileBytes>(pq[u], g[u].f[1]); pv = pq[u] + v_rel; }
     if constexpr (i == 2) r1_issue<0>(pv, g[u].f[2]);
-    if constexpr (i == 3) r1_issue<32 * kRowBytes<D>>(pv, g[u].f[3]);
+    if constexpr (i == 3) r1_issue<32 * kRowBytes>(pv, g[u].f[3]);
   };
   static_for<0, 4>([&](auto ic) { issue_one(IC<0>{}, ic); });
   // asm: two of the four products are equal and the compiler would compute them once and copy
@@ -120,9 +121,9 @@ __device__ __forceinline__ void score_products(const lds_cptr (&pq)[kNKS<D>], in
       }
     }
   }
-  static_for<0, kNKS<D>>([&](auto uc) {
+  static_for<0, kNKS>([&](auto uc) {
     constexpr int u = decltype(uc)::value;
-    constexpr bool more = u + 2 < kNKS<D>;
+    constexpr bool more = u + 2 < kNKS;
     lds_wait<4>(g[u]);                                  // behind step u: step u + 1 or, at the end, a batch of gradient reads
     s[0] = mfma32(g[u].f[0], kf[0][u], s[0]);
     if constexpr (more) issue_one(IC<u + 2>{}, IC<0>{});
@@ -202,10 +203,10 @@ __device__ __forceinline__ void ew_slot(floatx16 (&s)[2], floatx16 (&dp)[2], uin
 
 // Read i (of four) of gradient batch B: the dO^T fragment (reads 0, 1) and the Q^T fragment (2, 3) of
 // head-dim block B % 4, rows 16 (B / 4) .. +16 of the step's tiles.
-template <int D, int B, int I>
-__device__ __forceinline__ void grad_read(const lds_cptr (&pqt)[kNDB<D>][2], Tr2 (&tb)[kGradBatches<D>]) {
-  constexpr int st = B / kNDB<D>, db = B % kNDB<D>;
-  tr1_issue<st * 16 * kRowBytes<D> + (I < 2 ? kTileBytes<D> : 0)>(pqt[db][I & 1], tb[B].r[I]);
+template <int B, int I>
+__device__ __forceinline__ void grad_read(const lds_cptr (&pqt)[kNDB][2], Tr2 (&tb)[kGradBatches]) {
+  constexpr int st = B / kNDB, db = B % kNDB;
+  tr1_issue<st * 16 * kRowBytes + (I < 2 ? kTileBytes : 0)>(pqt[db][I & 1], tb[B].r[I]);
 }
 
 // Gradient products of one step, dV_kb^T += dO^T P_kb and dK_kb^T += Q^T dS_kb, with P, dS packed in
@@ -213,35 +214,35 @@ __device__ __forceinline__ void grad_read(const lds_cptr (&pqt)[kNDB<D>][2], Tr2
 // one batch of two transposed fragments (dO^T, Q^T), each feeding both key blocks.  The element-wise work
 // of the next step (its scores in s, dp) is spread between the products (see ew_slot), and its packed
 // results are left in pf[.][0], ds[.][0] (first 16-row half) and tp, td (second half).  FIRST: the block's first call, which starts the accumulators.
-template <int D, bool FIRST>
-__device__ __forceinline__ void gradient_products(const lds_cptr (&pqt)[kNDB<D>][2], uintx4 (&pf)[2][2], uintx4 (&ds)[2][2],
-                                                  floatx16 (&dk)[2][kNDB<D>], floatx16 (&dv)[2][kNDB<D>], floatx16 (&s)[2],
+template <bool FIRST>
+__device__ __forceinline__ void gradient_products(const lds_cptr (&pqt)[kNDB][2], uintx4 (&pf)[2][2], uintx4 (&ds)[2][2],
+                                                  floatx16 (&dk)[2][kNDB], floatx16 (&dv)[2][kNDB], floatx16 (&s)[2],
                                                   floatx16 (&dp)[2], uintx4 (&tp)[2], uintx4 (&td)[2],
-                                                  Tr2 (&tb)[kGradBatches<D>]) {
+                                                  Tr2 (&tb)[kGradBatches]) {
   // batch b: head-dim block b % 4 of 16-row half b / 4 (first half first: its P, dS die early); its
   // four reads are issued one behind each product of batch b - 2, those of batches 0 and 1 behind the
   // last score products (by the caller)
-  static_assert(4 * kGradBatches<D> == 32, "one element-wise value per product");
+  static_assert(4 * kGradBatches == 32, "one element-wise value per product");
   auto ew = [&](auto qc) { ew_slot<decltype(qc)::value>(s, dp, pf, ds, tp, td); };   // the element-wise work behind product q of the phase
-  static_for<0, kGradBatches<D>>([&](auto ic) {
-    constexpr int b = decltype(ic)::value, st = b / kNDB<D>, db = b % kNDB<D>;
-    constexpr bool more = b + 2 < kGradBatches<D>;
-    lds_wait<(b + 1 < kGradBatches<D>) ? 4 : 0>(tb[b]);
+  static_for<0, kGradBatches>([&](auto ic) {
+    constexpr int b = decltype(ic)::value, st = b / kNDB, db = b % kNDB;
+    constexpr bool more = b + 2 < kGradBatches;
+    lds_wait<(b + 1 < kGradBatches) ? 4 : 0>(tb[b]);
     constexpr bool kStart = FIRST && st == 0;
     mfma_acc<kStart>(dv[0][db], tr2_frag(tb[b], 0), as_frag(pf[0][st]));
-    if constexpr (more) grad_read<D, b + 2, 0>(pqt, tb);
+    if constexpr (more) grad_read<b + 2, 0>(pqt, tb);
     ew(IC<4 * b + 0>{});
     __builtin_amdgcn_sched_barrier(0);
     mfma_acc<kStart>(dv[1][db], tr2_frag(tb[b], 0), as_frag(pf[1][st]));
-    if constexpr (more) grad_read<D, b + 2, 1>(pqt, tb);
+    if constexpr (more) grad_read<b + 2, 1>(pqt, tb);
     ew(IC<4 * b + 1>{});
     __builtin_amdgcn_sched_barrier(0);
     mfma_acc<kStart>(dk[0][db], tr2_frag(tb[b], 1), as_frag(ds[0][st]));
-    if constexpr (more) grad_read<D, b + 2, 2>(pqt, tb);
+    if constexpr (more) grad_read<b + 2, 2>(pqt, tb);
     ew(IC<4 * b + 2>{});
     __builtin_amdgcn_sched_barrier(0);
     mfma_acc<kStart>(dk[1][db], tr2_frag(tb[b], 1), as_frag(ds[1][st]));
-    if constexpr (more) grad_read<D, b + 2, 3>(pqt, tb);
+    if constexpr (more) grad_read<b + 2, 3>(pqt, tb);
     ew(IC<4 * b + 3>{});
     __builtin_amdgcn_sched_barrier(0);
   });
@@ -257,13 +258,12 @@ __device__ __forceinline__ void lds_ptr_add(lds_cptr& p, int d) {
 
 struct Step { int i0, hi, head; };                      // rows [i0, min(i0 + 32, hi)) of one query head
 
-template <int D>
 __device__ __forceinline__ void dkdv_wide_block(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ dO,
     const bf16x8* __restrict__ stat3, float* __restrict__ acc_dk, float* __restrict__ acc_dv,
     bf16* __restrict__ dK, bf16* __restrict__ dV, const KvItem* __restrict__ items, int n_items, const Seg* __restrict__ segs,
     int T, int Hq, int Hkv, float scale, float* __restrict__ parts, int head_parts) {
-  __shared__ __attribute__((aligned(1024))) char smem[kVBase<D> + kVBytes<D>];   // three [Q, dO] stages, then the V tile
+  __shared__ __attribute__((aligned(1024))) char smem[kVBase + kVBytes];   // three [Q, dO] stages, then the V tile
 
   const int g = Hq / Hkv;
   // head_parts > 1: that many blocks share the item, each with a run of the group's heads; all store partial tiles
@@ -326,7 +326,7 @@ __device__ __forceinline__ void dkdv_wide_block(
   // gradient products, whatever the memory holds.
   const bf16* const q_base = q + (size_t)it.kv_row0 * Hq * D;
   const bf16* const do_base = dO + (size_t)it.kv_row0 * Hq * D;
-  auto run_range = [&](const Step& d) -> int { return (d.hi - it.kv_row0) * (Hq * kRowBytes<D>); };   // bytes up to the run's end
+  auto run_range = [&](const Step& d) -> int { return (d.hi - it.kv_row0) * (Hq * kRowBytes); };   // bytes up to the run's end
   auto rsrc_of = [&](const bf16* base, int bytes) -> __amdgpu_buffer_rsrc_t {
     return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
   };
@@ -335,10 +335,10 @@ __device__ __forceinline__ void dkdv_wide_block(
     TileSource a = srcQ, b = srcQ;
     a.rsrc = rsrc_of(q_base, run_range(d));
     b.rsrc = rsrc_of(do_base, run_range(d));
-    a.voff += d.head * kRowBytes<D>;
-    b.voff += d.head * kRowBytes<D>;
-    stage_tile<D, kQStep, 256>(lds + st * kStageBytes<D>, a, d.i0 - it.kv_row0, tid);
-    stage_tile<D, kQStep, 256>(lds + st * kStageBytes<D> + kTileBytes<D>, b, d.i0 - it.kv_row0, tid);
+    a.voff += d.head * kRowBytes;
+    b.voff += d.head * kRowBytes;
+    stage_tile<D, kQStep, 256>(lds + st * kStageBytes, a, d.i0 - it.kv_row0, tid);
+    stage_tile<D, kQStep, 256>(lds + st * kStageBytes + kTileBytes, b, d.i0 - it.kv_row0, tid);
   };
   // A step's statistics for this lane's row (-lse2, -delta as bf16 triples; rows past the end of the run
   // are masked later), through a buffer descriptor: a per-lane byte offset (stat_voff) plus a scalar one.
@@ -361,14 +361,14 @@ __device__ __forceinline__ void dkdv_wide_block(
   bool have_s = true;
   {
     const TileSource srcV = make_tile_source<D, 256>(v, it.kv_row0, Hkv, hk, kv_end, tid);
-    stage_tile<D, kKeys, 256>(lds + kVBase<D>, srcV, 0, tid);
+    stage_tile<D, kKeys, 256>(lds + kVBase, srcV, 0, tid);
   }
-  bf16x8 kf[2][kNKS<D>];
+  bf16x8 kf[2][kNKS];
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     const size_t off = ((size_t)min(kv0w + 32 * kb + l32, T - 1) * Hkv + hk) * D + 8 * half;
 #pragma unroll
-    for (int ks = 0; ks < kNKS<D>; ++ks) {
+    for (int ks = 0; ks < kNKS; ++ks) {
       kf[kb][ks] = scale8(*reinterpret_cast<const bf16x8*>(k + off + 16 * ks), scale * kLog2e);
       __builtin_amdgcn_sched_barrier(0);              // one fragment at a time: this set-up code must not need many registers
     }
@@ -376,13 +376,13 @@ __device__ __forceinline__ void dkdv_wide_block(
   // pq[]: row-fragment addresses in the stage of the step whose scores are computed next; pqt[][]:
   // transposed-fragment addresses in the stage of the step whose gradients are computed next.  Both move
   // one stage per iteration (with wrap-around), so every LDS offset in the products is an immediate.
-  lds_cptr pq[kNKS<D>], pqt[kNDB<D>][2];
+  lds_cptr pq[kNKS], pqt[kNDB][2];
 #pragma unroll
-  for (int ks = 0; ks < kNKS<D>; ++ks) pq[ks] = lds_row_ptr<D>(lds, l32, 16 * ks + 8 * half);
+  for (int ks = 0; ks < kNKS; ++ks) pq[ks] = lds_row_ptr<D>(lds, l32, 16 * ks + 8 * half);
 #pragma unroll
-  for (int db = 0; db < kNDB<D>; ++db) lds_tr_ptrs<D>(lds, 32 * db, lane, pqt[db][0], pqt[db][1]);
-  int v_rel = kVBase<D> + wave * 64 * kRowBytes<D>;           // the swizzle of row 64 w + 32 kb + l32 equals that of row l32
-  floatx16 dk[2][kNDB<D>], dv[2][kNDB<D>];                    // started by the first iteration's products
+  for (int db = 0; db < kNDB; ++db) lds_tr_ptrs<D>(lds, 32 * db, lane, pqt[db][0], pqt[db][1]);
+  int v_rel = kVBase + wave * 64 * kRowBytes;           // the swizzle of row 64 w + 32 kb + l32 equals that of row l32
+  floatx16 dk[2][kNDB], dv[2][kNDB];                    // started by the first iteration's products
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
@@ -419,30 +419,30 @@ __device__ __forceinline__ void dkdv_wide_block(
   auto iteration = [&](auto first_c) {
     constexpr bool first = decltype(first_c)::value != 0;
     const int st_n = st_s == 2 ? 0 : st_s + 1;
-    const int dq_ = st_s == 2 ? -2 * kStageBytes<D> : kStageBytes<D>;   // pq's move to the next stage
+    const int dq_ = st_s == 2 ? -2 * kStageBytes : kStageBytes;   // pq's move to the next stage
     bool have_n = false;
     int voff_n = 0, soff_n = 0;
-    Tr2 tb[kGradBatches<D>];                               // the gradient phase's batches of transposed fragments
-    const int m0_n = st_n * kStageBytes<D> + wave_off;     // where this wave's lines of the first pass go
+    Tr2 tb[kGradBatches];                               // the gradient phase's batches of transposed fragments
+    const int m0_n = st_n * kStageBytes + wave_off;     // where this wave's lines of the first pass go
     // slots of the pieces (behind score product k, of 32), spread out.
     // A piece is a handful of instructions: what does not fit behind its product delays the next one.
     constexpr int kSlotWalkA = 4, kSlotWalkB = 5, kSlotWalkC = 6;
     constexpr int kSlotStatA = 7, kSlotStat = 8, kSlotAddr = 9;
     constexpr int kSlotLoad = 10, kLoadStride = 2, kSlotMask = 18;
-    constexpr int kSlotGrad = 4 * (kNKS<D> - 2);
-    constexpr int kPasses = kTileBytes<D> / 4096;         // staging loads per tile (256 threads x 16 bytes each)
+    constexpr int kSlotGrad = 4 * (kNKS - 2);
+    constexpr int kPasses = kTileBytes / 4096;         // staging loads per tile (256 threads x 16 bytes each)
     bool ok_n = false;
     int stat_off = 0, range_n = 0;
     auto between = [&](auto kc) {                       // piece k of the bookkeeping, behind score product k
       constexpr int k = decltype(kc)::value;
-      if constexpr (k < kNDB<D>) { lds_ptr_add(pqt[k][0], dt_pend); lds_ptr_add(pqt[k][1], dt_pend); }
+      if constexpr (k < kNDB) { lds_ptr_add(pqt[k][0], dt_pend); lds_ptr_add(pqt[k][1], dt_pend); }
       if constexpr (k == kSlotWalkA) { ok_n = next_step_a(d_n); have_n = have_s && ok_n; }
       if constexpr (k == kSlotWalkB) next_step_b(ok_n);
       if constexpr (k == kSlotWalkC) next_step_c(ok_n);
       if constexpr (k == kSlotStatA) { stat_off = stat_voff(d_n); asm volatile("" : "+v"(stat_off)); }
       if constexpr (k == kSlotStat) stat_n = load_stat_at(d_n, stat_off);   // d_n always names a real step (the last one, when the walk has ended)
       if constexpr (k == kSlotAddr) {
-        voff_n = srcQ.voff + d_n.head * kRowBytes<D>;   // the Q and dO sources differ in their descriptors only
+        voff_n = srcQ.voff + d_n.head * kRowBytes;   // the Q and dO sources differ in their descriptors only
         soff_n = __builtin_amdgcn_readfirstlane((d_n.i0 - it.kv_row0) * srcQ.row_bytes);
         range_n = __builtin_amdgcn_readfirstlane(run_range(d_n));
         asm volatile("" : "+v"(voff_n), "+s"(soff_n), "+s"(range_n));
@@ -450,23 +450,23 @@ __device__ __forceinline__ void dkdv_wide_block(
       if constexpr (k >= kSlotLoad && k < kSlotLoad + 2 * kPasses * kLoadStride && (k - kSlotLoad) % kLoadStride == 0) {
         // one load each: the passes of the Q tile, then of the dO tile
         constexpr int x = (k - kSlotLoad) / kLoadStride, tile = x / kPasses, pass = x % kPasses;
-        constexpr int kRowsPerPass = 4096 / kRowBytes<D>;
+        constexpr int kRowsPerPass = 4096 / kRowBytes;
         // (when the walk has ended d_n still names the last step: its tile is staged once more, into a stage nobody reads)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_of(tile ? do_base : q_base, range_n), lds + m0_n + tile * kTileBytes<D> + pass * 4096, 16,
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc_of(tile ? do_base : q_base, range_n), lds + m0_n + tile * kTileBytes + pass * 4096, 16,
                                                  voff_n, soff_n + pass * kRowsPerPass * srcQ.row_bytes, 0, 0);
       }
       if constexpr (k == kSlotMask) m_n = masks(d_n);
       if constexpr (k >= kSlotGrad && k < kSlotGrad + 8) {   // the gradient phase's first two batches of reads
-        grad_read<D, (k - kSlotGrad) / 4, (k - kSlotGrad) % 4>(pqt, tb);
-        if constexpr (k - kSlotGrad < kNKS<D>) lds_ptr_add(pq[k - kSlotGrad], dq_);
+        grad_read<(k - kSlotGrad) / 4, (k - kSlotGrad) % 4>(pqt, tb);
+        if constexpr (k - kSlotGrad < kNKS) lds_ptr_add(pq[k - kSlotGrad], dq_);
       }
       if constexpr (k == kSlotGrad + 7) v_rel -= dq_;
     };
     floatx16 s[2], dp[2];
     uintx4 tp[2], td[2];                                // packed P, dS of the second 16-row half of the step being scored
     const int rel_lo[2] = {m_s.rel_lo0, m_s.rel_lo0 + 32};
-    score_products<D>(pq, v_rel, stat_s, ones_l, ones_d, kf, s, dp, m_s.masked, rel_lo, m_s.rel_hi, between);
-    gradient_products<D, first>(pqt, pf, ds, dk, dv, s, dp, tp, td, tb);
+    score_products(pq, v_rel, stat_s, ones_l, ones_d, kf, s, dp, m_s.masked, rel_lo, m_s.rel_hi, between);
+    gradient_products<first>(pqt, pf, ds, dk, dv, s, dp, tp, td, tb);
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) { pf[kb][1] = tp[kb]; ds[kb][1] = td[kb]; }
     __builtin_amdgcn_s_waitcnt(0);
@@ -476,7 +476,7 @@ __device__ __forceinline__ void dkdv_wide_block(
     m_s = m_n;
     stat_s = stat_n;
     have_s = have_n;
-    dt_pend = first ? 0 : (st_s == 0 ? -2 * kStageBytes<D> : kStageBytes<D>);   // pqt moves to the stage just scored
+    dt_pend = first ? 0 : (st_s == 0 ? -2 * kStageBytes : kStageBytes);   // pqt moves to the stage just scored
     st_s = st_n;
   };
   iteration(IC<1>{});
@@ -490,8 +490,8 @@ __device__ __forceinline__ void dkdv_wide_block(
     // the loop's last barrier; each wave uses a part of its own).  A lane owns a row's values in pieces of 4
     // columns, and written as they stand each store instruction would touch 32 rows with 16 bytes each;
     // transposed, a store instruction writes whole rows.
-    constexpr int kOutStride = kRowBytes<D> + 16, kChunks = kRowBytes<D> / 16, kRowsPerStore = 64 / kChunks;
-    static_assert(4 * 64 * kOutStride <= kVBase<D> + kVBytes<D>, "the transposition areas must fit the block's LDS");
+    constexpr int kOutStride = kRowBytes + 16, kChunks = kRowBytes / 16, kRowsPerStore = 64 / kChunks;
+    static_assert(4 * 64 * kOutStride <= kVBase + kVBytes, "the transposition areas must fit the block's LDS");
     LDS_PTR(char) ep = lds + wave * 64 * kOutStride;
     const int st_row = lane / kChunks, st_chunk = lane % kChunks;
 #pragma unroll
@@ -499,7 +499,7 @@ __device__ __forceinline__ void dkdv_wide_block(
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int db = 0; db < kNDB<D>; ++db)
+        for (int db = 0; db < kNDB; ++db)
 #pragma unroll
           for (int gq = 0; gq < 4; ++gq) {
             bf16x4 w;
@@ -525,7 +525,7 @@ __device__ __forceinline__ void dkdv_wide_block(
       float* pk_ = parts + ((size_t)slot * Hkv + hk) * (2 * kKeys * D) + (size_t)(64 * wave + 32 * kb + l32) * D;
       float* pv_ = pk_ + kKeys * D;
 #pragma unroll
-      for (int db = 0; db < kNDB<D>; ++db)
+      for (int db = 0; db < kNDB; ++db)
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
           const int off = 32 * db + 8 * gq + 4 * half;
@@ -539,7 +539,7 @@ __device__ __forceinline__ void dkdv_wide_block(
       const size_t base = ((size_t)my_key * Hkv + hk) * D;
       const bool load_acc = my_key < it.load_until, store_final = my_key >= it.final_from;
 #pragma unroll
-      for (int db = 0; db < kNDB<D>; ++db)
+      for (int db = 0; db < kNDB; ++db)
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
           const size_t off = base + 32 * db + 8 * gq + 4 * half;
@@ -570,7 +570,7 @@ __global__ __launch_bounds__(256, 1) void dkdv_wide_bf16_kernel_d128(
     const bf16x8* __restrict__ stat3, float* __restrict__ acc_dk, float* __restrict__ acc_dv, bf16* __restrict__ dK,
     bf16* __restrict__ dV, const KvItem* __restrict__ items, int n_items, const Seg* __restrict__ segs, int T, int Hq, int Hkv,
     float scale, float* __restrict__ parts, int head_parts) {
-  dkdv_wide_block<128>(q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n_items, segs, T, Hq, Hkv, scale, parts, head_parts);
+  dkdv_wide_block(q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n_items, segs, T, Hq, Hkv, scale, parts, head_parts);
 }
 
 }  // namespace

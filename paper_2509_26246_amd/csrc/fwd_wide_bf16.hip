@@ -41,13 +41,13 @@ namespace slimattn {
 namespace {
 
 constexpr int kKeys = 64;                               // keys per tile: two units of 32
-template <int D> constexpr int kNKS = D / 16;           // head-dim steps of a score product
-template <int D> constexpr int kNDB = D / 32;           // head-dim blocks of an O^T accumulator
-template <int D> constexpr int kNVF = 2 * kNDB<D>;      // V^T fragments of a unit: 2 key steps x head-dim blocks
-template <int D> constexpr int kRowBytes = D * 2;
-template <int D> constexpr int kTileBytes = kKeys * kRowBytes<D>;
-template <int D> constexpr int kVBase = 2 * kTileBytes<D>;   // LDS: K buffer 0, K buffer 1, V buffer 0, V buffer 1
-template <int D> constexpr int kPer = 128 / D;          // element-wise values per product slot
+constexpr int D = 128;                                  // head dim
+constexpr int kNKS = D / 16;                            // head-dim steps of a score product
+constexpr int kNDB = D / 32;                            // head-dim blocks of an O^T accumulator
+constexpr int kNVF = 2 * kNDB;                          // V^T fragments of a unit: 2 key steps x head-dim blocks
+constexpr int kRowBytes = D * 2;
+constexpr int kTileBytes = kKeys * kRowBytes;
+constexpr int kVBase = 2 * kTileBytes;                  // LDS: K buffer 0, K buffer 1, V buffer 0, V buffer 1
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 // the reference moves when a lane's sum of the 16 probabilities of a unit and head exceeds this (so no
@@ -56,7 +56,6 @@ constexpr float kLazySum = 4096.f;
 
 typedef __attribute__((__vector_size__(4 * sizeof(unsigned)))) unsigned uintx4;
 __device__ __forceinline__ bf16x8 as_frag(uintx4 x) { return __builtin_bit_cast(bf16x8, x); }
-__device__ __forceinline__ int fbits(float x) { return __builtin_bit_cast(int, x); }
 
 struct Tr1 { short4v r[2]; };                           // one transposed fragment: two 64-bit reads
 __device__ __forceinline__ bf16x8 tr1_frag(const Tr1& t) {
@@ -138,11 +137,11 @@ __device__ __forceinline__ void ew_flush(uintx4 (&pf)[2][2][2], float& e0, float
 // the walk is one part of the item (a part's own first key may take no part in the softmax: a score of -inf, or one so far below
 // the others that they would be lost against it).  PART: the walk may end before the diagonal.  out(head, O^T, reference, row
 // sum) takes the results of the wave's two heads.
-template <int D, bool PART, class Out>
+template <bool PART, class Out>
 __device__ __forceinline__ void fwd_wide_item(LDS_PTR(char) lds, const QItem it, const int first_key, const int n_tiles, const int hk,
                                               const int hp, const bf16* __restrict__ q, const bf16* __restrict__ k,
                                               const bf16* __restrict__ v, int Hq, int Hkv, float scale, Out&& out) {
-  constexpr int NKS = kNKS<D>, NDB = kNDB<D>, NVF = kNVF<D>, PER = kPer<D>;
+  constexpr int NKS = kNKS, NDB = kNDB, NVF = kNVF;
   const int g = Hq / Hkv;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int h0 = hk * g + 2 * hp;
@@ -167,14 +166,14 @@ __device__ __forceinline__ void fwd_wide_item(LDS_PTR(char) lds, const QItem it,
   const TileSource srcV = make_tile_source<D, 256>(v, it.kv_start, Hkv, hk, q_end, tid);
   // K(0), K(1) and V(0) are on their way before anything waits: one memory latency per item, not one per early tile
   stage_tile<D, kKeys, 256>(lds, srcK, 0, tid);
-  stage_tile<D, kKeys, 256>(lds + kTileBytes<D>, srcK, kKeys, tid);
-  stage_tile<D, kKeys, 256>(lds + kVBase<D>, srcV, 0, tid);
+  stage_tile<D, kKeys, 256>(lds + kTileBytes, srcK, kKeys, tid);
+  stage_tile<D, kKeys, 256>(lds + kVBase, srcV, 0, tid);
 
   lds_cptr pk[NKS], pv[NDB][2];                         // fragment addresses: K buffer 0, V buffer 0
 #pragma unroll
   for (int u = 0; u < NKS; ++u) pk[u] = lds_row_ptr<D>(lds, l32, 16 * u + 8 * half);
 #pragma unroll
-  for (int db = 0; db < NDB; ++db) lds_tr_ptrs<D>(lds + kVBase<D>, 32 * db, lane, pv[db][0], pv[db][1]);
+  for (int db = 0; db < NDB; ++db) lds_tr_ptrs<D>(lds + kVBase, 32 * db, lane, pv[db][0], pv[db][1]);
 
   floatx16 o[2][NDB];                                   // O^T of the two heads: accumulation registers
 #pragma unroll
@@ -233,12 +232,8 @@ __device__ __forceinline__ void fwd_wide_item(LDS_PTR(char) lds, const QItem it,
       for (int r = 0; r < 16; ++r) s[hb][KB][r] = (8 * (r >> 2) + (r & 3) > rel) ? -INFINITY : negm[hb][r];
   };
   auto settle = [&]() {                                 // results of the asm products become readable
-    if constexpr (NDB == 4)
-      asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15"
-                   : "+a"(o[0][0]), "+a"(o[0][1]), "+a"(o[0][2]), "+a"(o[0][3]), "+a"(o[1][0]), "+a"(o[1][1]), "+a"(o[1][2]),
-                     "+a"(o[1][3]));
-    else
-      asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" : "+a"(o[0][0]), "+a"(o[0][1]), "+a"(o[1][0]), "+a"(o[1][1]));
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15"
+                 : "+a"(o[0][0]), "+a"(o[0][1]), "+a"(o[0][2]), "+a"(o[0][3]), "+a"(o[1][0]), "+a"(o[1][1]), "+a"(o[1][2]), "+a"(o[1][3]));
   };
   // The reference moves (rare): unit KB has just been turned into probabilities against the old reference
   // and nobody has used them; unit 1 - KB has its scores and waits for its element-wise pass.
@@ -294,12 +289,12 @@ __device__ __forceinline__ void fwd_wide_item(LDS_PTR(char) lds, const QItem it,
   auto iteration = [&](auto first_c, auto masked_c) {
     constexpr bool first = decltype(first_c)::value != 0;
     using MaskT = decltype(masked_c);
-    const int dbuf = (t & 1) ? kTileBytes<D> : -kTileBytes<D>;   // both pointer sets move to buffer t & 1
-    const int kdst = (t & 1) * kTileBytes<D> + wave_off;                       // K(t+2) -> K buffer t & 1
-    const int vdst = kVBase<D> + ((t + 1) & 1) * kTileBytes<D> + wave_off;     // V(t+1) -> V buffer (t+1) & 1
+    const int dbuf = (t & 1) ? kTileBytes : -kTileBytes;   // both pointer sets move to buffer t & 1
+    const int kdst = (t & 1) * kTileBytes + wave_off;                       // K(t+2) -> K buffer t & 1
+    const int vdst = kVBase + ((t + 1) & 1) * kTileBytes + wave_off;     // V(t+1) -> V buffer (t+1) & 1
     bf16x8 ka[2][NKS];
     Tr1 va[2][NVF];
-    constexpr int kPasses = kTileBytes<D> / 4096, kRowsPerPass = 4096 / kRowBytes<D>;
+    constexpr int kPasses = kTileBytes / 4096, kRowsPerPass = 4096 / kRowBytes;
     // Tiles behind the item's last are not fetched: their loads get an offset beyond the tensor (the hardware's range
     // check answers with zeros at once), so that the wait that ends the item's last iterations does not sit out
     // the latency of loads nobody needs; the number of loads per iteration stays fixed.
@@ -309,7 +304,7 @@ __device__ __forceinline__ void fwd_wide_item(LDS_PTR(char) lds, const QItem it,
 
     auto ew = [&](auto kec, auto jc) {                  // the element-wise slots behind product slot j of a half
       constexpr int KE = decltype(kec)::value, j = decltype(jc)::value;
-      static_for<0, PER>([&](auto ec) { ew_slot<KE, PER * j + decltype(ec)::value>(s, pf, e0, e1, lr, lu); });
+      ew_slot<KE, j>(s, pf, e0, e1, lr, lu);
     };
     // Score products of unit (t+1, KB).  NEXT: what the last two fragments' slots prefetch: 1 the unit's first
     // V^T fragments (its O^T update comes next), 2 the K fragments of key block 1, 0 nothing.  EW: the
@@ -326,12 +321,12 @@ __device__ __forceinline__ void fwd_wide_item(LDS_PTR(char) lds, const QItem it,
         if constexpr (u == 0 && !kMasked) mfma_v_from(s[hb][KB], ka[KB][u], qf[hb][u], negm[hb]);
         else mfma_v(s[hb][KB], ka[KB][u], qf[hb][u]);
         if constexpr (u + 2 < NKS) {
-          if constexpr (hb == 0) r1_issue<KB * 32 * kRowBytes<D>>(pk[u + 2], ka[KB][u + 2]);
+          if constexpr (hb == 0) r1_issue<KB * 32 * kRowBytes>(pk[u + 2], ka[KB][u + 2]);
         } else if constexpr (NEXT == 1) {
           constexpr int f = u + 2 - NKS;                // ks = 0, db = f
-          tr1_issue<2 * KB * 16 * kRowBytes<D>>(pv[f][hb], va[KB][f].r[hb]);
+          tr1_issue<2 * KB * 16 * kRowBytes>(pv[f][hb], va[KB][f].r[hb]);
         } else if constexpr (NEXT == 2) {
-          if constexpr (hb == 0) r1_issue<32 * kRowBytes<D>>(pk[u + 2 - NKS], ka[1][u + 2 - NKS]);
+          if constexpr (hb == 0) r1_issue<32 * kRowBytes>(pk[u + 2 - NKS], ka[1][u + 2 - NKS]);
         }
         if constexpr (EW) ew(IC<1 - KB>{}, pc);
         extra(pc);
@@ -351,9 +346,9 @@ __device__ __forceinline__ void fwd_wide_item(LDS_PTR(char) lds, const QItem it,
         mfma_acc(o[hb][db], tr1_frag(va[KB][f]), as_frag(pf[hb][KB][ks]));
         if constexpr (f + 2 < NVF) {
           constexpr int f2 = f + 2, ks2 = f2 / NDB, db2 = f2 % NDB;
-          tr1_issue<(2 * KB + ks2) * 16 * kRowBytes<D>>(pv[db2][hb], va[KB][f2].r[hb]);
+          tr1_issue<(2 * KB + ks2) * 16 * kRowBytes>(pv[db2][hb], va[KB][f2].r[hb]);
         } else if constexpr (NEXT == 2) {
-          if constexpr (hb == 0) r1_issue<32 * kRowBytes<D>>(pk[f + 2 - NVF], ka[1][f + 2 - NVF]);
+          if constexpr (hb == 0) r1_issue<32 * kRowBytes>(pk[f + 2 - NVF], ka[1][f + 2 - NVF]);
         }
         ew(IC<1 - KB>{}, IC<2 * NVF + p>{});
         extra(pc);
@@ -424,11 +419,10 @@ __device__ __forceinline__ void fwd_wide_item(LDS_PTR(char) lds, const QItem it,
 }
 
 // LDS of a block: K and V buffers, then one transposition area per wave for the output rows
-template <int D> constexpr int kLdsBytes = 4 * kTileBytes<D> + 4 * kOutAreaBytes<D>;
+constexpr int kLdsBytes = 4 * kTileBytes + 4 * kOutAreaBytes<D>;
 
 // One wave's rows of head h: O = O^T / l, through the block's transposition areas, and lse.
-template <int D>
-__device__ __forceinline__ void fwd_wide_out(LDS_PTR(char) areas, const QItem& it, const floatx16 (&acc)[kNDB<D>], float m, float l,
+__device__ __forceinline__ void fwd_wide_out(LDS_PTR(char) areas, const QItem& it, const floatx16 (&acc)[kNDB], float m, float l,
                                              bf16* __restrict__ o, float* __restrict__ lse, int h, int T, int Hq) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int q0w = it.q_row0 + 32 * wave, my_row = q0w + (lane & 31), q_end = it.q_row0 + it.q_rows;
@@ -442,11 +436,10 @@ __device__ __forceinline__ void fwd_wide_out(LDS_PTR(char) areas, const QItem& i
 // The next item's descriptor is fetched while the current item runs -- with a vector load: a scalar load
 // in flight would make the hand-counted LDS waits of the tile loop unreliable -- so that an item starts with
 // its own loads instead of a chain of dependent ones.
-template <int D>
 __device__ __forceinline__ void fwd_wide_walk(const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v,
                                               bf16* __restrict__ o, float* __restrict__ lse, const QItem* __restrict__ items,
                                               int n_items, int T, int Hq, int Hkv, float scale) {
-  __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes<D>];
+  __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes];
   const int g2 = (Hq / Hkv) >> 1;
   const int total = ((n_items * Hkv + 7) / 8) * 8 * g2;   // block numbers of the mapping, padding included
   const __amdgpu_buffer_rsrc_t irsrc = __builtin_amdgcn_make_buffer_rsrc((void*)items, 0, n_items * (int)sizeof(QItem), 0x00020000);
@@ -471,9 +464,9 @@ __device__ __forceinline__ void fwd_wide_walk(const bf16* __restrict__ q, const 
     it.kv_start = __builtin_amdgcn_readfirstlane(cur[2]);
     it.pad = 0;
     if (it.q_rows > 0)
-      fwd_wide_item<D, false>((LDS_PTR(char))smem, it, it.kv_start, (it.q_row0 + it.q_rows - it.kv_start + kKeys - 1) / kKeys, hk, hp, q, k, v, Hq,
-                              Hkv, scale, [&](int hb, const floatx16 (&acc)[kNDB<D>], float m, float l) {
-                                fwd_wide_out<D>((LDS_PTR(char))smem + 4 * kTileBytes<D>, it, acc, m, l, o, lse, hk * (Hq / Hkv) + 2 * hp + hb, T, Hq);
+      fwd_wide_item<false>((LDS_PTR(char))smem, it, it.kv_start, (it.q_row0 + it.q_rows - it.kv_start + kKeys - 1) / kKeys, hk, hp, q, k, v, Hq,
+                              Hkv, scale, [&](int hb, const floatx16 (&acc)[kNDB], float m, float l) {
+                                fwd_wide_out((LDS_PTR(char))smem + 4 * kTileBytes, it, acc, m, l, o, lse, hk * (Hq / Hkv) + 2 * hp + hb, T, Hq);
                               });
     cur = nxt;
     hk = hk_n;
@@ -485,7 +478,7 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_bf16_kernel_d128(const bf16* 
                                                                      const bf16* __restrict__ v, bf16* __restrict__ o,
                                                                      float* __restrict__ lse, const QItem* __restrict__ items,
                                                                      int n_items, int T, int Hq, int Hkv, float scale) {
-  fwd_wide_walk<128>(q, k, v, o, lse, items, n_items, T, Hq, Hkv, scale);
+  fwd_wide_walk(q, k, v, o, lse, items, n_items, T, Hq, Hkv, scale);
 }
 
 // The launch whose items' keys are divided: one block per (item, head pair, part), parts innermost, so that an XCD keeps to
@@ -494,7 +487,7 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_bf16_split_kernel_d128(const 
                                                                            const bf16* __restrict__ v, bf16* __restrict__ o,
                                                                            float* __restrict__ lse, const QItem* __restrict__ items,
                                                                            int T, int Hq, int Hkv, float scale, FwdSplit sp) {
-  __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes<128>];
+  __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes];
   const int part = blockIdx.x % sp.parts, g = Hq / Hkv;
   int idx, hk, hp;
   split_block(blockIdx.x / sp.parts, g >> 1, Hkv, &idx, &hk, &hp);
@@ -504,13 +497,13 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_bf16_split_kernel_d128(const 
   const int region = n > 1 ? split_region(sp) : 0;
   if (region < 0) return;                               // the finishing kernel walks the parts
   const int n_tiles = split_range(it, part, n);
-  fwd_wide_item<128, true>((LDS_PTR(char))smem, it, first_key, n_tiles, hk, hp, q, k, v, Hq, Hkv, scale,
+  fwd_wide_item<true>((LDS_PTR(char))smem, it, first_key, n_tiles, hk, hp, q, k, v, Hq, Hkv, scale,
                            [&](int hb, const floatx16 (&acc)[4], float m, float l) {
                              const int h = hk * g + 2 * hp + hb;
                              if (n > 1)
-                               split_store<128>(split_unit<128>(sp, region, (idx * sp.parts + part) * Hq + h), threadIdx.x >> 6, threadIdx.x & 63, acc, m, l);
+                               split_store<D>(split_unit<D>(sp, region, (idx * sp.parts + part) * Hq + h), threadIdx.x >> 6, threadIdx.x & 63, acc, m, l);
                              else
-                               fwd_wide_out<128>((LDS_PTR(char))smem + 4 * kTileBytes<128>, it, acc, m, l, o, lse, h, T, Hq);
+                               fwd_wide_out((LDS_PTR(char))smem + 4 * kTileBytes, it, acc, m, l, o, lse, h, T, Hq);
                            });
 }
 
@@ -521,13 +514,13 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_bf16_finish_kernel_d128(const
                                                                             float* __restrict__ lse, const QItem* __restrict__ items,
                                                                             int T, int Hq, int Hkv, float scale, FwdSplit sp) {
   // K and V buffers (the transposition areas behind the last walk), then the second head's sums
-  constexpr int kWalkBytes = 4 * kTileBytes<128>;
-  static_assert(4 * kOutAreaBytes<128> <= kWalkBytes, "the transposition areas must fit the tile buffers");
+  constexpr int kWalkBytes = 4 * kTileBytes;
+  static_assert(4 * kOutAreaBytes<D> <= kWalkBytes, "the transposition areas must fit the tile buffers");
   __shared__ __attribute__((aligned(1024))) char smem[kWalkBytes + 128 * 128 * 4];
   const QItem it = items[blockIdx.x];
   const int n = split_parts(sp, it), region = split_region(sp);
   if (n > 1 && region >= 0) {
-    split_combine<128>(sp, region, n, it, o, lse, T, Hq);
+    split_combine<D>(sp, region, n, it, o, lse, T, Hq);
   } else if (n > 1 && blockIdx.z == 0 && blockIdx.y % 2 == 0) {
     const int g = Hq / Hkv, h0 = blockIdx.y;
     floatx16 sum0[4];
@@ -561,14 +554,14 @@ __global__ __launch_bounds__(256, 1) void fwd_wide_bf16_finish_kernel_d128(const
           }
         }
       };
-      fwd_wide_item<128, true>((LDS_PTR(char))smem, run, it.kv_start, n_tiles, h0 / g, h0 % g / 2, q, k, v, Hq, Hkv, scale, take);
+      fwd_wide_item<true>((LDS_PTR(char))smem, run, it.kv_start, n_tiles, h0 / g, h0 % g / 2, q, k, v, Hq, Hkv, scale, take);
     }
-    fwd_wide_out<128>((LDS_PTR(char))smem, it, sum0, m[0], l[0], o, lse, h0, T, Hq);
+    fwd_wide_out((LDS_PTR(char))smem, it, sum0, m[0], l[0], o, lse, h0, T, Hq);
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) sum0[db][r] = sum1[(db * 4 + r / 4) * 256][r % 4];
-    fwd_wide_out<128>((LDS_PTR(char))smem, it, sum0, m[1], l[1], o, lse, h0 + 1, T, Hq);
+    fwd_wide_out((LDS_PTR(char))smem, it, sum0, m[1], l[1], o, lse, h0 + 1, T, Hq);
   }
   split_release(sp, region);
 }
@@ -599,8 +592,6 @@ int launch_fwd_wide_bf16(const LaunchCtx& c, const void* q, const void* k, const
   }
   const int total = mapped_grid(n_items, p.n_kv_heads, g / 2);
   const dim3 grid(total < n_cu ? total : n_cu), block(256);
-  // (the body also instantiates at head dim 64, where it is bound by the vector unit and slower than the kernel of
-  // fwd_bf16.hip: not dispatched)
   hipLaunchKernelGGL(fwd_wide_bf16_kernel_d128, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
                      (const bf16*)v, (bf16*)o, lse, items, n_items, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale);
   return (int)hipGetLastError();

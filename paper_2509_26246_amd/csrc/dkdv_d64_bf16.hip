@@ -222,49 +222,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void dkdv_bf16_kernel_d64(
     LDS_PTR(char) ep = lds + wave * kOutAreaBytes<D>;   // the whole list in one launch: bf16 rows
     store_rows<D>(ep, dk, scale, dK, Hkv, hk, kv0w, kv_end, lane);
     store_rows<D>(ep, dv, 1.f, dV, Hkv, hk, kv0w, kv_end, lane);
-  } else if (slot >= 0) {
-    // one part of a divided key tile: fp32 partial tile [slot][kv head][dK, dV][256 rows][D]
-    float* pk_ = parts + ((size_t)slot * Hkv + hk) * (2 * kKeys * D) + (size_t)(32 * wave + l32) * D;
-    float* pv_ = pk_ + kKeys * D;
-#pragma unroll
-    for (int db = 0; db < kNDB; ++db)
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        const int off = 32 * db + 8 * gq + 4 * half;
-        floatx4 a, b;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) { a[x] = dk[db][4 * gq + x] * scale; b[x] = dv[db][4 * gq + x]; }
-        *reinterpret_cast<floatx4*>(pk_ + off) = a;
-        *reinterpret_cast<floatx4*>(pv_ + off) = b;
-      }
+  } else if (slot >= 0) {                               // partial tile [slot][kv head][dK, dV][256 rows][D]
+    store_part_row<D>(parts + ((size_t)slot * Hkv + hk) * (2 * kKeys * D) + (size_t)(32 * wave + l32) * D, kKeys, dk, dv, scale, half);
   } else if (my_key < kv_end) {
-    // rows below load_until continue the sum an earlier unit left in the fp32 accumulators; rows from final_from on get no later
-    // contribution and are written as dK/dV, the others into the accumulators
-    const size_t base = ((size_t)my_key * Hkv + hk) * D;
-    const bool load_acc = my_key < it.load_until, store_final = my_key >= it.final_from;
-#pragma unroll
-    for (int db = 0; db < kNDB; ++db)
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        const size_t off = base + 32 * db + 8 * gq + 4 * half;
-        floatx4 a, b;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) { a[x] = dk[db][4 * gq + x] * scale; b[x] = dv[db][4 * gq + x]; }
-        if (load_acc) {
-          a += *reinterpret_cast<const floatx4*>(acc_dk + off);
-          b += *reinterpret_cast<const floatx4*>(acc_dv + off);
-        }
-        if (store_final) {
-          bf16x4 wa, wb;
-#pragma unroll
-          for (int x = 0; x < 4; ++x) { wa[x] = (bf16)a[x]; wb[x] = (bf16)b[x]; }
-          *reinterpret_cast<bf16x4*>(dK + off) = wa;
-          *reinterpret_cast<bf16x4*>(dV + off) = wb;
-        } else {
-          *reinterpret_cast<floatx4*>(acc_dk + off) = a;
-          *reinterpret_cast<floatx4*>(acc_dv + off) = b;
-        }
-      }
+    store_key_row<D>(((size_t)my_key * Hkv + hk) * D, my_key < it.load_until, my_key >= it.final_from, dk, dv, scale, half, acc_dk, acc_dv, dK, dV);
   }
 }
 

@@ -520,48 +520,11 @@ __device__ __forceinline__ void dkdv_wide_block(
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) {
     const int my_key = kv0w + 32 * kb + l32;
-    if (slot >= 0) {
-      // one part of a divided key tile: fp32 partial tile [slot][kv head][dK, dV][256 rows][D]
-      float* pk_ = parts + ((size_t)slot * Hkv + hk) * (2 * kKeys * D) + (size_t)(64 * wave + 32 * kb + l32) * D;
-      float* pv_ = pk_ + kKeys * D;
-#pragma unroll
-      for (int db = 0; db < kNDB; ++db)
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          const int off = 32 * db + 8 * gq + 4 * half;
-          floatx4 a, b;
-#pragma unroll
-          for (int x = 0; x < 4; ++x) { a[x] = dk[kb][db][4 * gq + x] * scale; b[x] = dv[kb][db][4 * gq + x]; }
-          *reinterpret_cast<floatx4*>(pk_ + off) = a;
-          *reinterpret_cast<floatx4*>(pv_ + off) = b;
-        }
-    } else if (my_key < kv_end) {
-      const size_t base = ((size_t)my_key * Hkv + hk) * D;
-      const bool load_acc = my_key < it.load_until, store_final = my_key >= it.final_from;
-#pragma unroll
-      for (int db = 0; db < kNDB; ++db)
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          const size_t off = base + 32 * db + 8 * gq + 4 * half;
-          floatx4 a, b;
-#pragma unroll
-          for (int x = 0; x < 4; ++x) { a[x] = dk[kb][db][4 * gq + x] * scale; b[x] = dv[kb][db][4 * gq + x]; }
-          if (load_acc) {
-            a += *reinterpret_cast<const floatx4*>(acc_dk + off);
-            b += *reinterpret_cast<const floatx4*>(acc_dv + off);
-          }
-          if (store_final) {
-            bf16x4 wa, wb;
-#pragma unroll
-            for (int x = 0; x < 4; ++x) { wa[x] = (bf16)a[x]; wb[x] = (bf16)b[x]; }
-            *reinterpret_cast<bf16x4*>(dK + off) = wa;
-            *reinterpret_cast<bf16x4*>(dV + off) = wb;
-          } else {
-            *reinterpret_cast<floatx4*>(acc_dk + off) = a;
-            *reinterpret_cast<floatx4*>(acc_dv + off) = b;
-          }
-        }
-    }
+    if (slot >= 0)                                      // partial tile [slot][kv head][dK, dV][256 rows][D]
+      store_part_row<D>(parts + ((size_t)slot * Hkv + hk) * (2 * kKeys * D) + (size_t)(64 * wave + 32 * kb + l32) * D, kKeys, dk[kb], dv[kb], scale, half);
+    else if (my_key < kv_end)
+      store_key_row<D>(((size_t)my_key * Hkv + hk) * D, my_key < it.load_until, my_key >= it.final_from, dk[kb], dv[kb], scale, half, acc_dk,
+                       acc_dv, dK, dV);
   }
 }
 

@@ -496,4 +496,53 @@ __device__ __forceinline__ void store_rows(LDS_PTR(char) ep, const floatx16 (&ac
   }
 }
 
+// ---- gradient rows of a key --------------------------------------------------------------------
+// A lane's key row from its transposed accumulators (dK times `scale`), where it does not leave as a bf16 row of a whole-list
+// launch: into a partial tile of `tile_rows` rows at `row` (dK; dV behind the tile's dK rows), fp32 ...
+template <int D>
+__device__ __forceinline__ void store_part_row(float* row, int tile_rows, const floatx16 (&dk)[D / 32], const floatx16 (&dv)[D / 32], float scale,
+                                               int half) {
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+      const int off = 32 * db + 8 * gq + 4 * half;
+      floatx4 a, b;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) { a[x] = dk[db][4 * gq + x] * scale; b[x] = dv[db][4 * gq + x]; }
+      *reinterpret_cast<floatx4*>(row + off) = a;
+      *reinterpret_cast<floatx4*>(row + tile_rows * D + off) = b;
+    }
+}
+// ... or to element `base` of the fp32 accumulators or of dK and dV: rows below load_until continue the sum an earlier unit left
+// in the accumulators; rows from final_from on get no later contribution and are written in bf16.
+template <int D>
+__device__ __forceinline__ void store_key_row(size_t base, bool load_acc, bool store_final, const floatx16 (&dk)[D / 32],
+                                              const floatx16 (&dv)[D / 32], float scale, int half, float* __restrict__ acc_dk,
+                                              float* __restrict__ acc_dv, bf16* __restrict__ dK, bf16* __restrict__ dV) {
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+      const size_t off = base + 32 * db + 8 * gq + 4 * half;
+      floatx4 a, b;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) { a[x] = dk[db][4 * gq + x] * scale; b[x] = dv[db][4 * gq + x]; }
+      if (load_acc) {
+        a += *reinterpret_cast<const floatx4*>(acc_dk + off);
+        b += *reinterpret_cast<const floatx4*>(acc_dv + off);
+      }
+      if (store_final) {
+        bf16x4 wa, wb;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) { wa[x] = (bf16)a[x]; wb[x] = (bf16)b[x]; }
+        *reinterpret_cast<bf16x4*>(dK + off) = wa;
+        *reinterpret_cast<bf16x4*>(dV + off) = wb;
+      } else {
+        *reinterpret_cast<floatx4*>(acc_dk + off) = a;
+        *reinterpret_cast<floatx4*>(acc_dv + off) = b;
+      }
+    }
+}
+
 }  // namespace slimattn

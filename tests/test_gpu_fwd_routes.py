@@ -104,3 +104,29 @@ def test_rows_of_other_units_change_no_bit(L, hq, hkv, d):
     assert float(np.max(np.abs(H.device_to_f32(prob.o) - want_o))) <= TOL
     assert float(np.max(np.abs(prob.lse.cpu().numpy() - want_lse) / (1.0 + np.abs(want_lse)))) <= TOL
     assert torch.equal(got[0][0].view(torch.int16), got[1][0].view(torch.int16)) and torch.equal(got[0][1], got[1][1])
+
+
+# Keys that take no part in the softmax (scores of -inf, of a -1e9 mask, of bf16's lowest value), whole tiles of them too, on every
+# forward kernel; the sample's first key is an ordinary one.
+@pytest.mark.parametrize("low", [float("-inf"), -1e9, -3.3895e38])
+@pytest.mark.parametrize("L,hq,hkv,d,bf16", [([1000], 4, 2, 128, True), ([500, 90], 4, 2, 128, True), ([500], 3, 1, 128, True),
+                                             ([500], 4, 1, 64, True), ([300, 90], 4, 2, 64, False), ([300], 2, 2, 128, False)])
+def test_keys_without_weight(L, hq, hkv, d, bf16, low):
+    r = np.random.default_rng(4)
+    T, scale = sum(L), d ** -0.5
+    arrs = [r.standard_normal((T, h, d), dtype=np.float32) * np.float32(f) for h, f in ((hq, 0.5), (hkv, 0.5), (hkv, 0.5), (hq, 0.1))]
+    arrs[0][:, :, 0] = 4.0
+    arrs = [W.bf16_round(a) for a in arrs] if bf16 else arrs
+    st = 0
+    for n in L:
+        hidden = [j for j in range(1, n) if j % 3 == 1 or 64 <= j < 200]
+        arrs[1][st:st + n][hidden, :, 0] = low if np.isinf(low) else W.bf16_round(np.array([low], np.float32))[0]
+        st += n
+    cu, sl = S.build_slices(L, 192)
+    one = S.build_units(cu, sl, "ALL")
+    prob = H.make_problem(*arrs, cu, sl, one, one, bf16=bf16, scale=scale)
+    prob.forward()
+    torch.cuda.synchronize()
+    want_o, want_lse = A.fwd_packed(*arrs[:3], cu, scale)
+    tol = TOL if bf16 else 1e-5
+    assert np.max(np.abs(H.device_to_f32(prob.o) - want_o)) <= tol and np.max(np.abs(prob.lse.cpu().numpy() - want_lse)) <= tol

@@ -77,6 +77,34 @@ def test_bf16_key_tiles_divided_by_heads(L, hq, hkv, d):
     _fused_and_per_unit(L, hq, hkv, d, True, 320)
 
 
+# key tiles divided by query rows in the division classes of 16 and of 32 and more KV heads: 1536 rows on as many heads, where the
+# first tiles exceed three quarters of a slot's share (1536 against 336 and 672 rows)
+@pytest.mark.parametrize("heads,d", [(16, 128), (20, 64), (32, 64), (33, 128)])
+def test_bf16_key_tiles_divided_with_many_kv_heads(heads, d):
+    prob, ref = _problem([1536], heads, heads, d, True, 640)
+    _poison(prob)
+    prob.forward()
+    S.profile_enable(64)
+    prob.backward()
+    launches = S.profile_read()["reduce"][1]
+    S.profile_enable(0)
+    assert launches == 1
+    _check(prob, ref, True, f"{heads} KV heads, d {d}")
+
+
+# fp32 against fp64, relative 2-norm of each output: a random walk over sums of up to n = 4 x 900 terms in fp32, sqrt(n) 2^-24 = 3.6e-6 (largest
+# seen 9e-7); the max-abs bound above allows ten times as much
+@pytest.mark.parametrize("L,hq,hkv,d", [([511, 37, 200, 128], 2, 2, 64), ([900], 4, 1, 128), ([337], 3, 1, 32)])
+def test_fp32_relative_error(L, hq, hkv, d):
+    prob, ref = _problem(L, hq, hkv, d, False, 256)
+    prob.forward()
+    prob.backward()
+    torch.cuda.synchronize()
+    for name, want in ref.items():
+        got = getattr(prob, name).cpu().numpy().astype(np.float64)
+        assert np.linalg.norm(got - want) <= 3.6e-6 * np.linalg.norm(want), name
+
+
 def test_bf16_head_parts_leave_the_static_scratch_enough():
     """The partial tiles of a division by heads are limited so that the pack still fits the built-in scratch array."""
     L = [4000, 1300] + [256] * 17

@@ -392,7 +392,7 @@ int slimattn_bwd_static(const slimattn_params* p, const void* q, const void* k, 
 
 /* Kernel classes reported by slimattn_profile_read. */
 #define SLIMATTN_K_FWD       0
-#define SLIMATTN_K_DELTA     1
+#define SLIMATTN_K_DELTA     1          /* the statistics prepass (bf16; fp32 has none) */
 #define SLIMATTN_K_DQ        2
 #define SLIMATTN_K_DKDV      3
 #define SLIMATTN_K_REDUCE    4          /* the reduction of divided key tiles */

@@ -287,8 +287,9 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   auto finish = [&](int e) -> int { return hip_rc(e); };
 
   if (whole && !per_unit) {
-    // One scope holding every slice: each key tile's owner sums all later query rows itself and
-    // writes dK/dV directly; the fp32 accumulators in the workspace are not touched.
+    // One scope holding every slice: each key tile's owner sums all later query rows itself and writes dK/dV directly, without
+    // the fp32 accumulators in the workspace.  (Small fp32 launches divide every walk in two and keep the second half's
+    // sums there until the two are added.)
     int e = run_dq(t->d_fused.q_items[zq], (int)t->fused.q_items[zq].size());
     if (e == 0)
       e = f32 ? run_dkdv(t->d_fused.kv_items[zk], (int)t->fused.kv_items[zk].size(), t->d_fused.segs)

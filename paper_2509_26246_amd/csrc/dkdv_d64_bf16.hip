@@ -12,8 +12,10 @@
 // two waves per SIMD can have.  A barrier every two steps; tiles are staged one pair of steps ahead, two LDS stages.  A wave skips
 // steps before its keys, and all of them if it has none.
 // Measured (16K tokens, 32/8 heads, us, the one-wave kernel at 64 -> this one): 128-row samples 111 -> 75, 512 rows 131 -> 106,
-// 1024 rows 197 -> 165, 4096 rows 590 -> 529, one 16K sample 2050 -> 2060 (there both wait for the LDS: 128 transposed reads of
-// 64 bytes a cycle and 64 row reads per step and compute unit are about 1500 cycles); samples of 32 to 512 rows 129 -> 98.
+// 1024 rows 197 -> 165, 4096 rows 590 -> 529, one 16K sample 2050 -> 2060; samples of 32 to 512 rows 129 -> 98.  A step takes about
+// 1800 cycles there, 1152 of them products; its LDS reads (64 KB of rows and 64 KB transposed per compute unit) are worth about 620 at
+// the rates they reach alone, so what is left is latency: the transposed reads are issued behind the element-wise work and
+// waited for at once.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"

@@ -7,8 +7,8 @@
 // of 128 rows of one head, walk the sample's keys kv_start .. last row in tiles of 64, keep a
 // running reference and row sum, and accumulate O.
 //
-// Shape of the computation on CDNA4: the block's 4 waves own 32 query rows each; two blocks (head dim 128, 197 registers) or
-// three (64, 139) share a compute unit, so one wave's softmax overlaps another's products and one block's loads and stores
+// Shape of the computation on CDNA4: the block's 4 waves own 32 query rows each; two blocks (head dim 128, 201 registers; 224
+// with exact row sums) or three (64, 137) share a compute unit, so one wave's softmax overlaps another's products and one block's loads and stores
 // another's tiles.  Scores are produced transposed, S^T = K Q^T (A = K rows from LDS, B = Q held in registers), so that every
 // lane owns one query row: row sums need a cross-lane exchange once per item and the
 // accumulator registers of S^T are, as they stand, the B operand of O^T += V^T P^T.  V^T is read
@@ -352,10 +352,13 @@ int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const 
 
 // Even groups at head dim 128 go to the one-wave kernel, whose tiles are cheaper, unless the pack's samples are short: it
 // holds one block per compute unit, and what an item costs beside its tiles (11 us of loads and stores) is hidden by nothing, while
-// two blocks of this kernel overlap each other.  16K tokens in equal samples, 32/8 heads, one-wave against this kernel: 128-row
-// samples 105 / 96 us, 512 rows 151 / 130, 1024 rows 196 / 189, 2048 rows 297 / 307, 16384 rows 1634 / 1839.  The rule
-// looks at the pack alone, so that every launch of a handle takes the same kernel; a row of a 1024-row sample sees 512 keys
-// on average.  (At head dim 64 this kernel is bound by the vector unit, where a second head per wave saves nothing.)
+// two blocks of this kernel overlap each other.  Both cost a row about the same amount plus a share per key, so what
+// decides over a pack is the keys its rows see on average, whatever the lengths it is mixed from.  32/8 heads, one-wave kernel
+// against this one: 16K tokens in equal samples of 128 rows 104 / 84 us, 512 rows 137 / 119, 800 rows (400 keys) 167 / 161, 1024
+// rows 175 / 166, 2048 rows 263 / 277; one of 4096 rows among 200 of 100 (390 keys) 245 / 226, of 3000 among 45 of 300 (395) 184 /
+// 166; with 8/1 heads these two 98 / 72 and 78 / 55.  By units of 4096 tokens 128 rows 116 / 106, 800 rows 186 / 174; where the units' blocks
+// just fill the chip's rounds, 512 rows 140 / 147.  Every launch of a handle takes the same kernel.  (At head dim 64 this
+// kernel is bound by the vector unit, where a second head per wave saves nothing.)
 constexpr int kShortMeanKeys = 400;
 
 int launch_fwd_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse,

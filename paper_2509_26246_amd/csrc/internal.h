@@ -155,7 +155,8 @@ struct LaunchCtx {
 // A few query tiles against a long prefix (prefill by slices) are a launch of few blocks with a long serial walk: 1024 rows of
 // 8 heads after 31K keys are 32 blocks of 500 key tiles for 256 compute units.  The launch then has `parts` blocks per
 // (item, heads), each walking a run of the item's key tiles and moving its reference by itself (all start at the row's score against
-// the sample's first key), and stores unnormalised O, reference and row sum in fp32; a second kernel adds the parts up in order.  Row sums and O are sums over fewer terms than before.
+// the sample's first key), and stores unnormalised O, reference and row sum in fp32; a second kernel adds the parts up in order.
+// Row sums and O are sums over fewer terms than before.
 //
 // The forward has no workspace argument and allocates nothing, so the partial results live in one of kSplitRegions arrays
 // (34 MB each) built into the library, one set per device.

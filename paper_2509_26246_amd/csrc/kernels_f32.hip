@@ -26,8 +26,8 @@
 // What bounds it: the fp32 matrix rate (154 TFLOP/s for a large product here).  A pack of two samples, 1660 and 2436 rows,
 // 8 query and 2 KV heads, head dim 128: forward 5803 -> 195 us, dQ with delta 6743 -> 280 us, dK/dV 12757 -> 381 us against
 // one lane per row on the vector unit (2.5 -> 77 TFLOP/s, counting 7 products); the tiny pack of 876 rows, 2 heads of 64:
-// 1080 -> 55 us.  (The forward at head dim 128 with 256 registers, two blocks per compute unit and a few spills outside the
-// loop, and with 356 and one block: the same 195 us.)
+// 1080 -> 55 us.  (The forward at head dim 128 with 256 registers, two blocks per compute unit, 31 spilled registers and 24 reloads
+// per tile, and with 356 registers, one block and no spills: the same 195 us.)
 #include <hip/hip_runtime.h>
 
 #include "internal.h"

@@ -35,8 +35,8 @@ def _check(prob, arrs, cu, first, end, got_o, got_lse, tag):
 
 
 # Last slice of the first sample.  Prefixes around the shortest that is divided (48 tiles of 64 keys), parts of unequal size, a
-# slice that starts inside a tile, one-row slices, several query tiles; the kernel for even groups at head dim 128, the one
-# for even groups at 64, the one for odd groups at both.
+# slice that starts inside a tile, one-row slices, several query tiles; the one-wave kernel (even groups at head dim 128) and
+# the one-head kernel (odd groups, head dim 64).
 @pytest.mark.parametrize("hq,hkv,d", [(8, 1, 128), (4, 2, 128), (6, 1, 64), (5, 5, 128), (3, 1, 64)])
 @pytest.mark.parametrize("length,slice_size", [(3071, 3000), (3073, 3072), (6145, 256), (7777, 1000), (9000, 999)])
 def test_last_slice_of_a_long_sample(hq, hkv, d, length, slice_size):
@@ -114,7 +114,7 @@ def test_more_streams_than_arrays_and_graph_replays():
             with torch.cuda.stream(s):
                 S.fwd(prob.q, prob.k, prob.v, prob.tables, o, lse, **prob._kw(unit_lo=u, unit_hi=u + 1))
     torch.cuda.synchronize()
-    for i, (o, lse) in enumerate(outs):                     # divided or, where the stream's array was taken, not: to tolerance
+    for i, (o, lse) in enumerate(outs):                     # divided or, where no array was free, walked part by part
         _check(prob, arrs, cu, first, end, H.device_to_f32(o), lse.cpu().numpy(), f"stream {i}")
     side = torch.cuda.Stream()
     g = torch.cuda.CUDAGraph()

@@ -11,11 +11,12 @@
 // reads 16 KB of LDS per wave (Q and dO rows, and both transposed): half of what the LDS delivers in the products' time, and what
 // two waves per SIMD can have.  A barrier every two steps; tiles are staged one pair of steps ahead, two LDS stages.  A wave skips
 // steps before its keys, and all of them if it has none.
-// Measured (16K tokens, 32/8 heads, us, the one-wave kernel at 64 -> this one): 128-row samples 111 -> 75, 512 rows 131 -> 106,
-// 1024 rows 197 -> 165, 4096 rows 590 -> 529, one 16K sample 2050 -> 2060; samples of 32 to 512 rows 129 -> 98.  A step takes about
-// 1800 cycles there, 1152 of them products; its LDS reads (64 KB of rows and 64 KB transposed per compute unit) are worth about 620 at
-// the rates they reach alone, so what is left is latency: the transposed reads are issued behind the element-wise work and
-// waited for at once.
+// Measured (16K tokens, 32/8 heads, us, the one-wave kernel at 64 -> this one): 128-row samples 109 -> 77, 1024 rows 433 -> 380 (32K
+// tokens), samples of 32 to 512 rows 129 -> 98, one 16K sample 2049 -> 2045, one of 32K on 8/1 heads 2251 -> 2237.  On long samples a step
+// takes about 1800 cycles, 1152 of them products; its LDS reads (64 KB of rows and 64 KB transposed per compute unit) are worth
+// about 620 at the rates they reach alone, so what is left is latency: the first transposed reads are issued in front of the
+// element-wise work (behind it, and with the second batch's wait free to move up: 2079 and 2278), the next step's row reads
+// behind its last product.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -157,18 +158,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void dkdv_bf16_kernel_d64(
         if (c < rel_lo || c >= rel_hi) s[r] = -INFINITY;
       }
     }
-    bf16x8 pf[2], ds[2];
-    // at raised priority, as in the dQ kernel: 4K-row samples 566 -> 529 us
-    __builtin_amdgcn_s_setprio(3);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      s[r] = __builtin_amdgcn_exp2f(s[r]);
-      dp[r] *= s[r];
-    }
-#pragma unroll
-    for (int e = 0; e < 2; ++e) { pf[e] = pack8(s, 8 * e); ds[e] = pack8(dp, 8 * e); }
-    __builtin_amdgcn_s_setprio(0);
-    // per 16 rows one batch of transposed fragments: dO^T of both head-dim blocks, Q^T of both
+    // per 16 rows one batch of transposed fragments: dO^T of both head-dim blocks, Q^T of both; the first is on its way while the
+    // element-wise work runs
     Tr4 tb[2];
     auto issue = [&](auto ec) {
       constexpr int e = decltype(ec)::value, off = at + e * 16 * kRowBytes;
@@ -181,6 +172,18 @@ __global__ __launch_bounds__(64 * kWaves, 2) void dkdv_bf16_kernel_d64(
       });
     };
     issue(IC<0>{});
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 pf[2], ds[2];
+    // at raised priority, as in the dQ kernel: 4K-row samples 566 -> 529 us
+    __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = __builtin_amdgcn_exp2f(s[r]);
+      dp[r] *= s[r];
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) { pf[e] = pack8(s, 8 * e); ds[e] = pack8(dp, 8 * e); }
+    __builtin_amdgcn_s_setprio(0);
     static_for<0, 2>([&](auto ec) {
       constexpr int e = decltype(ec)::value;
       if constexpr (e == 0) issue(IC<1>{});
@@ -190,6 +193,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void dkdv_bf16_kernel_d64(
         dv[db] = mfma32(tr4_frag(tb[e], db), pf[e], dv[db]);
         dk[db] = mfma32(tr4_frag(tb[e], kNDB + db), ds[e], dk[db]);
       }
+      __builtin_amdgcn_sched_barrier(0);
     });
   };
 

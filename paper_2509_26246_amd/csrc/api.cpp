@@ -254,12 +254,14 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
                  : launch_bwd_dq_bf16(ctx, q, k, v, dO, o, lse, stat3, own_stats ? 1 : 0, dQ, items, n);
     });
   };
-  auto run_dkdv = [&](const KvItem* items, int n, const Seg* segs, int hp = 1) -> int {
+  auto run_dkdv = [&](const KvItem* items, int n, const Seg* segs, int hp = 1, bool short_walks = false) -> int {
     return timed(SLIMATTN_K_DKDV, stream, [&] {
       return f32 ? launch_bwd_dkdv_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (const float*)dO, lse,
                                        delta, acc_dk, acc_dv, (float*)dK, (float*)dV, items, n, segs, whole && !per_unit ? t->max_sample_len : 0)
              : p->head_dim == 64
                  ? launch_bwd_dkdv_d64_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp)
+             : short_walks
+                 ? launch_bwd_dkdv_pair_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp)
                  : launch_bwd_dkdv_wide_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp);
     });
   };
@@ -270,7 +272,8 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
     const int tile_rows = dkdv_kv_tile(p->dtype, p->head_dim), ti = split_tile_index(tile_rows);
     const int a = L.split_rng[ti][sc][u].begin, b = L.split_rng[ti][sc][u].end;
     const int hp = head_parts(b - a, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, L.longest[ti][sc][u], head_blocks);
-    int e = run_dkdv(D.split_items[ti] + a, b - a, D.segs, hp);
+    int e = run_dkdv(D.split_items[ti] + a, b - a, D.segs, hp,
+                     short_walks(L.walk_rows[ti][u], b - a, p->n_q_heads / p->n_kv_heads, hp));
     if (e != 0) return e;
     if (hp > 1) {
       const int ta = L.tile_rng[ti][sc][u].begin, tb = L.tile_rng[ti][sc][u].end;

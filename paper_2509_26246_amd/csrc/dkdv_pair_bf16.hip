@@ -1,0 +1,264 @@
+// dK/dV for bf16 inputs at head dim 128 where the walks are short (short_walks in internal.h): 128 key rows per block, two blocks per
+// compute unit, 32 key rows per wave.
+//
+// What it computes is the dK/dV step of the backward (see bwd_bf16.hip), with the work items, the walk and the output paths of
+// dkdv_wide_bf16.hip: a block owns key rows of one KV head and walks every query row of the launch scope at or after
+// them, for its query heads of the group, in a fixed order; S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS.  An item's 256 rows
+// are two blocks.
+//
+// Why beside the one-wave kernel.  That one holds a compute unit to itself, so what an item costs beside its steps (its first loads
+// and its last stores, 22 us: all compute units do them at about the same time, at the rate of the memory) is hidden by nothing.
+// Two blocks of half the keys overlap each other, steps before a wave's keys are skipped, and a sample that ends in a
+// tile's first half wastes half as much.  A step costs more: one product per LDS fragment (1.25 KB of LDS reads per product), and a
+// wave alone takes 2500 cycles for a step of 34 products (1088), two on a SIMD 3400 for both.
+// Measured, 16K tokens, one-wave kernel / this one, us: 32/32 heads, samples of 64 rows 426 / 157, 256 rows 235 / 164, 512 rows 297 / 213, 1024 rows
+// 398 / 330, 4096 rows 1003 / 1010; 32/8 heads, 256 rows 151 / 125, 512 rows 207 / 188, 1024 rows 304 / 288, 4096 rows 891 / 1007; 876 rows of
+// 8/1 heads 39 / 28.  (Raised priority for the element-wise work, as at head dim 64: 2 to 5 % slower here.  The next step's bookkeeping
+// behind its first LDS reads, the second half of the element-wise work behind the first gradient products: no gain.)
+//
+// Registers: 254 of 256.  The accumulators take 128, K fragments 32; V rows are in LDS, and a tile's fragment addresses are formed from one.
+#include <hip/hip_runtime.h>
+
+#include "internal.h"
+#include "mfma_utils.h"
+
+namespace slimattn {
+namespace {
+
+constexpr int D = 128;
+constexpr int kWaves = 4, kKeys = 32 * kWaves;          // key rows per block
+constexpr int kQStep = 32;
+constexpr int kNKS = D / 16, kNDB = D / 32, kRowBytes = D * 2;
+constexpr int kTileBytes = kQStep * kRowBytes;          // one Q or dO tile
+constexpr int kStageBytes = 2 * kTileBytes;             // Q tile, dO tile of a step
+constexpr int kVBase = 2 * kStageBytes;                 // two stages, then the block's V rows
+constexpr int kVBytes = kKeys * kRowBytes;
+constexpr float kLog2e = 1.4426950408889634f;
+
+struct Step { int i0, hi, head; };                      // rows [i0, min(i0 + 32, hi)) of one query head
+struct QdV { bf16x8 q, d, v; };
+
+// The fragment addresses of a tile differ from the first one's in the swizzled unit alone, by an exclusive or with the unit's number
+// (tiles are 256-byte aligned): formed at each use, one register in the place of eight.
+template <int X>
+__device__ __forceinline__ lds_cptr lds_xor(lds_cptr p) {
+  if constexpr (X == 0) return p;
+  unsigned x;
+  asm volatile("v_xor_b32 %0, %2, %1" : "=v"(x) : "v"((unsigned)(size_t)p), "n"(X));
+  return (lds_cptr)(size_t)x;
+}
+
+__global__ __launch_bounds__(64 * kWaves, 2) void dkdv_pair_bf16_kernel_d128(
+    const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ dO,
+    const bf16x8* __restrict__ stat3, float* __restrict__ acc_dk, float* __restrict__ acc_dv, bf16* __restrict__ dK,
+    bf16* __restrict__ dV, const KvItem* __restrict__ items, int n_items, const Seg* __restrict__ segs, int T, int Hq, int Hkv,
+    float scale, float* __restrict__ parts, int head_parts) {
+  __shared__ __attribute__((aligned(1024))) char smem[kVBase + kVBytes];
+
+  const int g = Hq / Hkv;
+  // the halves of a 256-row item are blocks of their own, next to each other with the item's heads in between
+  int b = blockIdx.x;
+  const int hk = b % Hkv;
+  b /= Hkv;
+  const int hpart = b % head_parts;
+  b /= head_parts;
+  const int item_idx = b >> 1, sub = b & 1;
+  const int h_lo = g * hpart / head_parts, h_hi = g * (hpart + 1) / head_parts;
+  if (item_idx >= n_items) return;
+  const KvItem it = items[item_idx];
+  const int row0 = it.kv_row0 + kKeys * sub, kv_end = it.kv_row0 + min(it.kv_rows, kKeys * (sub + 1));
+  if (row0 >= kv_end) return;
+  const int slot = head_parts > 1 ? it.number * head_parts + hpart : it.slot;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int kv0w = row0 + 32 * wave;
+  LDS_PTR(char) lds = (LDS_PTR(char))smem;
+
+  {
+    const TileSource srcV = make_tile_source<D, 256>(v, row0, Hkv, hk, kv_end, tid);
+    stage_tile<D, kKeys, 256>(lds + kVBase, srcV, 0, tid);
+  }
+  bf16x8 kf[kNKS];
+  {
+    const size_t off = ((size_t)min(kv0w + l32, T - 1) * Hkv + hk) * D + 8 * half;
+#pragma unroll
+    for (int ks = 0; ks < kNKS; ++ks) kf[ks] = *reinterpret_cast<const bf16x8*>(k + off + 16 * ks);
+  }
+
+  // Flattened walk (block-uniform): runs from the last to the first, inside a run steps of 32 rows from the top down, inside a
+  // step the block's heads of the group (co-resident blocks then read the same Q/dO rows at the same time).
+  int sgi = it.seg_end - 1, hh = h_lo, lo = 0, n = 0;
+  Seg sg;
+  bool more = true;
+  auto open_run = [&]() {                               // runs that end before the half's first row have no step
+    while (true) {
+      if (sgi < it.seg_begin) { more = false; return; }
+      sg = segs[sgi];
+      if (sg.q_hi > row0) break;
+      --sgi;
+    }
+    lo = max(sg.q_lo, row0);
+    n = (sg.q_hi - lo + kQStep - 1) / kQStep - 1;
+  };
+  open_run();
+  // The next step of the walk; behind its end an empty step (no row counts and none is read: hi = i0).
+  auto next_step = [&]() -> Step {
+    if (!more) return Step{row0, row0, hk * g};
+    Step d{lo + n * kQStep, sg.q_hi, hk * g + hh};
+    if (++hh == h_hi) {
+      hh = h_lo;
+      if (--n < 0) { --sgi; open_run(); }
+    }
+    return d;
+  };
+
+  const TileSource src = make_tile_source<D, 256>(q, row0, Hq, 0, T, tid);     // (voff, row_bytes)
+  const bf16* const q_base = q + (size_t)row0 * Hq * D;
+  const bf16* const do_base = dO + (size_t)row0 * Hq * D;
+  auto stage = [&](const Step& d, int at) {
+    TileSource a = src, b2 = src;
+    const int range = __builtin_amdgcn_readfirstlane((d.hi - row0) * (Hq * kRowBytes));
+    a.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)q_base, 0, range, 0x00020000);
+    b2.rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)do_base, 0, range, 0x00020000);
+    a.voff += d.head * kRowBytes;
+    b2.voff = a.voff;
+    stage_tile<D, kQStep, 256>(lds + at, a, d.i0 - row0, tid);
+    stage_tile<D, kQStep, 256>(lds + at + kTileBytes, b2, d.i0 - row0, tid);
+  };
+  const __amdgpu_buffer_rsrc_t stat_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)stat3, 0, (int)((size_t)T * Hq * 16), 0x00020000);
+  auto load_stat = [&](const Step& d) -> bf16x8 {
+    const int row = max(min(d.i0 + l32, d.hi - 1), row0);
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(stat_rsrc, row * 16, __builtin_amdgcn_readfirstlane(d.head * T * 16), 0));
+  };
+
+  Step cur = next_step(), nxt;
+  stage(cur, 0);
+  bf16x8 stat = load_stat(cur), stat_n;
+#pragma unroll
+  for (int ks = 0; ks < kNKS; ++ks) kf[ks] = scale8(kf[ks], scale * kLog2e);
+  const __bf16 one = half ? (bf16)0.f : (bf16)1.f, zero = (bf16)0.f;
+  const bf16x8 ones_l = {one, one, one, zero, zero, zero, zero, zero}, ones_d = {zero, zero, zero, zero, one, one, one, zero};
+  const lds_cptr pq = lds_row_ptr<D>(lds, l32, 8 * half);
+  lds_cptr pqt[2];
+  lds_tr_ptrs<D>(lds, 0, lane, pqt[0], pqt[1]);
+  const int v_rel = wave * 32 * kRowBytes;
+  floatx16 dk[kNDB], dv[kNDB];
+  const floatx16 zeros = {};
+#pragma unroll
+  for (int db = 0; db < kNDB; ++db) { dk[db] = zeros; dv[db] = zeros; }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+
+  auto compute = [&](const Step& d, const bf16x8& st3, auto xc) {
+    constexpr int at = decltype(xc)::value * kStageBytes;
+    if (min(d.i0 + kQStep, d.hi) <= kv0w || kv0w >= kv_end) return;
+    floatx16 s = mfma32(st3, ones_l, zeros), dp = mfma32(st3, ones_d, zeros);
+    {
+      constexpr int kPre = 2;
+      QdV f[kNKS];
+      auto load = [&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const lds_cptr p = lds_xor<32 * i>(pq);
+        r1_issue<at>(p, f[i].q);
+        r1_issue<at + kTileBytes>(p, f[i].d);
+        r1_issue<kVBase>(p + v_rel, f[i].v);
+      };
+      static_for<0, kPre>(load);
+      static_for<0, kNKS>([&](auto ic) {
+        constexpr int i = decltype(ic)::value, ahead = (kNKS - 1 - i < kPre - 1 ? kNKS - 1 - i : kPre - 1) + (i + kPre < kNKS ? 1 : 0);
+        if constexpr (i + kPre < kNKS) load(IC<i + kPre>{});
+        asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(f[i].q), "+v"(f[i].d), "+v"(f[i].v) : "n"(3 * ahead));
+        s = mfma32(f[i].q, kf[i], s);
+        dp = mfma32(f[i].d, f[i].v, dp);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+    if (d.i0 < kv0w + 31 || d.i0 + kQStep > d.hi) {
+      const int rel_lo = kv0w + l32 - d.i0 - 4 * half, rel_hi = d.hi - d.i0 - 4 * half;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int c = 8 * (r >> 2) + (r & 3);
+        if (c < rel_lo || c >= rel_hi) s[r] = -INFINITY;
+      }
+    }
+    Tr4 tb[4];
+    auto issue = [&](auto ec) {
+      constexpr int e = decltype(ec)::value, off = at + (e >> 1) * 16 * kRowBytes, db0 = 2 * (e & 1);
+      static_for<0, 2>([&](auto dc) {
+        constexpr int x = decltype(dc)::value;
+        const lds_cptr p0 = lds_xor<64 * (db0 + x)>(pqt[0]), p1 = lds_xor<64 * (db0 + x)>(pqt[1]);
+        tr1_issue<off + kTileBytes>(p0, tb[e].r[2 * x]);
+        tr1_issue<off + kTileBytes>(p1, tb[e].r[2 * x + 1]);
+        tr1_issue<off>(p0, tb[e].r[4 + 2 * x]);
+        tr1_issue<off>(p1, tb[e].r[4 + 2 * x + 1]);
+      });
+    };
+    issue(IC<0>{});
+    __builtin_amdgcn_sched_barrier(0);
+    bf16x8 pf[2], ds[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      s[r] = __builtin_amdgcn_exp2f(s[r]);
+      dp[r] *= s[r];
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) { pf[e] = pack8(s, 8 * e); ds[e] = pack8(dp, 8 * e); }
+    static_for<0, 4>([&](auto ec) {
+      constexpr int e = decltype(ec)::value, db0 = 2 * (e & 1);
+      if constexpr (e < 3) issue(IC<e + 1>{});
+      tr4_wait_n<e < 3 ? 8 : 0>(tb[e]);
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        dv[db0 + x] = mfma32(tr4_frag(tb[e], x), pf[e >> 1], dv[db0 + x]);
+        dk[db0 + x] = mfma32(tr4_frag(tb[e], 2 + x), ds[e >> 1], dk[db0 + x]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+
+  auto iteration = [&](auto xc) -> bool {
+    constexpr int x = decltype(xc)::value;
+    const bool last = !more;
+    if (!last) {
+      nxt = next_step();
+      stage(nxt, (1 - x) * kStageBytes);
+      stat_n = load_stat(nxt);
+    }
+    compute(cur, stat, xc);
+    if (last) return false;
+    cur = nxt;
+    stat = stat_n;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    return true;
+  };
+  while (iteration(IC<0>{}) && iteration(IC<1>{})) {}
+  __syncthreads();                                      // the stages are free
+
+  const int my_key = kv0w + l32;
+  if (slot < 0 && it.final_from <= it.kv_row0 && it.load_until <= it.kv_row0) {
+    LDS_PTR(char) ep = lds + wave * kOutAreaBytes<D>;   // the whole list in one launch: bf16 rows
+    store_rows<D>(ep, dk, scale, dK, Hkv, hk, kv0w, kv_end, lane);
+    store_rows<D>(ep, dv, 1.f, dV, Hkv, hk, kv0w, kv_end, lane);
+  } else if (slot >= 0) {                               // partial tile [slot][kv head][dK, dV][256 rows][D]
+    store_part_row<D>(parts + ((size_t)slot * Hkv + hk) * (2 * 2 * kKeys * D) + (size_t)(sub * kKeys + 32 * wave + l32) * D, 2 * kKeys, dk, dv, scale, half);
+  } else if (my_key < kv_end) {
+    store_key_row<D>(((size_t)my_key * Hkv + hk) * D, my_key < it.load_until, my_key >= it.final_from, dk, dv, scale, half, acc_dk, acc_dv, dK, dV);
+  }
+}
+
+}  // namespace
+
+int launch_bwd_dkdv_pair_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
+                              float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
+                              float* parts, int head_parts) {
+  if (n_items == 0) return 0;
+  const slimattn_params& p = *c.p;
+  return in_runs(n_items, 2 * (int64_t)p.n_kv_heads * head_parts, [&](int first, int n) {
+    hipLaunchKernelGGL(dkdv_pair_bf16_kernel_d128, dim3((unsigned)(2 * n * p.n_kv_heads * head_parts)), dim3(64 * kWaves), 0, (hipStream_t)c.stream,
+                       (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv,
+                       (bf16*)dK, (bf16*)dV, items + first, n, segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, head_parts);
+    return (int)hipGetLastError();
+  });
+}
+
+}  // namespace slimattn

@@ -79,6 +79,17 @@ inline int head_parts(int n_items, int n_kv_heads, int group, int longest_rows, 
   return parts > 1 && steps - steps / parts >= 20 ? parts : 1;
 }
 
+// Whether a dK/dV launch at head dim 128 takes the kernel with 128 keys and two blocks per compute unit (dkdv_pair_bf16.hip): what an item costs
+// beside its steps is then hidden by the other block, and steps before a wave's keys are skipped; a step of the one-wave kernel
+// (dkdv_wide_bf16.hip) is cheaper.  Per 256 keys the one-wave kernel takes about 22 us and 1.5 per step, the other 5 and 1.75, so
+// what decides is the steps an item has on average.  71 launches, fused and by units, dK/dV and reduction, one-wave kernel / this one: 4 to 20
+// steps 23.8 / 16.1, 42.4 / 31.2, 158 / 106, 165 / 139 us; 36 steps 696 / 657; 84 to 94 steps 233 / 206, 340 / 309, 188 / 192, 375 /
+// 384; 110 to 117 steps 431 / 434, 418 / 380; 158 steps 653 / 702; 240 and more 806 / 859, 4706 / 5598.
+constexpr int kShortWalkSteps = 112;
+inline bool short_walks(int64_t walk_rows, int n_items, int group, int head_parts) {
+  return walk_rows * group <= (int64_t)kShortWalkSteps * 32 * n_items * head_parts;
+}
+
 struct Range { int32_t begin, end; };
 
 // A launch scope is either one unit or the whole list ("fused").  Its items are stored heavy-first.
@@ -100,6 +111,7 @@ struct ScopeLists {
   std::vector<Range> tile_rng[kNumSplitTiles][kNumSplitClasses];
   std::vector<KvReduce> tile_items[kNumSplitTiles];
   std::vector<int32_t> longest[kNumSplitTiles][kNumSplitClasses];
+  std::vector<int64_t> walk_rows[kNumSplitTiles];             // per unit: rows of all the tiles' walks
 };
 
 struct DeviceLists {                            // device mirrors (pointers into one allocation)
@@ -218,10 +230,14 @@ int launch_bwd_stat_bf16(const LaunchCtx&, const void* o, const void* dO, const 
                          int n_items);
 int launch_bwd_dq_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* o,
                        const float* lse, void* stat3, int own_stats, void* dQ, const QItem* items, int n_items);
-// head_dim 128: one wave per SIMD, 256 key rows per block (dkdv_wide_bf16.hip); same arguments
+// head_dim 128, long walks: one wave per SIMD, 256 key rows per block (dkdv_wide_bf16.hip)
 int launch_bwd_dkdv_wide_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
                             float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
                             float* parts, int head_parts);
+// head_dim 128, short walks: two blocks of 128 key rows per compute unit (dkdv_pair_bf16.hip); same arguments
+int launch_bwd_dkdv_pair_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
+                              float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
+                              float* parts, int head_parts);
 // head_dim 64: two waves per SIMD (dkdv_d64_bf16.hip); same arguments
 int launch_bwd_dkdv_d64_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
                              float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,

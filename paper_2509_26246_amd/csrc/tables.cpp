@@ -71,6 +71,7 @@ void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const st
   const int64_t kBlockSlots = kSplitBlockSlots[ti];
   int64_t total = 0;
   for (int64_t w : weight) total += w;
+  L.walk_rows[ti].push_back(total);
   bool divided = true;                                       // in the class below
   for (int c = 0; c < kNumSplitClasses; ++c) {
     if (!divided) {      // shares grow with the class: nothing is divided here either, and the lists are the same

@@ -125,6 +125,19 @@ def test_bf16_dkdv_head_dim_64(L, hq, hkv, slice_size):
     _fused_and_per_unit(L, hq, hkv, 64, True, slice_size)
 
 
+# Head dim 128, short walks: the halves of 256-row items as blocks of their own, tiles with few waves in use, walks of one step, an odd and an
+# even number of steps, steps that end inside a run, runs that start inside a wave's keys
+@pytest.mark.parametrize("L", [[1, 31, 32, 33], [95, 127, 128, 129], [160, 255, 257, 385]], ids=["wave", "half", "tile"])
+@pytest.mark.parametrize("hq,hkv,slice_size", [(1, 1, 1000), (3, 1, 97), (4, 2, 64)])
+def test_bf16_dkdv_short_walks(L, hq, hkv, slice_size):
+    _fused_and_per_unit(L, hq, hkv, 128, True, slice_size)
+
+
+# ... and more than 112 steps per item on average in a launch that fills the chip (10 items of 16 KV heads, 123 steps): the one-wave kernel
+def test_bf16_dkdv_long_walks():
+    _fused_and_per_unit([510, 440, 330, 300, 290], 256, 16, 128, True, 1000)
+
+
 # fp32 dQ: a key with a NaN or an infinity reaches the rows that see it and no row in front of it, in the middle of a tile too; a key of
 # -inf (score -inf, probability 0) spoils only its own dim of those rows
 @pytest.mark.parametrize("d", [16, 32, 64, 128])

@@ -8,12 +8,15 @@
 // atomics.
 //
 // Shape on CDNA4.  The unit of work is a 32 x 32 tile of scores.  A product takes 64 cycles of the matrix unit for 64 + 64
-// operand registers' worth of data, eight times as long per byte as a bf16 product, so operands need no LDS: a wave reads
-// its fragments from global memory (the caches) straight into registers, one phase of products ahead of their use, and
-// shares nothing with the other waves of its block until the end.  A block owns 32 rows (query rows for the forward and
-// dQ, key rows for dK/dV), its 4 waves take the tiles of the walk in turn -- tile w, w + 4, ... -- and their partial sums
+// operand registers' worth of data, eight times as long per byte as a bf16 product, so the walk's operands need no LDS: a wave reads
+// its fragments from global memory (the caches) straight into registers, eight to ten loads ahead of their use, and shares nothing with
+// the other waves of its block until the end.  A block owns 32 rows (query rows for the forward and dQ, key rows for
+// dK/dV), its 4 waves take the tiles of the walk in turn -- tile w, w + 4, ... -- and their partial sums
 // are added up in wave order through LDS.  That keeps blocks small (a pack of a few hundred rows already fills dozens of
-// compute units, each with a quarter of the walk's latency) and the loop without barriers.
+// compute units, each with a quarter of the walk's latency) and the loop without barriers.  The block's own rows, an operand of every
+// score product, are in LDS (one read for four products): with them and whole phases of loads in registers a wave was alone
+// on its SIMD at head dim 128 and nothing hid a block's first loads and its last additions; now two blocks (forward: three) share a compute
+// unit.
 //
 // Operand layout of the product (lane l, half = l / 32, n = l % 32): A[m = n][k = half], B[k = half][n],
 // C[i = 8 (r / 4) + 4 half + r % 4][j = n].  The order of a contraction is free, so
@@ -23,11 +26,10 @@
 //     8 (r / 4) + r % 4 (lower half-wave) and + 4 (upper);
 //   - "column" fragments (contraction over rows) match that: for register r a lane reads D / 32 consecutive dims of row
 //     8 (r / 4) + 4 half + r % 4, one per accumulator block, so block b of an accumulator holds the dims (D / 32) i + b.
-// What bounds it: the fp32 matrix rate (154 TFLOP/s for a large product here).  A pack of two samples, 1660 and 2436 rows,
-// 8 query and 2 KV heads, head dim 128: forward 5803 -> 195 us, dQ with delta 6743 -> 280 us, dK/dV 12757 -> 381 us against
-// one lane per row on the vector unit (2.5 -> 77 TFLOP/s, counting 7 products); the tiny pack of 876 rows, 2 heads of 64:
-// 1080 -> 55 us.  (The forward at head dim 128 with 256 registers, two blocks per compute unit, 31 spilled registers and 24 reloads
-// per tile, and with 356 registers, one block and no spills: the same 195 us.)
+// What bounds it: the fp32 matrix rate (153 TFLOP/s for a large product here).  One sample of 4096 rows, 8 query and 2 KV heads, head dim
+// 128: forward 313 -> 270 us, dQ with delta 422 -> 398, dK/dV 610 -> 515 (123 to 128 TFLOP/s) against whole phases of loads and the
+// block's rows in registers; two samples, 1660 and 2436 rows, 187 -> 169, 264 -> 249, 361 -> 325, as the longest walks still decide; 2000 rows 124 -> 76, 123 -> 111, 268
+// -> 249; samples of 300 rows 66 -> 46, 95 -> 75, 92 -> 78.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -44,7 +46,6 @@ constexpr float kLn2 = 0.6931471805599453f;
 
 template <int D> constexpr int kNC = D / 8;                      // row-fragment chunks (4 products each)
 template <int D> constexpr int kNB = D >= 32 ? D / 32 : 1;       // accumulator blocks of 32 dims
-template <int D> constexpr int kPad = D + 4;                     // floats per row of the LDS areas the waves' sums meet in
 
 template <int N> struct FloatVec { typedef __attribute__((__vector_size__(N * sizeof(float)))) float type; };
 template <> struct FloatVec<1> { typedef float type; };
@@ -86,82 +87,113 @@ template <int D> __device__ __forceinline__ typename FloatVec<kNB<D>>::type load
   else return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(t.rsrc, voff, soff, 0));
 }
 
-template <int D> struct RowFrag { floatx4 x[kNC<D>]; };
-template <int D> struct ColFrag { typename FloatVec<kNB<D>>::type x[16]; };
+// The fragments of a walk come as a stream of slots, a slot being one load and the products it feeds: kNC row fragments for each score
+// product, 16 column fragments for each product over rows.  R slots are under way: behind slot i's products, the load of slot i + R goes into
+// the registers slot i gives free (R divides the slots of a tile, so the places are the same in every tile).
+constexpr int ring_slots(int slots) {
+  for (int r = 10; r > 1; --r) if (slots % r == 0) return r;
+  return 1;
+}
+template <int R> struct Ring { floatx4 x[R]; };
+template <int D> __device__ __forceinline__ void put_col(floatx4& f, const Rows32<D>& t, int voff, int r) {
+  const typename FloatVec<kNB<D>>::type c = load_col<D>(t, voff, r);
+#pragma unroll
+  for (int b = 0; b < kNB<D>; ++b) f[b] = elem<kNB<D>>(c, b);
+}
 
-// acc += rows . b^T over the head dimension; behind the products of chunk c: next(c), the loads of the following phase that
-// may go into the registers chunk c gives free.
-template <int D, class Next>
-__device__ __forceinline__ void row_products(floatx16& acc, const RowFrag<D>& a, const RowFrag<D>& b, Next&& next) {
+// The block's own rows (operands of every score product), in LDS as fragments: chunk c of lane l at [c][l].
+template <int D> struct OwnRows { floatx4 x[kNC<D>][64]; };
+template <int D>
+__device__ __forceinline__ void put_own(OwnRows<D>& own, const Rows32<D>& t, int voff, float factor, int wave, int lane) {
+#pragma unroll
+  for (int i = 0; i < (kNC<D> + kWaves - 1) / kWaves; ++i) {     // the waves share the chunks
+    const int c = kWaves * i + wave;
+    if (kNC<D> % kWaves == 0 || c < kNC<D>) own.x[c][lane] = load_row<D>(t, voff, c) * factor;
+  }
+}
+
+// acc += rows . own^T over the head dimension, slots FIRST .. FIRST + kNC - 1 of the stream; next(i) issues the load of slot i + R.
+template <int D, int R, int FIRST, class Next>
+__device__ __forceinline__ void row_products(floatx16& acc, Ring<R>& ring, const OwnRows<D>& own, int lane, Next&& next) {
+  floatx4 o[2];
+  o[0] = own.x[0][lane];
   static_for<0, kNC<D>>([&](auto cc) {
-    constexpr int c = decltype(cc)::value;
+    constexpr int c = decltype(cc)::value, at = (FIRST + c) % R;
+    if constexpr (c + 1 < kNC<D>) o[(c + 1) & 1] = own.x[c + 1][lane];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc = mfma_f32(a.x[c][j], b.x[c][j], acc);
-    next(cc);
+    for (int j = 0; j < 4; ++j) acc = mfma_f32(ring.x[at][j], o[c & 1][j], acc);
+    next(IC<FIRST + c>{});
     __builtin_amdgcn_sched_barrier(0);
   });
 }
-// acc[b] += columns . s over the tile's rows (s: a score tile's C registers)
-template <int D, class Next>
-__device__ __forceinline__ void col_products(floatx16 (&acc)[kNB<D>], const ColFrag<D>& a, const floatx16& s, Next&& next) {
+// acc[b] += columns . s over the tile's rows (s: a score tile's C registers), slots FIRST .. FIRST + 15.  FINITE: columns that are
+// not finite count as 0.
+template <int D, int R, int FIRST, bool FINITE = false, class Next>
+__device__ __forceinline__ void col_products(floatx16 (&acc)[kNB<D>], Ring<R>& ring, const floatx16& s, Next&& next) {
   static_for<0, 16>([&](auto rc) {
-    constexpr int r = decltype(rc)::value;
+    constexpr int r = decltype(rc)::value, at = (FIRST + r) % R;
 #pragma unroll
-    for (int b = 0; b < kNB<D>; ++b) acc[b] = mfma_f32(elem<kNB<D>>(a.x[r], b), s[r], acc[b]);
-    next(rc);
+    for (int b = 0; b < kNB<D>; ++b) {
+      float x = ring.x[at][b];
+      if constexpr (FINITE) x = fabsf(x) < INFINITY ? x : 0.f;
+      acc[b] = mfma_f32(x, s[r], acc[b]);
+    }
+    next(IC<FIRST + r>{});
     __builtin_amdgcn_sched_barrier(0);
   });
-}
-// The loads of one fragment, cut into pieces: piece c of kNC (behind a row phase's chunk) or piece r of 16.
-template <int D, int C> __device__ __forceinline__ void cols_by_chunk(ColFrag<D>& f, const Rows32<D>& t, int voff) {
-  constexpr int per = 16 / kNC<D>;
-  static_for<0, per>([&](auto i) { constexpr int r = C * per + decltype(i)::value; f.x[r] = load_col<D>(t, voff, r); });
-}
-template <int D, int R> __device__ __forceinline__ void rows_by_reg(RowFrag<D>& f, const Rows32<D>& t, int voff) {
-  constexpr int per = 16 / kNC<D>;
-  if constexpr (R % per == 0) f.x[R / per] = load_row<D>(t, voff, R / per);
-}
-template <int D> __device__ __forceinline__ void load_rows(RowFrag<D>& f, const Rows32<D>& t, int voff) {
-#pragma unroll
-  for (int c = 0; c < kNC<D>; ++c) f.x[c] = load_row<D>(t, voff, c);
 }
 
 // Keys of the diagonal's tile with a NaN or an infinity: the product over the tile would carry them, times a probability of 0, into
-// the rows in front of them, which do not see them.  If there are any (kr and kc hold the same keys), their values become 0 in kc
-// and NaN goes to the rows that do see them, which is what the product would have given those (their scores are NaN or infinite).
+// the rows in front of them, which do not see them.  Where there are any, the product takes their values as 0 (FINITE above) and NaN
+// goes to the rows that do see them, which is what it would have given those (their scores are NaN or infinite).
 template <int D>
-__device__ __forceinline__ void unseen_keys(floatx16 (&acc)[kNB<D>], const RowFrag<D>& kr, ColFrag<D>& kc, int rel) {
-  float odd = 0.f;
-#pragma unroll
-  for (int c = 0; c < kNC<D>; ++c)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) odd = fmaf(kr.x[c][j], 0.f, odd);     // stays 0 unless one is not finite
-  if (__builtin_expect(!__any(odd != 0.f), 1)) return;
+__device__ __forceinline__ void unseen_keys(floatx16 (&acc)[kNB<D>], const Rows32<D>& tk, int cvoff, int rel) {
 #pragma unroll
   for (int b = 0; b < kNB<D>; ++b) {
     floatx16 seen = {};                                               // how many such keys a row sees, per dim
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float x = elem<kNB<D>>(kc.x[r], b);
-      const bool bad = !(fabsf(x) < INFINITY);
-      seen = mfma_f32(bad ? 1.f : 0.f, c_row(r) > rel ? 0.f : 1.f, seen);
-      if constexpr (kNB<D> == 1) kc.x[r] = bad ? 0.f : x; else kc.x[r][b] = bad ? 0.f : x;
+      const float x = elem<kNB<D>>(load_col<D>(tk, cvoff, r), b);
+      seen = mfma_f32(fabsf(x) < INFINITY ? 0.f : 1.f, c_row(r) > rel ? 0.f : 1.f, seen);
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[b][r] = seen[r] > 0.f ? __builtin_nanf("") : acc[b][r];
   }
 }
 
-// A wave's accumulator (C layout, lane = row l32) into its LDS area, one row of D floats per lane pair.
-template <int D>
+// The waves' sums meet in LDS, D / kHalves dims at a time, one row of them per lane pair.
+template <int D> constexpr int kHalves = D == 128 ? 2 : 1;
+template <int D> constexpr int kPad = D / kHalves<D> + 4;
+template <int D> struct Partials { float x[kWaves][kSub][kPad<D>]; };
+template <int D, int H>
 __device__ __forceinline__ void put_partial(float (*area)[kPad<D>], const floatx16 (&acc)[kNB<D>], int l32, int half) {
+  constexpr int n = 16 / kHalves<D>;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int i = c_row(r) + 4 * half;
+  for (int r = n * H; r < n * H + n; ++r) {
+    const int i = c_row(r) + 4 * half - 2 * n * H;
     if (D >= 32 || i < D)
 #pragma unroll
       for (int b = 0; b < kNB<D>; ++b) area[l32][kNB<D> * i + b] = acc[b][r];
   }
+}
+// For each part of the dims: every wave's sums into the area, then take(row of the block, first dim of four, offset in the area's rows).
+template <int D, class Take>
+__device__ __forceinline__ void meet(Partials<D>& p, const floatx16 (&acc)[kNB<D>], int wave, int l32, int half, Take&& take) {
+  static_for<0, kHalves<D>>([&](auto hc) {
+    constexpr int h = decltype(hc)::value, dims = D / kHalves<D>;
+    __syncthreads();                                             // the area's last readers are through
+    put_partial<D, h>(p.x[wave], acc, l32, half);
+    __syncthreads();
+    for (int c = (threadIdx.x & 7) * 4; c < dims; c += 32) take((int)threadIdx.x >> 3, h * dims + c, c);
+  });
+}
+
+// The lists are heavy-first, and two or more blocks share a compute unit from the start.  The second round of 256 blocks (what there is of it)
+// runs backwards, so that the longest walks share theirs with the shortest of the round (one sample of 4096 rows, dK/dV 718 -> 515 us; 2000 rows,
+// forward 100 -> 76).  (The low three bits, the XCD, stay.)
+__device__ __forceinline__ int paired(int block) {
+  const int end = min((int)gridDim.x, 512) & ~7;
+  return block >= 256 && block < end ? 256 + end - 8 - (block & ~7) + (block & 7) : block;
 }
 
 template <int D>
@@ -169,11 +201,12 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(const float* __restrict
                                                          const float* __restrict__ v, float* __restrict__ o,
                                                          float* __restrict__ lse, const QItem* __restrict__ items, int n_items,
                                                          int T, int Hq, int Hkv, float scale) {
-  __shared__ __attribute__((aligned(16))) float part[kWaves][kSub][kPad<D>];
+  constexpr int kRows = kNC<D>, kSlots = kRows + 16, R = ring_slots(kSlots);       // a tile's slots: K rows, V columns
+  __shared__ __attribute__((aligned(16))) union { OwnRows<D> own; Partials<D> part; } sh;
   __shared__ float part_m[kWaves][kSub], part_l[kWaves][kSub];
   const int g = Hq / Hkv;
   int idx, hk, hg;
-  if (!map_block(blockIdx.x, g, Hkv, 2 * n_items, &idx, &hk, &hg)) return;
+  if (!map_block(paired(blockIdx.x), g, Hkv, 2 * n_items, &idx, &hk, &hg)) return;
   const QItem it = items[idx >> 1];
   const int h = hk * g + hg, q0 = it.q_row0 + kSub * (idx & 1), q_end = it.q_row0 + min(it.q_rows, kSub * ((idx & 1) + 1));
   if (q0 >= q_end) return;
@@ -182,12 +215,22 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(const float* __restrict
 
   auto tile = [&](const float* base, int kb) { return Rows32<D>(base, it.kv_start + kSub * kb, q_end - it.kv_start - kSub * kb, Hkv, hk); };
   const int rvoff = row_voff<D>(Hkv * D * 4, l32, half), cvoff = col_voff<D>(Hkv * D * 4, l32, half);
-  RowFrag<D> kr, qf;
-  ColFrag<D> vc;
-  load_rows<D>(kr, tile(k, wave), rvoff);
-  load_rows<D>(qf, Rows32<D>(q, q0, q_end - q0, Hq, h), row_voff<D>(Hq * D * 4, l32, half));
-#pragma unroll
-  for (int c = 0; c < kNC<D>; ++c) qf.x[c] *= scale * kLog2e;    // scores in log2 units
+  Ring<R> ring;
+  auto load = [&](auto ic, const Rows32<D>& tk, const Rows32<D>& tv) {
+    constexpr int i = decltype(ic)::value;
+    if constexpr (i < kRows) ring.x[i % R] = load_row<D>(tk, rvoff, i);
+    else put_col<D>(ring.x[i % R], tv, cvoff, i - kRows);
+  };
+  {
+    const Rows32<D> tk = tile(k, wave), tv = tile(v, wave);
+    static_for<0, R>([&](auto ic) { load(ic, tk, tv); });
+  }
+  {
+    const Rows32<D> tq(q, q0, q_end - q0, Hq, h);
+    const int qvoff = row_voff<D>(Hq * D * 4, l32, half);
+    put_own<D>(sh.own, tq, qvoff, scale * kLog2e, wave, lane);   // scores in log2 units
+  }
+  __syncthreads();
   floatx16 acc[kNB<D>];
 #pragma unroll
   for (int b = 0; b < kNB<D>; ++b) acc[b] = floatx16{};
@@ -195,8 +238,12 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(const float* __restrict
   for (int kb = wave; kb < n; kb += kWaves) {
     const int key0 = it.kv_start + kSub * kb;
     floatx16 s = {};
-    const Rows32<D> tv = tile(v, kb), tk = tile(k, kb + kWaves);
-    row_products<D>(s, kr, qf, [&](auto cc) { cols_by_chunk<D, decltype(cc)::value>(vc, tv, cvoff); });
+    const Rows32<D> tk = tile(k, kb), tv = tile(v, kb), nk = tile(k, kb + kWaves), nv = tile(v, kb + kWaves);
+    auto next = [&](auto ic) {
+      constexpr int i = decltype(ic)::value + R;
+      if constexpr (i < kSlots) load(IC<i>{}, tk, tv); else load(IC<i - kSlots>{}, nk, nv);
+    };
+    row_products<D, R, 0>(s, ring, sh.own, lane, next);
     if (key0 + kSub - 1 > q0) {                                  // the tile touches the diagonal of some row
       const int rel = q0 + l32 - key0 - 4 * half;
 #pragma unroll
@@ -217,41 +264,40 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(const float* __restrict
     for (int b = 0; b < kNB<D>; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[b][r] *= alpha;
-    col_products<D>(acc, vc, s, [&](auto rc) { rows_by_reg<D, decltype(rc)::value>(kr, tk, rvoff); });
+    col_products<D, R, kRows>(acc, ring, s, next);
   }
   l += xor32(l);
-  put_partial<D>(part[wave], acc, l32, half);
   if (half == 0) { part_m[wave][l32] = m; part_l[wave][l32] = l; }
   __syncthreads();
   const int row = tid >> 3;
-  if (q0 + row >= q_end) return;
   float w[kWaves], top = part_m[0][row], l_tot = 0.f;            // wave 0 has the sample's first keys: finite
 #pragma unroll
   for (int x = 1; x < kWaves; ++x) top = fmaxf(top, part_m[x][row]);
 #pragma unroll
   for (int x = 0; x < kWaves; ++x) { w[x] = __builtin_amdgcn_exp2f(part_m[x][row] - top); l_tot += w[x] * part_l[x][row]; }
   const float inv = 1.f / l_tot;
-  float* out = o + ((size_t)(q0 + row) * Hq + h) * D;
-  for (int c = (tid & 7) * 4; c < D; c += 32) {
+  meet<D>(sh.part, acc, wave, l32, half, [&](int row, int dim, int c) {
+    if (q0 + row >= q_end) return;
     floatx4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int x = 0; x < kWaves; ++x) sum += w[x] * *reinterpret_cast<const floatx4*>(&part[x][row][c]);
-    *reinterpret_cast<floatx4*>(out + c) = sum * inv;
-  }
-  if ((tid & 7) == 0) lse[(size_t)h * T + q0 + row] = top * kLn2 + logf(l_tot);
+    for (int x = 0; x < kWaves; ++x) sum += w[x] * *reinterpret_cast<const floatx4*>(&sh.part.x[x][row][c]);
+    *reinterpret_cast<floatx4*>(o + ((size_t)(q0 + row) * Hq + h) * D + dim) = sum * inv;
+  });
+  if ((tid & 7) == 0 && q0 + row < q_end) lse[(size_t)h * T + q0 + row] = top * kLn2 + logf(l_tot);
 }
 
 // dQ, and delta = rowsum(dO * O) of the block's rows (every (row, head) of the launch scope belongs to one block), stored for
 // the dK/dV launch that follows.
 template <int D>
-__global__ __launch_bounds__(256, D == 128 ? 1 : 2) void dq_f32_kernel(
+__global__ __launch_bounds__(256, 2) void dq_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ o,
     const float* __restrict__ dO, const float* __restrict__ lse, float* __restrict__ delta, float* __restrict__ dQ,
     const QItem* __restrict__ items, int n_items, int T, int Hq, int Hkv, float scale) {
-  __shared__ __attribute__((aligned(16))) float part[kWaves][kSub][kPad<D>];
+  constexpr int kRows = kNC<D>, kSlots = 2 * kRows + 16, R = ring_slots(kSlots);   // a tile's slots: K rows, V rows, K columns
+  __shared__ __attribute__((aligned(16))) union { OwnRows<D> own[2]; Partials<D> part; } sh;     // Q, dO
   const int g = Hq / Hkv;
   int idx, hk, hg;
-  if (!map_block(blockIdx.x, g, Hkv, 2 * n_items, &idx, &hk, &hg)) return;
+  if (!map_block(paired(blockIdx.x), g, Hkv, 2 * n_items, &idx, &hk, &hg)) return;
   const QItem it = items[idx >> 1];
   const int h = hk * g + hg, q0 = it.q_row0 + kSub * (idx & 1), q_end = it.q_row0 + min(it.q_rows, kSub * ((idx & 1) + 1));
   if (q0 >= q_end) return;
@@ -260,89 +306,101 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void dq_f32_kernel(
 
   auto tile = [&](const float* base, int kb) { return Rows32<D>(base, it.kv_start + kSub * kb, q_end - it.kv_start - kSub * kb, Hkv, hk); };
   const int rvoff = row_voff<D>(Hkv * D * 4, l32, half), cvoff = col_voff<D>(Hkv * D * 4, l32, half);
-  RowFrag<D> kr, vr, qf, dof;
-  ColFrag<D> kc;
-  load_rows<D>(kr, tile(k, wave), rvoff);
-  const int qvoff = row_voff<D>(Hq * D * 4, l32, half);
-  load_rows<D>(qf, Rows32<D>(q, q0, q_end - q0, Hq, h), qvoff);
-  load_rows<D>(dof, Rows32<D>(dO, q0, q_end - q0, Hq, h), qvoff);
+  Ring<R> ring;
+  auto load = [&](auto ic, const Rows32<D>& tk, const Rows32<D>& tv) {
+    constexpr int i = decltype(ic)::value;
+    if constexpr (i < 2 * kRows) ring.x[i % R] = load_row<D>(i < kRows ? tk : tv, rvoff, i % kRows);
+    else put_col<D>(ring.x[i % R], tk, cvoff, i - 2 * kRows);
+  };
+  {
+    const Rows32<D> tk = tile(k, wave), tv = tile(v, wave);
+    static_for<0, R>([&](auto ic) { load(ic, tk, tv); });
+  }
   const size_t stat_at = (size_t)h * T + min(q0 + l32, q_end - 1);
   const float row_lse = lse[stat_at];
   float dlt = 0.f;
   {
-    const Rows32<D> to(o, q0, q_end - q0, Hq, h);
+    const int qvoff = row_voff<D>(Hq * D * 4, l32, half);
+    const Rows32<D> tq(q, q0, q_end - q0, Hq, h), to(o, q0, q_end - q0, Hq, h), td(dO, q0, q_end - q0, Hq, h);
+    put_own<D>(sh.own[0], tq, qvoff, scale * kLog2e, wave, lane);
 #pragma unroll
-    for (int c = 0; c < kNC<D>; ++c) {
-      const floatx4 x = load_row<D>(to, qvoff, c);
+    for (int c = 0; c < kRows; ++c) {                            // (every wave needs delta, so each has all of dO and writes the same)
+      const floatx4 x = load_row<D>(to, qvoff, c), y = load_row<D>(td, qvoff, c);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) dlt = fmaf(x[j], dof.x[c][j], dlt);
-      qf.x[c] *= scale * kLog2e;
+      for (int j = 0; j < 4; ++j) dlt = fmaf(x[j], y[j], dlt);
+      sh.own[1].x[c][lane] = y;
     }
     dlt += xor32(dlt);
     if (wave == 0 && half == 0 && q0 + l32 < q_end) delta[stat_at] = dlt;
   }
+  __syncthreads();
   floatx16 acc[kNB<D>];
 #pragma unroll
   for (int b = 0; b < kNB<D>; ++b) acc[b] = floatx16{};
   auto step = [&](int kb, auto masked_c) {
     constexpr bool masked = decltype(masked_c)::value != 0;      // the tile touches the diagonal of some row
-    const Rows32<D> tk = tile(k, kb), tv = tile(v, kb), tn = tile(k, kb + kWaves);
+    const Rows32<D> tk = tile(k, kb), tv = tile(v, kb), nk = tile(k, kb + kWaves), nv = tile(v, kb + kWaves);
+    float odd = 0.f;                                             // stays 0 unless a key of the tile is not finite
+    auto next = [&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      if constexpr (masked && i < kRows)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) odd = fmaf(ring.x[i % R][j], 0.f, odd);
+      if constexpr (i + R < kSlots) load(IC<i + R>{}, tk, tv); else load(IC<i + R - kSlots>{}, nk, nv);
+    };
     floatx16 s = {}, dp = {};
-    row_products<D>(s, kr, qf, [&](auto cc) { constexpr int c = decltype(cc)::value; vr.x[c] = load_row<D>(tv, rvoff, c); });
-    row_products<D>(dp, vr, dof, [&](auto cc) { cols_by_chunk<D, decltype(cc)::value>(kc, tk, cvoff); });
+    row_products<D, R, 0>(s, ring, sh.own[0], lane, next);
+    row_products<D, R, kRows>(dp, ring, sh.own[1], lane, next);
     const int rel = q0 + l32 - it.kv_start - kSub * kb - 4 * half;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float ds = __builtin_amdgcn_exp2f(fmaf(row_lse, -kLog2e, s[r])) * (dp[r] - dlt);
       s[r] = masked && c_row(r) > rel ? 0.f : ds;
     }
-    if constexpr (masked) unseen_keys<D>(acc, kr, kc, rel);
-    col_products<D>(acc, kc, s, [&](auto rc) { rows_by_reg<D, decltype(rc)::value>(kr, tn, rvoff); });
+    if constexpr (masked) { if (__builtin_expect(__any(odd != 0.f), 0)) unseen_keys<D>(acc, tk, cvoff, rel); }
+    col_products<D, R, 2 * kRows, masked>(acc, ring, s, next);
   };
   int kb = wave;
   for (const int n_full = (q0 + 1 - it.kv_start) / kSub; kb < n_full; kb += kWaves) step(kb, IC<0>{});
   for (; kb < n; kb += kWaves) step(kb, IC<1>{});
-  put_partial<D>(part[wave], acc, l32, half);
-  __syncthreads();
-  const int row = tid >> 3;
-  if (q0 + row >= q_end) return;
-  float* out = dQ + ((size_t)(q0 + row) * Hq + h) * D;
-  for (int c = (tid & 7) * 4; c < D; c += 32) {
+  meet<D>(sh.part, acc, wave, l32, half, [&](int row, int dim, int c) {
+    if (q0 + row >= q_end) return;
     floatx4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int x = 0; x < kWaves; ++x) sum += *reinterpret_cast<const floatx4*>(&part[x][row][c]);
-    *reinterpret_cast<floatx4*>(out + c) = sum * scale;
-  }
+    for (int x = 0; x < kWaves; ++x) sum += *reinterpret_cast<const floatx4*>(&sh.part.x[x][row][c]);
+    *reinterpret_cast<floatx4*>(dQ + ((size_t)(q0 + row) * Hq + h) * D + dim) = sum * scale;
+  });
 }
 
 // dK/dV of 32 key rows of one KV head: S = Q K^T - lse and dP = dO V^T - delta (a lane owns a key; the row statistics enter
 // as one product each, the statistic in the lower half-wave's contraction slot times a constant), dV^T += dO^T P,
 // dK^T += Q^T dS.  The walk: the scope's query runs at or after the tile, in each run steps of 32 rows, in each step the
-// heads of the group; with P = gridDim.y parts, step x belongs to wave x % 4 of part (x / 4) % P.  P = 1: the block owns its
+// heads of the group; with P = n_parts, step x belongs to wave x % 4 of part (x / 4) % P.  P = 1: the block owns its
 // rows' dK/dV.  P = 2 (whole-list scope only): part 0 leaves its sums in dK/dV, part 1 in the accumulators, which that scope
 // does not use otherwise, and add_parts_f32_kernel adds the two.
 template <int D>
-__global__ __launch_bounds__(256, D == 128 ? 1 : 2) void dkdv_f32_kernel(
+__global__ __launch_bounds__(256, 2) void dkdv_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v, const float* __restrict__ dO,
     const float* __restrict__ lse, const float* __restrict__ delta, float* __restrict__ acc_dk, float* __restrict__ acc_dv,
     float* __restrict__ dK, float* __restrict__ dV, const KvItem* __restrict__ items, const Seg* __restrict__ segs, int T, int Hq,
-    int Hkv, float scale) {
-  __shared__ __attribute__((aligned(16))) float part[kWaves][kSub][kPad<D>];
-  const int idx = blockIdx.x / Hkv, hk = blockIdx.x % Hkv, g = Hq / Hkv;
+    int Hkv, float scale, int n_parts) {
+  // a step's slots: Q rows, dO rows, dO columns, Q columns
+  constexpr int kRows = kNC<D>, kSlots = 2 * kRows + 32, R = ring_slots(kSlots);
+  __shared__ __attribute__((aligned(16))) union { OwnRows<D> own[2]; Partials<D> part; } sh;     // K, V
+  const int block = paired(blockIdx.x), part_no = block % n_parts, idx = block / n_parts / Hkv, hk = block / n_parts % Hkv, g = Hq / Hkv;
   const KvItem it = items[idx >> 1];
   const int k0 = it.kv_row0 + kSub * (idx & 1), k_end = it.kv_row0 + min(it.kv_rows, kSub * ((idx & 1) + 1));
   if (k0 >= k_end) return;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
 
-  const int kvoff = row_voff<D>(Hkv * D * 4, l32, half);
-  RowFrag<D> kf, vf;
-  load_rows<D>(kf, Rows32<D>(k, k0, k_end - k0, Hkv, hk), kvoff);
-  load_rows<D>(vf, Rows32<D>(v, k0, k_end - k0, Hkv, hk), kvoff);
-#pragma unroll
-  for (int c = 0; c < kNC<D>; ++c) kf.x[c] *= scale * kLog2e;
+  {
+    const int kvoff = row_voff<D>(Hkv * D * 4, l32, half);
+    const Rows32<D> tk(k, k0, k_end - k0, Hkv, hk), tv(v, k0, k_end - k0, Hkv, hk);
+    put_own<D>(sh.own[0], tk, kvoff, scale * kLog2e, wave, lane);
+    put_own<D>(sh.own[1], tv, kvoff, 1.f, wave, lane);
+  }
 
   // this wave's walk: step `pos` of the run sgi (rows [lo, hi), n_run steps), step = 32 rows and a head
-  const int n_parts = gridDim.y, part_no = blockIdx.y;
   int sgi = it.seg_begin, pos = kWaves * part_no + wave, lo = 0, hi = 0, n_run = 0;
   auto open_run = [&]() {
     const Seg sg = segs[sgi];
@@ -360,7 +418,7 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void dkdv_f32_kernel(
   };
   open_run();
   bool live = settle();
-  int i0 = 0, n_rows = 0, head = 0;                              // the step whose row fragments are loaded
+  int i0 = 0, n_rows = 0, head = 0;                              // the step whose first slots are under way
   float nl = 0.f, nd = 0.f;                                      // its lse, delta (lane = row)
   const int qrow = row_voff<D>(Hq * D * 4, l32, half), qcol = col_voff<D>(Hq * D * 4, l32, half);
   auto take = [&]() {                                            // (an ended walk keeps naming its last step, with no rows)
@@ -374,15 +432,23 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void dkdv_f32_kernel(
       nd = delta[at];
     }
   };
-  RowFrag<D> qr, dr;
-  ColFrag<D> dc, qc;
+  Ring<R> ring;
+  auto load = [&](auto ic, const Rows32<D>& tq, const Rows32<D>& td) {
+    constexpr int i = decltype(ic)::value;
+    if constexpr (i < 2 * kRows) ring.x[i % R] = load_row<D>(i < kRows ? tq : td, qrow, i % kRows);
+    else put_col<D>(ring.x[i % R], i < 2 * kRows + 16 ? td : tq, qcol, (i - 2 * kRows) % 16);
+  };
   floatx16 dk[kNB<D>], dv[kNB<D>];
 #pragma unroll
   for (int b = 0; b < kNB<D>; ++b) { dk[b] = floatx16{}; dv[b] = floatx16{}; }
   const float one = half ? 0.f : 1.f;
   take();
   stats();
-  load_rows<D>(qr, Rows32<D>(q, i0, n_rows, Hq, head), qrow);
+  {
+    const Rows32<D> tq(q, i0, n_rows, Hq, head), td(dO, i0, n_rows, Hq, head);
+    static_for<0, R>([&](auto ic) { load(ic, tq, td); });
+  }
+  __syncthreads();
   while (live) {
     const int c_i0 = i0, c_rows = n_rows;
     const Rows32<D> tq(q, i0, n_rows, Hq, head), td(dO, i0, n_rows, Hq, head);
@@ -392,9 +458,13 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void dkdv_f32_kernel(
     live = settle();
     take();
     stats();
-    const Rows32<D> tn(q, i0, n_rows, Hq, head);
-    row_products<D>(s, qr, kf, [&](auto cc) { constexpr int c = decltype(cc)::value; dr.x[c] = load_row<D>(td, qrow, c); });
-    row_products<D>(dp, dr, vf, [&](auto cc) { cols_by_chunk<D, decltype(cc)::value>(dc, td, qcol); });
+    const Rows32<D> nq(q, i0, n_rows, Hq, head), no(dO, i0, n_rows, Hq, head);
+    auto next = [&](auto ic) {
+      constexpr int i = decltype(ic)::value + R;
+      if constexpr (i < kSlots) load(IC<i>{}, tq, td); else load(IC<i - kSlots>{}, nq, no);
+    };
+    row_products<D, R, 0>(s, ring, sh.own[0], lane, next);
+    row_products<D, R, kRows>(dp, ring, sh.own[1], lane, next);
     s = mfma_f32(c_nl, -one * kLog2e, s);                        // the statistics last: added to the small accumulators they would
     dp = mfma_f32(c_nd, -one, dp);                               // cost every later addition its low bits
     const bool masked = c_i0 < k0 + kSub - 1 || c_rows < kSub;   // rows before the lane's key or past the end of the run
@@ -405,32 +475,28 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void dkdv_f32_kernel(
       s[r] = p;
       dp[r] *= p;
     }
-    col_products<D>(dv, dc, s, [&](auto rc) { constexpr int r = decltype(rc)::value; qc.x[r] = load_col<D>(tq, qcol, r); });
-    col_products<D>(dk, qc, dp, [&](auto rc) { rows_by_reg<D, decltype(rc)::value>(qr, tn, qrow); });
+    col_products<D, R, 2 * kRows>(dv, ring, s, next);
+    col_products<D, R, 2 * kRows + 16>(dk, ring, dp, next);
   }
   // the waves' sums in wave order; an earlier unit's partial sum of a row is added (rows below load_until); rows no later
   // unit reaches (from final_from on) are written as dK/dV, the others into the accumulators
-#pragma unroll
-  for (int which = 0; which < 2; ++which) {
-    if (which) __syncthreads();
-    put_partial<D>(part[wave], which ? dv : dk, l32, half);
-    __syncthreads();
-    const int row = k0 + (tid >> 3);
-    if (row < k_end) {
+  static_for<0, 2>([&](auto wc) {
+    constexpr int which = decltype(wc)::value;
+    meet<D>(sh.part, which ? dv : dk, wave, l32, half, [&](int r, int dim, int c) {
+      const int row = k0 + r;
+      if (row >= k_end) return;
       const bool load_acc = row < it.load_until, store_final = row >= it.final_from && part_no == 0;
-      const size_t at = ((size_t)row * Hkv + hk) * D;
+      const size_t at = ((size_t)row * Hkv + hk) * D + dim;
       const float* in = (which ? acc_dv : acc_dk) + at;
       float* out = (which ? (store_final ? dV : acc_dv) : (store_final ? dK : acc_dk)) + at;
-      for (int c = (tid & 7) * 4; c < D; c += 32) {
-        floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+      floatx4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int x = 0; x < kWaves; ++x) sum += *reinterpret_cast<const floatx4*>(&part[x][tid >> 3][c]);
-        if (!which) sum *= scale;
-        if (load_acc) sum += *reinterpret_cast<const floatx4*>(in + c);
-        *reinterpret_cast<floatx4*>(out + c) = sum;
-      }
-    }
-  }
+      for (int x = 0; x < kWaves; ++x) sum += *reinterpret_cast<const floatx4*>(&sh.part.x[x][r][c]);
+      if (!which) sum *= scale;
+      if (load_acc) sum += *reinterpret_cast<const floatx4*>(in);
+      *reinterpret_cast<floatx4*>(out) = sum;
+    });
+  });
 }
 
 // dK += acc_dk, dV += acc_dv: the second part of a divided whole-list dK/dV launch.
@@ -483,14 +549,16 @@ int launch_bwd_dkdv_f32(const LaunchCtx& c, const float* q, const float* k, cons
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
   const int64_t blocks = 2 * (int64_t)n_items * p.n_kv_heads;
-  // Few long walks (up to three rounds of the chip's compute units): the first tiles of the longest sample decide the
-  // launch, so every walk is divided in two (the pack above: 634 -> 381 us with the addition).  A wave's longest walk has
-  // to be worth the second launch (about 7 us): from 16 steps on (a step is 4 to 8 us at head dims 64 to 128).
-  const int parts = longest * (p.n_q_heads / p.n_kv_heads) >= 16 * kSub * kWaves && blocks <= 768 ? 2 : 1;
+  // Few blocks: the first tiles of the longest sample decide the launch, so every walk is divided in two where that is worth
+  // the second launch (about 5 us; a step is 3 to 7 us at head dims 64 to 128).  While both parts of all blocks have a place on the chip
+  // at once, from two steps of a wave on: 876 rows, 2/2 heads of 64, 4 steps 23.0 -> 17.3 us, of 128, 38.7 -> 27.1; 1000 rows, 8/2 heads of 128, 16 steps
+  // 127.9 -> 71.8.  With more blocks the longest walk has to stand out more: 280 blocks, 9 steps 103 -> 78, 2 steps 41 -> 45; 560 blocks, 9 steps 65 -> 81.
+  const int64_t steps = (int64_t)longest * (p.n_q_heads / p.n_kv_heads) / (kSub * kWaves);
+  const int parts = blocks <= 256 ? (steps >= 2 ? 2 : 1) : blocks <= 768 && 48 * steps >= blocks ? 2 : 1;
   const int e = in_runs(n_items, 2 * (int64_t)p.n_kv_heads, [&](int first, int n) -> int {
-    const dim3 grid((unsigned)(2 * n * p.n_kv_heads), parts), block(64 * kWaves);
+    const dim3 grid((unsigned)(2 * n * p.n_kv_heads * parts)), block(64 * kWaves);
     DISPATCH_D(p.head_dim, hipLaunchKernelGGL(dkdv_f32_kernel<D>, grid, block, 0, (hipStream_t)c.stream, q, k, v, dO, lse, delta,
-                                              acc_dk, acc_dv, dK, dV, items + first, segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale));
+                                              acc_dk, acc_dv, dK, dV, items + first, segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts));
     return (int)hipGetLastError();
   });
   if (e != 0) return e;

@@ -222,7 +222,7 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   // bf16 path: -lse*log2e and -delta as bf16 triples, 16 bytes per row and head (written by the dQ kernel, read by the dK/dV kernel)
   void* stat3 = (char*)delta + align_up(T * p->n_q_heads * sizeof(float));
   float* parts = (float*)((char*)stat3 + align_up(T * p->n_q_heads * 16));              // partial tiles of divided key tiles
-  const int sc = split_class(p->n_kv_heads);
+  const int sc = dkdv_class(t, p->n_q_heads, p->n_kv_heads, p->head_dim);
   const int64_t head_blocks = head_part_blocks(t, p->n_q_heads, p->n_kv_heads, p->head_dim);
   const int n_units = t->n_units[1];
   const bool whole = lo == 0 && hi == n_units;
@@ -258,9 +258,7 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
     return timed(SLIMATTN_K_DKDV, stream, [&] {
       return f32 ? launch_bwd_dkdv_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (const float*)dO, lse,
                                        delta, acc_dk, acc_dv, (float*)dK, (float*)dV, items, n, segs, whole && !per_unit ? t->max_sample_len : 0)
-             : p->head_dim == 64
-                 ? launch_bwd_dkdv_d64_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp)
-             : short_walks
+             : p->head_dim == 64 || short_walks
                  ? launch_bwd_dkdv_pair_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp)
                  : launch_bwd_dkdv_wide_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp);
     });

@@ -1,5 +1,5 @@
-// dK/dV for bf16 inputs at head dim 128 where the walks are short (short_walks in internal.h): 128 key rows per block, two blocks per
-// compute unit, 32 key rows per wave.
+// dK/dV for bf16 inputs: 128 key rows per block, 32 per wave, two blocks per compute unit at head dim 128, three at 64.  Head dim 64, and 128
+// where the walks are short (short_walks in internal.h).
 //
 // What it computes is the dK/dV step of the backward (see bwd_bf16.hip), with the work items, the walk and the output paths of
 // dkdv_wide_bf16.hip: a block owns key rows of one KV head and walks every query row of the launch scope at or after
@@ -8,15 +8,20 @@
 //
 // Why beside the one-wave kernel.  That one holds a compute unit to itself, so what an item costs beside its steps (its first loads
 // and its last stores, 22 us: all compute units do them at about the same time, at the rate of the memory) is hidden by nothing.
-// Two blocks of half the keys overlap each other, steps before a wave's keys are skipped, and a sample that ends in a
-// tile's first half wastes half as much.  A step costs more: one product per LDS fragment (1.25 KB of LDS reads per product), and a
+// Blocks of half the keys overlap each other, steps before a wave's keys are skipped, and a sample that ends in a
+// tile's first half wastes half as much.  At 128 a step costs more: one product per LDS fragment (1.25 KB of LDS reads per product), and a
 // wave alone takes 2500 cycles for a step of 34 products (1088), two on a SIMD 3400 for both.
-// Measured, 16K tokens, one-wave kernel / this one, us: 32/32 heads, samples of 64 rows 426 / 157, 256 rows 235 / 164, 512 rows 297 / 213, 1024 rows
-// 398 / 330, 4096 rows 1003 / 1010; 32/8 heads, 256 rows 151 / 125, 512 rows 207 / 188, 1024 rows 304 / 288, 4096 rows 891 / 1007; 876 rows of
-// 8/1 heads 39 / 28.  (Raised priority for the element-wise work, as at head dim 64: 2 to 5 % slower here.  The next step's bookkeeping
+// Measured at 128, 16K tokens, one-wave kernel / this one, us: 32/32 heads, samples of 64 rows 426 / 157, 256 rows 235 / 164, 512 rows 297 / 213, 1024
+// rows 398 / 322, 4096 rows 1003 / 1010; 32/8 heads, 128 rows 158 / 117, 512 rows 207 / 176, 1024 rows 304 / 288, 4096 rows 891 / 1007; 876 rows of
+// 8/1 heads 39 / 28.  (Raised priority for the element-wise work: 2 to 5 % slower.  The next step's bookkeeping
 // behind its first LDS reads, the second half of the element-wise work behind the first gradient products: no gain.)
+// At 64 a score costs the same exponential, product and packing as at 128 but half the matrix work, and a step is mostly latency: what counts
+// are waves.  Against 256 keys in 8 waves, two per SIMD, K and V in registers: 16K tokens, 32/8 heads, samples of 128 rows 78 / 63, 2048 rows 305 /
+// 287, one sample 2021 / 2046; 32/32 heads, 1024 rows 200 / 162, 4096 rows 601 / 524; a 32K pack of 10 samples, 32/8 heads, 3148 / 2783.  (V in registers
+// takes 7 more than the 168 three blocks leave: 340 us at 2048 rows.)
 //
-// Registers: 254 of 256.  The accumulators take 128, K fragments 32; V rows are in LDS, and a tile's fragment addresses are formed from one.
+// Registers: 254 of 256 at 128, 166 of 168 at 64.  The accumulators take D, K fragments D / 4; V rows are in LDS, and a tile's fragment
+// addresses are formed from one.
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -25,18 +30,20 @@
 namespace slimattn {
 namespace {
 
-constexpr int D = 128;
 constexpr int kWaves = 4, kKeys = 32 * kWaves;          // key rows per block
 constexpr int kQStep = 32;
-constexpr int kNKS = D / 16, kNDB = D / 32, kRowBytes = D * 2;
-constexpr int kTileBytes = kQStep * kRowBytes;          // one Q or dO tile
-constexpr int kStageBytes = 2 * kTileBytes;             // Q tile, dO tile of a step
-constexpr int kVBase = 2 * kStageBytes;                 // two stages, then the block's V rows
-constexpr int kVBytes = kKeys * kRowBytes;
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct Step { int i0, hi, head; };                      // rows [i0, min(i0 + 32, hi)) of one query head
 struct QdV { bf16x8 q, d, v; };
+
+// The items are heavy-first, and two or three blocks share a compute unit from the start.  The second round of 256 blocks (what there is of
+// it) runs backwards, so that the longest walks share theirs with the shortest of the round: one 16K sample of 32/8 heads at 128 3887 -> 3728
+// us, 128-row samples 124 -> 117; 32K pack at 64 2925 -> 2783.  (The low three bits, the XCD, stay.)
+__device__ __forceinline__ int paired_block(int block) {
+  const int end = min((int)gridDim.x, 512) & ~7;
+  return block >= 256 && block < end ? 256 + end - 8 - (block & ~7) + (block & 7) : block;
+}
 
 // The fragment addresses of a tile differ from the first one's in the swizzled unit alone, by an exclusive or with the unit's number
 // (tiles are 256-byte aligned): formed at each use, one register in the place of eight.
@@ -48,16 +55,22 @@ __device__ __forceinline__ lds_cptr lds_xor(lds_cptr p) {
   return (lds_cptr)(size_t)x;
 }
 
-__global__ __launch_bounds__(64 * kWaves, 2) void dkdv_pair_bf16_kernel_d128(
+template <int D>
+__global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_kernel(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ dO,
     const bf16x8* __restrict__ stat3, float* __restrict__ acc_dk, float* __restrict__ acc_dv, bf16* __restrict__ dK,
     bf16* __restrict__ dV, const KvItem* __restrict__ items, int n_items, const Seg* __restrict__ segs, int T, int Hq, int Hkv,
     float scale, float* __restrict__ parts, int head_parts) {
-  __shared__ __attribute__((aligned(1024))) char smem[kVBase + kVBytes];
+  constexpr int kNKS = D / 16, kNDB = D / 32, kRowBytes = D * 2;
+  constexpr int kTileBytes = kQStep * kRowBytes;        // one Q or dO tile
+  constexpr int kStageBytes = 2 * kTileBytes;           // Q tile, dO tile of a step
+  constexpr int kVBase = 2 * kStageBytes;               // two stages, then the block's V rows
+  constexpr int kLoop = kVBase + kKeys * kRowBytes, kOut = kWaves * kOutAreaBytes<D>;
+  __shared__ __attribute__((aligned(1024))) char smem[kLoop > kOut ? kLoop : kOut];
 
   const int g = Hq / Hkv;
   // the halves of a 256-row item are blocks of their own, next to each other with the item's heads in between
-  int b = blockIdx.x;
+  int b = paired_block(blockIdx.x);
   const int hk = b % Hkv;
   b /= Hkv;
   const int hpart = b % head_parts;
@@ -153,7 +166,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void dkdv_pair_bf16_kernel_d128(
     if (min(d.i0 + kQStep, d.hi) <= kv0w || kv0w >= kv_end) return;
     floatx16 s = mfma32(st3, ones_l, zeros), dp = mfma32(st3, ones_d, zeros);
     {
-      constexpr int kPre = 2;
+      constexpr int kPre = D == 128 ? 2 : 1;            // head-dim steps read ahead (registers)
       QdV f[kNKS];
       auto load = [&](auto ic) {
         constexpr int i = decltype(ic)::value;
@@ -180,9 +193,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void dkdv_pair_bf16_kernel_d128(
         if (c < rel_lo || c >= rel_hi) s[r] = -INFINITY;
       }
     }
-    Tr4 tb[4];
+    constexpr int kPairs = kNDB / 2;                    // of head-dim blocks
+    Tr4 tb[2 * kPairs];
     auto issue = [&](auto ec) {
-      constexpr int e = decltype(ec)::value, off = at + (e >> 1) * 16 * kRowBytes, db0 = 2 * (e & 1);
+      constexpr int e = decltype(ec)::value, off = at + e / kPairs * 16 * kRowBytes, db0 = 2 * (e % kPairs);
       static_for<0, 2>([&](auto dc) {
         constexpr int x = decltype(dc)::value;
         const lds_cptr p0 = lds_xor<64 * (db0 + x)>(pqt[0]), p1 = lds_xor<64 * (db0 + x)>(pqt[1]);
@@ -202,14 +216,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void dkdv_pair_bf16_kernel_d128(
     }
 #pragma unroll
     for (int e = 0; e < 2; ++e) { pf[e] = pack8(s, 8 * e); ds[e] = pack8(dp, 8 * e); }
-    static_for<0, 4>([&](auto ec) {
-      constexpr int e = decltype(ec)::value, db0 = 2 * (e & 1);
-      if constexpr (e < 3) issue(IC<e + 1>{});
-      tr4_wait_n<e < 3 ? 8 : 0>(tb[e]);
+    static_for<0, 2 * kPairs>([&](auto ec) {
+      constexpr int e = decltype(ec)::value, db0 = 2 * (e % kPairs);
+      constexpr bool last = e + 1 == 2 * kPairs;
+      if constexpr (!last) issue(IC<e + 1>{});
+      tr4_wait_n<last ? 0 : 8>(tb[e]);
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
-        dv[db0 + x] = mfma32(tr4_frag(tb[e], x), pf[e >> 1], dv[db0 + x]);
-        dk[db0 + x] = mfma32(tr4_frag(tb[e], 2 + x), ds[e >> 1], dk[db0 + x]);
+        dv[db0 + x] = mfma32(tr4_frag(tb[e], x), pf[e / kPairs], dv[db0 + x]);
+        dk[db0 + x] = mfma32(tr4_frag(tb[e], 2 + x), ds[e / kPairs], dk[db0 + x]);
       }
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -254,8 +269,8 @@ int launch_bwd_dkdv_pair_bf16(const LaunchCtx& c, const void* q, const void* k, 
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
   return in_runs(n_items, 2 * (int64_t)p.n_kv_heads * head_parts, [&](int first, int n) {
-    hipLaunchKernelGGL(dkdv_pair_bf16_kernel_d128, dim3((unsigned)(2 * n * p.n_kv_heads * head_parts)), dim3(64 * kWaves), 0, (hipStream_t)c.stream,
-                       (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv,
+    hipLaunchKernelGGL(p.head_dim == 128 ? dkdv_pair_bf16_kernel<128> : dkdv_pair_bf16_kernel<64>, dim3((unsigned)(2 * n * p.n_kv_heads * head_parts)),
+                       dim3(64 * kWaves), 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv,
                        (bf16*)dK, (bf16*)dV, items + first, n, segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, head_parts);
     return (int)hipGetLastError();
   });

@@ -47,23 +47,27 @@ struct KvItem { int32_t kv_row0, kv_rows, seg_begin, seg_end, slot, load_until, 
 // A divided key tile: partial tiles first_slot .. first_slot + n_parts - 1 are its parts.
 struct KvReduce { int32_t kv_row0, kv_rows, first_slot, n_parts, load_until, final_from, pad0, pad1; };
 
-// Divided lists exist for the 256-row key tile (the bf16 dK/dV kernel) and six classes
-// of KV-head count (1, 2, 4, 8, 16, >= 32): a launch has items x KV heads blocks, so the fewer KV heads, the
+// Divided lists exist for the 256-row key tile (the bf16 dK/dV kernels) and seven classes
+// of KV-head count (a half, 1, 2, 4, 8, 16, >= 32): a launch has items x KV heads blocks, so the fewer KV heads, the
 // fewer blocks share the work and the more a single long sample's first tiles dominate the makespan.
 constexpr int kNumSplitTiles = 1;                               // key-tile sizes for which divided lists are built
-constexpr int kSplitTileRows[kNumSplitTiles] = {256};           // the bf16 dK/dV kernel's tile
-// Slots the per-slot share of the work is taken over: 3/4 of the kernel's 256 resident blocks (measured: a
+constexpr int kSplitTileRows[kNumSplitTiles] = {256};           // the bf16 dK/dV kernels' item
+// Slots the per-slot share of the work is taken over: 3/4 of the one-wave kernel's 256 resident blocks (measured: a
 // part costs a V tile, K fragments and an fp32 partial tile to set up, and dividing more finely lost 1-4 %).
 constexpr int kSplitBlockSlots[kNumSplitTiles] = {192};
 inline int split_tile_index(int rows) { return rows == 256 ? 0 : -1; }
-constexpr int kNumSplitClasses = 6;
+constexpr int kNumSplitClasses = 7;
 // (The share of a class is taken over its lower end; with 8 as the last one a launch on 32 KV heads was divided four times too
 // finely: 10567-token pack, 32/32 heads, dK/dV 499 + reduction 79 us against 458.)
 inline int split_class(int n_kv_heads) {
-  int c = 0;
-  while (c + 1 < kNumSplitClasses && (2 << c) <= n_kv_heads) ++c;
+  int c = 1;
+  while (c + 1 < kNumSplitClasses && (1 << c) <= n_kv_heads) ++c;
   return c;
 }
+// The class of a launch.  At head dim 64 six half items share a compute unit, and few KV heads leave little beside the divided tiles to even the
+// parts out: 1 to 3 of them take the class below (one 32K sample of 8/1 heads 2329 -> 2153 us, a 32K pack of long ones 489 -> 466), unless
+// its partial tiles alone would lift the workspace above the built-in scratch array's size.  (From 4 on no gain: 32K pack of 32/8 heads 2783 -> 2818.)
+int dkdv_class(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d);
 
 // Blocks of a dK/dV launch that share one item by query heads: a launch of few items (one small unit, a small pack, few KV
 // heads) leaves most compute units idle while each of its blocks walks the item's rows once per head of the group.  Every
@@ -234,14 +238,10 @@ int launch_bwd_dq_bf16(const LaunchCtx&, const void* q, const void* k, const voi
 int launch_bwd_dkdv_wide_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
                             float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
                             float* parts, int head_parts);
-// head_dim 128, short walks: two blocks of 128 key rows per compute unit (dkdv_pair_bf16.hip); same arguments
+// head_dim 64, and 128 with short walks: two or three blocks of 128 key rows per compute unit (dkdv_pair_bf16.hip); same arguments
 int launch_bwd_dkdv_pair_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
                               float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
                               float* parts, int head_parts);
-// head_dim 64: two waves per SIMD (dkdv_d64_bf16.hip); same arguments
-int launch_bwd_dkdv_d64_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
-                             float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
-                             float* parts, int head_parts);
 // adds up the partial tiles (tile_rows rows each) of divided key tiles, in slot order, into dK/dV or the
 // fp32 accumulators; per_slot: partial tiles per slot (the blocks that share an item by query heads)
 int launch_bwd_reduce_bf16(const LaunchCtx&, const float* parts, float* acc_dk, float* acc_dv, void* dK, void* dV,

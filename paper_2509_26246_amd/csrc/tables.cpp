@@ -81,11 +81,10 @@ void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const st
       L.longest[ti][c].push_back(L.longest[ti][c - 1].back());
       continue;
     }
-    const int64_t heads = int64_t(1) << c;
     // A tile is divided when it exceeds three quarters of the per-slot share (below that, the
     // heavy-first dispatch already hides it), into parts of about half a share: the divided tiles
     // then no longer decide the makespan.
-    const int64_t share = total * heads / kBlockSlots;
+    const int64_t share = total * (int64_t(1) << c) / (2 * kBlockSlots);
     const int64_t target = std::max(kMinPartRows, (share / 2 + 127) / 128 * 128);
     std::vector<KvItem>& items = tmp.items;
     std::vector<int64_t>& w = tmp.w;
@@ -218,16 +217,21 @@ size_t fixed_bytes(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d)
   const size_t T = (size_t)t->total_tokens;
   return align_up(2 * T * hkv * d * sizeof(float)) + align_up(T * hq * sizeof(float)) + align_up(T * hq * 16) + 256;
 }
-size_t row_slots(const slimattn_tables* t, int32_t hkv) {
-  const int c = split_class(hkv);
-  return (size_t)std::max(t->per_unit[1].max_slots[0][c], t->fused.max_slots[0][c]);
-}
+size_t row_slots(const slimattn_tables* t, int c) { return (size_t)std::max(t->per_unit[1].max_slots[0][c], t->fused.max_slots[0][c]); }
 size_t tile_bytes(int32_t d) { return (size_t)2 * kSplitTileRows[0] * d * sizeof(float); }
 }  // namespace
 
+int dkdv_class(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d) {
+  const int c = split_class(hkv);
+  if (d != 64 || hkv > 3) return c;
+  const size_t room = SLIMATTN_STATIC_SCRATCH_BYTES, fixed = fixed_bytes(t, hq, hkv, d);
+  auto fits = [&](int x) { return fixed + align_up(row_slots(t, x) * hkv * tile_bytes(d)) <= room; };
+  return fits(c - 1) || !fits(c) ? c - 1 : c;
+}
+
 int64_t head_part_blocks(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d) {
   const size_t room = SLIMATTN_STATIC_SCRATCH_BYTES, fixed = fixed_bytes(t, hq, hkv, d);
-  if (fixed + align_up(row_slots(t, hkv) * hkv * tile_bytes(d)) > room) return kHeadPartBlocks;
+  if (fixed + align_up(row_slots(t, dkdv_class(t, hq, hkv, d)) * hkv * tile_bytes(d)) > room) return kHeadPartBlocks;
   return std::min<int64_t>(kHeadPartBlocks, (int64_t)((room - fixed - 256) / tile_bytes(d)));
 }
 
@@ -393,7 +397,7 @@ int64_t slimattn_tables_count(const slimattn_tables* t, int what) {
     case 2: return t->n_slices;
     case 3: return t->n_units[0];
     case 4: return t->n_units[1];
-    case 5: case 6: case 7: case 8: return (int64_t)t->fused.reduce_items[0][what - 5].size();
+    case 5: case 6: case 7: case 8: return (int64_t)t->fused.reduce_items[0][what - 4].size();
     default: return -1;
   }
 }
@@ -424,9 +428,9 @@ int slimattn_bwd_released_rows(const slimattn_tables* t, int32_t unit, int32_t* 
 
 size_t slimattn_bwd_workspace_bytes(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d) {
   if (!t || hq < 1 || hkv < 1 || d < 1) return 0;
-  const int c = split_class(hkv);
+  const int c = dkdv_class(t, hq, hkv, d);
   const int64_t max_blocks = head_part_blocks(t, hq, hkv, d);
-  size_t slots = row_slots(t, hkv);
+  size_t slots = row_slots(t, c);
   for (const ScopeLists* L : {&t->per_unit[1], &t->fused})
     for (size_t u = 0; u < L->longest[0][c].size(); ++u) {
       const int n = L->split_rng[0][c][u].end - L->split_rng[0][c][u].begin;

@@ -160,23 +160,23 @@ __device__ __forceinline__ void dq_tile(const lds_cptr (&pk)[D / 16], const lds_
 }
 
 template <int D, bool OWN_STATS>
-__global__ __launch_bounds__(256, 2) void dq_bf16_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k,
+__global__ __launch_bounds__(256, D == 128 ? 2 : 3) void dq_bf16_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k,
                                                          const bf16* __restrict__ v, const bf16* __restrict__ dO,
                                                          const bf16* __restrict__ o, const float* __restrict__ lse,
                                                          bf16x8* __restrict__ stat3, bf16* __restrict__ dQ,
-                                                         const QItem* __restrict__ items, int n_items,
+                                                         const QItem* __restrict__ items, QBlocks n_items,
                                                          int T, int Hq, int Hkv, float scale) {
   constexpr int NKS = D / 16, NDB = D / 32;
   constexpr int kTileBytes = kDqBK * D * 2, kBufBytes = 2 * kTileBytes;
   __shared__ __attribute__((aligned(1024))) char smem[2 * kBufBytes];   // [buffer][K tile, V tile]
 
   const int g = Hq / Hkv;
-  int item_idx, hk, hg;
-  if (!map_block(blockIdx.x, g, Hkv, n_items, &item_idx, &hk, &hg)) return;
-  const int h = hk * g + hg;
+  int item_idx, hk, hg, share;
+  if (!map_shared_block(blockIdx.x, g, Hkv, n_items, &item_idx, &hk, &hg, &share)) return;
   const QItem it = items[item_idx];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-  const int q0w = it.q_row0 + 32 * wave, my_row = q0w + l32, q_end = it.q_row0 + it.q_rows;
+  const int h = __builtin_amdgcn_readfirstlane(hk * g + hg + (wave >> (2 - share)));
+  const int q0w = it.q_row0 + 32 * (wave & (3 >> share)), my_row = q0w + l32, q_end = it.q_row0 + it.q_rows;
   const int ld_row = min(my_row, T - 1);
   LDS_PTR(char) lds = (LDS_PTR(char))smem;
   const TileSource srcK = make_tile_source<D, 256>(k, it.kv_start, Hkv, hk, q_end, tid);
@@ -342,7 +342,7 @@ int launch_bwd_stat_bf16(const LaunchCtx& c, const void* o, const void* dO, cons
 namespace {
 template <int D, bool OWN>
 void launch_dq(const LaunchCtx& c, dim3 grid, dim3 block, const void* q, const void* k, const void* v, const void* dO, const void* o,
-               const float* lse, void* stat3, void* dQ, const QItem* items, int n_items) {
+               const float* lse, void* stat3, void* dQ, const QItem* items, const QBlocks& n_items) {
   const slimattn_params& p = *c.p;
   hipLaunchKernelGGL((dq_bf16_kernel<D, OWN>), grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
                      (const bf16*)v, (const bf16*)dO, (const bf16*)o, lse, (bf16x8*)stat3, (bf16*)dQ, items, n_items, (int)c.T,
@@ -351,11 +351,12 @@ void launch_dq(const LaunchCtx& c, dim3 grid, dim3 block, const void* q, const v
 }  // namespace
 
 int launch_bwd_dq_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, const void* dO, const void* o,
-                       const float* lse, void* stat3, int own_stats, void* dQ, const QItem* items, int n_items) {
-  if (n_items == 0) return 0;
+                       const float* lse, void* stat3, int own_stats, void* dQ, const QItem* items, const QGroups& groups) {
+  if (groups.total() == 0) return 0;
   const slimattn_params& p = *c.p;
   const int g = p.n_q_heads / p.n_kv_heads;
-  const dim3 grid(mapped_grid(n_items, p.n_kv_heads, g)), block(256);
+  const QBlocks n_items = shared_blocks(groups, p.n_kv_heads, g);
+  const dim3 grid((unsigned)n_items.end[2]), block(256);
   if (p.head_dim == 128) {
     if (own_stats) launch_dq<128, true>(c, grid, block, q, k, v, dO, o, lse, stat3, dQ, items, n_items);
     else launch_dq<128, false>(c, grid, block, q, k, v, dO, o, lse, stat3, dQ, items, n_items);

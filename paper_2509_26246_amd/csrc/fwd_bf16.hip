@@ -127,18 +127,17 @@ __device__ __forceinline__ void fwd_tile(const lds_cptr (&pk)[D / 16], const lds
   }
 }
 
-// The walk of one block: rows q_row0 .. q_end - 1 of head h (at most 128) over n_tiles key tiles from kv_start on, up to row q_end - 1.
+// The walk of one wave: rows q0w .. min(q0w + 32, q_end) - 1 of head h, over n_tiles key tiles from kv_start on, up to row q_end - 1.
 // first_key: of the sample.  Leaves O^T, the reference (log2 units) and the row sum of this thread's row; all of the block's
 // threads are behind a barrier and done with the LDS.
 template <int D, bool EXACT>
 __device__ __forceinline__ void fwd_walk(LDS_PTR(char) lds, const bf16* __restrict__ q, const bf16* __restrict__ k,
-                                         const bf16* __restrict__ v, int q_row0, int q_end, int first_key, int kv_start, int n_tiles,
+                                         const bf16* __restrict__ v, int q0w, int q_end, int first_key, int kv_start, int n_tiles,
                                          int h, int hk, int Hq, int Hkv, float scale, floatx16 (&oacc)[D / 32], float& m_ref, float& l_tot) {
   constexpr int NKS = D / 16;   // contraction steps over the head dimension
   constexpr int NDB = D / 32;   // 32-wide blocks of the head dimension
   constexpr int kTileBytes = kFwdBK * D * 2, kBufBytes = 2 * kTileBytes;   // LDS: [buffer][K tile, V tile]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-  const int q0w = q_row0 + 32 * wave;             // first query row of this wave
+  const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int my_row = q0w + l32;                   // the query row this lane owns
 
   const TileSource srcK = make_tile_source<D, 256>(k, kv_start, Hkv, hk, q_end, tid);
@@ -224,11 +223,11 @@ __device__ __forceinline__ void fwd_walk(LDS_PTR(char) lds, const bf16* __restri
   l_tot = l_run + xor32(l_run);
 }
 
-// Rows of the block out: O = O^T / l through LDS, lse.
+// Rows of the wave out: O = O^T / l through LDS, lse.
 template <int D>
 __device__ __forceinline__ void fwd_out(LDS_PTR(char) lds, const floatx16 (&oacc)[D / 32], float m_ref, float l_tot, bf16* __restrict__ o,
-                                        float* __restrict__ lse, int q_row0, int q_end, int h, int T, int Hq) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q0w = q_row0 + 32 * wave, my_row = q0w + (lane & 31);
+                                        float* __restrict__ lse, int q0w, int q_end, int h, int T, int Hq) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, my_row = q0w + (lane & 31);
   // (the tile buffers are free behind the walk's last barrier; each wave uses a part of its own)
   static_assert(4 * kOutAreaBytes<D> <= kFwdLdsBytes<D>, "the transposition areas must fit the tile buffers");
   store_rows<D>(lds + __builtin_amdgcn_readfirstlane(wave) * kOutAreaBytes<D>, oacc, 1.f / l_tot, o, Hq, h, q0w, q_end, lane);
@@ -239,18 +238,19 @@ template <int D, bool EXACT>
 __global__ __launch_bounds__(256, 2) void fwd_bf16_kernel(const bf16* __restrict__ q, const bf16* __restrict__ k,
                                                           const bf16* __restrict__ v, bf16* __restrict__ o,
                                                           float* __restrict__ lse, const QItem* __restrict__ items,
-                                                          int n_items, int T, int Hq, int Hkv, float scale) {
+                                                          QBlocks n_items, int T, int Hq, int Hkv, float scale) {
   __shared__ __attribute__((aligned(1024))) char smem[kFwdLdsBytes<D>];
   const int g = Hq / Hkv;
-  int item_idx, hk, hg;
-  if (!map_block(blockIdx.x, g, Hkv, n_items, &item_idx, &hk, &hg)) return;
+  int item_idx, hk, hg, share;
+  if (!map_shared_block(blockIdx.x, g, Hkv, n_items, &item_idx, &hk, &hg, &share)) return;
   const QItem it = items[item_idx];
-  const int q_end = it.q_row0 + it.q_rows;
+  const int wave = threadIdx.x >> 6, h = __builtin_amdgcn_readfirstlane(hk * g + hg + (wave >> (2 - share)));
+  const int q0w = it.q_row0 + 32 * (wave & (3 >> share)), q_end = it.q_row0 + it.q_rows;
   floatx16 oacc[D / 32];
   float m, l;
-  fwd_walk<D, EXACT>((LDS_PTR(char))smem, q, k, v, it.q_row0, q_end, it.kv_start, it.kv_start,
-                     (q_end - it.kv_start + kFwdBK - 1) / kFwdBK, hk * g + hg, hk, Hq, Hkv, scale, oacc, m, l);
-  fwd_out<D>((LDS_PTR(char))smem, oacc, m, l, o, lse, it.q_row0, q_end, hk * g + hg, T, Hq);
+  fwd_walk<D, EXACT>((LDS_PTR(char))smem, q, k, v, q0w, q_end, it.kv_start, it.kv_start,
+                     (q_end - it.kv_start + kFwdBK - 1) / kFwdBK, h, hk, Hq, Hkv, scale, oacc, m, l);
+  fwd_out<D>((LDS_PTR(char))smem, oacc, m, l, o, lse, q0w, q_end, h, T, Hq);
 }
 
 // The launch whose items' keys are divided: one block per (item, head, part), parts innermost, so that an XCD keeps to the same runs
@@ -269,14 +269,14 @@ __global__ __launch_bounds__(256, 2) void fwd_bf16_split_kernel(const bf16* __re
   if (part >= n) return;
   const int region = n > 1 ? split_region(sp) : 0;
   if (region < 0) return;                         // the finishing kernel walks the parts
-  const int n_tiles = split_range(it, part, n);
+  const int n_tiles = split_range(it, part, n), q0w = it.q_row0 + 32 * (int)(threadIdx.x >> 6);
   floatx16 oacc[D / 32];
   float m, l;
-  fwd_walk<D, EXACT>((LDS_PTR(char))smem, q, k, v, it.q_row0, q_end, first_key, it.kv_start, n_tiles, h, hk, Hq, Hkv, scale, oacc, m, l);
+  fwd_walk<D, EXACT>((LDS_PTR(char))smem, q, k, v, q0w, q_end, first_key, it.kv_start, n_tiles, h, hk, Hq, Hkv, scale, oacc, m, l);
   if (n > 1)
     split_store<D>(split_unit<D>(sp, region, (item_idx * sp.parts + part) * Hq + h), threadIdx.x >> 6, threadIdx.x & 63, oacc, m, l);
   else
-    fwd_out<D>((LDS_PTR(char))smem, oacc, m, l, o, lse, it.q_row0, q_end, h, T, Hq);
+    fwd_out<D>((LDS_PTR(char))smem, oacc, m, l, o, lse, q0w, q_end, h, T, Hq);
 }
 
 // Adds the parts up, grid (items, heads, head-dim blocks).  Without a region the blocks of the first head-dim block walk them, with the
@@ -292,7 +292,7 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void fwd_bf16_finish_kernel(
   if (n > 1 && region >= 0) {
     split_combine<D>(sp, region, n, it, o, lse, T, Hq);
   } else if (n > 1 && blockIdx.z == 0) {
-    const int h = blockIdx.y, q_end = it.q_row0 + it.q_rows;
+    const int h = blockIdx.y, q_end = it.q_row0 + it.q_rows, q0w = it.q_row0 + 32 * (int)(threadIdx.x >> 6);
     LDS_PTR(floatx4) sum = (LDS_PTR(floatx4))(smem + kFwdLdsBytes<D>) + threadIdx.x;     // D / 8 vectors of a row, 256 apart
     floatx16 oacc[D / 32];
     float m = 0.f, l = 0.f;
@@ -300,7 +300,7 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void fwd_bf16_finish_kernel(
       QItem run = it;
       const int n_tiles = split_range(run, part, n);
       float mp, lp;
-      fwd_walk<D, EXACT>((LDS_PTR(char))smem, q, k, v, it.q_row0, q_end, it.kv_start, run.kv_start, n_tiles, h, h / (Hq / Hkv), Hq, Hkv,
+      fwd_walk<D, EXACT>((LDS_PTR(char))smem, q, k, v, q0w, q_end, it.kv_start, run.kv_start, n_tiles, h, h / (Hq / Hkv), Hq, Hkv,
                          scale, oacc, mp, lp);
       const bool first = part == 0;
       if (first) m = mp;
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void fwd_bf16_finish_kernel(
           sum[(db * 4 + gq) * 256] = x;
         }
     }
-    fwd_out<D>((LDS_PTR(char))smem, oacc, m, l, o, lse, it.q_row0, q_end, h, T, Hq);
+    fwd_out<D>((LDS_PTR(char))smem, oacc, m, l, o, lse, q0w, q_end, h, T, Hq);
   }
   split_release(sp, region);
 }
@@ -328,8 +328,9 @@ int fwd_q_tile(int dtype, int) { return dtype == SLIMATTN_F32 ? 64 : kFwdBQ; }
 namespace {
 template <int D, bool EXACT>
 int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse, const QItem* items,
-                        int n_items, const FwdSplit& sp) {
+                        const QGroups& groups, const FwdSplit& sp) {
   const slimattn_params& p = *c.p;
+  const int g = p.n_q_heads / p.n_kv_heads, n_items = groups.total();
   const dim3 block(256);
   if (sp.parts > 1) {
     hipLaunchKernelGGL((fwd_bf16_split_kernel<D, EXACT>), dim3((unsigned)(n_items * p.n_q_heads * sp.parts)), block, 0, (hipStream_t)c.stream,
@@ -342,8 +343,9 @@ int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const 
     return (int)hipGetLastError();
   }
   return in_runs(n_items, p.n_q_heads, [&](int first, int n) {
-    hipLaunchKernelGGL((fwd_bf16_kernel<D, EXACT>), dim3((unsigned)mapped_grid(n, p.n_kv_heads, p.n_q_heads / p.n_kv_heads)), block, 0,
-                       (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items + first, n, (int)c.T,
+    const QBlocks run = shared_blocks(n == n_items ? groups : QGroups::plain(n), p.n_kv_heads, g);
+    hipLaunchKernelGGL((fwd_bf16_kernel<D, EXACT>), dim3((unsigned)run.end[2]), block, 0,
+                       (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items + first, run, (int)c.T,
                        p.n_q_heads, p.n_kv_heads, p.scale);
     return (int)hipGetLastError();
   });
@@ -362,17 +364,18 @@ int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const 
 constexpr int kShortMeanKeys = 400;
 
 int launch_fwd_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse,
-                    const QItem* items, int n_items, int divide_rows) {
+                    const QItem* items, const QGroups& groups, int divide_rows) {
+  const int n_items = groups.total();
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
   const bool even = p.n_q_heads / p.n_kv_heads % 2 == 0;
   FwdSplit sp;
   int e = split_begin(c, n_items, divide_rows, &sp);
   if (e == 0) {
-    if (p.head_dim == 64) e = launch_fwd_one_head<64, false>(c, q, k, v, o, lse, items, n_items, sp);
-    else if (!even) e = launch_fwd_one_head<128, false>(c, q, k, v, o, lse, items, n_items, sp);
+    if (p.head_dim == 64) e = launch_fwd_one_head<64, false>(c, q, k, v, o, lse, items, groups, sp);
+    else if (!even) e = launch_fwd_one_head<128, false>(c, q, k, v, o, lse, items, groups, sp);
     else if (c.mean_keys > kShortMeanKeys) e = launch_fwd_wide_bf16(c, q, k, v, o, lse, items, n_items, sp);
-    else e = launch_fwd_one_head<128, true>(c, q, k, v, o, lse, items, n_items, sp);
+    else e = launch_fwd_one_head<128, true>(c, q, k, v, o, lse, items, groups, sp);
   }
   if (e != 0) split_abandon(c, sp);
   return e;

@@ -328,6 +328,33 @@ __device__ __forceinline__ bool map_block(int block, int g, int Hkv, int n_items
 }
 inline int mapped_grid(int n_items, int Hkv, int g) { return ((n_items * Hkv + 7) / 8) * 8 * g; }
 
+// The same for a launch over groups of items (QGroups): a block takes 1 << *share heads from *hg on.
+struct QBlocks { int n[3], share[3], end[3]; };   // per group: items, log 2 of the heads per block, first block behind it
+inline QBlocks shared_blocks(const QGroups& groups, int Hkv, int g) {
+  QBlocks b;
+  const int most = g % 4 == 0 ? 2 : g % 2 == 0 ? 1 : 0;
+  int end = 0;
+  for (int i = 0; i < 3; ++i) {
+    b.n[i] = groups.n[i];
+    b.share[i] = groups.share[i] < most ? groups.share[i] : most;
+    b.end[i] = end += mapped_grid(b.n[i], Hkv, g >> b.share[i]);
+  }
+  return b;
+}
+__device__ __forceinline__ bool map_shared_block(int block, int g, int Hkv, const QBlocks& b, int* item, int* hk, int* hg, int* share) {
+  // (in front of a block's first load: selects between scalars, where branches, or the array indexed in memory, cost up to a microsecond.
+  // The empty statement keeps the compiler from making either out of it.)
+  int n0 = b.n[0], n1 = b.n[1], n2 = b.n[2], s0 = b.share[0], s1 = b.share[1], s2 = b.share[2], e0 = b.end[0], e1 = b.end[1];
+  asm volatile("" : "+s"(n0), "+s"(n1), "+s"(n2), "+s"(s0), "+s"(s1), "+s"(s2), "+s"(e0), "+s"(e1));
+  const bool behind0 = block >= e0, behind1 = block >= e1;
+  const int n = behind1 ? n2 : behind0 ? n1 : n0, first = behind1 ? n0 + n1 : behind0 ? n0 : 0, start = behind1 ? e1 : behind0 ? e0 : 0;
+  *share = behind1 ? s2 : behind0 ? s1 : s0;
+  if (!map_block(block - start, g >> *share, Hkv, n, item, hk, hg)) return false;
+  *item += first;
+  *hg <<= *share;
+  return true;
+}
+
 // ---- forward launches whose keys are divided (FwdSplit in internal.h) --------------------------------------
 // Block (without its part) -> item, KV head, head in group: the blocks that read the same keys are neighbours.
 __device__ __forceinline__ void split_block(int j, int g, int Hkv, int* item, int* hk, int* hg) {

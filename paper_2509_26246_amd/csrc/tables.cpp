@@ -50,7 +50,7 @@ constexpr int64_t kMinPartRows = 256;
 
 // (Buffers of append_scope and append_split, kept over the calls of one table build.)
 struct Scratch {
-  std::vector<QItem> qi;
+  std::vector<QItem> qi, qi_sorted;
   std::vector<KvItem> ki, items;
   std::vector<int64_t> weight, w;
   std::vector<std::pair<int64_t, int32_t>> order;
@@ -155,9 +155,20 @@ void append_scope(ScopeLists& L, const std::vector<Run>& runs, bool want_kv, Scr
     if (is_query_tile(B))
       for (const Run& r : runs)
         for (int32_t a = r.q_lo; a < r.q_hi; a += B) qi.push_back(QItem{a, std::min(B, r.q_hi - a), r.kv_start, 0});
-    std::stable_sort(qi.begin(), qi.end(), [](const QItem& a, const QItem& b) {
-      return (a.q_row0 + a.q_rows - a.kv_start) > (b.q_row0 + b.q_rows - b.kv_start);
-    });
+    auto keys = [](const QItem& it) { return it.q_row0 + it.q_rows - it.kv_start; };
+    std::stable_sort(qi.begin(), qi.end(), [&](const QItem& a, const QItem& b) { return keys(a) > keys(b); });
+    if (B == 128) {                                          // ... in each of the groups
+      const bool tails_last = !qi.empty() && keys(qi[0]) > kSharedKeys;
+      QGroups g{{0, 0, 0}, {0, 1, 2}};
+      if (!tails_last) std::swap(g.share[0], g.share[2]);
+      std::vector<QItem>& sorted = tmp.qi_sorted;
+      sorted.clear();
+      for (int i = 0; i < 3; ++i)
+        for (const QItem& it : qi)
+          if (query_share(it) == g.share[i]) { sorted.push_back(it); ++g.n[i]; }
+      qi.swap(sorted);
+      L.q_groups.push_back(g);
+    }
     L.q_items[z].insert(L.q_items[z].end(), qi.begin(), qi.end());
     L.q_off[z].push_back((int32_t)L.q_items[z].size());
     // key tiles: per sample, prefix [kv_start, last run's end); heavy-first by query rows at or after the tile

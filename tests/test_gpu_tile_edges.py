@@ -138,6 +138,14 @@ def test_bf16_dkdv_long_walks():
     _fused_and_per_unit([510, 440, 330, 300, 290], 256, 16, 128, True, 1000)
 
 
+# Tails of at most 64 (32) rows, for which a block takes two (four) heads, as far as the group's size allows: on the edges, in lists with and
+# without samples of more than 1024 keys (tails last, tails first), tails only, a long sample's own tail included (one head)
+@pytest.mark.parametrize("L", [[160, 33, 1, 192, 300], [32, 64, 65], [1153, 20, 190, 129]], ids=["short", "tails", "long"])
+@pytest.mark.parametrize("hq,hkv,d", [(2, 1, 64), (4, 1, 128), (8, 1, 64), (6, 2, 128), (3, 1, 64), (12, 2, 128)])
+def test_bf16_tails_shared_by_heads(L, hq, hkv, d):
+    _fused_and_per_unit(L, hq, hkv, d, True, 500)
+
+
 # fp32 dQ: a key with a NaN or an infinity reaches the rows that see it and no row in front of it, in the middle of a tile too; a key of
 # -inf (score -inf, probability 0) spoils only its own dim of those rows
 @pytest.mark.parametrize("d", [16, 32, 64, 128])

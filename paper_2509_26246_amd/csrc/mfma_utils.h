@@ -479,7 +479,9 @@ inline unsigned split_finish_z(int n_items, int n_heads, int head_dim) {
   while (z > 1 && (int64_t)n_items * n_heads * z > 256) z /= 2;
   return z;
 }
-// The end of a finishing kernel's block: the last one to get here gives the region back.
+// The end of a finishing kernel's block: the last one to get here gives the region back.  A block has only read the region, and what
+// it read has arrived (its results are made of it), so nothing has to be written back in front of the count: relaxed atomics in the order of one
+// thread.  (A fence for the device here writes the L2 back, once per block: 1024 rows of 8/1 heads after 31K keys, 256 blocks, 16.6 us for the kernel against 9.9.)
 __device__ __forceinline__ void split_release(const FwdSplit& sp, int region) {
   __syncthreads();
   if (threadIdx.x != 0) return;
@@ -487,11 +489,10 @@ __device__ __forceinline__ void split_release(const FwdSplit& sp, int region) {
     if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) atomicAdd(&sp.state->launches[1], 1ull);
     return;
   }
-  __threadfence();
-  if (atomicAdd(&sp.state->done[region], 1u) == gridDim.x * gridDim.y * gridDim.z - 1) {
-    atomicAdd(&sp.state->launches[0], 1ull);
-    __threadfence();
-    atomicExch(&sp.state->owner[region], 0ull);
+  const unsigned before = __hip_atomic_fetch_add(&sp.state->done[region], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (before == gridDim.x * gridDim.y * gridDim.z - 1) {
+    __hip_atomic_fetch_add(&sp.state->launches[0], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&sp.state->owner[region], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 

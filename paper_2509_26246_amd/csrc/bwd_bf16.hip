@@ -103,9 +103,9 @@ __device__ __forceinline__ void dq_tile(const lds_cptr (&pk)[D / 16], const lds_
           if (i & 1) dpc = mfma32(f, dof[i >> 1], i == 1 ? negd : dpc);
           else sc = mfma32(f, qf[i >> 1], i == 0 ? negl : sc);
         });
-    // the element-wise part runs at raised priority: a wave that streams products would otherwise
-    // keep the vector issue port and starve the other wave's softmax
-    __builtin_amdgcn_s_setprio(3);
+    // at 64 the element-wise part runs at raised priority: a wave that streams products would otherwise
+    // keep the vector issue port and starve the other wave's softmax.  (At 128, with twice the products per score, 0.5 to 2 % slower.)
+    if constexpr (D == 64) __builtin_amdgcn_s_setprio(3);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const float p = __builtin_amdgcn_exp2f(sc[r]);
@@ -114,7 +114,7 @@ __device__ __forceinline__ void dq_tile(const lds_cptr (&pk)[D / 16], const lds_
     }
     dsf[2 * b] = pack8(sc, 0);
     dsf[2 * b + 1] = pack8(sc, 8);
-    __builtin_amdgcn_s_setprio(0);
+    if constexpr (D == 64) __builtin_amdgcn_s_setprio(0);
   }
   // dQ^T += K^T dS^T: one batch of K^T fragments per 16-key step j (one fragment per head-dim block), so that
   // consecutive products go to different accumulators (a product on the accumulator of the one right

@@ -53,13 +53,13 @@ struct Scratch {
   std::vector<QItem> qi, qi_sorted;
   std::vector<KvItem> ki, items;
   std::vector<int64_t> weight, w;
-  std::vector<std::pair<int64_t, int32_t>> order;
-  // indices 0 .. n-1 by descending weight, equal ones in index order
-  const std::vector<std::pair<int64_t, int32_t>>& heavy_first(const std::vector<int64_t>& by) {
+  std::vector<uint64_t> order;
+  // indices 0 .. n-1 (low 32 bits) by descending weight (below 2^32), equal ones in index order
+  const std::vector<uint64_t>& heavy_first(const std::vector<int64_t>& by) {
     order.resize(by.size());
     bool sorted = true;
     for (size_t x = 0; x < by.size(); ++x) {
-      order[x] = {-by[x], (int32_t)x};
+      order[x] = (uint64_t)(0xFFFFFFFF - by[x]) << 32 | (uint32_t)x;
       sorted = sorted && (x == 0 || by[x - 1] >= by[x]);
     }
     if (!sorted) std::sort(order.begin(), order.end());
@@ -67,13 +67,15 @@ struct Scratch {
   }
 };
 
-void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const std::vector<int64_t>& weight, Scratch& tmp) {
+void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const std::vector<int64_t>& weight, bool whole_list, Scratch& tmp) {
   const int64_t kBlockSlots = kSplitBlockSlots[ti];
   int64_t total = 0;
   for (int64_t w : weight) total += w;
   L.walk_rows[ti].push_back(total);
+  const bool few = 2 * ki.size() <= kHeadPartBlocks;         // a launch over them may be divided by query heads
   bool divided = true;                                       // in the class below
-  for (int c = 0; c < kNumSplitClasses; ++c) {
+  const int lowest = whole_list ? 0 : 1;                     // (the class below 1 takes longest to build: units share class 1's lists)
+  for (int c = lowest; c < kNumSplitClasses; ++c) {
     if (!divided) {      // shares grow with the class: nothing is divided here either, and the lists are the same
       L.split_rng[ti][c].push_back(L.split_rng[ti][c - 1].back());
       L.tile_rng[ti][c].push_back(L.tile_rng[ti][c - 1].back());
@@ -94,7 +96,7 @@ void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const st
     const int32_t item0 = (int32_t)L.split_items[ti].size(), tile0 = (int32_t)L.tile_items[ti].size();
     for (size_t x = 0; x < ki.size(); ++x) {
       const int64_t parts = std::min<int64_t>((weight[x] + target - 1) / target, weight[x] / kMinPartRows);
-      L.tile_items[ti].push_back(KvReduce{ki[x].kv_row0, ki[x].kv_rows, number, 1, ki[x].load_until, ki[x].final_from, 0, 0});
+      if (few) L.tile_items[ti].push_back(KvReduce{ki[x].kv_row0, ki[x].kv_rows, number, 1, ki[x].load_until, ki[x].final_from, 0, 0});
       if (parts < 2 || 4 * weight[x] <= 3 * share) {
         items.push_back(ki[x]);
         items.back().number = number++;
@@ -128,23 +130,33 @@ void append_split(ScopeLists& L, int ti, const std::vector<KvItem>& ki, const st
         }
       }
       if (have > 0) close_part();
-      L.tile_items[ti].back().n_parts = red.n_parts;
+      if (few) L.tile_items[ti].back().n_parts = red.n_parts;
     }
     const auto& order = tmp.heavy_first(w);
-    for (const auto& x : order) L.split_items[ti].push_back(items[x.second]);
+    for (const uint64_t x : order) L.split_items[ti].push_back(items[(uint32_t)x]);
     divided = slots > 0;
     L.split_rng[ti][c].push_back(Range{item0, (int32_t)L.split_items[ti].size()});
     L.reduce_off[ti][c].push_back((int32_t)L.reduce_items[ti][c].size());
     L.max_slots[ti][c] = std::max(L.max_slots[ti][c], slots);
     L.tile_rng[ti][c].push_back(Range{tile0, (int32_t)L.tile_items[ti].size()});
-    L.longest[ti][c].push_back(order.empty() ? 0 : (int32_t)w[order[0].second]);
+    L.longest[ti][c].push_back(order.empty() ? 0 : (int32_t)w[(uint32_t)order[0]]);
+  }
+  if (lowest == 1) {
+    L.split_rng[ti][0].push_back(L.split_rng[ti][1].back());
+    L.tile_rng[ti][0].push_back(L.tile_rng[ti][1].back());
+    const auto& red = L.reduce_items[ti][1];
+    const auto& off = L.reduce_off[ti][1];
+    L.reduce_items[ti][0].insert(L.reduce_items[ti][0].end(), red.begin() + off[off.size() - 2], red.end());
+    L.reduce_off[ti][0].push_back((int32_t)L.reduce_items[ti][0].size());
+    L.max_slots[ti][0] = L.max_slots[ti][1];
+    L.longest[ti][0].push_back(L.longest[ti][1].back());
   }
 }
 
 // `row_marks(sample)`: {load_until, final_from} of the sample's key rows for this scope.
 // want_kv: key-tile lists are only needed by the backward pass.
 template <class Marks>
-void append_scope(ScopeLists& L, const std::vector<Run>& runs, bool want_kv, Scratch& tmp, Marks&& row_marks) {
+void append_scope(ScopeLists& L, const std::vector<Run>& runs, bool want_kv, bool whole_list, Scratch& tmp, Marks&& row_marks) {
   const int32_t seg_base = (int32_t)L.segs.size();
   for (const Run& r : runs) L.segs.push_back(Seg{r.q_lo, r.q_hi});
   for (int z = 0; z < kNumTileSizes; ++z) {
@@ -193,9 +205,10 @@ void append_scope(ScopeLists& L, const std::vector<Run>& runs, bool want_kv, Scr
       }
       i = j;
     }
-    for (const auto& x : tmp.heavy_first(weight)) L.kv_items[z].push_back(ki[x.second]);
+    if (split_tile_index(B) < 0)                          // (the split lists hold the others, undivided tiles included)
+      for (const uint64_t x : tmp.heavy_first(weight)) L.kv_items[z].push_back(ki[(uint32_t)x]);
     L.kv_off[z].push_back((int32_t)L.kv_items[z].size());
-    if (split_tile_index(B) >= 0) append_split(L, split_tile_index(B), ki, weight, tmp);
+    if (split_tile_index(B) >= 0) append_split(L, split_tile_index(B), ki, weight, whole_list, tmp);
   }
 }
 
@@ -310,7 +323,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
         }
       for (int32_t u = 0; u < t->n_units[pass]; ++u) {
         const int32_t a = t->unit_ptr[pass][u], b = t->unit_ptr[pass][u + 1];
-        append_scope(t->per_unit[pass], merge_runs(slices, t->unit_slices[pass].data() + a, b - a), pass == 1, tmp,
+        append_scope(t->per_unit[pass], merge_runs(slices, t->unit_slices[pass].data() + a, b - a), pass == 1, false, tmp,
                      [&](int32_t sample) -> std::pair<int32_t, int32_t> {
                        int32_t before = 0, after = 0;      // furthest reach of an earlier / a later unit (0: none)
                        for (const auto& ur : reach[sample]) {
@@ -326,7 +339,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
     for (int z = 0; z < kNumTileSizes; ++z) { t->fused.q_off[z].push_back(0); t->fused.kv_off[z].push_back(0); }
     for (int ti = 0; ti < kNumSplitTiles; ++ti)
       for (int c = 0; c < kNumSplitClasses; ++c) t->fused.reduce_off[ti][c].push_back(0);
-    append_scope(t->fused, merge_runs(slices, all.data(), n_slices), true, tmp,
+    append_scope(t->fused, merge_runs(slices, all.data(), n_slices), true, true, tmp,
                  [](int32_t) -> std::pair<int32_t, int32_t> { return {0, 0}; });
 
     // one blob, one upload

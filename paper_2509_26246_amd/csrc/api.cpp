@@ -255,29 +255,28 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
                  : launch_bwd_dq_bf16(ctx, q, k, v, dO, o, lse, stat3, own_stats ? 1 : 0, dQ, items, groups);
     });
   };
-  auto run_dkdv = [&](const KvItem* items, int n, const Seg* segs, int hp = 1, bool short_walks = false) -> int {
+  auto run_dkdv = [&](const KvItem* items, int n, const Seg* segs, const DkdvParts& by = DkdvParts{1, 1, false}) -> int {
     return timed(SLIMATTN_K_DKDV, stream, [&] {
       return f32 ? launch_bwd_dkdv_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (const float*)dO, lse,
                                        delta, acc_dk, acc_dv, (float*)dK, (float*)dV, items, n, segs, whole && !per_unit ? t->max_sample_len : 0)
-             : p->head_dim == 64 || short_walks
-                 ? launch_bwd_dkdv_pair_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp)
-                 : launch_bwd_dkdv_wide_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, hp);
+             : by.pair
+                 ? launch_bwd_dkdv_pair_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, by)
+                 : launch_bwd_dkdv_wide_bf16(ctx, q, k, v, dO, stat3, acc_dk, acc_dv, dK, dV, items, n, segs, parts, by.heads);
     });
   };
   // bf16: the key-tile list in which heavy tiles are divided among several blocks, followed by the
   // launch that adds the parts up (a scope without divided tiles has an empty reduction list); small launches also
-  // divide every item by query heads, and then every tile is reduced
+  // divide every item by query heads and steps, and then every tile is reduced
   auto run_dkdv_split = [&](const ScopeLists& L, const DeviceLists& D, int u) -> int {
     const int tile_rows = dkdv_kv_tile(p->dtype, p->head_dim), ti = split_tile_index(tile_rows);
     const int a = L.split_rng[ti][sc][u].begin, b = L.split_rng[ti][sc][u].end;
-    const int hp = head_parts(b - a, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, L.longest[ti][sc][u], head_blocks);
-    int e = run_dkdv(D.split_items[ti] + a, b - a, D.segs, hp,
-                     short_walks(L.walk_rows[ti][u], b - a, p->n_q_heads / p->n_kv_heads, hp));
+    const DkdvParts by = dkdv_parts(b - a, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, L.walk_rows[ti][u], L.longest[ti][sc][u], p->head_dim, head_blocks);
+    int e = run_dkdv(D.split_items[ti] + a, b - a, D.segs, by);
     if (e != 0) return e;
-    if (hp > 1) {
+    if (by.total() > 1) {
       const int ta = L.tile_rng[ti][sc][u].begin, tb = L.tile_rng[ti][sc][u].end;
       return timed(SLIMATTN_K_REDUCE, stream, [&] {
-        return launch_bwd_reduce_bf16(ctx, parts, acc_dk, acc_dv, dK, dV, D.tile_items[ti] + ta, tb - ta, tile_rows, hp);
+        return launch_bwd_reduce_bf16(ctx, parts, acc_dk, acc_dv, dK, dV, D.tile_items[ti] + ta, tb - ta, tile_rows, by.total());
       });
     }
     const int ra = L.reduce_off[ti][sc][u], rb = L.reduce_off[ti][sc][u + 1];

@@ -55,12 +55,21 @@ __device__ __forceinline__ lds_cptr lds_xor(lds_cptr p) {
   return (lds_cptr)(size_t)x;
 }
 
+// Bits MASK of tid >> SHIFT, formed where it is used: the kernels are at their register limit, and only the thread's number stays in one.
+template <int SHIFT, int MASK>
+__device__ __forceinline__ int at_use(int tid) {
+  int x;
+  if constexpr (SHIFT == 0) asm volatile("v_and_b32 %0, %2, %1" : "=v"(x) : "v"(tid), "n"(MASK));
+  else asm volatile("v_bfe_u32 %0, %1, %2, 8\n\tv_and_b32 %0, %3, %0" : "=&v"(x) : "v"(tid), "n"(SHIFT), "n"(MASK));
+  return x;
+}
+
 template <int D>
 __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_kernel(
     const bf16* __restrict__ q, const bf16* __restrict__ k, const bf16* __restrict__ v, const bf16* __restrict__ dO,
     const bf16x8* __restrict__ stat3, float* __restrict__ acc_dk, float* __restrict__ acc_dv, bf16* __restrict__ dK,
     bf16* __restrict__ dV, const KvItem* __restrict__ items, int n_items, const Seg* __restrict__ segs, int T, int Hq, int Hkv,
-    float scale, float* __restrict__ parts, int head_parts) {
+    float scale, float* __restrict__ parts, int head_parts, int row_parts) {
   constexpr int kNKS = D / 16, kNDB = D / 32, kRowBytes = D * 2;
   constexpr int kTileBytes = kQStep * kRowBytes;        // one Q or dO tile
   constexpr int kStageBytes = 2 * kTileBytes;           // Q tile, dO tile of a step
@@ -73,15 +82,15 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
   int b = paired_block(blockIdx.x);
   const int hk = b % Hkv;
   b /= Hkv;
-  const int hpart = b % head_parts;
-  b /= head_parts;
+  const int part = b % (head_parts * row_parts), hpart = part / row_parts, rpart = part % row_parts;
+  b /= head_parts * row_parts;
   const int item_idx = b >> 1, sub = b & 1;
   const int h_lo = g * hpart / head_parts, h_hi = g * (hpart + 1) / head_parts;
   if (item_idx >= n_items) return;
   const KvItem it = items[item_idx];
   const int row0 = it.kv_row0 + kKeys * sub, kv_end = it.kv_row0 + min(it.kv_rows, kKeys * (sub + 1));
   if (row0 >= kv_end) return;
-  const int slot = head_parts > 1 ? it.number * head_parts + hpart : it.slot;
+  const int slot = head_parts * row_parts > 1 ? it.number * (head_parts * row_parts) + part : it.slot;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int kv0w = row0 + 32 * wave;
   LDS_PTR(char) lds = (LDS_PTR(char))smem;
@@ -113,13 +122,29 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
     n = (sg.q_hi - lo + kQStep - 1) / kQStep - 1;
   };
   open_run();
+  int todo = 0x7FFFFFFF;                                // steps of 32 rows still to hand out
+  if (row_parts > 1) {                                  // this block's share of them
+    int total = 0;
+    for (int x = it.seg_begin; x < it.seg_end; ++x) total += max(0, segs[x].q_hi - max(segs[x].q_lo, row0) + kQStep - 1) / kQStep;
+    total = __builtin_amdgcn_readfirstlane(total);      // (block-uniform anyway: tells the compiler)
+    int skip = total * rpart / row_parts;
+    todo = total * (rpart + 1) / row_parts - skip;
+    if (todo == 0) more = false;
+    while (more && skip > n) {
+      skip -= n + 1;
+      --sgi;
+      open_run();
+    }
+    n -= skip;
+  }
   // The next step of the walk; behind its end an empty step (no row counts and none is read: hi = i0).
   auto next_step = [&]() -> Step {
     if (!more) return Step{row0, row0, hk * g};
     Step d{lo + n * kQStep, sg.q_hi, hk * g + hh};
     if (++hh == h_hi) {
       hh = h_lo;
-      if (--n < 0) { --sgi; open_run(); }
+      if (--todo == 0) more = false;
+      else if (--n < 0) { --sgi; open_run(); }
     }
     return d;
   };
@@ -139,7 +164,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
   };
   const __amdgpu_buffer_rsrc_t stat_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)stat3, 0, (int)((size_t)T * Hq * 16), 0x00020000);
   auto load_stat = [&](const Step& d) -> bf16x8 {
-    const int row = max(min(d.i0 + l32, d.hi - 1), row0);
+    const int row = max(min(d.i0 + at_use<0, 31>(tid), d.hi - 1), row0);
     return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(stat_rsrc, row * 16, __builtin_amdgcn_readfirstlane(d.head * T * 16), 0));
   };
 
@@ -186,7 +211,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
       });
     }
     if (d.i0 < kv0w + 31 || d.i0 + kQStep > d.hi) {
-      const int rel_lo = kv0w + l32 - d.i0 - 4 * half, rel_hi = d.hi - d.i0 - 4 * half;
+      const int half4 = at_use<3, 4>(tid), rel_lo = kv0w + at_use<0, 31>(tid) - d.i0 - half4, rel_hi = d.hi - d.i0 - half4;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int c = 8 * (r >> 2) + (r & 3);
@@ -249,15 +274,15 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
   while (iteration(IC<0>{}) && iteration(IC<1>{})) {}
   __syncthreads();                                      // the stages are free
 
-  const int my_key = kv0w + l32;
+  const int out_lane = at_use<0, 63>(tid), out_half = out_lane >> 5, out_l32 = out_lane & 31, my_key = kv0w + out_l32;
   if (slot < 0 && it.final_from <= it.kv_row0 && it.load_until <= it.kv_row0) {
     LDS_PTR(char) ep = lds + wave * kOutAreaBytes<D>;   // the whole list in one launch: bf16 rows
-    store_rows<D>(ep, dk, scale, dK, Hkv, hk, kv0w, kv_end, lane);
-    store_rows<D>(ep, dv, 1.f, dV, Hkv, hk, kv0w, kv_end, lane);
+    store_rows<D>(ep, dk, scale, dK, Hkv, hk, kv0w, kv_end, out_lane);
+    store_rows<D>(ep, dv, 1.f, dV, Hkv, hk, kv0w, kv_end, out_lane);
   } else if (slot >= 0) {                               // partial tile [slot][kv head][dK, dV][256 rows][D]
-    store_part_row<D>(parts + ((size_t)slot * Hkv + hk) * (2 * 2 * kKeys * D) + (size_t)(sub * kKeys + 32 * wave + l32) * D, 2 * kKeys, dk, dv, scale, half);
+    if (my_key < kv_end) store_part_row<D>(parts + ((size_t)slot * Hkv + hk) * (2 * 2 * kKeys * D) + (size_t)(sub * kKeys + 32 * wave + out_l32) * D, 2 * kKeys, dk, dv, scale, out_half);
   } else if (my_key < kv_end) {
-    store_key_row<D>(((size_t)my_key * Hkv + hk) * D, my_key < it.load_until, my_key >= it.final_from, dk, dv, scale, half, acc_dk, acc_dv, dK, dV);
+    store_key_row<D>(((size_t)my_key * Hkv + hk) * D, my_key < it.load_until, my_key >= it.final_from, dk, dv, scale, out_half, acc_dk, acc_dv, dK, dV);
   }
 }
 
@@ -265,13 +290,13 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
 
 int launch_bwd_dkdv_pair_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
                               float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
-                              float* parts, int head_parts) {
+                              float* parts, const DkdvParts& by) {
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
-  return in_runs(n_items, 2 * (int64_t)p.n_kv_heads * head_parts, [&](int first, int n) {
-    hipLaunchKernelGGL(p.head_dim == 128 ? dkdv_pair_bf16_kernel<128> : dkdv_pair_bf16_kernel<64>, dim3((unsigned)(2 * n * p.n_kv_heads * head_parts)),
+  return in_runs(n_items, 2 * (int64_t)p.n_kv_heads * by.total(), [&](int first, int n) {
+    hipLaunchKernelGGL(p.head_dim == 128 ? dkdv_pair_bf16_kernel<128> : dkdv_pair_bf16_kernel<64>, dim3((unsigned)(2 * n * p.n_kv_heads * by.total())),
                        dim3(64 * kWaves), 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv,
-                       (bf16*)dK, (bf16*)dV, items + first, n, segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, head_parts);
+                       (bf16*)dK, (bf16*)dV, items + first, n, segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, by.heads, by.rows);
     return (int)hipGetLastError();
   });
 }

@@ -110,6 +110,29 @@ inline bool short_walks(int64_t walk_rows, int n_items, int group, int head_part
   return walk_rows * group <= (int64_t)kShortWalkSteps * 32 * n_items * head_parts;
 }
 
+// Blocks that share an item: `heads` by the query heads of the group, each of them `rows` by the steps of its walk (kernel of
+// dkdv_pair_bf16.hip only).  What is left of the longest walk of a launch of few blocks then runs on compute units that are otherwise idle, a
+// step in about 1.2 us; a further part costs its share of the item's first loads, 256 KB of partial tile to write and read (kRowPartTiles
+// bounds them), and the reduction launch where there was none.  dK/dV and reduction, us: 876 rows of 8/1 heads of 128, 16 steps in 40 blocks 34.5,
+// 8 in 80 29.0, 5 in 120 29; 1428 rows of 3/1 heads 29.1 -> 26.8; 900 rows of 16/4 heads, 64 blocks 35.1, 128 30.5.
+constexpr int kRowPartTiles = 128;
+struct DkdvParts {
+  int heads, rows;
+  bool pair;                                                    // the kernel of dkdv_pair_bf16.hip
+  int total() const { return heads * rows; }
+};
+inline DkdvParts dkdv_parts(int n_items, int n_kv_heads, int group, int64_t walk_rows, int longest_rows, int head_dim, int64_t max_blocks) {
+  DkdvParts p{head_parts(n_items, n_kv_heads, group, longest_rows, max_blocks), 1, false};
+  p.pair = head_dim == 64 || short_walks(walk_rows, n_items, group, p.heads);
+  const int64_t blocks = (int64_t)n_items * n_kv_heads * p.heads, tiles = max_blocks < kRowPartTiles ? max_blocks : kRowPartTiles;
+  if (p.pair && blocks > 0 && blocks <= tiles / 2) {
+    const int64_t steps = (int64_t)longest_rows * group / p.heads / 32;
+    const int64_t rows = tiles / blocks < steps / 4 ? tiles / blocks : steps / 4;
+    if (rows > 1 && steps - steps / rows >= (p.heads > 1 ? 6 : 12)) p.rows = (int)rows;
+  }
+  return p;
+}
+
 struct Range { int32_t begin, end; };
 
 // A launch scope is either one unit or the whole list ("fused").  Its items are stored heavy-first.
@@ -258,7 +281,7 @@ int launch_bwd_dkdv_wide_bf16(const LaunchCtx&, const void* q, const void* k, co
 // head_dim 64, and 128 with short walks: two or three blocks of 128 key rows per compute unit (dkdv_pair_bf16.hip); same arguments
 int launch_bwd_dkdv_pair_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
                               float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,
-                              float* parts, int head_parts);
+                              float* parts, const DkdvParts& by);
 // adds up the partial tiles (tile_rows rows each) of divided key tiles, in slot order, into dK/dV or the
 // fp32 accumulators; per_slot: partial tiles per slot (the blocks that share an item by query heads)
 int launch_bwd_reduce_bf16(const LaunchCtx&, const float* parts, float* acc_dk, float* acc_dv, void* dK, void* dV,

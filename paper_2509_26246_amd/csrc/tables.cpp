@@ -458,8 +458,8 @@ size_t slimattn_bwd_workspace_bytes(const slimattn_tables* t, int32_t hq, int32_
   for (const ScopeLists* L : {&t->per_unit[1], &t->fused})
     for (size_t u = 0; u < L->longest[0][c].size(); ++u) {
       const int n = L->split_rng[0][c][u].end - L->split_rng[0][c][u].begin;
-      const int hp = head_parts(n, hkv, hq / hkv, L->longest[0][c][u], max_blocks);
-      if (hp > 1) slots = std::max(slots, (size_t)n * hp);
+      const int parts = dkdv_parts(n, hkv, hq / hkv, L->walk_rows[0][u], L->longest[0][c][u], d, max_blocks).total();
+      if (parts > 1) slots = std::max(slots, (size_t)n * parts);
     }
   return fixed_bytes(t, hq, hkv, d) + align_up(slots * hkv * tile_bytes(d));
 }

@@ -77,6 +77,27 @@ def test_bf16_key_tiles_divided_by_heads(L, hq, hkv, d):
     _fused_and_per_unit(L, hq, hkv, d, True, 320)
 
 
+# walks divided by steps too: over several runs of query rows (every third slice, ragged), parts that begin inside a run and at its end, halves of
+# an item with fewer steps than parts
+@pytest.mark.parametrize("hq,hkv,d", [(3, 1, 128), (8, 2, 64), (1, 1, 128)])
+def test_bf16_key_tiles_divided_by_steps(hq, hkv, d):
+    r = np.random.default_rng(5)
+    L = [1100, 290]
+    q, k, v, dO = (W.bf16_round(r.standard_normal((sum(L), h, d), dtype=np.float32) * np.float32(x)) for h, x in ((hq, .5), (hkv, .5), (hkv, .5), (hq, .1)))
+    cu, sl = S.build_slices(L, 97)
+    fu = S.build_units(cu, sl, "PREFIX_FILL", m=4, w_quad=2, w_lin=0)
+    bu = S.build_units(cu, sl, "ROUND_ROBIN", m=3, descending=True, backward=True)
+    prob = H.make_problem(q, k, v, dO, cu, sl, fu, bu, bf16=True, scale=d ** -0.5)
+    o, lse = A.fwd_packed(q, k, v, cu, d ** -0.5)
+    dq, dk, dv = A.bwd_packed(q, k, v, o, lse, dO, cu, d ** -0.5)
+    for flags in (0, S.FLAG_PER_UNIT_LAUNCH):
+        _poison(prob)
+        prob.forward(flags=flags)
+        prob.backward(flags=flags)
+        torch.cuda.synchronize()
+        _check(prob, {"o": o, "lse": lse, "dQ": dq, "dK": dk, "dV": dv}, True, f"{hq}/{hkv}/{d} flags={flags}")
+
+
 # key tiles divided by query rows in the division classes of 16 and of 32 and more KV heads: 1536 rows on as many heads, where the
 # first tiles exceed three quarters of a slot's share (1536 against 336 and 672 rows)
 @pytest.mark.parametrize("heads,d", [(16, 128), (20, 64), (32, 64), (33, 128)])

@@ -11,17 +11,18 @@
 // Blocks of half the keys overlap each other, steps before a wave's keys are skipped, and a sample that ends in a
 // tile's first half wastes half as much.  At 128 a step costs more: one product per LDS fragment (1.25 KB of LDS reads per product), and a
 // wave alone takes 2500 cycles for a step of 34 products (1088), two on a SIMD 3400 for both.
-// Measured at 128, 16K tokens, one-wave kernel / this one, us: 32/32 heads, samples of 64 rows 426 / 157, 256 rows 235 / 164, 512 rows 297 / 213, 1024
-// rows 398 / 322, 4096 rows 1003 / 1010; 32/8 heads, 128 rows 158 / 117, 512 rows 207 / 176, 1024 rows 304 / 288, 4096 rows 891 / 1007; 876 rows of
-// 8/1 heads 39 / 28.  (Raised priority for the element-wise work: 2 to 5 % slower.  The next step's bookkeeping
+// Measured at 128, 16K tokens, one-wave kernel / this one, us: 32/32 heads, samples of 64 rows 426 / 157, 256 rows 235 / 164, 512 rows 281 / 202, 1024
+// rows 398 / 322; 32/8 heads, 128 rows 158 / 117, 256 rows 141 / 114, 1024 rows 283 / 270, 4096 rows 891 / 1007; 876 rows of
+// 8/1 heads 39 / 27.  (Raised priority for the element-wise work: 2 to 5 % slower.  The next step's bookkeeping
 // behind its first LDS reads, the second half of the element-wise work behind the first gradient products: no gain.)
 // At 64 a score costs the same exponential, product and packing as at 128 but half the matrix work, and a step is mostly latency: what counts
-// are waves.  Against 256 keys in 8 waves, two per SIMD, K and V in registers: 16K tokens, 32/8 heads, samples of 128 rows 78 / 63, 2048 rows 305 /
-// 287, one sample 2021 / 2046; 32/32 heads, 1024 rows 200 / 162, 4096 rows 601 / 524; a 32K pack of 10 samples, 32/8 heads, 3148 / 2783.  (V in registers
-// takes 7 more than the 168 three blocks leave: 340 us at 2048 rows.)
+// are waves, and barriers, of which there is one every two steps.  Against 256 keys in 8 waves, two per SIMD: 16K tokens, 32/8 heads, samples of 128 rows
+// 75 / 64, 2048 rows 301 / 276, one sample 1973 / 1909; 32/32 heads, 1024 rows 198 / 166, 4096 rows 601 / 513; a 32K pack of 10 samples, 32/8 heads, 3148 /
+// 2791.  (V rows in LDS instead: 61, 283, 1972, 158, 514.  A barrier for each step: 62 to 1957.)
 //
-// Registers: 254 of 256 at 128, 166 of 168 at 64.  The accumulators take D, K fragments D / 4; V rows are in LDS, and a tile's fragment
-// addresses are formed from one.
+// Registers: 245 of 256 at 128, 167 of 168 at 64.  The accumulators take D, K fragments D / 4; V rows are in LDS at 128 and in registers at 64; a tile's fragment
+// addresses are formed from one, and the row statistics, 16 bytes per row, come through LDS with the tiles (in registers, for this step and the next,
+// they took 3 % at 128 and left no room for V at 64).
 #include <hip/hip_runtime.h>
 
 #include "internal.h"
@@ -72,9 +73,11 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
     float scale, float* __restrict__ parts, int head_parts, int row_parts) {
   constexpr int kNKS = D / 16, kNDB = D / 32, kRowBytes = D * 2;
   constexpr int kTileBytes = kQStep * kRowBytes;        // one Q or dO tile
-  constexpr int kStageBytes = 2 * kTileBytes;           // Q tile, dO tile of a step
-  constexpr int kVBase = 2 * kStageBytes;               // two stages, then the block's V rows
-  constexpr int kLoop = kVBase + kKeys * kRowBytes, kOut = kWaves * kOutAreaBytes<D>;
+  constexpr int kStepBytes = 2 * kTileBytes + 1024;     // Q tile, dO tile, row statistics of a step
+  constexpr int kSteps = D == 128 ? 1 : 2;              // steps of a stage, between two barriers
+  constexpr bool kVInLds = D == 128;                    // or fragments in registers, where they fit
+  constexpr int kVBase = 2 * kSteps * kStepBytes;       // two stages, then the block's V rows
+  constexpr int kLoop = kVBase + (kVInLds ? kKeys * kRowBytes : 0), kOut = kWaves * kOutAreaBytes<D>;
   __shared__ __attribute__((aligned(1024))) char smem[kLoop > kOut ? kLoop : kOut];
 
   const int g = Hq / Hkv;
@@ -95,15 +98,18 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
   const int kv0w = row0 + 32 * wave;
   LDS_PTR(char) lds = (LDS_PTR(char))smem;
 
-  {
+  if constexpr (kVInLds) {
     const TileSource srcV = make_tile_source<D, 256>(v, row0, Hkv, hk, kv_end, tid);
     stage_tile<D, kKeys, 256>(lds + kVBase, srcV, 0, tid);
   }
-  bf16x8 kf[kNKS];
+  bf16x8 kf[kNKS], vf[kNKS];
   {
     const size_t off = ((size_t)min(kv0w + l32, T - 1) * Hkv + hk) * D + 8 * half;
 #pragma unroll
-    for (int ks = 0; ks < kNKS; ++ks) kf[ks] = *reinterpret_cast<const bf16x8*>(k + off + 16 * ks);
+    for (int ks = 0; ks < kNKS; ++ks) {
+      kf[ks] = *reinterpret_cast<const bf16x8*>(k + off + 16 * ks);
+      if constexpr (!kVInLds) vf[ks] = *reinterpret_cast<const bf16x8*>(v + off + 16 * ks);
+    }
   }
 
   // Flattened walk (block-uniform): runs from the last to the first, inside a run steps of 32 rows from the top down, inside a
@@ -152,6 +158,9 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
   const TileSource src = make_tile_source<D, 256>(q, row0, Hq, 0, T, tid);     // (voff, row_bytes)
   const bf16* const q_base = q + (size_t)row0 * Hq * D;
   const bf16* const do_base = dO + (size_t)row0 * Hq * D;
+  // A step's statistics (-lse2 and -delta as bf16 triples) come with its tiles, 16 bytes per row.  (A row past the end of the run takes the
+  // run's last row: finite numbers of this launch's own scope; its scores are masked.  An empty step takes the tile's first row.)
+  const __amdgpu_buffer_rsrc_t stat_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)stat3, 0, (int)((size_t)T * Hq * 16), 0x00020000);
   auto stage = [&](const Step& d, int at) {
     TileSource a = src, b2 = src;
     const int range = __builtin_amdgcn_readfirstlane((d.hi - row0) * (Hq * kRowBytes));
@@ -161,16 +170,18 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
     b2.voff = a.voff;
     stage_tile<D, kQStep, 256>(lds + at, a, d.i0 - row0, tid);
     stage_tile<D, kQStep, 256>(lds + at + kTileBytes, b2, d.i0 - row0, tid);
-  };
-  const __amdgpu_buffer_rsrc_t stat_rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)stat3, 0, (int)((size_t)T * Hq * 16), 0x00020000);
-  auto load_stat = [&](const Step& d) -> bf16x8 {
-    const int row = max(min(d.i0 + at_use<0, 31>(tid), d.hi - 1), row0);
-    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(stat_rsrc, row * 16, __builtin_amdgcn_readfirstlane(d.head * T * 16), 0));
+    if (wave == 0) {
+      const int row = max(min(d.i0 + at_use<0, 63>(tid), d.hi - 1), row0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(stat_rsrc, lds + at + 2 * kTileBytes, 16, row * 16, __builtin_amdgcn_readfirstlane(d.head * T * 16), 0, 0);
+    }
   };
 
-  Step cur = next_step(), nxt;
-  stage(cur, 0);
-  bf16x8 stat = load_stat(cur), stat_n;
+  Step cur[kSteps], nxt[kSteps];
+#pragma unroll
+  for (int x = 0; x < kSteps; ++x) {
+    cur[x] = next_step();
+    stage(cur[x], x * kStepBytes);
+  }
 #pragma unroll
   for (int ks = 0; ks < kNKS; ++ks) kf[ks] = scale8(kf[ks], scale * kLog2e);
   const __bf16 one = half ? (bf16)0.f : (bf16)1.f, zero = (bf16)0.f;
@@ -178,6 +189,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
   const lds_cptr pq = lds_row_ptr<D>(lds, l32, 8 * half);
   lds_cptr pqt[2];
   lds_tr_ptrs<D>(lds, 0, lane, pqt[0], pqt[1]);
+  const lds_cptr pst = keep(lds + 16 * l32);            // a lane's row statistics
   const int v_rel = wave * 32 * kRowBytes;
   floatx16 dk[kNDB], dv[kNDB];
   const floatx16 zeros = {};
@@ -186,10 +198,10 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
-  auto compute = [&](const Step& d, const bf16x8& st3, auto xc) {
-    constexpr int at = decltype(xc)::value * kStageBytes;
+  auto compute = [&](const Step& d, auto xc) {
+    constexpr int at = decltype(xc)::value * kStepBytes;
     if (min(d.i0 + kQStep, d.hi) <= kv0w || kv0w >= kv_end) return;
-    floatx16 s = mfma32(st3, ones_l, zeros), dp = mfma32(st3, ones_d, zeros);
+    floatx16 s, dp;
     {
       constexpr int kPre = D == 128 ? 2 : 1;            // head-dim steps read ahead (registers)
       QdV f[kNKS];
@@ -198,15 +210,22 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
         const lds_cptr p = lds_xor<32 * i>(pq);
         r1_issue<at>(p, f[i].q);
         r1_issue<at + kTileBytes>(p, f[i].d);
-        r1_issue<kVBase>(p + v_rel, f[i].v);
+        if constexpr (kVInLds) r1_issue<kVBase>(p + v_rel, f[i].v);
       };
+      bf16x8 st3;
+      r1_issue<at + 2 * kTileBytes>(pst, st3);
       static_for<0, kPre>(load);
+      asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(st3) : "n"((kVInLds ? 3 : 2) * kPre));
+      s = mfma32(st3, ones_l, zeros);
+      dp = mfma32(st3, ones_d, zeros);
       static_for<0, kNKS>([&](auto ic) {
         constexpr int i = decltype(ic)::value, ahead = (kNKS - 1 - i < kPre - 1 ? kNKS - 1 - i : kPre - 1) + (i + kPre < kNKS ? 1 : 0);
         if constexpr (i + kPre < kNKS) load(IC<i + kPre>{});
-        asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(f[i].q), "+v"(f[i].d), "+v"(f[i].v) : "n"(3 * ahead));
+        if constexpr (kVInLds) asm volatile("s_waitcnt lgkmcnt(%3)" : "+v"(f[i].q), "+v"(f[i].d), "+v"(f[i].v) : "n"(3 * ahead));
+        else asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(f[i].q), "+v"(f[i].d) : "n"(2 * ahead));
         s = mfma32(f[i].q, kf[i], s);
-        dp = mfma32(f[i].d, f[i].v, dp);
+        if constexpr (kVInLds) dp = mfma32(f[i].d, f[i].v, dp);
+        else dp = mfma32(f[i].d, vf[i], dp);
         __builtin_amdgcn_sched_barrier(0);
       });
     }
@@ -258,16 +277,18 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
   auto iteration = [&](auto xc) -> bool {
     constexpr int x = decltype(xc)::value;
     const bool last = !more;
-    if (!last) {
-      nxt = next_step();
-      stage(nxt, (1 - x) * kStageBytes);
-      stat_n = load_stat(nxt);
+    if (!last) {                                        // the next steps, into the stage the iteration before this one read
+#pragma unroll
+      for (int y = 0; y < kSteps; ++y) {
+        nxt[y] = next_step();
+        stage(nxt[y], ((1 - x) * kSteps + y) * kStepBytes);
+      }
     }
-    compute(cur, stat, xc);
+    static_for<0, kSteps>([&](auto yc) { compute(cur[decltype(yc)::value], IC<x * kSteps + decltype(yc)::value>{}); });
     if (last) return false;
-    cur = nxt;
-    stat = stat_n;
-    __builtin_amdgcn_s_waitcnt(0);
+#pragma unroll
+    for (int y = 0; y < kSteps; ++y) cur[y] = nxt[y];
+    __builtin_amdgcn_s_waitcnt(0);                      // this thread's direct loads have landed
     __syncthreads();
     return true;
   };

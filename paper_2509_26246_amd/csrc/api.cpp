@@ -175,7 +175,7 @@ static int fwd_impl(const slimattn_params* p, const void* q, const void* k, cons
     // reference moves and the row's query tile holds other rows there.
     int longest = 0;
     for (int u = lo; u < hi; ++u)
-      if (off[u + 1] > off[u]) {                            // the longest is first, where it is longer than kSharedKeys
+      if (off[u + 1] > off[u]) {                            // the longest is first, if it is longer than kSharedKeys
         const QItem& it = t->per_unit[0].q_items[z][off[u]];
         const int rows = it.q_row0 + it.q_rows - it.kv_start;
         longest = rows > longest ? rows : longest;

@@ -5,7 +5,7 @@
 // the forward).  Two kernels:
 //   dQ    : a block owns 128 query rows of one head and walks the keys it can see;
 //           S^T = K Q^T, dP^T = V dO^T, dS^T = P^T o (dP^T - delta), dQ^T += K^T dS^T.
-//   dK/dV : (dkdv_wide_bf16.hip) a block owns 256 key rows of one KV head and walks every query row of
+//   dK/dV : (dkdv_wide_bf16.hip, dkdv_pair_bf16.hip) a block owns 256 or 128 key rows of one KV head and walks every query row of
 //           the launch scope at or after them, for every query head of the group, in a fixed order;
 //           S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS.  A key tile's gradient, which collects
 //           from every later slice of its sample (the inter-slice dependency of the backward pass in the

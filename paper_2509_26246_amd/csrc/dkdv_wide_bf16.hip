@@ -1,4 +1,4 @@
-// dK/dV for bf16 inputs at head dim 128 (64: dkdv_d64_bf16.hip): 256 key rows per block, one wave per SIMD, 64 key rows per wave.
+// dK/dV for bf16 inputs at head dim 128, long walks (short ones and 64: dkdv_pair_bf16.hip): 256 key rows per block, one wave per SIMD, 64 key rows per wave.
 //
 // What it computes is the dK/dV step of the backward (see bwd_bf16.hip): a block owns key rows of one
 // KV head and walks every query row of the launch scope at or after them, for every query head of the

@@ -26,8 +26,9 @@ struct QItem { int32_t q_row0, q_rows, kv_start, pad; };
 // heads, as far as the size of the head group allows.  The last tile of a sample leaves waves without rows where it has at most 64 (32); a
 // block costs nearly the same, so there it takes a second head (three more) against the same keys.  16K tokens, 32/8 heads of 128, forward / dQ,
 // us: samples of 64 rows 99 / 183 -> 72 / 125, 160 rows 109 / 203 -> 87 / 134, 272 rows 123 / 200 -> 103 / 161.  (The blocks that are saved must not
-// be launched: as blocks that end at once the 64-row samples took 125 / 203.)  Only tiles that see at most kSharedKeys keys: groups are heavy-first
-// in themselves only, and tiles of few keys do no harm at the end of a list with longer ones; in a list without, they come first.
+// be launched: as blocks that end at once the 64-row samples took 125 / 203.)  Only in lists without a tile of more than kSharedKeys keys: groups are
+// heavy-first in themselves only, tails first, and with long samples beside them that order costs more than the few tails save (forward of
+// a 32K pack of 18 samples by units: 1120 -> 1128 us).
 constexpr int kSharedKeys = 1024;
 struct QGroups {
   int n[3], share[3];
@@ -35,7 +36,7 @@ struct QGroups {
   static QGroups plain(int n_items) { return QGroups{{n_items, 0, 0}, {0, 0, 0}}; }
 };
 inline int query_share(const QItem& it) {
-  return it.q_row0 + it.q_rows - it.kv_start > kSharedKeys || it.q_rows > 64 ? 0 : it.q_rows > 32 ? 1 : 2;
+  return it.q_rows > 64 ? 0 : it.q_rows > 32 ? 1 : 2;
 }
 
 // A run of query rows [q_lo, q_hi) of one sample that belong to the launch scope.
@@ -138,7 +139,7 @@ struct Range { int32_t begin, end; };
 // A launch scope is either one unit or the whole list ("fused").  Its items are stored heavy-first.
 struct ScopeLists {
   std::vector<int32_t> q_off[kNumTileSizes];    // per-unit offsets into q_items (size n_units + 1)
-  std::vector<QItem> q_items[kNumTileSizes];    // unit-major, each unit heavy-first (128 rows: in each of its groups)
+  std::vector<QItem> q_items[kNumTileSizes];    // unit-major, each unit heavy-first (128 rows: in each of its groups, if it has any)
   std::vector<QGroups> q_groups;                // per unit, of the 128-row tiles
   std::vector<int32_t> kv_off[kNumTileSizes];
   std::vector<KvItem> kv_items[kNumTileSizes];

@@ -169,16 +169,17 @@ void append_scope(ScopeLists& L, const std::vector<Run>& runs, bool want_kv, boo
         for (int32_t a = r.q_lo; a < r.q_hi; a += B) qi.push_back(QItem{a, std::min(B, r.q_hi - a), r.kv_start, 0});
     auto keys = [](const QItem& it) { return it.q_row0 + it.q_rows - it.kv_start; };
     std::stable_sort(qi.begin(), qi.end(), [&](const QItem& a, const QItem& b) { return keys(a) > keys(b); });
-    if (B == 128) {                                          // ... in each of the groups
-      const bool tails_last = !qi.empty() && keys(qi[0]) > kSharedKeys;
-      QGroups g{{0, 0, 0}, {0, 1, 2}};
-      if (!tails_last) std::swap(g.share[0], g.share[2]);
-      std::vector<QItem>& sorted = tmp.qi_sorted;
-      sorted.clear();
-      for (int i = 0; i < 3; ++i)
-        for (const QItem& it : qi)
-          if (query_share(it) == g.share[i]) { sorted.push_back(it); ++g.n[i]; }
-      qi.swap(sorted);
+    if (B == 128) {
+      QGroups g = QGroups::plain((int)qi.size());
+      if (!qi.empty() && keys(qi[0]) <= kSharedKeys) {       // ... in each of the groups
+        g = QGroups{{0, 0, 0}, {2, 1, 0}};
+        std::vector<QItem>& sorted = tmp.qi_sorted;
+        sorted.clear();
+        for (int i = 0; i < 3; ++i)
+          for (const QItem& it : qi)
+            if (query_share(it) == g.share[i]) { sorted.push_back(it); ++g.n[i]; }
+        qi.swap(sorted);
+      }
       L.q_groups.push_back(g);
     }
     L.q_items[z].insert(L.q_items[z].end(), qi.begin(), qi.end());

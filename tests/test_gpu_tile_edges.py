@@ -159,8 +159,8 @@ def test_bf16_dkdv_long_walks():
     _fused_and_per_unit([510, 440, 330, 300, 290], 256, 16, 128, True, 1000)
 
 
-# Tails of at most 64 (32) rows, for which a block takes two (four) heads, as far as the group's size allows: on the edges, in lists with and
-# without samples of more than 1024 keys (tails last, tails first), tails only, a long sample's own tail included (one head)
+# Tails of at most 64 (32) rows, for which a block takes two (four) heads, as far as the group's size allows: on the edges, tails only, and beside a sample
+# of more than 1024 keys (whole list: one head per block; the units of the short samples: shared)
 @pytest.mark.parametrize("L", [[160, 33, 1, 192, 300], [32, 64, 65], [1153, 20, 190, 129]], ids=["short", "tails", "long"])
 @pytest.mark.parametrize("hq,hkv,d", [(2, 1, 64), (4, 1, 128), (8, 1, 64), (6, 2, 128), (3, 1, 64), (12, 2, 128)])
 def test_bf16_tails_shared_by_heads(L, hq, hkv, d):

@@ -106,9 +106,11 @@ inline int head_parts(int n_items, int n_kv_heads, int group, int longest_rows, 
 // what decides is the steps an item has on average.  71 launches, fused and by units, dK/dV and reduction, one-wave kernel / this one: 4 to 20
 // steps 23.8 / 16.1, 42.4 / 31.2, 158 / 106, 165 / 139 us; 36 steps 696 / 657; 84 to 94 steps 233 / 206, 340 / 309, 188 / 192, 375 /
 // 384; 110 to 117 steps 431 / 434, 418 / 380; 158 steps 653 / 702; 240 and more 806 / 859, 4706 / 5598.
-constexpr int kShortWalkSteps = 112;
+// With one query head per KV head the line lies at 68: 16K tokens of 32/32 heads, 50 steps 764 / 729, 68 steps 984 / 989, 88 steps 1259 / 1280; a pack of
+// 40/40 heads with one long sample, 78 steps 2112 / 2167.
 inline bool short_walks(int64_t walk_rows, int n_items, int group, int head_parts) {
-  return walk_rows * group <= (int64_t)kShortWalkSteps * 32 * n_items * head_parts;
+  const int64_t most = group == 1 ? 68 : 112;
+  return walk_rows * group <= most * 32 * n_items * head_parts;
 }
 
 // Blocks that share an item: `heads` by the query heads of the group, each of them `rows` by the steps of its walk (kernel of

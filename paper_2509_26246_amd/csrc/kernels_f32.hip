@@ -222,13 +222,13 @@ __global__ __launch_bounds__(256, 2) void fwd_f32_kernel(const float* __restrict
     else put_col<D>(ring.x[i % R], tv, cvoff, i - kRows);
   };
   {
-    const Rows32<D> tk = tile(k, wave), tv = tile(v, wave);
-    static_for<0, R>([&](auto ic) { load(ic, tk, tv); });
-  }
-  {
     const Rows32<D> tq(q, q0, q_end - q0, Hq, h);
     const int qvoff = row_voff<D>(Hq * D * 4, l32, half);
     put_own<D>(sh.own, tq, qvoff, scale * kLog2e, wave, lane);   // scores in log2 units
+  }
+  {
+    const Rows32<D> tk = tile(k, wave), tv = tile(v, wave);
+    static_for<0, R>([&](auto ic) { load(ic, tk, tv); });
   }
   __syncthreads();
   floatx16 acc[kNB<D>];
@@ -312,10 +312,6 @@ __global__ __launch_bounds__(256, 2) void dq_f32_kernel(
     if constexpr (i < 2 * kRows) ring.x[i % R] = load_row<D>(i < kRows ? tk : tv, rvoff, i % kRows);
     else put_col<D>(ring.x[i % R], tk, cvoff, i - 2 * kRows);
   };
-  {
-    const Rows32<D> tk = tile(k, wave), tv = tile(v, wave);
-    static_for<0, R>([&](auto ic) { load(ic, tk, tv); });
-  }
   const size_t stat_at = (size_t)h * T + min(q0 + l32, q_end - 1);
   const float row_lse = lse[stat_at];
   float dlt = 0.f;
@@ -332,6 +328,10 @@ __global__ __launch_bounds__(256, 2) void dq_f32_kernel(
     }
     dlt += xor32(dlt);
     if (wave == 0 && half == 0 && q0 + l32 < q_end) delta[stat_at] = dlt;
+  }
+  {
+    const Rows32<D> tk = tile(k, wave), tv = tile(v, wave);
+    static_for<0, R>([&](auto ic) { load(ic, tk, tv); });
   }
   __syncthreads();
   floatx16 acc[kNB<D>];

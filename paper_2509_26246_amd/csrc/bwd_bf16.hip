@@ -329,42 +329,38 @@ int launch_bwd_stat_bf16(const LaunchCtx& c, const void* o, const void* dO, cons
                          int n_items) {
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
-  const dim3 grid((unsigned)n_items, kStatSplit), block(256);
-  if (p.head_dim == 128)
-    hipLaunchKernelGGL(stat_bf16_kernel<128>, grid, block, 0, (hipStream_t)c.stream, (const bf16*)o, (const bf16*)dO, lse,
-                       (bf16x8*)stat3, items, (int)c.T, p.n_q_heads);
-  else
-    hipLaunchKernelGGL(stat_bf16_kernel<64>, grid, block, 0, (hipStream_t)c.stream, (const bf16*)o, (const bf16*)dO, lse,
-                       (bf16x8*)stat3, items, (int)c.T, p.n_q_heads);
-  return (int)hipGetLastError();
+  return in_runs(n_items, kStatSplit, [&](int first, int n) {
+    const dim3 grid((unsigned)n, kStatSplit), block(256);
+    hipLaunchKernelGGL(p.head_dim == 128 ? stat_bf16_kernel<128> : stat_bf16_kernel<64>, grid, block, 0, (hipStream_t)c.stream, (const bf16*)o,
+                       (const bf16*)dO, lse, (bf16x8*)stat3, items + first, (int)c.T, p.n_q_heads);
+    return (int)hipGetLastError();
+  });
 }
 
 namespace {
 template <int D, bool OWN>
-void launch_dq(const LaunchCtx& c, dim3 grid, dim3 block, const void* q, const void* k, const void* v, const void* dO, const void* o,
-               const float* lse, void* stat3, void* dQ, const QItem* items, const QBlocks& n_items) {
+int launch_dq(const LaunchCtx& c, const void* q, const void* k, const void* v, const void* dO, const void* o, const float* lse, void* stat3,
+              void* dQ, const QItem* items, const QGroups& groups) {
   const slimattn_params& p = *c.p;
-  hipLaunchKernelGGL((dq_bf16_kernel<D, OWN>), grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
-                     (const bf16*)v, (const bf16*)dO, (const bf16*)o, lse, (bf16x8*)stat3, (bf16*)dQ, items, n_items, (int)c.T,
-                     p.n_q_heads, p.n_kv_heads, p.scale);
+  const int g = p.n_q_heads / p.n_kv_heads, n_items = groups.total();
+  return in_runs(n_items, p.n_q_heads, [&](int first, int n) {
+    const QBlocks run = shared_blocks(n == n_items ? groups : QGroups::plain(n), p.n_kv_heads, g);
+    hipLaunchKernelGGL((dq_bf16_kernel<D, OWN>), dim3((unsigned)run.end[2]), dim3(256), 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
+                       (const bf16*)v, (const bf16*)dO, (const bf16*)o, lse, (bf16x8*)stat3, (bf16*)dQ, items + first, run, (int)c.T,
+                       p.n_q_heads, p.n_kv_heads, p.scale);
+    return (int)hipGetLastError();
+  });
 }
 }  // namespace
 
 int launch_bwd_dq_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, const void* dO, const void* o,
                        const float* lse, void* stat3, int own_stats, void* dQ, const QItem* items, const QGroups& groups) {
   if (groups.total() == 0) return 0;
-  const slimattn_params& p = *c.p;
-  const int g = p.n_q_heads / p.n_kv_heads;
-  const QBlocks n_items = shared_blocks(groups, p.n_kv_heads, g);
-  const dim3 grid((unsigned)n_items.end[2]), block(256);
-  if (p.head_dim == 128) {
-    if (own_stats) launch_dq<128, true>(c, grid, block, q, k, v, dO, o, lse, stat3, dQ, items, n_items);
-    else launch_dq<128, false>(c, grid, block, q, k, v, dO, o, lse, stat3, dQ, items, n_items);
-  } else {
-    if (own_stats) launch_dq<64, true>(c, grid, block, q, k, v, dO, o, lse, stat3, dQ, items, n_items);
-    else launch_dq<64, false>(c, grid, block, q, k, v, dO, o, lse, stat3, dQ, items, n_items);
-  }
-  return (int)hipGetLastError();
+  if (c.p->head_dim == 128)
+    return own_stats ? launch_dq<128, true>(c, q, k, v, dO, o, lse, stat3, dQ, items, groups)
+                     : launch_dq<128, false>(c, q, k, v, dO, o, lse, stat3, dQ, items, groups);
+  return own_stats ? launch_dq<64, true>(c, q, k, v, dO, o, lse, stat3, dQ, items, groups)
+                   : launch_dq<64, false>(c, q, k, v, dO, o, lse, stat3, dQ, items, groups);
 }
 
 namespace {

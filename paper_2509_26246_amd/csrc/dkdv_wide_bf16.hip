@@ -543,11 +543,12 @@ int launch_bwd_dkdv_wide_bf16(const LaunchCtx& c, const void* q, const void* k, 
                             float* parts, int head_parts) {
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
-  const dim3 grid((unsigned)(n_items * p.n_kv_heads * head_parts)), block(256);
-  hipLaunchKernelGGL(dkdv_wide_bf16_kernel_d128, grid, block, 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
-                     (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv, (bf16*)dK, (bf16*)dV, items, n_items,
-                     segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, head_parts);
-  return (int)hipGetLastError();
+  return in_runs(n_items, (int64_t)p.n_kv_heads * head_parts, [&](int first, int n) {
+    hipLaunchKernelGGL(dkdv_wide_bf16_kernel_d128, dim3((unsigned)(n * p.n_kv_heads * head_parts)), dim3(256), 0, (hipStream_t)c.stream, (const bf16*)q,
+                       (const bf16*)k, (const bf16*)v, (const bf16*)dO, (const bf16x8*)stat3, acc_dk, acc_dv, (bf16*)dK, (bf16*)dV, items + first, n,
+                       segs, (int)c.T, p.n_q_heads, p.n_kv_heads, p.scale, parts, head_parts);
+    return (int)hipGetLastError();
+  });
 }
 
 }  // namespace slimattn

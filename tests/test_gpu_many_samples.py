@@ -11,10 +11,10 @@ from paper_2509_26246_amd import harness as H
 pytestmark = pytest.mark.gpu
 
 
-# items x heads x 2 (fp32, both passes), items x heads (bf16 forward of short samples) and items x KV heads (dK/dV at head dim 64)
+# items x heads x 2 (fp32, both passes), items x heads (bf16 forward of short samples, dQ) and items x KV heads x 2 (dK/dV at head dim 64)
 # just reach 2^32 threads
 @pytest.mark.parametrize("T,hq,hkv,d,bf16,backward", [(131073, 64, 64, 16, False, True), (262145, 64, 8, 128, True, False),
-                                                      (131073, 64, 64, 64, True, True)])
+                                                      (131073, 64, 64, 64, True, True), (262145, 64, 64, 64, True, True)])
 def test_more_items_than_a_launch_has_blocks(T, hq, hkv, d, bf16, backward):
     dt = torch.bfloat16 if bf16 else torch.float32
     gen = torch.Generator(device="cuda").manual_seed(1)

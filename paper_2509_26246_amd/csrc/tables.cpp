@@ -257,7 +257,7 @@ int dkdv_class(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d) {
 int64_t head_part_blocks(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d) {
   const size_t room = SLIMATTN_STATIC_SCRATCH_BYTES, fixed = fixed_bytes(t, hq, hkv, d);
   if (fixed + align_up(row_slots(t, dkdv_class(t, hq, hkv, d)) * hkv * tile_bytes(d)) > room) return kHeadPartBlocks;
-  return std::min<int64_t>(kHeadPartBlocks, (int64_t)((room - fixed - 256) / tile_bytes(d)));
+  return std::min<int64_t>(kHeadPartBlocks, room - fixed > 256 ? (int64_t)((room - fixed - 256) / tile_bytes(d)) : 0);
 }
 
 }  // namespace slimattn

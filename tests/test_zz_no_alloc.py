@@ -83,3 +83,23 @@ def test_static_scratch_refuses_a_pack_that_does_not_fit():
     with pytest.raises(S.SlimAttnError) as e:
         S.bwd_static(x, x, x, x, x, x, tables, x, x, x, n_q_heads=hq, n_kv_heads=hkv, head_dim=d, dtype=S.BF16, scale=1.0)
     assert e.value.code == -6 and "scratch" in str(e.value)
+
+
+def test_static_scratch_takes_a_pack_that_just_fills_it():
+    """Accumulators and statistics fill the array to the last byte: nothing is left for partial tiles, and small units are not divided."""
+    hq, hkv, d, T = 4, 1, 64, 113359
+    aligned = lambda n: (n + 255) // 256 * 256
+    assert aligned(2 * T * hkv * d * 4) + aligned(T * hq * 4) + aligned(T * hq * 16) + 256 == S.STATIC_SCRATCH_BYTES
+    cu, sl = S.build_slices([256] * 442 + [207], 256)
+    units = S.build_units(cu, sl, "ROUND_ROBIN", m=64)                # of 7 short samples: launches that would be divided by query heads
+    tables = S.tables_create(cu, sl, *units, *units)
+    assert S.bwd_workspace_bytes(tables, hq, hkv, d) == S.STATIC_SCRATCH_BYTES
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    new = lambda h, f: (f * torch.randn((T, h, d), generator=gen, device="cuda")).to(torch.bfloat16)
+    out = lambda h: torch.empty((T, h, d), dtype=torch.bfloat16, device="cuda")
+    prob = H.Problem(tables, hq, hkv, d, S.BF16, d ** -0.5, new(hq, 0.5), new(hkv, 0.5), new(hkv, 0.5), new(hq, 0.1), out(hq),
+                     torch.empty((hq, T), device="cuda"), out(hq), out(hkv), out(hkv), torch.empty(S.STATIC_SCRATCH_BYTES, dtype=torch.uint8, device="cuda"))
+    prob.forward()
+    for flags in (0, S.FLAG_PER_UNIT_LAUNCH):
+        for which, a, b in zip(("dQ", "dK", "dV"), *_both(prob, flags)):
+            assert np.array_equal(a, b), f"flags {flags}: {which} differs"

@@ -188,12 +188,14 @@ __device__ __forceinline__ void meet(Partials<D>& p, const floatx16 (&acc)[kNB<D
   });
 }
 
-// The lists are heavy-first, and two or more blocks share a compute unit from the start.  The second round of 256 blocks (what there is of it)
-// runs backwards, so that the longest walks share theirs with the shortest of the round (one sample of 4096 rows, dK/dV 718 -> 515 us; 2000 rows,
-// forward 100 -> 76).  (The low three bits, the XCD, stay.)
+// The lists are heavy-first, and two or more blocks share a compute unit from the start.  The second round of 256 blocks runs backwards, so
+// that the longest walks share theirs with the shortest of the round (one sample of 4096 rows, dK/dV 718 -> 515 us; 2000 rows, forward 100
+// -> 76).  Where that round is not full, the longest walks go to the compute units that get no second block (9 samples of 512 rows, 2/2 heads of 128,
+// 288 blocks, forward, dQ, dK/dV: 27.8, 43.9, 49.6 with the first 32 blocks beside a second one, now 23.9, 35.2, 41.4).  (The low three bits, the XCD, stay.)
 __device__ __forceinline__ int paired(int block) {
-  const int end = min((int)gridDim.x, 512) & ~7;
-  return block >= 256 && block < end ? 256 + end - 8 - (block & ~7) + (block & 7) : block;
+  const int end = min((int)gridDim.x, 512) & ~7, second = max(end - 256, 0);
+  if (second == 0 || block >= end) return block;
+  return block >= 256 ? 256 + end - 8 - (block & ~7) + (block & 7) : block < second ? 256 - second + block : block - second;
 }
 
 template <int D>

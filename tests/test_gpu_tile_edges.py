@@ -69,6 +69,13 @@ def test_fp32_tile_edges(L, hq, hkv, d):
     assert all(torch.equal(a, b) for a, b in zip(*first))
 
 
+# launches of more than 256 and fewer than 512 blocks of 32 rows, a multiple of 8 and not, dK/dV undivided: a second block for some compute units
+@pytest.mark.parametrize("L,h", [([300, 333, 395], 8), ([700, 1013], 9), ([1010, 999], 8)])
+@pytest.mark.parametrize("d", [16, 128])
+def test_fp32_partial_second_round(L, h, d):
+    _fused_and_per_unit(L, h, h, d, False, 4096)
+
+
 # few key tiles for the chip and several query heads per KV head: every tile's walk divided by heads, group sizes that the
 # number of parts does not divide included, beside tiles divided by rows (4096 rows on one KV head)
 @pytest.mark.parametrize("L,hq,hkv,d", [([511, 37, 200, 128], 8, 1, 128), ([300, 257, 1], 6, 1, 64), ([900, 255, 256], 7, 1, 128),

@@ -551,12 +551,19 @@ int launch_bwd_dkdv_f32(const LaunchCtx& c, const float* q, const float* k, cons
   if (n_items == 0) return 0;
   const slimattn_params& p = *c.p;
   const int64_t blocks = 2 * (int64_t)n_items * p.n_kv_heads;
-  // Few blocks: the first tiles of the longest sample decide the launch, so every walk is divided in two where that is worth
-  // the second launch (about 5 us; a step is 3 to 7 us at head dims 64 to 128).  While both parts of all blocks have a place on the chip
-  // at once, from two steps of a wave on: 876 rows, 2/2 heads of 64, 4 steps 23.0 -> 17.3 us, of 128, 38.7 -> 27.1; 1000 rows, 8/2 heads of 128, 16 steps
-  // 127.9 -> 71.8.  With more blocks the longest walk has to stand out more: 280 blocks, 9 steps 103 -> 78, 2 steps 41 -> 45; 560 blocks, 9 steps 65 -> 81.
+  // Few blocks: the first tiles of the longest sample decide the launch, so every walk is divided in two where that is worth the second launch (about
+  // 5 us; a step of a wave is 2 to 3 us at head dims 16 and 32, 3 to 7 at 64 and 128) and the second parts' blocks.  dK/dV undivided / divided, us:
+  //   both parts of all blocks on compute units of their own, from two steps on: 48 blocks, 1 step 7.2 / 9.1 at 16, 15.6 / 18.0 at 128; 2 steps 9.1 / 9.1,
+  //   23.7 / 19.4; 4 steps 12.7 / 11.0, 38.5 / 26.2; 876 rows, 2/2 heads of 64, 23.0 / 17.3;
+  //   up to 256 blocks, whose second parts share compute units, from four: 136 blocks, 2 steps 9.3 / 11.1, 23.4 / 29.3; 4 steps 13.0 / 11.5, 38.4 / 30.3;
+  //   more blocks: where the longest walk stands out from a compute unit's share of all of them, the less the longer it is.  At 128, steps of the longest and of
+  //   the share: 264 blocks, 12 and 6.6, 1.37 times as fast; 288 blocks, 4 and 2.2, 42 / 62; 384 blocks, 8 and 6, 72 / 93; 16 and 12, 135 / 147; 64 and 48,
+  //   518 / 425; 512 blocks, 16 and 16, 142 / 176; 520 blocks, 22 and 13, 1.10 times as fast; 528 blocks, 12 and 11, 0.89.  852 launches of more than 256
+  //   blocks take 0.7 % longer than each with the better choice; by steps alone, from 16 on and up to 768 blocks, 4.4 %.
   const int64_t steps = (int64_t)longest * (p.n_q_heads / p.n_kv_heads) / (kSub * kWaves);
-  const int parts = blocks <= 256 ? (steps >= 2 ? 2 : 1) : blocks <= 768 && 48 * steps >= blocks ? 2 : 1;
+  const double share = (double)c.T * c.mean_keys * p.n_q_heads / (kSub * kSub * kWaves * 256);
+  const bool divided = blocks <= 128 ? steps >= 2 : blocks <= 256 ? steps >= 4 : steps >= 6 && steps * steps >= share * (0.6 * steps + 9);
+  const int parts = divided ? 2 : 1;
   const int e = in_runs(n_items, 2 * (int64_t)p.n_kv_heads, [&](int first, int n) -> int {
     const dim3 grid((unsigned)(2 * n * p.n_kv_heads * parts)), block(64 * kWaves);
     DISPATCH_D(p.head_dim, hipLaunchKernelGGL(dkdv_f32_kernel<D>, grid, block, 0, (hipStream_t)c.stream, q, k, v, dO, lse, delta,

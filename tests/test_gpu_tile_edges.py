@@ -76,6 +76,14 @@ def test_fp32_partial_second_round(L, h, d):
     _fused_and_per_unit(L, h, h, d, False, 4096)
 
 
+# fp32 walks divided and not, on either side of the rule's lines: 128 blocks of up to 2 steps and 132; 136 of 4; of more, 272 blocks of up to 6 steps (a compute
+# unit's share is 2.5), 320 of 8 (4.3), 400 of 8 (5.6, undivided)
+@pytest.mark.parametrize("L,hq,hkv", [([256] * 8, 2, 2), ([256] * 8 + [64], 2, 2), ([512, 512, 64], 4, 4), ([768, 256, 64], 8, 8), ([640, 384, 64], 8, 8),
+                                      ([1024, 256], 8, 8), ([1024, 1024, 512], 5, 5)])
+def test_fp32_walks_divided_in_two(L, hq, hkv):
+    _fused_and_per_unit(L, hq, hkv, 32, False, 4096)
+
+
 # few key tiles for the chip and several query heads per KV head: every tile's walk divided by heads, group sizes that the
 # number of parts does not divide included, beside tiles divided by rows (4096 rows on one KV head)
 @pytest.mark.parametrize("L,hq,hkv,d", [([511, 37, 200, 128], 8, 1, 128), ([300, 257, 1], 6, 1, 64), ([900, 255, 256], 7, 1, 128),

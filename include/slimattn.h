@@ -303,8 +303,9 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
 void slimattn_tables_destroy(slimattn_tables* t);
 
 /* Counts held by a handle: what = 0 tokens, 1 samples, 2 slices, 3 forward units, 4 backward units,
- * 5..8: 256-row key tiles of the whole-list scope whose dK/dV work is divided among several blocks
- * when the launch has 1, 2, 4, 8 KV heads (heavy-tile balancing; informational). */
+ * 5..8: 256-row key tiles of the whole-list scope whose dK/dV work is divided among several blocks by query
+ * rows when the launch has 1, 2, 4, 8 KV heads of 128 (heavy-tile balancing; informational; for any shape:
+ * slimattn_bwd_dkdv_plan). */
 int64_t slimattn_tables_count(const slimattn_tables* t, int what);
 
 /* Bytes of DEVICE scratch slimattn_bwd needs (fp32 dK/dV accumulators, the per-row statistics in
@@ -372,6 +373,14 @@ int slimattn_bwd(const slimattn_params* p, const void* q, const void* k, const v
  * footprint simulation -- KV gradients are managed per slice).  Over all units the ranges partition
  * [0, T).  HOST arrays; ECAP if cap < n_ranges (n_ranges is still set). */
 int slimattn_bwd_released_rows(const slimattn_tables* t, int32_t unit, int32_t* ranges, int32_t cap, int32_t* n_ranges);
+
+/* How slimattn_bwd runs the bf16 dK/dV launch of backward unit `unit` (of the whole list in one launch: -1) at this
+ * shape (informational): plan [4], HOST: key rows per block (256: one wave per SIMD; 128: two or three blocks per
+ * compute unit); blocks that share a 256-row key tile by query heads of the group; blocks that share each of those
+ * by query rows; key tiles that are divided among blocks by query rows beforehand.  EINVAL on a shape that
+ * slimattn_shape_supported refuses or a unit that is not in the list. */
+int slimattn_bwd_dkdv_plan(const slimattn_tables* t, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t unit,
+                           int32_t* plan);
 
 /* For callers that cannot allocate device memory and have no workspace to pass: code under HIP graph
  * capture, tight serving or training loops, harnesses that forbid hipMalloc.  Same computation, arguments,

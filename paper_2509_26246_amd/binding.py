@@ -20,7 +20,7 @@ EXPORTED_SYMBOLS = [
     "slimattn_build_slices", "slimattn_build_slices_from_bounds", "slimattn_build_units", "slimattn_validate",
     "slimattn_solve_partition", "slimattn_solve_bottlenecks", "slimattn_dag_timeline", "slimattn_dag_build_1f1b", "slimattn_dag_memory", "slimattn_dag_buffers_1f1b", "slimattn_candidate_unit_counts", "slimattn_search_unit_count", "slimattn_shape_supported", "slimattn_slice_pairs", "slimattn_flops_fwd", "slimattn_flops_bwd", "slimattn_tables_create", "slimattn_tables_create_async",
     "slimattn_tables_destroy", "slimattn_tables_count", "slimattn_bwd_workspace_bytes", "slimattn_fwd", "slimattn_fwd_divided_counts",
-    "slimattn_bwd", "slimattn_bwd_static", "slimattn_bwd_released_rows", "slimattn_strerror", "slimattn_last_hip_error", "slimattn_version", "slimattn_profile_enable",
+    "slimattn_bwd", "slimattn_bwd_static", "slimattn_bwd_released_rows", "slimattn_bwd_dkdv_plan", "slimattn_strerror", "slimattn_last_hip_error", "slimattn_version", "slimattn_profile_enable",
     "slimattn_profile_read", "slimattn_profile_read_launches"]
 KERNEL_CLASSES = ["fwd", "delta", "dq", "dkdv", "reduce", "unused", "fwd_call", "bwd_call"]
 
@@ -98,6 +98,7 @@ def load_library():
     lib.slimattn_bwd.argtypes = [C.POINTER(_Params)] + [vp] * 12
     lib.slimattn_bwd_static.argtypes = [C.POINTER(_Params)] + [vp] * 11
     lib.slimattn_bwd_released_rows.argtypes = [vp, C.c_int32, i32p, C.c_int32, i32p]
+    lib.slimattn_bwd_dkdv_plan.argtypes = [vp, C.c_int32, C.c_int32, C.c_int32, C.c_int32, i32p]
     lib.slimattn_fwd_divided_counts.argtypes = [C.POINTER(C.c_int64)]
     lib.slimattn_strerror.argtypes = [C.c_int]
     lib.slimattn_strerror.restype = C.c_char_p
@@ -457,6 +458,16 @@ def bwd_released_rows(tables: Tables, unit: int) -> np.ndarray:
     if rc != 0:
         raise SlimAttnError(rc, "slimattn_bwd_released_rows")
     return out[:n.value].copy()
+
+
+def bwd_dkdv_plan(tables: Tables, n_q_heads: int, n_kv_heads: int, head_dim: int, unit: int = -1) -> Tuple[int, int, int, int]:
+    """The bf16 dK/dV launch of a backward unit (-1: the whole list): (key rows per block, blocks per key tile by query heads, by query rows,
+    key tiles divided by query rows beforehand)."""
+    plan = np.zeros(4, np.int32)
+    rc = load_library().slimattn_bwd_dkdv_plan(tables.handle, n_q_heads, n_kv_heads, head_dim, unit, _p(plan))
+    if rc != 0:
+        raise SlimAttnError(rc, "slimattn_bwd_dkdv_plan")
+    return tuple(int(x) for x in plan)
 
 
 STATIC_SCRATCH_BYTES = 64 << 20

@@ -223,8 +223,6 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   // bf16 path: -lse*log2e and -delta as bf16 triples, 16 bytes per row and head (written by the dQ kernel, read by the dK/dV kernel)
   void* stat3 = (char*)delta + align_up(T * p->n_q_heads * sizeof(float));
   float* parts = (float*)((char*)stat3 + align_up(T * p->n_q_heads * 16));              // partial tiles of divided key tiles
-  const int sc = dkdv_class(t, p->n_q_heads, p->n_kv_heads, p->head_dim);
-  const int64_t head_blocks = head_part_blocks(t, p->n_q_heads, p->n_kv_heads, p->head_dim);
   const int n_units = t->n_units[1];
   const bool whole = lo == 0 && hi == n_units;
   const bool per_unit = (p->flags & SLIMATTN_FLAG_PER_UNIT_LAUNCH) != 0;
@@ -269,8 +267,9 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   // divide every item by query heads and steps, and then every tile is reduced
   auto run_dkdv_split = [&](const ScopeLists& L, const DeviceLists& D, int u) -> int {
     const int tile_rows = dkdv_kv_tile(p->dtype, p->head_dim), ti = split_tile_index(tile_rows);
-    const int a = L.split_rng[ti][sc][u].begin, b = L.split_rng[ti][sc][u].end;
-    const DkdvParts by = dkdv_parts(b - a, p->n_kv_heads, p->n_q_heads / p->n_kv_heads, L.walk_rows[ti][u], L.longest[ti][sc][u], p->head_dim, head_blocks);
+    const DkdvLaunch launch = dkdv_launch(t, L, u, p->n_q_heads, p->n_kv_heads, p->head_dim);
+    const DkdvParts& by = launch.by;
+    const int sc = launch.cls, a = L.split_rng[ti][sc][u].begin, b = L.split_rng[ti][sc][u].end;
     int e = run_dkdv(D.split_items[ti] + a, b - a, D.segs, by);
     if (e != 0) return e;
     if (by.total() > 1) {

@@ -81,17 +81,17 @@ inline int split_class(int n_kv_heads) {
   while (c + 1 < kNumSplitClasses && (1 << c) <= n_kv_heads) ++c;
   return c;
 }
-// The class of a launch.  At head dim 64 six half items share a compute unit, and few KV heads leave little beside the divided tiles to even the
+// The class of a launch (dkdv_launch below).  At head dim 64 six half items share a compute unit, and few KV heads leave little beside the divided tiles to even the
 // parts out: 1 to 3 of them take the class below (one 32K sample of 8/1 heads 2329 -> 2153 us, a 32K pack of long ones 489 -> 466), unless
 // its partial tiles alone would lift the workspace above the built-in scratch array's size.  (From 4 on no gain: 32K pack of 32/8 heads 2783 -> 2818.)
-int dkdv_class(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d);
 
 // Blocks of a dK/dV launch that share one item by query heads: a launch of few items (one small unit, a small pack, few KV
 // heads) leaves most compute units idle while each of its blocks walks the item's rows once per head of the group.  Every
 // block then stores a partial tile and all tiles go through the reduction, so the walk that is saved has to be worth
 // that: a step takes about 1.35 us, the reduction launch and the partial tiles about 15 (876-row pack, 8 heads on one KV
 // head: 5 blocks of up to 128 steps, 177 us; 40 blocks of up to 16, 40 us and 6 for the reduction).
-// max_blocks: one per compute unit, or as many partial tiles as the workspace has room for (head_part_blocks).
+// max_blocks: one per compute unit, or fewer where their partial tiles would lift a workspace that fits the built-in scratch array above
+// its size (slimattn_bwd_static then still takes the pack, and computes the same).
 constexpr int kHeadPartBlocks = 256;
 inline int head_parts(int n_items, int n_kv_heads, int group, int longest_rows, int64_t max_blocks) {
   const int64_t blocks = (int64_t)n_items * n_kv_heads;
@@ -290,9 +290,10 @@ int launch_bwd_dkdv_pair_bf16(const LaunchCtx&, const void* q, const void* k, co
 int launch_bwd_reduce_bf16(const LaunchCtx&, const float* parts, float* acc_dk, float* acc_dv, void* dK, void* dV,
                            const KvReduce* items, int n_items, int tile_rows, int per_slot);
 
-// Most partial tiles a launch divided by query heads may store: kHeadPartBlocks, or fewer where they would lift a workspace
-// that fits the built-in scratch array above its size (slimattn_bwd_static then still takes the pack, and computes the same).
-int64_t head_part_blocks(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d);
+// How the bf16 dK/dV launch of a scope runs, unit u of t->per_unit[1] or t->fused (u = 0): the division class of its items and the blocks that
+// share one.  The launch, the workspace's size and slimattn_bwd_dkdv_plan all go by it.
+struct DkdvLaunch { int cls; DkdvParts by; };
+DkdvLaunch dkdv_launch(const slimattn_tables* t, const ScopeLists& scope, int u, int32_t hq, int32_t hkv, int32_t d);
 
 // Looks up the built-in scratch array of slimattn_bwd_static on the current device (so that the first such call
 // finds it ready); returns a SLIMATTN_* code.

@@ -244,7 +244,6 @@ size_t fixed_bytes(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d)
 }
 size_t row_slots(const slimattn_tables* t, int c) { return (size_t)std::max(t->per_unit[1].max_slots[0][c], t->fused.max_slots[0][c]); }
 size_t tile_bytes(int32_t d) { return (size_t)2 * kSplitTileRows[0] * d * sizeof(float); }
-}  // namespace
 
 int dkdv_class(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d) {
   const int c = split_class(hkv);
@@ -258,6 +257,12 @@ int64_t head_part_blocks(const slimattn_tables* t, int32_t hq, int32_t hkv, int3
   const size_t room = SLIMATTN_STATIC_SCRATCH_BYTES, fixed = fixed_bytes(t, hq, hkv, d);
   if (fixed + align_up(row_slots(t, dkdv_class(t, hq, hkv, d)) * hkv * tile_bytes(d)) > room) return kHeadPartBlocks;
   return std::min<int64_t>(kHeadPartBlocks, room - fixed > 256 ? (int64_t)((room - fixed - 256) / tile_bytes(d)) : 0);
+}
+}  // namespace
+
+DkdvLaunch dkdv_launch(const slimattn_tables* t, const ScopeLists& scope, int u, int32_t hq, int32_t hkv, int32_t d) {
+  const int c = dkdv_class(t, hq, hkv, d), n_items = scope.split_rng[0][c][u].end - scope.split_rng[0][c][u].begin;
+  return {c, dkdv_parts(n_items, hkv, hq / hkv, scope.walk_rows[0][u], scope.longest[0][c][u], d, head_part_blocks(t, hq, hkv, d))};
 }
 
 }  // namespace slimattn
@@ -454,15 +459,27 @@ int slimattn_bwd_released_rows(const slimattn_tables* t, int32_t unit, int32_t* 
 size_t slimattn_bwd_workspace_bytes(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d) {
   if (!t || hq < 1 || hkv < 1 || d < 1) return 0;
   const int c = dkdv_class(t, hq, hkv, d);
-  const int64_t max_blocks = head_part_blocks(t, hq, hkv, d);
   size_t slots = row_slots(t, c);
   for (const ScopeLists* L : {&t->per_unit[1], &t->fused})
-    for (size_t u = 0; u < L->longest[0][c].size(); ++u) {
-      const int n = L->split_rng[0][c][u].end - L->split_rng[0][c][u].begin;
-      const int parts = dkdv_parts(n, hkv, hq / hkv, L->walk_rows[0][u], L->longest[0][c][u], d, max_blocks).total();
-      if (parts > 1) slots = std::max(slots, (size_t)n * parts);
+    for (size_t u = 0; u < L->walk_rows[0].size(); ++u) {
+      const int parts = dkdv_launch(t, *L, (int)u, hq, hkv, d).by.total();
+      if (parts > 1) slots = std::max(slots, (size_t)(L->split_rng[0][c][u].end - L->split_rng[0][c][u].begin) * parts);
     }
   return fixed_bytes(t, hq, hkv, d) + align_up(slots * hkv * tile_bytes(d));
+}
+
+int slimattn_bwd_dkdv_plan(const slimattn_tables* t, int32_t hq, int32_t hkv, int32_t d, int32_t unit, int32_t* plan) {
+  if (!t || !plan || unit < -1 || unit >= t->n_units[1]) return SLIMATTN_EINVAL;
+  const int rc = slimattn_shape_supported(t->total_tokens, t->max_sample_len, hq, hkv, d, SLIMATTN_BF16);
+  if (rc != SLIMATTN_OK) return rc;
+  const ScopeLists& scope = unit < 0 ? t->fused : t->per_unit[1];
+  const int u = unit < 0 ? 0 : unit;
+  const DkdvLaunch launch = dkdv_launch(t, scope, u, hq, hkv, d);
+  plan[0] = launch.by.pair ? 128 : 256;
+  plan[1] = launch.by.heads;
+  plan[2] = launch.by.rows;
+  plan[3] = scope.reduce_off[0][launch.cls][u + 1] - scope.reduce_off[0][launch.cls][u];
+  return SLIMATTN_OK;
 }
 
 }  // extern "C"

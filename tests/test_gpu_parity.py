@@ -185,8 +185,8 @@ def test_bf16_divided_key_tiles(hq, hkv, d):
     scale = d ** -0.5
     ref = _oracle(q, k, v, dO, cu, scale)
     prob = H.make_problem(q, k, v, dO, cu, sl, fu, bu, bf16=True, scale=scale)
-    cls = {1: 0, 2: 1}[hkv]
-    assert prob.tables.count(5 + cls) > 0, "no key tile was divided: the case does not cover the reduction path"
+    for unit in (-1, 0, 1):
+        assert S.bwd_dkdv_plan(prob.tables, hq, hkv, d, unit)[3] > 0, "no key tile was divided: the case does not cover the reduction path"
     _run_modes(prob, ref, TOL_O, TOL_G, f"divided {hq}/{hkv}/{d}")
     runs = []
     for flags in (0, 0, S.FLAG_PER_UNIT_LAUNCH, S.FLAG_PER_UNIT_LAUNCH):
@@ -196,6 +196,28 @@ def test_bf16_divided_key_tiles(hq, hkv, d):
     for a, b in ((runs[0], runs[1]), (runs[2], runs[3])):
         for x, y in zip(a, b):
             assert np.array_equal(x, y), "dK/dV differ between two identical runs"
+
+
+@pytest.mark.parametrize("L,hq,hkv,d", [([4500, 300, 64], 4, 1, 64), ([4500, 300, 64], 4, 2, 128), ([511, 37, 200, 128], 8, 1, 128), ([300, 64], 32, 32, 64)])
+def test_dkdv_plan_is_what_runs(L, hq, hkv, d):
+    """slimattn_bwd_dkdv_plan against the launches: a reduction exactly where blocks share key tiles or tiles are divided, whole list and units."""
+    cu, sl, fu, bu = _tables(L, 512, ("PER_SAMPLE", {}), ("ROUND_ROBIN", {"m": 2, "descending": True}))
+    q, k, v, dO = _draw(sum(L), hq, hkv, d, 3, True, 0.5, 0.1)
+    prob = H.make_problem(q, k, v, dO, cu, sl, fu, bu, bf16=True, scale=d ** -0.5)
+    prob.forward()
+    reduces = lambda unit: int(S.bwd_dkdv_plan(prob.tables, hq, hkv, d, unit)[1:3] != (1, 1) or S.bwd_dkdv_plan(prob.tables, hq, hkv, d, unit)[3] > 0)
+    for flags, units in ((0, [-1]), (S.FLAG_PER_UNIT_LAUNCH, list(range(prob.tables.n_bwd_units)))):
+        S.profile_enable(64)
+        prob.backward(flags=flags)
+        launches = S.profile_read()["reduce"][1]
+        S.profile_enable(0)
+        assert launches == sum(reduces(u) for u in units)
+    if d == 128:                                        # what slimattn_tables_count reports
+        assert prob.tables.count({1: 5, 2: 6}[hkv]) == S.bwd_dkdv_plan(prob.tables, hq, hkv, d)[3]
+    for bad in ((3, 2, d, -1), (hq, hkv, 96, -1), (hq, hkv, d, prob.tables.n_bwd_units), (hq, hkv, d, -2)):
+        with pytest.raises(S.SlimAttnError) as e:
+            S.bwd_dkdv_plan(prob.tables, *bad)
+        assert e.value.code == -1
 
 
 @pytest.mark.parametrize("hq,hkv,d", [(4, 2, 128), (2, 1, 64), (3, 1, 128)])

@@ -102,14 +102,18 @@ inline int head_parts(int n_items, int n_kv_heads, int group, int longest_rows, 
 
 // Whether a dK/dV launch at head dim 128 takes the kernel with 128 keys and two blocks per compute unit (dkdv_pair_bf16.hip): what an item costs
 // beside its steps is then hidden by the other block, and steps before a wave's keys are skipped; a step of the one-wave kernel
-// (dkdv_wide_bf16.hip) is cheaper.  Per 256 keys the one-wave kernel takes about 22 us and 1.5 per step, the other 5 and 1.75, so
-// what decides is the steps an item has on average.  71 launches, fused and by units, dK/dV and reduction, one-wave kernel / this one: 4 to 20
-// steps 23.8 / 16.1, 42.4 / 31.2, 158 / 106, 165 / 139 us; 36 steps 696 / 657; 84 to 94 steps 233 / 206, 340 / 309, 188 / 192, 375 /
-// 384; 110 to 117 steps 431 / 434, 418 / 380; 158 steps 653 / 702; 240 and more 806 / 859, 4706 / 5598.
-// With one query head per KV head the line lies at 68: 16K tokens of 32/32 heads, 50 steps 764 / 729, 68 steps 984 / 989, 88 steps 1259 / 1280; a pack of
-// 40/40 heads with one long sample, 78 steps 2112 / 2167.
-inline bool short_walks(int64_t walk_rows, int n_items, int group, int head_parts) {
-  const int64_t most = group == 1 ? 68 : 112;
+// (dkdv_wide_bf16.hip) is cheaper.  What decides is therefore the steps an item has on average (its last part's where blocks share it).  Where
+// the lines lie is measured, 16K to 32K tokens in samples of one length, one-wave kernel / this one, us:
+//   one query head per KV head: 36 steps 883 / 829 (32 KV heads), 60 steps alike (18 launches, this one 0.99 of the other on average, 0.90 to 1.05), 68 steps 483
+//   / 494, 229 / 242 (8);
+//   two: 56 steps 857 / 815 (16), 72 and 80 steps alike, 88 steps 283 / 302 (4), 1202 / 1196, 112 steps 333 / 354, 1440 / 1469;
+//   three and more: 84 steps 793 / 776 (10 KV heads of 3), 112 steps 829 / 768 (8 of 4), 247 / 256 (2 of 4), 120 steps 572 / 517 (5 of 6), 144 steps
+//   984 / 997 (8 of 4).
+// With one or two heads the lines are for launches of more than 256 items and KV heads.  Below that the one-wave kernel leaves compute units without a block, and
+// the halves pay at any of these lengths: two heads, 112 steps, 2 samples on 4 KV heads 148 / 128, 4 on one 108 / 84.
+inline bool short_walks(int64_t walk_rows, int n_items, int n_kv_heads, int group, int head_parts) {
+  const bool fills = (int64_t)n_items * n_kv_heads * head_parts > 256;
+  const int64_t most = group > 2 ? 112 : group == 2 ? (fills ? 80 : 112) : fills ? 64 : 68;
   return walk_rows * group <= most * 32 * n_items * head_parts;
 }
 
@@ -126,7 +130,7 @@ struct DkdvParts {
 };
 inline DkdvParts dkdv_parts(int n_items, int n_kv_heads, int group, int64_t walk_rows, int longest_rows, int head_dim, int64_t max_blocks) {
   DkdvParts p{head_parts(n_items, n_kv_heads, group, longest_rows, max_blocks), 1, false};
-  p.pair = head_dim == 64 || short_walks(walk_rows, n_items, group, p.heads);
+  p.pair = head_dim == 64 || short_walks(walk_rows, n_items, n_kv_heads, group, p.heads);
   const int64_t blocks = (int64_t)n_items * n_kv_heads * p.heads, tiles = max_blocks < kRowPartTiles ? max_blocks : kRowPartTiles;
   if (p.pair && blocks > 0 && blocks <= tiles / 2) {
     const int64_t steps = (int64_t)longest_rows * group / p.heads / 32;

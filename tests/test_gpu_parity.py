@@ -220,6 +220,15 @@ def test_dkdv_plan_is_what_runs(L, hq, hkv, d):
         assert e.value.code == -1
 
 
+# the kernel of a dK/dV launch at head dim 128 by the steps of its walks (steps per key tile, one query head per KV head: 60, 68; two: 80, 88, and 112 where
+# the launch leaves compute units without a block; four: 112, 144)
+@pytest.mark.parametrize("L,hq,hkv,keys", [([3584] * 4, 32, 32, 128), ([4096] * 4, 32, 32, 256), ([2304] * 7, 32, 16, 128), ([2560] * 6, 32, 16, 256),
+                                           ([3328] * 2, 8, 4, 128), ([1536] * 10, 32, 8, 128), ([2048] * 8, 32, 8, 256)])
+def test_dkdv_kernel_by_length_of_walks(L, hq, hkv, keys):
+    cu, sl, fu, bu = _tables(L, 4096, ("ALL", {}), ("ALL", {}))
+    assert S.bwd_dkdv_plan(S.tables_create(cu, sl, *fu, *bu), hq, hkv, 128)[:3] == (keys, 1, 1)
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(4, 2, 128), (2, 1, 64), (3, 1, 128)])
 @pytest.mark.parametrize("jump", [6.0, 40.0, 200.0])
 def test_bf16_forward_reference_moves(hq, hkv, d, jump):

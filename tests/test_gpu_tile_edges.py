@@ -1,12 +1,13 @@
 """GPU parity at the sizes where a kernel's tiling can go wrong: tile edges, remainders and the ends of each variant's
 range, against the CPU fp64 oracle.  Tolerances as in test_gpu_parity.py (max-abs: fp32 1e-5; bf16 2e-2 on O and lse,
-5e-2 on the gradients)."""
+5e-2 on the gradients), and relative to the result in every 32 rows (gradient_bounds.py)."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2509_26246_amd as S
 import workloads as W
+from gradient_bounds import REL_BF16, REL_F32, relative_error
 from oracle import attention as A
 from paper_2509_26246_amd import harness as H
 
@@ -43,6 +44,9 @@ def _check(prob, ref, bf16, tag):
         err = float(np.max(np.abs(got.astype(np.float64) - want)))
         tol = 1e-5 if not bf16 else 2e-2 if name in ("o", "lse") else 5e-2
         assert err <= tol, f"{tag} {name}: max-abs {err:.3e} > {tol}"
+        if name != "lse":
+            rel = relative_error(name, got, want)
+            assert rel <= (REL_BF16 if bf16 else REL_F32), f"{tag} {name}: {rel:.3e} of the result in a block of rows"
 
 
 def _fused_and_per_unit(L, hq, hkv, d, bf16, slice_size):
@@ -93,16 +97,17 @@ def test_bf16_key_tiles_divided_by_heads(L, hq, hkv, d):
 
 
 # walks divided by steps too: over several runs of query rows (every third slice, ragged), parts that begin inside a run and at its end, halves of
-# an item with fewer steps than parts
-@pytest.mark.parametrize("hq,hkv,d", [(3, 1, 128), (8, 2, 64), (1, 1, 128)])
-def test_bf16_key_tiles_divided_by_steps(hq, hkv, d):
+# an item with fewer steps than parts; beside a division by heads and without one
+@pytest.mark.parametrize("L,hq,hkv,d,whole,units", [([1100, 290], 3, 1, 128, (3, 3), [(3, 3), (3, 3), (3, 1)]), ([1100, 290], 8, 2, 64, (4, 1), [(4, 3), (4, 2), (4, 1)]),
+                                                    ([300, 290], 2, 1, 128, (1, 4), [(1, 1)] * 3)])
+def test_bf16_key_tiles_divided_by_steps(L, hq, hkv, d, whole, units):
     r = np.random.default_rng(5)
-    L = [1100, 290]
     q, k, v, dO = (W.bf16_round(r.standard_normal((sum(L), h, d), dtype=np.float32) * np.float32(x)) for h, x in ((hq, .5), (hkv, .5), (hkv, .5), (hq, .1)))
     cu, sl = S.build_slices(L, 97)
     fu = S.build_units(cu, sl, "PREFIX_FILL", m=4, w_quad=2, w_lin=0)
     bu = S.build_units(cu, sl, "ROUND_ROBIN", m=3, descending=True, backward=True)
     prob = H.make_problem(q, k, v, dO, cu, sl, fu, bu, bf16=True, scale=d ** -0.5)
+    assert [S.bwd_dkdv_plan(prob.tables, hq, hkv, d, u)[:3] for u in range(-1, 3)] == [(128,) + by for by in [whole] + units]
     o, lse = A.fwd_packed(q, k, v, cu, d ** -0.5)
     dq, dk, dv = A.bwd_packed(q, k, v, o, lse, dO, cu, d ** -0.5)
     for flags in (0, S.FLAG_PER_UNIT_LAUNCH):
@@ -166,12 +171,14 @@ def test_bf16_dkdv_head_dim_64(L, hq, hkv, slice_size):
 @pytest.mark.parametrize("L", [[1, 31, 32, 33], [95, 127, 128, 129], [160, 255, 257, 385]], ids=["wave", "half", "tile"])
 @pytest.mark.parametrize("hq,hkv,slice_size", [(1, 1, 1000), (3, 1, 97), (4, 2, 64)])
 def test_bf16_dkdv_short_walks(L, hq, hkv, slice_size):
-    _fused_and_per_unit(L, hq, hkv, 128, True, slice_size)
+    prob = _fused_and_per_unit(L, hq, hkv, 128, True, slice_size)
+    assert S.bwd_dkdv_plan(prob.tables, hq, hkv, 128)[0] == 128
 
 
 # ... and more than 112 steps per item on average in a launch that fills the chip (10 items of 16 KV heads, 123 steps): the one-wave kernel
 def test_bf16_dkdv_long_walks():
-    _fused_and_per_unit([510, 440, 330, 300, 290], 256, 16, 128, True, 1000)
+    prob = _fused_and_per_unit([510, 440, 330, 300, 290], 256, 16, 128, True, 1000)
+    assert S.bwd_dkdv_plan(prob.tables, 256, 16, 128) == (256, 1, 1, 0)
 
 
 # Tails of at most 64 (32) rows, for which a block takes two (four) heads, as far as the group's size allows: on the edges, tails only, and beside a sample

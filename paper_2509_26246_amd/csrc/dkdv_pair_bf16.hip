@@ -87,7 +87,14 @@ __global__ __launch_bounds__(64 * kWaves, D == 128 ? 2 : 3) void dkdv_pair_bf16_
   b /= Hkv;
   const int part = b % (head_parts * row_parts), hpart = part / row_parts, rpart = part % row_parts;
   b /= head_parts * row_parts;
-  const int item_idx = b >> 1, sub = b & 1;
+  // Which half of an item comes first.  Blocks go to the XCDs in turn and inside an XCD to its four engines; the second halves have few keys or none
+  // where samples, or their tails, end in the first.  With the first halves always first all the work of a launch of 1, 2 or 4 KV heads was on every
+  // second XCD, and of 8 on every second engine.  So the order changes with the item's place in groups of eight blocks, in a pattern over eight of them that was the best
+  // of six tried (334 launches: 1.5 % behind each with its best; first halves first 8 %).  120-row samples, us: 32K tokens of 8/1 heads of 128 94 -> 57, 16/4 151 -> 101, 5/5 58
+  // -> 51, 16K tokens of 32/8 heads of 64 68 -> 52.  (Two rounds of blocks at most, the halves of a round on all XCDs: the reversed second round evens them out.)
+  const int item_idx = b >> 1, half_blocks = Hkv * head_parts * row_parts, group8 = item_idx * half_blocks >> 2;
+  const bool first_first = gridDim.x <= 512 && half_blocks % 8 == 0;
+  const int sub = (first_first ? b : b ^ group8 ^ group8 >> 2 ^ (half_blocks & 1 ? 0 : group8 >> 1)) & 1;
   const int h_lo = g * hpart / head_parts, h_hi = g * (hpart + 1) / head_parts;
   if (item_idx >= n_items) return;
   const KvItem it = items[item_idx];

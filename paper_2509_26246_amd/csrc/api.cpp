@@ -62,6 +62,16 @@ int hip_rc(int e) {
 
 size_t align_up(size_t x) { return (x + 255) & ~size_t(255); }
 
+// The query tiles (size z) of units [lo, hi) of a list; in groups, for tails that share blocks, where it is one unit.
+QList query_list(const ScopeLists& L, const DeviceLists& D, int z, int lo, int hi) {
+  QList q{D.q_items[z] + L.q_off[z][lo], L.q_off[z][hi] - L.q_off[z][lo], nullptr, QGroups::plain(0)};
+  if (kTileSizes[z] == 128 && hi - lo == 1) {
+    q.grouped = D.grouped_items + L.grouped_off[lo];
+    q.groups = L.q_groups[lo];
+  }
+  return q;
+}
+
 // Optional per-launch timing (slimattn_profile_enable).  Events are created up front; recording
 // an event allocates nothing.  A launch that finds the pool used up runs untimed and is counted as dropped.
 struct Profiler {
@@ -156,18 +166,18 @@ static int fwd_impl(const slimattn_params* p, const void* q, const void* k, cons
   int rc = SLIMATTN_OK;
   const int z = tile_index(fwd_q_tile(p->dtype, p->head_dim));
   const LaunchCtx ctx{p, stream, t->total_tokens, t->mean_keys};
-  auto run = [&](const QItem* items, int n, const QGroups& groups, int divide_rows = 0) -> int {
+  auto run = [&](const QList& list, int divide_rows = 0) -> int {
     return timed(SLIMATTN_K_FWD, stream, [&] {
       return p->dtype == SLIMATTN_F32
-                 ? launch_fwd_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (float*)o, lse, items, n)
-                 : launch_fwd_bf16(ctx, q, k, v, o, lse, items, groups, divide_rows);
+                 ? launch_fwd_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (float*)o, lse, list.items, list.n)
+                 : launch_fwd_bf16(ctx, q, k, v, o, lse, list, divide_rows);
     });
   };
   const bool whole = lo == 0 && hi == t->n_units[0];
   g_prof.cur_pass = 0;
   g_prof.cur_unit = -1;
   if (whole && !(p->flags & SLIMATTN_FLAG_PER_UNIT_LAUNCH))
-    return hip_rc(run(t->d_fused.q_items[z], (int)t->fused.q_items[z].size(), t->fused.q_groups[0]));
+    return hip_rc(run(query_list(t->fused, t->d_fused, z, 0, 1)));
   const auto& off = t->per_unit[0].q_off[z];
   if (!(p->flags & SLIMATTN_FLAG_PER_UNIT_LAUNCH)) {
     // Part of the list in one launch (prefill by slices): the keys of long prefixes may be divided among blocks.  Whole-list
@@ -175,17 +185,16 @@ static int fwd_impl(const slimattn_params* p, const void* q, const void* k, cons
     // reference moves and the row's query tile holds other rows there.
     int longest = 0;
     for (int u = lo; u < hi; ++u)
-      if (off[u + 1] > off[u]) {                            // the longest is first, if it is longer than kSharedKeys
+      if (off[u + 1] > off[u]) {                            // a unit's items are in descending order of visible keys
         const QItem& it = t->per_unit[0].q_items[z][off[u]];
         const int rows = it.q_row0 + it.q_rows - it.kv_start;
         longest = rows > longest ? rows : longest;
       }
-    const QGroups groups = hi - lo == 1 ? t->per_unit[0].q_groups[lo] : QGroups::plain(off[hi] - off[lo]);
-    return hip_rc(run(t->d_per_unit[0].q_items[z] + off[lo], off[hi] - off[lo], groups, longest));
+    return hip_rc(run(query_list(t->per_unit[0], t->d_per_unit[0], z, lo, hi), longest));
   }
   for (int u = lo; u < hi; ++u) {
     g_prof.cur_unit = u;
-    rc = hip_rc(run(t->d_per_unit[0].q_items[z] + off[u], off[u + 1] - off[u], t->per_unit[0].q_groups[u]));
+    rc = hip_rc(run(query_list(t->per_unit[0], t->d_per_unit[0], z, u, u + 1)));
     if (rc != SLIMATTN_OK) return rc;
   }
   return SLIMATTN_OK;
@@ -242,15 +251,15 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
                                 (size_t)t->max_sample_len * p->n_kv_heads * p->head_dim * 4 <= (size_t(128) << 20));
   const int zq = tile_index(dq_q_tile(p->dtype, p->head_dim));
   const int zk = tile_index(dkdv_kv_tile(p->dtype, p->head_dim));
-  auto run_dq = [&](const QItem* items, int n, const QGroups& groups) -> int {
+  auto run_dq = [&](const QList& list) -> int {
     if (!own_stats) {
-      const int e = timed(SLIMATTN_K_DELTA, stream, [&] { return launch_bwd_stat_bf16(ctx, o, dO, lse, stat3, items, n); });
+      const int e = timed(SLIMATTN_K_DELTA, stream, [&] { return launch_bwd_stat_bf16(ctx, o, dO, lse, stat3, list.items, list.n); });
       if (e != 0) return e;
     }
     return timed(SLIMATTN_K_DQ, stream, [&] {
       return f32 ? launch_bwd_dq_f32(ctx, (const float*)q, (const float*)k, (const float*)v, (const float*)o, (const float*)dO,
-                                     lse, delta, (float*)dQ, items, n)
-                 : launch_bwd_dq_bf16(ctx, q, k, v, dO, o, lse, stat3, own_stats ? 1 : 0, dQ, items, groups);
+                                     lse, delta, (float*)dQ, list.items, list.n)
+                 : launch_bwd_dq_bf16(ctx, q, k, v, dO, o, lse, stat3, own_stats ? 1 : 0, dQ, list);
     });
   };
   auto run_dkdv = [&](const KvItem* items, int n, const Seg* segs, const DkdvParts& by = DkdvParts{1, 1, false}) -> int {
@@ -290,24 +299,23 @@ static int bwd_impl(const slimattn_params* p, const void* q, const void* k, cons
     // One scope holding every slice: each key tile's owner sums all later query rows itself and writes dK/dV directly, without
     // the fp32 accumulators in the workspace.  (Small fp32 launches divide every walk in two and keep the second half's
     // sums there until the two are added.)
-    int e = run_dq(t->d_fused.q_items[zq], (int)t->fused.q_items[zq].size(), t->fused.q_groups[0]);
+    int e = run_dq(query_list(t->fused, t->d_fused, zq, 0, 1));
     if (e == 0)
       e = f32 ? run_dkdv(t->d_fused.kv_items[zk], (int)t->fused.kv_items[zk].size(), t->d_fused.segs)
               : run_dkdv_split(t->fused, t->d_fused, 0);
     return finish(e);
   }
 
-  const auto& qoff = t->per_unit[1].q_off[zq];
   const auto& koff = t->per_unit[1].kv_off[zk];
   int e = 0;
-  if (!per_unit) e = run_dq(t->d_per_unit[1].q_items[zq] + qoff[lo], qoff[hi] - qoff[lo], QGroups::plain(qoff[hi] - qoff[lo]));
+  if (!per_unit) e = run_dq(query_list(t->per_unit[1], t->d_per_unit[1], zq, lo, hi));
   for (int u = lo; u < hi && e == 0; ++u) {
     // Units run one after another on the stream; each adds its queries' contributions to every key row of the
     // prefix it sees.  A row's single owner block continues from the fp32 accumulator an earlier unit left
     // (the row's first unit starts from zero, so nothing has to be cleared) and the row's last unit writes
     // dK/dV themselves: the summation order is the unit order, and a row is released as soon as it is complete.
     g_prof.cur_unit = u;
-    if (per_unit) e = run_dq(t->d_per_unit[1].q_items[zq] + qoff[u], qoff[u + 1] - qoff[u], t->per_unit[1].q_groups[u]);
+    if (per_unit) e = run_dq(query_list(t->per_unit[1], t->d_per_unit[1], zq, u, u + 1));
     if (e == 0)
       e = f32 ? run_dkdv(t->d_per_unit[1].kv_items[zk] + koff[u], koff[u + 1] - koff[u], t->d_per_unit[1].segs)
               : run_dkdv_split(t->per_unit[1], t->d_per_unit[1], u);

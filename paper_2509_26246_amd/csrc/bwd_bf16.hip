@@ -340,11 +340,13 @@ int launch_bwd_stat_bf16(const LaunchCtx& c, const void* o, const void* dO, cons
 namespace {
 template <int D, bool OWN>
 int launch_dq(const LaunchCtx& c, const void* q, const void* k, const void* v, const void* dO, const void* o, const float* lse, void* stat3,
-              void* dQ, const QItem* items, const QGroups& groups) {
+              void* dQ, const QList& list) {
   const slimattn_params& p = *c.p;
-  const int g = p.n_q_heads / p.n_kv_heads, n_items = groups.total();
-  return in_runs(n_items, p.n_q_heads, [&](int first, int n) {
-    const QBlocks run = shared_blocks(n == n_items ? groups : QGroups::plain(n), p.n_kv_heads, g);
+  const int g = p.n_q_heads / p.n_kv_heads;
+  const bool shared = shares_heads(list, g);
+  const QItem* items = shared ? list.grouped : list.items;
+  return in_runs(list.n, p.n_q_heads, [&](int first, int n) {
+    const QBlocks run = shared_blocks(shared && n == list.n ? list.groups : QGroups::plain(n), p.n_kv_heads, g);
     hipLaunchKernelGGL((dq_bf16_kernel<D, OWN>), dim3((unsigned)run.end[2]), dim3(256), 0, (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k,
                        (const bf16*)v, (const bf16*)dO, (const bf16*)o, lse, (bf16x8*)stat3, (bf16*)dQ, items + first, run, (int)c.T,
                        p.n_q_heads, p.n_kv_heads, p.scale);
@@ -354,13 +356,13 @@ int launch_dq(const LaunchCtx& c, const void* q, const void* k, const void* v, c
 }  // namespace
 
 int launch_bwd_dq_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, const void* dO, const void* o,
-                       const float* lse, void* stat3, int own_stats, void* dQ, const QItem* items, const QGroups& groups) {
-  if (groups.total() == 0) return 0;
+                       const float* lse, void* stat3, int own_stats, void* dQ, const QList& list) {
+  if (list.n == 0) return 0;
   if (c.p->head_dim == 128)
-    return own_stats ? launch_dq<128, true>(c, q, k, v, dO, o, lse, stat3, dQ, items, groups)
-                     : launch_dq<128, false>(c, q, k, v, dO, o, lse, stat3, dQ, items, groups);
-  return own_stats ? launch_dq<64, true>(c, q, k, v, dO, o, lse, stat3, dQ, items, groups)
-                   : launch_dq<64, false>(c, q, k, v, dO, o, lse, stat3, dQ, items, groups);
+    return own_stats ? launch_dq<128, true>(c, q, k, v, dO, o, lse, stat3, dQ, list)
+                     : launch_dq<128, false>(c, q, k, v, dO, o, lse, stat3, dQ, list);
+  return own_stats ? launch_dq<64, true>(c, q, k, v, dO, o, lse, stat3, dQ, list)
+                   : launch_dq<64, false>(c, q, k, v, dO, o, lse, stat3, dQ, list);
 }
 
 namespace {

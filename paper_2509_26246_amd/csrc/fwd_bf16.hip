@@ -327,10 +327,11 @@ int fwd_q_tile(int dtype, int) { return dtype == SLIMATTN_F32 ? 64 : kFwdBQ; }
 
 namespace {
 template <int D, bool EXACT>
-int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse, const QItem* items,
-                        const QGroups& groups, const FwdSplit& sp) {
+int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse, const QList& list, const FwdSplit& sp) {
   const slimattn_params& p = *c.p;
-  const int g = p.n_q_heads / p.n_kv_heads, n_items = groups.total();
+  const int g = p.n_q_heads / p.n_kv_heads, n_items = list.n;
+  const bool shared = sp.parts == 1 && shares_heads(list, g);
+  const QItem* items = shared ? list.grouped : list.items;
   const dim3 block(256);
   if (sp.parts > 1) {
     hipLaunchKernelGGL((fwd_bf16_split_kernel<D, EXACT>), dim3((unsigned)(n_items * p.n_q_heads * sp.parts)), block, 0, (hipStream_t)c.stream,
@@ -343,7 +344,7 @@ int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const 
     return (int)hipGetLastError();
   }
   return in_runs(n_items, p.n_q_heads, [&](int first, int n) {
-    const QBlocks run = shared_blocks(n == n_items ? groups : QGroups::plain(n), p.n_kv_heads, g);
+    const QBlocks run = shared_blocks(shared && n == n_items ? list.groups : QGroups::plain(n), p.n_kv_heads, g);
     hipLaunchKernelGGL((fwd_bf16_kernel<D, EXACT>), dim3((unsigned)run.end[2]), block, 0,
                        (hipStream_t)c.stream, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)o, lse, items + first, run, (int)c.T,
                        p.n_q_heads, p.n_kv_heads, p.scale);
@@ -363,19 +364,17 @@ int launch_fwd_one_head(const LaunchCtx& c, const void* q, const void* k, const 
 // kernel is bound by the vector unit, where a second head per wave saves nothing.)
 constexpr int kShortMeanKeys = 400;
 
-int launch_fwd_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse,
-                    const QItem* items, const QGroups& groups, int divide_rows) {
-  const int n_items = groups.total();
-  if (n_items == 0) return 0;
+int launch_fwd_bf16(const LaunchCtx& c, const void* q, const void* k, const void* v, void* o, float* lse, const QList& list, int divide_rows) {
+  if (list.n == 0) return 0;
   const slimattn_params& p = *c.p;
   const bool even = p.n_q_heads / p.n_kv_heads % 2 == 0;
   FwdSplit sp;
-  int e = split_begin(c, n_items, divide_rows, &sp);
+  int e = split_begin(c, list.n, divide_rows, &sp);
   if (e == 0) {
-    if (p.head_dim == 64) e = launch_fwd_one_head<64, false>(c, q, k, v, o, lse, items, groups, sp);
-    else if (!even) e = launch_fwd_one_head<128, false>(c, q, k, v, o, lse, items, groups, sp);
-    else if (c.mean_keys > kShortMeanKeys) e = launch_fwd_wide_bf16(c, q, k, v, o, lse, items, n_items, sp);
-    else e = launch_fwd_one_head<128, true>(c, q, k, v, o, lse, items, groups, sp);
+    if (p.head_dim == 64) e = launch_fwd_one_head<64, false>(c, q, k, v, o, lse, list, sp);
+    else if (!even) e = launch_fwd_one_head<128, false>(c, q, k, v, o, lse, list, sp);
+    else if (c.mean_keys > kShortMeanKeys) e = launch_fwd_wide_bf16(c, q, k, v, o, lse, list.items, list.n, sp);
+    else e = launch_fwd_one_head<128, true>(c, q, k, v, o, lse, list, sp);
   }
   if (e != 0) split_abandon(c, sp);
   return e;

@@ -23,17 +23,26 @@ inline int tile_index(int rows) {
 struct QItem { int32_t q_row0, q_rows, kv_start, pad; };
 
 // Groups of a list of 128-row query tiles, in list order: n[i] items for which one block of the one-head kernels takes 1 << share[i] query
-// heads, as far as the size of the head group allows.  The last tile of a sample leaves waves without rows where it has at most 64 (32); a
-// block costs nearly the same, so there it takes a second head (three more) against the same keys.  16K tokens, 32/8 heads of 128, forward / dQ,
-// us: samples of 64 rows 99 / 183 -> 72 / 125, 160 rows 109 / 203 -> 87 / 134, 272 rows 123 / 200 -> 103 / 161.  (The blocks that are saved must not
-// be launched: as blocks that end at once the 64-row samples took 125 / 203.)  Only in lists without a tile of more than kSharedKeys keys: groups are
-// heavy-first in themselves only, tails first, and with long samples beside them that order costs more than the few tails save (forward of
-// a 32K pack of 18 samples by units: 1120 -> 1128 us).
+// heads, as far as the size of the head group allows (four with groups of 4, 8, ..., two with other even ones).  The last tile of a sample
+// leaves waves without rows where it has at most 64 (32); a block costs nearly the same, so there it takes a second head (three more)
+// against the same keys.  16K tokens, 32/8 heads of 128, forward / dQ, us: samples of 64 rows 99 / 183 -> 72 / 125, 160 rows 109 / 203 ->
+// 87 / 134, 272 rows 123 / 200 -> 103 / 161.  (The blocks that are saved must not be launched: as blocks that end at once the 64-row samples
+// took 125 / 203.)  Only for lists without a tile of more than kSharedKeys keys: groups are heavy-first in themselves only, tails first, and
+// with long samples beside them that order costs more than the few tails save (forward of a 32K pack of 18 samples by units: 1120 -> 1128 us).
+// Launches that share no heads walk the list heavy-first (in groups, 32K tokens of short samples, forward: 40/40 heads of 128 457 -> 472 us,
+// 32/32 353 -> 361).
 constexpr int kSharedKeys = 1024;
 struct QGroups {
   int n[3], share[3];
   int total() const { return n[0] + n[1] + n[2]; }
   static QGroups plain(int n_items) { return QGroups{{n_items, 0, 0}, {0, 0, 0}}; }
+};
+// The query tiles of a launch: heavy-first and, where tails may share blocks, the same tiles in groups (otherwise groups.total() is 0).
+struct QList {
+  const QItem* items;
+  int n;
+  const QItem* grouped;
+  QGroups groups;
 };
 inline int query_share(const QItem& it) {
   return it.q_rows > 64 ? 0 : it.q_rows > 32 ? 1 : 2;
@@ -145,8 +154,10 @@ struct Range { int32_t begin, end; };
 // A launch scope is either one unit or the whole list ("fused").  Its items are stored heavy-first.
 struct ScopeLists {
   std::vector<int32_t> q_off[kNumTileSizes];    // per-unit offsets into q_items (size n_units + 1)
-  std::vector<QItem> q_items[kNumTileSizes];    // unit-major, each unit heavy-first (128 rows: in each of its groups, if it has any)
-  std::vector<QGroups> q_groups;                // per unit, of the 128-row tiles
+  std::vector<QItem> q_items[kNumTileSizes];    // unit-major, each unit heavy-first
+  std::vector<int32_t> grouped_off;             // the 128-row tiles of units with tails that share blocks, once more in groups
+  std::vector<QItem> grouped_items;
+  std::vector<QGroups> q_groups;                // per unit
   std::vector<int32_t> kv_off[kNumTileSizes];
   std::vector<KvItem> kv_items[kNumTileSizes];
   std::vector<Seg> segs;                        // all units' runs (and the parts' cut runs), referenced by the items
@@ -167,6 +178,7 @@ struct ScopeLists {
 
 struct DeviceLists {                            // device mirrors (pointers into one allocation)
   const QItem* q_items[kNumTileSizes];
+  const QItem* grouped_items;
   const KvItem* kv_items[kNumTileSizes];
   const Seg* segs;
   const KvItem* split_items[kNumSplitTiles];
@@ -268,8 +280,7 @@ int launch_bwd_dkdv_f32(const LaunchCtx&, const float* q, const float* k, const 
                         int n_items, const Seg* segs, int longest);
 
 // divide_rows: keys the longest item sees, if the keys of the items may be divided among blocks (below); 0: one block walks them
-int launch_fwd_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, void* o, float* lse,
-                    const QItem* items, const QGroups& groups, int divide_rows);
+int launch_fwd_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, void* o, float* lse, const QList& list, int divide_rows);
 // even group sizes at head dim 128: one wave per SIMD, two heads per wave (fwd_wide_bf16.hip)
 int launch_fwd_wide_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, void* o, float* lse,
                          const QItem* items, int n_items, const FwdSplit& sp);
@@ -280,7 +291,7 @@ int launch_fwd_wide_bf16(const LaunchCtx&, const void* q, const void* k, const v
 int launch_bwd_stat_bf16(const LaunchCtx&, const void* o, const void* dO, const float* lse, void* stat3, const QItem* items,
                          int n_items);
 int launch_bwd_dq_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* o,
-                       const float* lse, void* stat3, int own_stats, void* dQ, const QItem* items, const QGroups& groups);
+                       const float* lse, void* stat3, int own_stats, void* dQ, const QList& list);
 // head_dim 128, long walks: one wave per SIMD, 256 key rows per block (dkdv_wide_bf16.hip)
 int launch_bwd_dkdv_wide_bf16(const LaunchCtx&, const void* q, const void* k, const void* v, const void* dO, const void* stat3,
                             float* acc_dk, float* acc_dv, void* dK, void* dV, const KvItem* items, int n_items, const Seg* segs,

@@ -330,6 +330,8 @@ inline int mapped_grid(int n_items, int Hkv, int g) { return ((n_items * Hkv + 7
 
 // The same for a launch over groups of items (QGroups): a block takes 1 << *share heads from *hg on.
 struct QBlocks { int n[3], share[3], end[3]; };   // per group: items, log 2 of the heads per block, first block behind it
+// Whether blocks of a launch with groups of g query heads take several of them: the list to walk is then the grouped one.
+inline bool shares_heads(const QList& list, int g) { return g % 2 == 0 && list.groups.total() > 0; }
 inline QBlocks shared_blocks(const QGroups& groups, int Hkv, int g) {
   QBlocks b;
   const int most = g % 4 == 0 ? 2 : g % 2 == 0 ? 1 : 0;

@@ -50,7 +50,7 @@ constexpr int64_t kMinPartRows = 256;
 
 // (Buffers of append_scope and append_split, kept over the calls of one table build.)
 struct Scratch {
-  std::vector<QItem> qi, qi_sorted;
+  std::vector<QItem> qi;
   std::vector<KvItem> ki, items;
   std::vector<int64_t> weight, w;
   std::vector<uint64_t> order;
@@ -170,17 +170,13 @@ void append_scope(ScopeLists& L, const std::vector<Run>& runs, bool want_kv, boo
     auto keys = [](const QItem& it) { return it.q_row0 + it.q_rows - it.kv_start; };
     std::stable_sort(qi.begin(), qi.end(), [&](const QItem& a, const QItem& b) { return keys(a) > keys(b); });
     if (B == 128) {
-      QGroups g = QGroups::plain((int)qi.size());
-      if (!qi.empty() && keys(qi[0]) <= kSharedKeys) {       // ... in each of the groups
-        g = QGroups{{0, 0, 0}, {2, 1, 0}};
-        std::vector<QItem>& sorted = tmp.qi_sorted;
-        sorted.clear();
+      QGroups g{{0, 0, 0}, {2, 1, 0}};
+      if (!qi.empty() && keys(qi[0]) <= kSharedKeys && std::any_of(qi.begin(), qi.end(), [](const QItem& it) { return query_share(it) > 0; }))
         for (int i = 0; i < 3; ++i)
           for (const QItem& it : qi)
-            if (query_share(it) == g.share[i]) { sorted.push_back(it); ++g.n[i]; }
-        qi.swap(sorted);
-      }
+            if (query_share(it) == g.share[i]) { L.grouped_items.push_back(it); ++g.n[i]; }
       L.q_groups.push_back(g);
+      L.grouped_off.push_back((int32_t)L.grouped_items.size());
     }
     L.q_items[z].insert(L.q_items[z].end(), qi.begin(), qi.end());
     L.q_off[z].push_back((int32_t)L.q_items[z].size());
@@ -223,7 +219,7 @@ size_t place(std::vector<char>& blob, const std::vector<T>& v) {
   return off;
 }
 size_t list_bytes(const ScopeLists& L) {                     // at least what place() takes for one scope's lists
-  size_t n = L.segs.size() * sizeof(Seg) + 256;
+  size_t n = L.segs.size() * sizeof(Seg) + L.grouped_items.size() * sizeof(QItem) + 512;
   for (int z = 0; z < kNumTileSizes; ++z) n += L.q_items[z].size() * sizeof(QItem) + L.kv_items[z].size() * sizeof(KvItem) + 512;
   for (int ti = 0; ti < kNumSplitTiles; ++ti) {
     n += L.split_items[ti].size() * sizeof(KvItem) + L.tile_items[ti].size() * sizeof(KvReduce) + 512;
@@ -315,6 +311,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
     Scratch tmp;
     for (int pass = 0; pass < 2; ++pass) {
       for (int z = 0; z < kNumTileSizes; ++z) { t->per_unit[pass].q_off[z].push_back(0); t->per_unit[pass].kv_off[z].push_back(0); }
+      t->per_unit[pass].grouped_off.push_back(0);
       for (int ti = 0; ti < kNumSplitTiles; ++ti)
         for (int c = 0; c < kNumSplitClasses; ++c) t->per_unit[pass].reduce_off[ti][c].push_back(0);
       // reach[s]: (unit, end of the unit's last query row in sample s), in list order.  A unit collects into the
@@ -343,6 +340,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
     std::vector<int32_t> all(n_slices);
     for (int32_t i = 0; i < n_slices; ++i) all[i] = i;
     for (int z = 0; z < kNumTileSizes; ++z) { t->fused.q_off[z].push_back(0); t->fused.kv_off[z].push_back(0); }
+    t->fused.grouped_off.push_back(0);
     for (int ti = 0; ti < kNumSplitTiles; ++ti)
       for (int c = 0; c < kNumSplitClasses; ++c) t->fused.reduce_off[ti][c].push_back(0);
     append_scope(t->fused, merge_runs(slices, all.data(), n_slices), true, true, tmp,
@@ -353,7 +351,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
     blob.reserve(t->cu.size() * 4 + t->slices.size() * sizeof(slimattn_slice) + 2048 + list_bytes(t->per_unit[0]) +
                  list_bytes(t->per_unit[1]) + list_bytes(t->fused));
     const size_t off_cu = place(blob, t->cu), off_sl = place(blob, t->slices);
-    size_t off_q[3][kNumTileSizes], off_kv[3][kNumTileSizes], off_seg[3], off_sp[3][kNumSplitTiles], off_rd[3][kNumSplitTiles][kNumSplitClasses],
+    size_t off_q[3][kNumTileSizes], off_kv[3][kNumTileSizes], off_gr[3], off_seg[3], off_sp[3][kNumSplitTiles], off_rd[3][kNumSplitTiles][kNumSplitClasses],
         off_ta[3][kNumSplitTiles];
     ScopeLists* lists[3] = {&t->per_unit[0], &t->per_unit[1], &t->fused};
     for (int s = 0; s < 3; ++s) {
@@ -361,6 +359,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
         off_q[s][z] = place(blob, lists[s]->q_items[z]);
         off_kv[s][z] = place(blob, lists[s]->kv_items[z]);
       }
+      off_gr[s] = place(blob, lists[s]->grouped_items);
       off_seg[s] = place(blob, lists[s]->segs);
       for (int ti = 0; ti < kNumSplitTiles; ++ti) {
         off_sp[s][ti] = place(blob, lists[s]->split_items[ti]);
@@ -397,6 +396,7 @@ int slimattn_tables_create_async(const int32_t* cu, int32_t n, const slimattn_sl
         dl[s]->q_items[z] = (const QItem*)(base + off_q[s][z]);
         dl[s]->kv_items[z] = (const KvItem*)(base + off_kv[s][z]);
       }
+      dl[s]->grouped_items = (const QItem*)(base + off_gr[s]);
       dl[s]->segs = (const Seg*)(base + off_seg[s]);
       for (int ti = 0; ti < kNumSplitTiles; ++ti) {
         dl[s]->split_items[ti] = (const KvItem*)(base + off_sp[s][ti]);

@@ -189,6 +189,24 @@ def test_bf16_tails_shared_by_heads(L, hq, hkv, d):
     _fused_and_per_unit(L, hq, hkv, d, True, 500)
 
 
+# Calls of one unit take the same blocks as the unit's own launches in a call of all units; calls of several units share no heads.  The rows are the same bits
+@pytest.mark.parametrize("hq,hkv,d", [(2, 1, 64), (8, 2, 128), (3, 1, 128), (6, 1, 64)])
+def test_bf16_tails_by_calls_of_units(hq, hkv, d):
+    prob = _fused_and_per_unit([160, 33, 1, 192, 300, 64, 32], hq, hkv, d, True, 90)
+    want = [x.clone() for x in (prob.o, prob.lse, prob.dQ, prob.dK, prob.dV)]
+    nf, nb = prob.tables.n_fwd_units, prob.tables.n_bwd_units
+    for step in (1, 3):
+        for x in (prob.o, prob.lse, prob.dQ, prob.dK, prob.dV):
+            x.fill_(7.0)
+        for u in range(0, nf, step):
+            prob.forward(unit_lo=u, unit_hi=min(u + step, nf))
+        for u in range(0, nb, step):
+            prob.backward(unit_lo=u, unit_hi=min(u + step, nb))
+        torch.cuda.synchronize()
+        for name, x, w in zip(("o", "lse", "dQ", "dK", "dV"), (prob.o, prob.lse, prob.dQ, prob.dK, prob.dV), want):
+            assert torch.equal(x, w), f"{name}, {step} units a call"
+
+
 # fp32 dQ: a key with a NaN or an infinity reaches the rows that see it and no row in front of it, in the middle of a tile too; a key of
 # -inf (score -inf, probability 0) spoils only its own dim of those rows
 @pytest.mark.parametrize("d", [16, 32, 64, 128])

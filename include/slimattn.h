@@ -309,7 +309,8 @@ void slimattn_tables_destroy(slimattn_tables* t);
 int64_t slimattn_tables_count(const slimattn_tables* t, int what);
 
 /* Bytes of DEVICE scratch slimattn_bwd needs (fp32 dK/dV accumulators, the per-row statistics in
- * fp32 and as bf16 triples, partial tiles of divided key tiles).  Its contents need no initialisation. */
+ * fp32 and as bf16 triples, partial tiles of divided key tiles).  One size for both data types: an fp32 pass
+ * leaves the triples and the partial tiles unused.  Its contents need no initialisation. */
 size_t slimattn_bwd_workspace_bytes(const slimattn_tables* t, int32_t n_q_heads, int32_t n_kv_heads,
                                     int32_t head_dim);
 
@@ -389,8 +390,8 @@ int slimattn_bwd_dkdv_plan(const slimattn_tables* t, int32_t n_q_heads, int32_t 
  * ends; its address is looked up once per device, by slimattn_tables_create or by the first call).  The call
  * allocates nothing and frees nothing.  SLIMATTN_ESCRATCH when slimattn_bwd_workspace_bytes() for this
  * pack exceeds the array (nothing is launched).  Every call on a GPU uses that GPU's one array, which keeps
- * what the last call left: a call with unit_lo == 0 clears what must start at zero, as slimattn_bwd does,
- * and calls that overlap in time on one GPU (two streams, two threads) race on it -- serialise them.  A
+ * what the last call left (the first unit that reaches a key row starts its sum, as in slimattn_bwd), and
+ * calls that overlap in time on one GPU (two streams, two threads) race on it -- serialise them.  A
  * unit list split over several calls must not be interleaved with calls for another pack. */
 #define SLIMATTN_STATIC_SCRATCH_BYTES (64u << 20)
 int slimattn_bwd_static(const slimattn_params* p, const void* q, const void* k, const void* v, const void* o,

@@ -11,14 +11,15 @@
 // Blocks of half the keys overlap each other, steps before a wave's keys are skipped, and a sample that ends in a
 // tile's first half wastes half as much.  At 128 a step costs more: one product per LDS fragment (1.25 KB of LDS reads per product), and a
 // wave alone takes 2500 cycles for a step of 34 products (1088), two on a SIMD 3400 for both.
-// Measured at 128, 16K tokens, one-wave kernel / this one, us: 32/32 heads, samples of 64 rows 426 / 157, 256 rows 235 / 164, 512 rows 281 / 202, 1024
-// rows 398 / 322; 32/8 heads, 128 rows 158 / 117, 256 rows 141 / 114, 1024 rows 283 / 270, 4096 rows 891 / 1007; 876 rows of
-// 8/1 heads 39 / 27.  (Raised priority for the element-wise work: 2 to 5 % slower.  The next step's bookkeeping
+// Measured at 128, 16K tokens, one-wave kernel / this one, us: 32/32 heads, samples of 64 rows 430 / 165, 256 rows 244 / 164, 512 rows 286 / 210, 1024
+// rows 379 / 316; 32/8 heads, 128 rows 161 / 104, 256 rows 144 / 116, 1024 rows 293 / 272, 4096 rows 891 / 1007; 876 rows of
+// 8/1 heads, with the reduction, 45 / 27.  (Raised priority for the element-wise work: 2 to 5 % slower.  The next step's bookkeeping
 // behind its first LDS reads, the second half of the element-wise work behind the first gradient products: no gain.)
 // At 64 a score costs the same exponential, product and packing as at 128 but half the matrix work, and a step is mostly latency: what counts
 // are waves, and barriers, of which there is one every two steps.  Against 256 keys in 8 waves, two per SIMD: 16K tokens, 32/8 heads, samples of 128 rows
-// 75 / 64, 2048 rows 301 / 276, one sample 1973 / 1909; 32/32 heads, 1024 rows 198 / 166, 4096 rows 601 / 513; a 32K pack of 10 samples, 32/8 heads, 3148 /
-// 2791.  (V rows in LDS instead: 61, 283, 1972, 158, 514.  A barrier for each step: 62 to 1957.)
+// 76 / 52, 2048 rows 291 / 275, one sample 1944 / 1890; 32/32 heads, 1024 rows 207 / 163, 4096 rows 587 / 502; a 32K pack of 10 samples, 32/8 heads, 3128 /
+// 2644 (matrix unit busy 0.77 of its time, waves waiting on LDS 0.03 of theirs).  (With first halves first throughout, against 64, 276, 1909, 166, 513: V rows in
+// LDS 61, 283, 1972, 158, 514; a barrier for each step 62 to 1957.)
 //
 // Registers: 245 of 256 at 128, 167 of 168 at 64.  The accumulators take D, K fragments D / 4; V rows are in LDS at 128 and in registers at 64; a tile's fragment
 // addresses are formed from one, and the row statistics, 16 bytes per row, come through LDS with the tiles (in registers, for this step and the next,
@@ -40,7 +41,7 @@ struct QdV { bf16x8 q, d, v; };
 
 // The items are heavy-first, and two or three blocks share a compute unit from the start.  The second round of 256 blocks (what there is of
 // it) runs backwards, so that the longest walks share theirs with the shortest of the round: one 16K sample of 32/8 heads at 128 3887 -> 3728
-// us, 128-row samples 124 -> 117; 32K pack at 64 2925 -> 2783.  (The low three bits, the XCD, stay.)
+// us, 128-row samples, first halves first, 124 -> 117; 32K pack at 64 2925 -> 2783.  (The low three bits, the XCD, stay.)
 __device__ __forceinline__ int paired_block(int block) {
   const int end = min((int)gridDim.x, 512) & ~7;
   return block >= 256 && block < end ? 256 + end - 8 - (block & ~7) + (block & 7) : block;

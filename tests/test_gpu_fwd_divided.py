@@ -175,7 +175,8 @@ def test_handles_hold_their_tables_only():
 
 
 # More launches at once than there are arrays: those that find none free walk their parts one after another, to the same bits.  Every
-# kernel that divides; eager calls on many streams beside replays of a graph.
+# kernel that divides; eager calls on many streams beside replays of a graph.  The streams start together, behind some milliseconds of other
+# work: small launches would otherwise end before the host has issued the next ones.
 @pytest.mark.parametrize("L,hq,hkv,d", [([32768], 8, 1, 128), ([20000], 3, 1, 128), ([20000], 4, 2, 64), ([9000] + [64] * 3000, 2, 1, 128)])
 def test_concurrent_launches_have_the_bits_of_one_alone(L, hq, hkv, d):
     prob, arrs, cu, sl = _slices(L, hq, hkv, d, 1024)
@@ -191,10 +192,16 @@ def test_concurrent_launches_have_the_bits_of_one_alone(L, hq, hkv, d):
     streams = [torch.cuda.Stream() for _ in range(8)]
     outs = [(torch.empty_like(prob.o), torch.empty_like(prob.lse)) for _ in streams]
     before, in_turn = S.fwd_divided_counts(), 0
+    other, start = torch.empty(1 << 30, dtype=torch.uint8, device="cuda"), torch.cuda.Event()
     for _ in range(4):
         for t in [prob.o, prob.lse] + [t for pair in outs for t in pair]:
             t.fill_(float("nan"))
         torch.cuda.synchronize()
+        for n in range(32):
+            other.fill_(n)
+        start.record()
+        for s in streams + [side]:
+            s.wait_event(start)
         for _ in range(3):
             for s, (o, lse) in zip(streams, outs):
                 with torch.cuda.stream(s):
@@ -210,7 +217,7 @@ def test_concurrent_launches_have_the_bits_of_one_alone(L, hq, hkv, d):
             assert torch.equal(o[first:end].view(torch.int16), want[0].view(torch.int16)), f"stream {i}: O"
             assert torch.equal(lse[:, first:end], want[1]), f"stream {i}: lse"
             assert torch.isnan(o[:first]).all() and torch.isnan(o[end:]).all()
-    assert in_turn > 0                                      # both ways to finish a launch have run
+    assert in_turn > 0, "no launch found both arrays taken" # both ways to finish a launch have run
 
 
 @pytest.mark.parametrize("L,hq,hkv,d", [([9000], 8, 1, 128), ([9000], 3, 1, 128), ([9000], 4, 2, 64), ([3500] + [64] * 260, 2, 1, 128),
